@@ -96,6 +96,9 @@ __device__ void load_weights(ColorWeights<BWD>& w, const ColorArgs& a) {
     __syncthreads();
 }
 
+// internal column of the caller's column e of W_1
+__device__ __forceinline__ int internal_column(int e) { return e < 6 ? 16 + e : e < 22 ? 18 + e : e - 22; }
+
 // real orthonormal spherical harmonics, degree 0..3, index l*l + l + m
 __device__ __forceinline__ void sh16(float x, float y, float z, float* sh) {
     const float xx = x * x, yy = y * y, zz = z * z;
@@ -339,8 +342,7 @@ __global__ __launch_bounds__(kThreads) void color_bwd_kernel(ColorArgs a) {
         }
     }
     __syncthreads();
-    // ---- every wave gets a quarter of the registers of the block's sums and adds it to global
-    // memory: one barrier, and the atomics of the four waves run side by side
+    // ---- the block's sums go to global memory in the gradients' own order
     float* scratch = reinterpret_cast<float*>(&sm);
     static_assert(sizeof(sm) >= kWaves * 9 * 1024 * sizeof(float), "scratch for the block sum");
     v16f g3;                   // the four 16-column blocks of G3 side by side
@@ -348,27 +350,23 @@ __global__ __launch_bounds__(kThreads) void color_bwd_kernel(ColorArgs a) {
     for (int cb = 0; cb < 4; ++cb)
 #pragma unroll
         for (int v = 0; v < 4; ++v) g3[4 * cb + v] = G3[cb][v];
-    v16f* all[9] = {&G1[0][0], &G1[0][1], &G1[1][0], &G1[1][1], &G2[0][0], &G2[0][1], &G2[1][0], &G2[1][1], &g3};
-    block_sum_shared<kWaves, 9>(scratch, all, wave, lane);
-    constexpr int kShare = 16 / kWaves;
-#pragma unroll
-    for (int mb = 0; mb < 2; ++mb)
-#pragma unroll
-        for (int nb = 0; nb < 2; ++nb)
-#pragma unroll
-            for (int r = 0; r < 16; ++r) {
-                if (r / kShare != wave) continue;
-                const int o = 32 * mb + neuron_of(r, h), c = 32 * nb + j;
-                atomicAdd(a.dW[1] + o * 64 + c, G2[mb][nb][r]);
-                const int e = external_column(c);
-                if (e >= 0) atomicAdd(a.dW[0] + o * 38 + e, G1[mb][nb][r]);
-            }
-    if (lane < 16) {           // rows 0..3 of a block live in lanes 0..15; three of them are real
-#pragma unroll
-        for (int cb = 0; cb < 4; ++cb)
-#pragma unroll
-            for (int v = 0; v < 3; ++v)
-                if (cb == wave) atomicAdd(a.dW[2] + v * 64 + 16 * cb + lane, g3[4 * cb + v]);
+    const v16f* const all[9] = {&G1[0][0], &G1[0][1], &G1[1][0], &G1[1][1], &G2[0][0], &G2[0][1], &G2[1][0], &G2[1][1], &g3};
+    block_store<9>(scratch, all, wave, lane);
+    __syncthreads();
+    constexpr int kOf1 = 64 * 38, kOf2 = 64 * 64, kOf3 = 3 * 64;
+    constexpr int kChunks = (kOf1 + kOf2 + kOf3 + kThreads - 1) / kThreads;
+    for (int k = 0; k < kChunks; ++k) {
+        const int x = rotated_chunk<kChunks>(k) * kThreads + threadIdx.x;
+        if (x < kOf1) {
+            const int o = x / 38, c = internal_column(x - 38 * o);
+            atomicAdd(a.dW[0] + x, block_element<kWaves, 9, 2>(scratch, 0, o, c));
+        } else if (x < kOf1 + kOf2) {
+            const int e = x - kOf1;
+            atomicAdd(a.dW[1] + e, block_element<kWaves, 9, 2>(scratch, 4, e >> 6, e & 63));
+        } else if (x < kOf1 + kOf2 + kOf3) {
+            const int e = x - kOf1 - kOf2;
+            atomicAdd(a.dW[2] + e, block_element16<kWaves, 9>(scratch, 8, e >> 6, e & 63));
+        }
     }
 }
 

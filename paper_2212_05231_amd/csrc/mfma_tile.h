@@ -412,6 +412,52 @@ __device__ __forceinline__ void outer_accumulate16(v4f* G, const float* __restri
     }
 }
 
+// The end of a kernel that accumulates V register vectors (weight gradients) in each of its WAVES waves: every wave
+// writes its vectors to LDS (block_store, one barrier by the caller), then any thread reads the block's sum of one
+// element (block_total) and adds it to global memory.  The threads walk over the gradient in its own memory order, so
+// an atomic instruction covers 64 consecutive floats, four 64-byte requests, whatever the row length: adding from
+// the registers instead meant two rows of 32 columns an instruction, which for the 38-column matrix of the colour
+// network straddles lines and took 22 us at the end of its backward kernel (colour backward at
+// 32 576 points: 42.5 -> 20.2 us; SDF backward 31.8 -> 25.9).  Workgroups start at
+// different places (rotated_chunk): requests to one line are served one after the other, 12 ns each, so 256 workgroups
+// that walk in step queue up behind one another.
+// scratch: WAVES * V * 1024 floats of LDS nobody reads any more (the caller has put a barrier before).
+template <int V>
+__device__ __forceinline__ void block_store(float* __restrict__ scratch, const v16f* const (&vec)[V], int wave, int lane) {
+#pragma unroll
+    for (int k = 0; k < V; ++k)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) scratch[((wave * V + k) * 16 + r) * 64 + lane] = (*vec[k])[r];
+}
+
+template <int WAVES, int V>
+__device__ __forceinline__ float block_total(const float* __restrict__ scratch, int k, int r, int lane) {
+    float sum = 0.f;
+#pragma unroll
+    for (int w = 0; w < WAVES; ++w) sum += scratch[((w * V + k) * 16 + r) * 64 + lane];
+    return sum;
+}
+
+// step k of CHUNKS of a walk that starts at another place in every workgroup
+template <int CHUNKS>
+__device__ __forceinline__ int rotated_chunk(int k) {
+    const int c = k + (int)((blockIdx.x / 8 + 3 * (blockIdx.x % 8)) % CHUNKS);      // workgroups of one XCD (equal modulo 8) differ too
+    return c < CHUNKS ? c : c - CHUNKS;
+}
+
+// Element (o, i) of a 64-column gradient kept as blocks vec[first + XB * mb + nb] of outer_accumulate_split (XB blocks
+// of 32 columns), and of a 16-row gradient kept as the four 16-column blocks of outer_accumulate16 side by side in
+// vec[first].
+template <int WAVES, int V, int XB>
+__device__ __forceinline__ float block_element(const float* __restrict__ scratch, int first, int o, int i) {
+    const int h = (o >> 2) & 1, r = 4 * ((o & 31) >> 3) + (o & 3);          // inverse of neuron_of
+    return block_total<WAVES, V>(scratch, first + XB * (o >> 5) + (i >> 5), r, 32 * h + (i & 31));
+}
+template <int WAVES, int V>
+__device__ __forceinline__ float block_element16(const float* __restrict__ scratch, int first, int o, int i) {
+    return block_total<WAVES, V>(scratch, first, 4 * (i >> 4) + (o & 3), 16 * (o >> 2) + (i & 15));
+}
+
 // Sum V register vectors over the block's WAVES waves such that every wave ends up with a share of
 // the totals: wave w holds, in registers 16/WAVES * w .. 16/WAVES * (w+1) - 1 of every vector, the
 // block's sums (its other registers keep its own partial sums).  All waves then flush their share

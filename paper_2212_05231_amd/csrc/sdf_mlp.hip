@@ -381,23 +381,6 @@ struct SdfBwdSmem {
     float tiles[kWaves][2][kTileWords];
 };
 
-// add the registers [r0, r0 + count) of this wave's accumulator into dst[rows][cols] (row-major,
-// ld = cols) with atomics; r0 is the same for all lanes
-template <int ZB, int XB>
-__device__ __forceinline__ void flush_grad(float* __restrict__ dst, int rows, int cols, v16f (*G)[XB], int j, int h,
-                                           int r0, int count) {
-#pragma unroll
-    for (int mb = 0; mb < ZB; ++mb)
-#pragma unroll
-        for (int nb = 0; nb < XB; ++nb)
-#pragma unroll
-            for (int r = 0; r < 16; ++r) {
-                if (r < r0 || r >= r0 + count) continue;
-                const int o = 32 * mb + neuron_of(r, h), i = 32 * nb + j;
-                if (o < rows && i < cols) atomicAdd(dst + o * cols + i, G[mb][nb][r]);
-            }
-}
-
 // GIVEN: the masks come from the forward kernel (a.masks).  The forward pass is then recomputed
 // only for its values, which enter weight gradients and further products at gradient tolerance:
 // two terms and three products like the rest of this kernel, and a plain ReLU (where its sign
@@ -569,8 +552,7 @@ __global__ __launch_bounds__(kThreads) void sdf_bwd_kernel(SdfArgs a) {
         outer_accumulate16<2, kLd64, kLd64>(GL, Zt, Xt, lane);
     }
     __syncthreads();
-    // ---- every wave gets a quarter of the registers of the block's sums and adds it to global
-    // memory: one barrier, and the atomics of the four waves run side by side
+    // ---- the block's sums go to global memory in the gradients' own order
     float* scratch = reinterpret_cast<float*>(&sm);
     constexpr int kVecs = K == 3 ? 7 : 3;
     static_assert(sizeof(sm) >= kWaves * kVecs * 1024 * sizeof(float), "scratch for the block sum");
@@ -579,23 +561,29 @@ __global__ __launch_bounds__(kThreads) void sdf_bwd_kernel(SdfArgs a) {
     for (int cb = 0; cb < 4; ++cb)
 #pragma unroll
         for (int v = 0; v < 4; ++v) gl[4 * cb + v] = GL[cb][v];
-    constexpr int kShare = 16 / kWaves;
-    if (K == 3) {
-        v16f* all[7] = {&G1[0][0], &G1[1][0], &G2[0][0], &G2[0][1], &G2[1][0], &G2[1][1], &gl};
-        block_sum_shared<kWaves, 7>(scratch, all, wave, lane);
-        flush_grad<2, 2>(a.dH[1], 64, 64, G2, j, h, wave * kShare, kShare);
+    if constexpr (K == 3) {
+        const v16f* const all[7] = {&G1[0][0], &G1[1][0], &gl, &G2[0][0], &G2[0][1], &G2[1][0], &G2[1][1]};
+        block_store<7>(scratch, all, wave, lane);
     } else {
-        v16f* all[3] = {&G1[0][0], &G1[1][0], &gl};
-        block_sum_shared<kWaves, 3>(scratch, all, wave, lane);
+        const v16f* const all[3] = {&G1[0][0], &G1[1][0], &gl};
+        block_store<3>(scratch, all, wave, lane);
     }
-    flush_grad<2, 1>(a.dH[0], 64, D, G1, j, h, wave * kShare, kShare);
-    // register 4 cb + v of gl: row 4 (lane / 16) + v, column 16 cb + lane % 16 of the last matrix; a wave's
-    // quarter is one block of 16 columns
-#pragma unroll
-    for (int cb = 0; cb < 4; ++cb)
-#pragma unroll
-        for (int v = 0; v < 4; ++v)
-            if (cb == wave) atomicAdd(a.dH[K - 1] + (4 * (lane >> 4) + v) * 64 + 16 * cb + (lane & 15), gl[4 * cb + v]);
+    __syncthreads();
+    constexpr int kOf1 = 64 * D, kOf2 = K == 3 ? 64 * 64 : 0, kOfL = 16 * 64;
+    constexpr int kChunks = (kOf1 + kOf2 + kOfL) / kThreads;
+    static_assert((kOf1 + kOf2 + kOfL) % kThreads == 0, "whole chunks");
+    for (int k = 0; k < kChunks; ++k) {
+        const int x = rotated_chunk<kChunks>(k) * kThreads + threadIdx.x;
+        if (x < kOf1) {
+            atomicAdd(a.dH[0] + x, block_element<kWaves, kVecs, 1>(scratch, 0, x / D, x % D));
+        } else if (x < kOf1 + kOf2) {
+            const int e = x - kOf1;
+            atomicAdd(a.dH[1] + e, block_element<kWaves, kVecs, 2>(scratch, 3, e >> 6, e & 63));
+        } else {
+            const int e = x - kOf1 - kOf2;
+            atomicAdd(a.dH[K - 1] + e, block_element16<kWaves, kVecs>(scratch, 2, e >> 6, e & 63));
+        }
+    }
 }
 
 template <int D, int K>
@@ -722,6 +710,23 @@ __global__ __launch_bounds__(kThreads) void deep_forward_kernel(DeepArgs a) {
             store_lane(a.t_out, tile, lane, tz);
         }
     }
+}
+
+// add the registers [r0, r0 + count) of this wave's accumulator into dst[rows][cols] (row-major,
+// ld = cols) with atomics; r0 is the same for all lanes
+template <int ZB, int XB>
+__device__ __forceinline__ void flush_grad(float* __restrict__ dst, int rows, int cols, v16f (*G)[XB], int j, int h,
+                                           int r0, int count) {
+#pragma unroll
+    for (int mb = 0; mb < ZB; ++mb)
+#pragma unroll
+        for (int nb = 0; nb < XB; ++nb)
+#pragma unroll
+            for (int r = 0; r < 16; ++r) {
+                if (r < r0 || r >= r0 + count) continue;
+                const int o = 32 * mb + neuron_of(r, h), i = 32 * nb + j;
+                if (o < rows && i < cols) atomicAdd(dst + o * cols + i, G[mb][nb][r]);
+            }
 }
 
 struct DeepRevSmem {
