@@ -72,7 +72,8 @@ void scatter_header(const neus2_config* cfg, int64_t n, bool want_pos, void* wor
 bool scatter_gathers_position(const neus2_config* cfg, int64_t n, const void* workspace, int64_t workspace_bytes);
 int64_t scatter_workspace_bytes(const neus2_config* cfg, int64_t n);
 // Bytes of workspace the scatter-add needs for n points when no position gradient is wanted
-// (0 if it would take the path without a workspace).
+// through 12-byte records (0 below the size from which those are used: the entry point with the static buffer, which
+// asks, keeps small batches out of the buffer that all its calls share).
 int64_t scatter_records_bytes(const neus2_config* cfg, int64_t n);
 int64_t sdf_deep_workspace_bytes(int n_mats, int64_t n);
 int launch_sdf_deep_fwd(int n_mats, int enc_dim, const float* enc, const float* jac, const float* const* H, int64_t n,

@@ -505,7 +505,14 @@ __global__ __launch_bounds__(kBlock) void sum_levels_kernel(const float* __restr
 // owner task takes a segment of such a list; with more ranges they get row records like a hashed
 // level.  Workgroups take tasks from a counter, heaviest tasks first.
 constexpr int kOwnerThreads = 1024;
-constexpr int64_t kOwnerMinPoints = 1 << 16;
+// Below kOwnerMinPoints the atomic kernel is used: its time is proportional to the points (3.4 us per 1000 with 16
+// levels), the lists cost 45 us (T = 2^19) to 60 us (T = 2^21) before the first point.  Measured at 24 576 points:
+// atomics 87 us, lists 58 (T = 2^19), 86 and 79 (2^21), 45 and 46 (8 active levels); at 32 768: 112 and 61, 115 and 92, 57 and 49.
+constexpr int64_t kOwnerMinPoints = 7 << 12;
+// Below kNarrowMinPoints a row record keeps its four values as floats (20 bytes), from there on it shares an exponent
+// (12 bytes): below, the records are a small part of the time, and the values keep the atomic kernel's binary32 (gradient
+// off by 7e-8 of its norm from 64-bit sums, atomics 9e-8, packed records 5e-6).
+constexpr int64_t kNarrowMinPoints = 1 << 16;
 constexpr int kOwnerSlotBits = 13;
 constexpr int kOwnerSlots = 1 << kOwnerSlotBits;
 constexpr int kMaxRanges = 256;
@@ -582,10 +589,13 @@ __device__ __forceinline__ RowRecord pack_row(uint32_t slot, uint32_t code, cons
     return r;
 }
 
+__device__ __forceinline__ uint32_t second_slot(uint32_t s0, uint32_t code) {
+    return code == kCodeNext ? s0 + 1u : code == kCodeSame ? s0 : s0 ^ ((2u << code) - 1u);
+}
+
 __device__ __forceinline__ void unpack_row(const RowRecord& r, uint32_t& s0, uint32_t& s1, float (&v)[4]) {
     s0 = r.a & (kOwnerSlots - 1);
-    const uint32_t code = (r.a >> 13) & 15u;
-    s1 = code == kCodeNext ? s0 + 1u : code == kCodeSame ? s0 : s0 ^ ((2u << code) - 1u);
+    s1 = second_slot(s0, (r.a >> 13) & 15u);
     const int E = (int)((r.a >> 17) & 127u);
     const int m0 = sext(r.b, 0, 18);
     const int m1 = (sext(r.c, 0, 4) << 14) | (int)(r.b >> 18);
@@ -596,10 +606,38 @@ __device__ __forceinline__ void unpack_row(const RowRecord& r, uint32_t& s0, uin
     v[0] = (float)m0 * scale; v[1] = (float)m1 * scale; v[2] = (float)m2 * scale; v[3] = (float)m3 * scale;
 }
 
+// The same with the four values as floats, for batches below kNarrowMinPoints.  head: slot 0..12 | code 13..16.
+struct __attribute__((packed, aligned(4))) WideRecord {
+    uint32_t head;
+    float v[4];
+};
+
+__device__ __forceinline__ void make_record(RowRecord& r, uint32_t slot, uint32_t code, const float4& v) { r = pack_row(slot, code, v); }
+__device__ __forceinline__ void make_record(WideRecord& r, uint32_t slot, uint32_t code, const float4& v) {
+    r.head = slot | (code << 13);
+    r.v[0] = v.x; r.v[1] = v.y; r.v[2] = v.z; r.v[3] = v.w;
+}
+
+__device__ __forceinline__ void open_record(const RowRecord& r, uint32_t& s0, uint32_t& s1, float (&v)[4]) { unpack_row(r, s0, s1, v); }
+__device__ __forceinline__ void open_record(const WideRecord& r, uint32_t& s0, uint32_t& s1, float (&v)[4]) {
+    s0 = r.head & (kOwnerSlots - 1);
+    s1 = second_slot(s0, (r.head >> 13) & 15u);
+#pragma unroll
+    for (int k = 0; k < 4; ++k) v[k] = r.v[k];
+}
+
+// a record is read once: non-temporal load, the 12-byte one in one instruction
+__device__ __forceinline__ RowRecord stream_record(const RowRecord* p) {
+    typedef uint32_t u3 __attribute__((ext_vector_type(3), aligned(4)));
+    const u3 w = __builtin_nontemporal_load(reinterpret_cast<const u3*>(p));
+    return RowRecord{w.x, w.y, w.z};
+}
+__device__ __forceinline__ WideRecord stream_record(const WideRecord* p) { return *p; }
+
 struct Records {
     int* cursor;            // [n_listed + n_indexed][kMaxRanges]
     uint32_t* index;        // levels with point lists: per entry [ranges][idx_capacity] point numbers
-    RowRecord* rows;        // per entry [ranges][capacity]
+    void* rows;             // per entry [ranges][capacity] RowRecord or WideRecord
 };
 
 // Records of one workgroup are first put in LDS in list order (range by range), then written
@@ -609,8 +647,9 @@ constexpr int kBinThreads = 512;
 constexpr int kBinRecords = 4 * kBinThreads;
 constexpr uint32_t kNoRecord = 0xFFFFFFFFu;
 
+template <typename Rec>
 struct BinSmem {
-    uint32_t ra[kBinRecords], rb[kBinRecords], rc[kBinRecords];   // the staged records, word by word
+    uint32_t word[sizeof(Rec) / 4][kBinRecords];                  // the staged records, word by word
     uint32_t dest[kBinRecords];          // record index within the entry's lists, kNoRecord if it went elsewhere
     int cnt[kMaxRanges];                 // records of this workgroup per range
     int base[kMaxRanges];                // first position of this workgroup in the list of the range
@@ -696,6 +735,7 @@ __device__ void bin_points(const GridDesc& g, const OwnerPlan& plan, const Recor
 // grp, grp + level_groups, ...): position and dL/dn are fetched once, and the next level's dL/de and
 // dd/de are requested before the current level's records are made, so that only the first level of a
 // workgroup waits for memory.  Workgroups beyond the level groups handle the levels with point lists.
+template <typename Rec>
 __global__ __launch_bounds__(kBinThreads) void bin_rows_kernel(GridDesc g, OwnerPlan plan, Records rec,
                                                               const float* __restrict__ pos,
                                                               const float* __restrict__ q,
@@ -703,7 +743,8 @@ __global__ __launch_bounds__(kBinThreads) void bin_rows_kernel(GridDesc g, Owner
                                                               const float* __restrict__ d_normal, int64_t n,
                                                               int point_blocks, int level_groups,
                                                               float* __restrict__ d_tables) {
-    __shared__ BinSmem sm;
+    __shared__ BinSmem<Rec> sm;
+    constexpr int kWords = sizeof(Rec) / 4;
     const int grp = blockIdx.x / point_blocks;
     if (grp >= level_groups) {                // uniform over the workgroup
         bin_points(g, plan, rec, pos, q, d_enc, d_normal, n, point_blocks, plan.n_listed + grp - level_groups, d_tables, sm.cnt,
@@ -739,7 +780,7 @@ __global__ __launch_bounds__(kBinThreads) void bin_rows_kernel(GridDesc g, Owner
         __syncthreads();
 
         uint32_t range[4];
-        RowRecord row_rec[4];
+        Rec row_rec[4];
         int rank[4];
         if (valid) {
             const int res = g.res[level];
@@ -788,7 +829,7 @@ __global__ __launch_bounds__(kBinThreads) void bin_rows_kernel(GridDesc g, Owner
                     val.z = 0.f; val.w = 0.f;
                     code = kCodeSame;
                 }
-                row_rec[row] = pack_row(s0 & (kOwnerSlots - 1), code, val);
+                make_record(row_rec[row], s0 & (kOwnerSlots - 1), code, val);
                 rank[row] = atomicAdd(&sm.cnt[range[row]], 1);
             }
         }
@@ -820,14 +861,17 @@ __global__ __launch_bounds__(kBinThreads) void bin_rows_kernel(GridDesc g, Owner
                 const int r = (int)range[row];
                 const int in_list = sm.base[r] + rank[row];
                 const int at = sm.first[r] + rank[row];
-                sm.ra[at] = row_rec[row].a; sm.rb[at] = row_rec[row].b; sm.rc[at] = row_rec[row].c;
+                struct Words { uint32_t w[kWords]; };
+                const Words words = __builtin_bit_cast(Words, row_rec[row]);
+#pragma unroll
+                for (int k = 0; k < kWords; ++k) sm.word[k][at] = words.w[k];
                 if (in_list < capacity) {
                     sm.dest[at] = (uint32_t)r * (uint32_t)capacity + (uint32_t)in_list;
                 } else {                                                 // list full: straight to the global gradient
                     sm.dest[at] = kNoRecord;
                     uint32_t s0, s1;
                     float v[4];
-                    unpack_row(row_rec[row], s0, s1, v);
+                    open_record(row_rec[row], s0, s1, v);
                     float* gt = d_tables + ((size_t)level * g.table_size + ((size_t)r << kOwnerSlotBits)) * 2;
                     atomicAdd(gt + 2 * s0 + 0, v[0]);
                     atomicAdd(gt + 2 * s0 + 1, v[1]);
@@ -838,13 +882,14 @@ __global__ __launch_bounds__(kBinThreads) void bin_rows_kernel(GridDesc g, Owner
         }
         __syncthreads();
         const int total = sm.total;
-        RowRecord* out = rec.rows + plan.list_base[e];
+        Rec* out = reinterpret_cast<Rec*>(rec.rows) + plan.list_base[e];
         for (int at = threadIdx.x; at < total; at += kBinThreads) {
             const uint32_t d = sm.dest[at];
             if (d != kNoRecord) {
-                RowRecord r;
-                r.a = sm.ra[at]; r.b = sm.rb[at]; r.c = sm.rc[at];
-                out[d] = r;            // (a non-temporal store here costs 0.2 ms: measured)
+                struct Words { uint32_t w[kWords]; } words;
+#pragma unroll
+                for (int k = 0; k < kWords; ++k) words.w[k] = sm.word[k][at];
+                out[d] = __builtin_bit_cast(Rec, words);            // (a non-temporal store here costs 0.2 ms: measured)
             }
         }
         // the next round writes cnt only after the barrier that follows its clearing, base/first/total
@@ -902,6 +947,7 @@ __device__ __forceinline__ void add_point_to_range(const GridDesc& g, int level,
     add_loaded_point(g, level, range, load_point(level, i, n, (float)g.res[level], pos, q, d_enc, d_normal), acc, odd);
 }
 
+template <typename Rec>
 __global__ __launch_bounds__(kOwnerThreads) void scatter_owner_kernel(GridDesc g, OwnerPlan plan, Records rec,
                                                                      const float* __restrict__ pos,
                                                                      const float* __restrict__ q,
@@ -949,7 +995,7 @@ __global__ __launch_bounds__(kOwnerThreads) void scatter_owner_kernel(GridDesc g
             // A listed task streams the list of its range.
             const int count = min(rec.cursor[e * kMaxRanges + range], plan.capacity[e]);
             const size_t at = (size_t)plan.list_base[e] + (size_t)range * plan.capacity[e];
-            const RowRecord* rs = rec.rows + at;
+            const Rec* rs = reinterpret_cast<const Rec*>(rec.rows) + at;
             // this task's stretch of the list (the whole list unless the plan shares lists out)
             const int stretch = ((count + n_chunks - 1) / n_chunks + 63) / 64 * 64;
             const int first = chunk * stretch, stop = min(count, first + stretch);
@@ -957,23 +1003,18 @@ __global__ __launch_bounds__(kOwnerThreads) void scatter_owner_kernel(GridDesc g
             // four records per thread in flight: the list is streamed from HBM
             constexpr int kAhead = 4;
             for (int j0 = first + threadIdx.x; j0 < stop; j0 += kAhead * kOwnerThreads) {
-                RowRecord rr[kAhead];
+                Rec rr[kAhead];
 #pragma unroll
                 for (int k = 0; k < kAhead; ++k) {
                     const int j = j0 + k * kOwnerThreads;
-                    // a record is read once: non-temporal load, 12 bytes in one instruction
-                    if (j < stop) {
-                        typedef uint32_t u3 __attribute__((ext_vector_type(3), aligned(4)));
-                        const u3 w = __builtin_nontemporal_load(reinterpret_cast<const u3*>(rs + j));
-                        rr[k].a = w.x; rr[k].b = w.y; rr[k].c = w.z;
-                    }
+                    if (j < stop) rr[k] = stream_record(rs + j);
                 }
 #pragma unroll
                 for (int k = 0; k < kAhead; ++k) {
                     if (j0 + k * kOwnerThreads < stop) {
                         uint32_t s0, s1;
                         float v[4];
-                        unpack_row(rr[k], s0, s1, v);
+                        open_record(rr[k], s0, s1, v);
                         double* a0 = acc + 2 * s0;
                         double* a1 = acc + 2 * s1;
                         atomicAdd(a0 + odd, (double)(odd ? v[1] : v[0]));
@@ -1255,8 +1296,10 @@ int launch_encode(const neus2_config* cfg, const float* pos, const void* tables,
     return check_launch("hash encode");
 }
 
-int64_t owner_workspace_need(const OwnerPlan& plan) {
-    return kWorkspaceHeader + plan.list_base[plan.n_listed] * 12 + plan.idx_base[plan.n_listed + plan.n_indexed] * 4 + 256;
+int64_t record_bytes(int64_t n) { return n < kNarrowMinPoints ? sizeof(WideRecord) : sizeof(RowRecord); }
+
+int64_t owner_workspace_need(const OwnerPlan& plan, int64_t n) {
+    return kWorkspaceHeader + plan.list_base[plan.n_listed] * record_bytes(n) + plan.idx_base[plan.n_listed + plan.n_indexed] * 4 + 256;
 }
 
 // scratch of the position-gradient path, behind the records: either part[active levels][n][3] (the gather
@@ -1269,7 +1312,7 @@ float* scatter_hessian_region(const neus2_config* cfg, int64_t n, void* workspac
     if (!scatter_gathers_position(cfg, n, workspace, workspace_bytes)) return nullptr;
     bool ok = false;
     const OwnerPlan plan = make_owner_plan(cfg, n, ok);
-    return reinterpret_cast<float*>(reinterpret_cast<char*>(workspace) + (owner_workspace_need(plan) + 255) / 256 * 256);
+    return reinterpret_cast<float*>(reinterpret_cast<char*>(workspace) + (owner_workspace_need(plan, n) + 255) / 256 * 256);
 }
 
 int64_t scatter_workspace_bytes(const neus2_config* cfg, int64_t n) {
@@ -1277,21 +1320,21 @@ int64_t scatter_workspace_bytes(const neus2_config* cfg, int64_t n) {
     bool ok = false;
     const OwnerPlan plan = make_owner_plan(cfg, n, ok);
     if (!ok) return 0;
-    return (owner_workspace_need(plan) + 255) / 256 * 256 + (int64_t)cfg->n_levels * n * 24;
+    return (owner_workspace_need(plan, n) + 255) / 256 * 256 + (int64_t)cfg->n_levels * n * 24;
 }
 
 int64_t scatter_records_bytes(const neus2_config* cfg, int64_t n) {
-    if (n < kOwnerMinPoints || cfg->active_levels == 0) return 0;
+    if (n < kNarrowMinPoints || cfg->active_levels == 0) return 0;
     bool ok = false;
     const OwnerPlan plan = make_owner_plan(cfg, n, ok);
-    return ok ? owner_workspace_need(plan) : 0;
+    return ok ? owner_workspace_need(plan, n) : 0;
 }
 
 bool scatter_gathers_position(const neus2_config* cfg, int64_t n, const void* workspace, int64_t workspace_bytes) {
     if (n < kOwnerMinPoints || !workspace || cfg->active_levels <= cfg->frozen_levels) return false;
     bool ok = false;
     const OwnerPlan plan = make_owner_plan(cfg, n, ok);
-    return ok && workspace_bytes >= (owner_workspace_need(plan) + 255) / 256 * 256 + pos_scratch_bytes(cfg, n);
+    return ok && workspace_bytes >= (owner_workspace_need(plan, n) + 255) / 256 * 256 + pos_scratch_bytes(cfg, n);
 }
 
 // must mirror the condition under which launch_scatter takes the path with the workspace
@@ -1302,8 +1345,8 @@ void scatter_header(const neus2_config* cfg, int64_t n, bool want_pos, void* wor
     if (n == 0 || cfg->active_levels == 0 || n < kOwnerMinPoints || !workspace) return;
     bool ok = false;
     const OwnerPlan plan = make_owner_plan(cfg, n, ok);
-    const int64_t records_end = (owner_workspace_need(plan) + 255) / 256 * 256;
-    if (ok && workspace_bytes >= (want_pos ? records_end + pos_scratch_bytes(cfg, n) : owner_workspace_need(plan))) {
+    const int64_t records_end = (owner_workspace_need(plan, n) + 255) / 256 * 256;
+    if (ok && workspace_bytes >= (want_pos ? records_end + pos_scratch_bytes(cfg, n) : owner_workspace_need(plan, n))) {
         *p = reinterpret_cast<float*>(workspace);
         *count = kWorkspaceHeader / 4;
     }
@@ -1316,19 +1359,20 @@ int launch_scatter(const neus2_config* cfg, const float* pos, const void* tables
     if (n == 0 || cfg->active_levels == 0) return NEUS2_OK;
     const GridDesc g = make_grid_desc(cfg);
     // Large batches with a workspace: LDS-owner kernel (no global atomics on the big levels);
-    // the position gradient, if wanted, comes from a gather pass of its own.  Below ~2^16
+    // the position gradient, if wanted, comes from a gather pass of its own.  Below kOwnerMinPoints
     // points the atomic kernel is cheaper.
     if (n >= kOwnerMinPoints && workspace) {
         bool ok = false;
         const OwnerPlan plan = make_owner_plan(cfg, n, ok);
-        const int64_t records_end = (owner_workspace_need(plan) + 255) / 256 * 256;
-        if (ok && workspace_bytes >= (d_pos ? records_end + pos_scratch_bytes(cfg, n) : owner_workspace_need(plan))) {
+        const int64_t records_end = (owner_workspace_need(plan, n) + 255) / 256 * 256;
+        if (ok && workspace_bytes >= (d_pos ? records_end + pos_scratch_bytes(cfg, n) : owner_workspace_need(plan, n))) {
             char* ws = reinterpret_cast<char*>(workspace);
             int* counter = reinterpret_cast<int*>(ws);
             Records rec;
             rec.cursor = reinterpret_cast<int*>(ws + kCursorOffset);
-            rec.rows = reinterpret_cast<RowRecord*>(ws + kWorkspaceHeader);
-            rec.index = reinterpret_cast<uint32_t*>(ws + kWorkspaceHeader + plan.list_base[plan.n_listed] * 12);
+            rec.rows = ws + kWorkspaceHeader;
+            rec.index = reinterpret_cast<uint32_t*>(ws + kWorkspaceHeader + plan.list_base[plan.n_listed] * record_bytes(n));
+            const bool wide = n < kNarrowMinPoints;
             if (!header_cleared)                                                                 // task counter and cursors
                 NEUS2_TRY(launch_zero(reinterpret_cast<float*>(ws), kWorkspaceHeader / 4, st));
             if (plan.n_listed + plan.n_indexed > 0) {
@@ -1337,13 +1381,14 @@ int launch_scatter(const neus2_config* cfg, const float* pos, const void* tables
                 int groups = (8 * compute_units() + pbs - 1) / pbs;
                 if (groups > plan.n_listed) groups = plan.n_listed;
                 if (groups < 1 && plan.n_listed > 0) groups = 1;
-                hipLaunchKernelGGL(bin_rows_kernel, dim3(pbs * (groups + plan.n_indexed)), dim3(kBinThreads), 0, st, g, plan,
+                hipLaunchKernelGGL(wide ? bin_rows_kernel<WideRecord> : bin_rows_kernel<RowRecord>, dim3(pbs * (groups + plan.n_indexed)), dim3(kBinThreads), 0, st, g, plan,
                                    rec, pos, q, d_enc, d_normal, n, pbs, groups, d_tables);
             }
             const int wgs = compute_units();
             if (plan.n_tasks > 0)
-                hipLaunchKernelGGL(scatter_owner_kernel, dim3(plan.n_tasks < wgs ? plan.n_tasks : wgs), dim3(kOwnerThreads), 0,
-                                   st, g, plan, rec, pos, q, d_enc, d_normal, n, counter, d_tables);
+                hipLaunchKernelGGL(wide ? scatter_owner_kernel<WideRecord> : scatter_owner_kernel<RowRecord>,
+                                   dim3(plan.n_tasks < wgs ? plan.n_tasks : wgs), dim3(kOwnerThreads), 0, st, g, plan,
+                                   rec, pos, q, d_enc, d_normal, n, counter, d_tables);
             if (d_pos && hessian_stored) {
                 // the training step's encode kernel left the second derivatives where `part` would go
                 const float* hess = reinterpret_cast<const float*>(ws + records_end);
