@@ -46,6 +46,7 @@ typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 constexpr int kLd64 = 68;   // row stride (floats) of fp32 tiles [32 points][64 neurons]
 constexpr int kLdT = 36;    // row stride (words) of a transposed split tile [64 neurons][32 points]
 constexpr int kTileWords = 64 * kLdT;   // a per-wave tile holds either layout
+constexpr int kLd16 = 20;   // row stride (floats) of fp32 tiles [32 points][16 neurons]
 
 __device__ __forceinline__ v16f zero16() {
     v16f z;
@@ -119,6 +120,14 @@ __device__ __forceinline__ void stage(float* __restrict__ tile, const v16f* v, i
         for (int g = 0; g < 4; ++g)
             *reinterpret_cast<float4*>(&tile[j * LD + 32 * b + 8 * g + 4 * h]) =
                 make_float4(v[b][4 * g], v[b][4 * g + 1], v[b][4 * g + 2], v[b][4 * g + 3]);
+}
+
+// The first 16 neurons of a register vector to an fp32 tile [32 points][LD].
+template <int LD>
+__device__ __forceinline__ void stage16(float* __restrict__ tile, const v16f& v, int j, int h) {
+#pragma unroll
+    for (int g = 0; g < 2; ++g)
+        *reinterpret_cast<float4*>(&tile[j * LD + 8 * g + 4 * h]) = make_float4(v[4 * g], v[4 * g + 1], v[4 * g + 2], v[4 * g + 3]);
 }
 
 // Orders a wave's LDS writes before its following LDS reads by other lanes.
@@ -249,6 +258,93 @@ __device__ __forceinline__ void outer_accumulate_split(v16f (*G)[XB], const uint
             }
         __builtin_amdgcn_sched_barrier(0);
     }
+}
+
+// ---- point-major tiles, read back transposed ------------------------------------------------------
+// The same products for kernels with two wavefronts per SIMD, where the vector unit has no slot to spare: a split vector
+// goes to LDS as the registers hold it, 16 bytes a store, one plane of bf16 per term, and ds_read_b64_tr_b16 returns it
+// transposed (16 lanes read four rows of 16 elements, lane c gets column c; checked on the chip), so there is no byte
+// permute on either side: per 64-wide vector 8 stores of 16 bytes instead of 32 permutes and 32 stores of 4, and none of
+// the 8 permutes per operand on the way back.
+// A block tile holds 32 points x 32 neurons: [term 2][point 32][neuron 32] bf16, rows of four 16-byte pieces.  Piece p
+// of row j lies at p ^ swizzle(j): eight consecutive rows of one piece (a store) and four rows of two neighbouring pieces
+// (16 lanes of a read) each cover every bank once.  Neurons are kept in the order a lane half stores them: position
+// 16 a + 8 h + 4 b + e for neuron 16 a + 8 b + 4 h + e, so the gradient's rows and columns are permuted within 32
+// (tile_position) and put right where it leaves the kernel.
+constexpr int kBlockTile = 4096;        // bytes
+constexpr int kTilesPerWave = 3;        // two blocks of one factor, one of the other
+
+__device__ __forceinline__ constexpr int tile_position(int neuron) {
+    return (neuron & ~12) | ((neuron & 4) << 1) | ((neuron & 8) >> 1);
+}
+
+template <int NB, int P>
+__device__ __forceinline__ void stage_block(unsigned char* __restrict__ tile, const Split<NB, P>& x, int b, int j, int h) {
+    const int swizzle = (j & 2) | ((j >> 2) & 1);
+    unsigned char* row = tile + j * 64;
+#pragma unroll
+    for (int term = 0; term < 2; ++term)
+#pragma unroll
+        for (int u = 0; u < 2; ++u) {
+            u32x4 v;
+#pragma unroll
+            for (int e = 0; e < 4; ++e) v[e] = x.t[term][b][4 * u + e];
+            *reinterpret_cast<u32x4*>(row + term * (kBlockTile / 2) + (((2 * u + h) ^ swizzle) << 4)) = v;
+        }
+}
+
+// operand of k-step t (points 16 t .. 16 t + 15) of one term: lane's column, its eight points
+__device__ __forceinline__ bf8 read_block(const unsigned char* __restrict__ tile, int term, int t, int lane) {
+    typedef short v4s __attribute__((ext_vector_type(4)));
+    typedef short v8s __attribute__((ext_vector_type(8)));
+    const int piece = 2 * ((lane >> 4) & 1) + ((lane >> 1) & 1), swizzle = (lane >> 2) & 2;
+    const unsigned char* at = tile + term * (kBlockTile / 2) + (16 * t + 8 * (lane >> 5) + ((lane >> 2) & 3)) * 64 + (lane & 1) * 8;
+    const unsigned char* first = at + ((piece ^ swizzle) << 4);
+    const unsigned char* second = at + 4 * 64 + ((piece ^ swizzle ^ 1) << 4);
+    const v4s lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) v4s*)(first));
+    const v4s hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) v4s*)(second));
+    return __builtin_bit_cast(bf8, __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7));
+}
+
+// G[mb][nb] += sum over the tile's 32 points of z[32 mb + .] (x) x[32 nb + .], two terms and three products, rows and
+// columns of G in tile_position order.  tiles: this wave's kTilesPerWave block tiles.
+template <int ZB, int XB, int PZ, int PX>
+__device__ __forceinline__ void outer_accumulate_points(v16f (*G)[XB], const Split<ZB, PZ>& z, const Split<XB, PX>& x,
+                                                        unsigned char* __restrict__ tiles, int lane) {
+    const int j = lane & 31, h = lane >> 5;
+    constexpr bool kRoom = XB + ZB <= kTilesPerWave;        // every block has a tile of its own
+    wave_lds_fence();
+#pragma unroll
+    for (int nb = 0; nb < XB; ++nb) stage_block(tiles + nb * kBlockTile, x, nb, j, h);
+    if (kRoom) {
+#pragma unroll
+        for (int mb = 0; mb < ZB; ++mb) stage_block(tiles + (XB + mb) * kBlockTile, z, mb, j, h);
+        wave_lds_fence();
+    }
+    // The operands of a k-step are read when its instructions are due, those of x once per block of z: kept, they would be 32
+    // more registers, and the other wavefront of the SIMD fills the wait.
+#pragma unroll
+    for (int mb = 0; mb < ZB; ++mb) {
+        unsigned char* zt = tiles + (kRoom ? XB + mb : XB) * kBlockTile;
+        if (!kRoom) {
+            if (mb > 0) wave_lds_fence();
+            stage_block(zt, z, mb, j, h);
+            wave_lds_fence();
+        }
+#pragma unroll
+        for (int t = 0; t < 2; ++t) {
+            const bf8 zh = read_block(zt, 0, t, lane), zm = read_block(zt, 1, t, lane);
+#pragma unroll
+            for (int nb = 0; nb < XB; ++nb) {
+                const bf8 xh = read_block(tiles + nb * kBlockTile, 0, t, lane), xm = read_block(tiles + nb * kBlockTile, 1, t, lane);
+                G[mb][nb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(zh, xh, G[mb][nb], 0, 0, 0);
+                G[mb][nb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(zh, xm, G[mb][nb], 0, 0, 0);
+                G[mb][nb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(zm, xh, G[mb][nb], 0, 0, 0);
+            }
+            __builtin_amdgcn_sched_barrier(0);
+        }
+    }
+    wave_lds_fence();
 }
 
 // ---- split matrices ----------------------------------------------------------------------------
@@ -456,6 +552,12 @@ __device__ __forceinline__ float block_element(const float* __restrict__ scratch
 template <int WAVES, int V>
 __device__ __forceinline__ float block_element16(const float* __restrict__ scratch, int first, int o, int i) {
     return block_total<WAVES, V>(scratch, first, 4 * (i >> 4) + (o & 3), 16 * (o >> 2) + (i & 15));
+}
+
+// block_element of a gradient whose rows and columns are in tile_position order
+template <int WAVES, int V, int XB>
+__device__ __forceinline__ float block_element_points(const float* __restrict__ scratch, int first, int o, int i) {
+    return block_element<WAVES, V, XB>(scratch, first, tile_position(o), tile_position(i));
 }
 
 // Sum V register vectors over the block's WAVES waves such that every wave ends up with a share of

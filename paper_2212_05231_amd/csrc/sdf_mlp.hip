@@ -13,6 +13,8 @@
 // Both products contract over points and run as MFMA outer-product accumulations.
 // Activations and masks are recomputed in the backward kernel from the encoding (cheaper
 // than storing and re-reading four 64-wide vectors per point).
+#include <type_traits>
+
 #include "common.h"
 #include "mfma_tile.h"
 
@@ -43,11 +45,12 @@ __device__ __forceinline__ int64_t mask_word(int layer, int64_t n, int64_t i, in
 // factor and six products: as accurate as fp32 arithmetic, and the same arithmetic in both
 // kernels, so the ReLU masks agree.  The adjoint, S and t sweeps of the backward kernel use
 // two terms and three products.
-template <int D, int K, bool BWD>
+// PF: terms of the matrices of the forward direction.
+template <int D, int K, bool BWD, int PF = 3>
 struct SdfWeights {
     static constexpr int KS1 = D / 16;
-    typedef SplitMatrix<KS1, 3> M1f;               // [64][D]
-    typedef SplitMatrix<4, 3> M2f;                 // [64][64]
+    typedef SplitMatrix<KS1, PF> M1f;              // [64][D]
+    typedef SplitMatrix<4, PF> M2f;                // [64][64]
     typedef SplitMatrix<4, 3> MLf;                 // last matrix [16 -> 32][64]
     typedef SplitMatrix<4, BWD ? 2 : 3> M1t;       // [D -> 32][64]
     typedef SplitMatrix<4, BWD ? 2 : 3> M2t;
@@ -65,9 +68,9 @@ struct SdfWeights {
 
 // Every matrix is fetched from global memory before the first is written to LDS, so the fetches
 // are in flight together; the copies cover every slot a product reads, so nothing is cleared.
-template <int D, int K, bool BWD, int THREADS>
-__device__ void load_weights(SdfWeights<D, K, BWD>& w, const SdfArgs& a) {
-    typedef SdfWeights<D, K, BWD> W;
+template <int D, int K, bool BWD, int THREADS, int PF = 3>
+__device__ void load_weights(SdfWeights<D, K, BWD, PF>& w, const SdfArgs& a) {
+    typedef SdfWeights<D, K, BWD, PF> W;
     const int tid = threadIdx.x;
     const float* __restrict__ H1 = a.H[0];
     const float* __restrict__ H2 = a.H[1];
@@ -381,13 +384,9 @@ struct SdfBwdSmem {
     float tiles[kWaves][2][kTileWords];
 };
 
-// GIVEN: the masks come from the forward kernel (a.masks).  The forward pass is then recomputed
-// only for its values, which enter weight gradients and further products at gradient tolerance:
-// two terms and three products like the rest of this kernel, and a plain ReLU (where its sign
-// differs from the given mask the value is within rounding of zero); every masked product uses
-// the given masks.  Without them the forward pass is recomputed in the forward kernel's own
-// arithmetic, which yields the same masks bit for bit.
-template <int D, int K, bool GIVEN>
+// Without masks from the forward kernel: the forward pass is recomputed in the forward kernel's own arithmetic, which
+// yields the same masks bit for bit, and one wavefront carries a tile through both orders.
+template <int D, int K>
 __global__ __launch_bounds__(kThreads) void sdf_bwd_kernel(SdfArgs a) {
     __shared__ SdfBwdSmem<D, K> sm;
     SdfWeights<D, K, true>& w = sm.w;
@@ -430,13 +429,7 @@ __global__ __launch_bounds__(kThreads) void sdf_bwd_kernel(SdfArgs a) {
             dK[0][0] = a_.x; dK[0][1] = a_.y; dK[0][2] = a_.z; dK[0][3] = a_.w;
             dK[0][4] = b_.x; dK[0][5] = b_.y; dK[0][6] = b_.z; dK[0][7] = b_.w;
         }
-        // given masks are first needed after the forward pass has been recomputed
-        uint32_t m1 = 0u, m_last = 0u;
-        if (GIVEN && valid) {
-            // masks and the adjoint of (d,g) are read here for the last time in the step: non-temporal loads
-            m1 = __builtin_nontemporal_load(a.masks + mask_word(0, a.n, i, h));
-            m_last = K == 3 ? __builtin_nontemporal_load(a.masks + mask_word(1, a.n, i, h)) : m1;
-        }
+        uint32_t m1, m_last;
         float nb3[3] = {0.f, 0.f, 0.f};
         if (valid) { nb3[0] = a.d_normal[3 * i]; nb3[1] = a.d_normal[3 * i + 1]; nb3[2] = a.d_normal[3 * i + 2]; }
         const JacRegs<D> J = load_jac<D>(a.jac, a.n, i, valid, a.active_levels, h);
@@ -445,19 +438,17 @@ __global__ __launch_bounds__(kThreads) void sdf_bwd_kernel(SdfArgs a) {
             x_next = load_levels<D>(a.enc, a.n, in, tile + stride < tiles && in < a.n, a.active_levels, h);
         }
         // ---- forward pass again
-        constexpr int PF = GIVEN ? 2 : 3;
+        constexpr int PF = 3;
         v16f a1[2], a2[2];
         Split<1, PF> px;         // x0: input of the first layer, factor of its weight gradient
         Split<2, PF> p1;         // a1 likewise for the second layer
         split(x0, px);
         matvec_split<2, KS1, 3, PF>(w.H1f, px, a1, lane);
-        if (GIVEN) relu<2>(a1);
-        else m_last = m1 = relu_mask<2>(a1);
+        m_last = m1 = relu_mask<2>(a1);
         split(a1, p1);
         if (K == 3) {
             matvec_split<2, 4, 3, PF>(w.H2f, p1, a2, lane);
-            if (GIVEN) relu<2>(a2);
-            else m_last = relu_mask<2>(a2);
+            m_last = relu_mask<2>(a2);
         }
         // t_0 = (de/dx) dL/dn, computed now so that the Jacobian's registers are free again
         v16f t0[1] = {apply_jac_regs<D>(J, nb3)};
@@ -586,6 +577,344 @@ __global__ __launch_bounds__(kThreads) void sdf_bwd_kernel(SdfArgs a) {
     }
 }
 
+// ------------------------------------------------------------------------------------------
+// With the masks from the forward kernel (a.masks) the two orders of a tile have nothing in common but the masks: the
+// first-order chain (activations, delta sweep) reads enc and dL/d(d,g), the second-order one (S and t sweeps) the
+// Jacobian and dL/dn.  So two wavefronts share a tile, one per order, and each needs only its own working registers beside
+// its copy of the weight gradients: 256 registers instead of 512, eight wavefronts a workgroup, two per SIMD (waves w and
+// w + 4 share a SIMD, so every SIMD holds one of each), and one's waits for LDS, memory and matrix results are filled by
+// the other.  The chains are about equally long: 114 and 96 matrix instructions of 32 clocks.
+// Everything here is at gradient tolerance: two terms and three products, a plain ReLU for the recomputed
+// activations (where its sign differs from the given mask the value is within rounding of zero).
+constexpr int kPairThreads = 512;
+constexpr int kPairs = kPairThreads / 128;        // tiles a workgroup works on
+
+// Accesses of a tile: a uniform address (scalar registers: array, tile, level) plus a 32-bit byte offset of the lane.  Written
+// with one 64-bit index per lane, the compiler kept two dozen addresses in vector registers through the whole loop and spilled
+// them.  The largest lane offset is 48 n bytes (upper lane half, Jacobian), so n stays below 2^26 here.
+constexpr int64_t kPairMaxPoints = (int64_t)1 << 26;
+
+template <typename V>
+__device__ __forceinline__ V* lane_address(V* base, uint32_t bytes) {
+    typedef std::conditional_t<std::is_const_v<V>, const char, char> Byte;
+    return reinterpret_cast<V*>(reinterpret_cast<Byte*>(base) + bytes);
+}
+
+// The same word in another register, as far as the compiler can tell: what is worked out from it is not worked out ahead
+// of the loop or shared with an earlier use, and so holds no register in between (expanded masks: 32 of them).
+__device__ __forceinline__ uint32_t again(uint32_t x) {
+    uint32_t r;
+    asm volatile("v_mov_b32 %0, %1" : "=v"(r) : "v"(x));
+    return r;
+}
+
+__device__ __forceinline__ int64_t again(int64_t x) {             // x is uniform
+    int64_t r;
+    asm volatile("s_mov_b64 %0, %1" : "=s"(r) : "s"(x));
+    return r;
+}
+
+typedef float f2v __attribute__((ext_vector_type(2)));
+
+// Levels 4 g + 2 h + u of the tile's points as in load_levels, store_levels and load_jac, first: the tile's first point.
+// Loads are unconditional: a lane without a point reads the tile's last one, a level beyond the active ones is read in
+// the lower lane half's place (in bounds: the arrays hold every level), and what does not count is replaced by zeros
+// afterwards.  A branch per level instead kept 48 zeroed registers alive across the loads.
+__device__ __forceinline__ int last_point(int64_t n, int64_t first) { return n - first < 32 ? (int)(n - first) - 1 : 31; }
+
+template <int D>
+__device__ __forceinline__ v16f load_levels_tile(const float* __restrict__ src, int64_t n, int64_t first, int active, int j, int h) {
+    v16f x = zero16();
+    const f2v* tile = reinterpret_cast<const f2v*>(src) + first;
+    const int64_t plane = again(n);
+    const int last = last_point(n, first);
+    const uint32_t off = 8u * (uint32_t)min(j, last), upper = again(h ? 16u * (uint32_t)n : 0u);
+#pragma unroll
+    for (int g = 0; g < D / 8; ++g)
+#pragma unroll
+        for (int u = 0; u < 2; ++u) {
+            const bool on = 4 * g + 2 * h + u < active;
+            const f2v v = *lane_address(tile + (4 * g + u) * plane, off + (on ? upper : 0u));
+            x[4 * g + 2 * u] = on && j <= last ? v.x : 0.f;
+            x[4 * g + 2 * u + 1] = on && j <= last ? v.y : 0.f;
+        }
+    return x;
+}
+
+template <int D, bool STREAM>
+__device__ __forceinline__ void store_levels_tile(float* __restrict__ dst, int64_t n, int64_t first, bool valid, const v16f& x, int j, int h) {
+    if (!valid) return;
+    f2v* tile = reinterpret_cast<f2v*>(dst) + first;
+    const int64_t plane = again(n);
+    const uint32_t off = again(8u * ((uint32_t)j + 2u * (uint32_t)h * (uint32_t)n));
+#pragma unroll
+    for (int g = 0; g < D / 8; ++g)
+#pragma unroll
+        for (int u = 0; u < 2; ++u) {
+            const f2v v = {x[4 * g + 2 * u], x[4 * g + 2 * u + 1]};
+            if (STREAM) __builtin_nontemporal_store(v, lane_address(tile + (4 * g + u) * plane, off));
+            else *lane_address(tile + (4 * g + u) * plane, off) = v;
+        }
+}
+
+// (de/dx)^T dL/de of the tile's points: this lane's levels
+template <int D>
+__device__ __forceinline__ void contract_jac_tile(const float* __restrict__ jac, int64_t n, int64_t first, int active, int j, int h,
+                                                  const v16f& x, float out[3]) {
+    out[0] = out[1] = out[2] = 0.f;
+    const f2v* tile = reinterpret_cast<const f2v*>(jac) + first;
+    const int64_t plane = again(n);
+    const int last = last_point(n, first);
+    const uint32_t off = 8u * (uint32_t)min(j, last), upper = again(h ? 48u * (uint32_t)n : 0u);
+#pragma unroll
+    for (int g = 0; g < D / 8; ++g)
+#pragma unroll
+        for (int u = 0; u < 2; ++u) {
+            const bool on = 4 * g + 2 * h + u < active;
+            f2v J[3];
+#pragma unroll
+            for (int c = 0; c < 3; ++c) J[c] = *lane_address(tile + (3 * (4 * g + u) + c) * plane, off + (on ? upper : 0u));
+            const float x0 = x[4 * g + 2 * u], x1 = x[4 * g + 2 * u + 1];
+            out[0] += on ? x0 * J[0].x + x1 * J[1].y : 0.f;
+            out[1] += on ? x0 * J[0].y + x1 * J[2].x : 0.f;
+            out[2] += on ? x0 * J[1].x + x1 * J[2].y : 0.f;
+        }
+}
+
+// t_0 = (de/dx) dL/dn of the tile's points
+template <int D>
+__device__ __forceinline__ v16f apply_jac_tile(const float* __restrict__ jac, int64_t n, int64_t first, int active, int j, int h, const float v[3]) {
+    f2v J[D / 4][3];           // (J00,J01) (J02,J10) (J11,J12) per level of this lane
+    const f2v* tile = reinterpret_cast<const f2v*>(jac) + first;
+    const int64_t plane = again(n);
+    const int last = last_point(n, first);
+    const uint32_t off = 8u * (uint32_t)min(j, last), upper = again(h ? 48u * (uint32_t)n : 0u);
+#pragma unroll
+    for (int g = 0; g < D / 8; ++g)
+#pragma unroll
+        for (int u = 0; u < 2; ++u) {
+            const bool on = 4 * g + 2 * h + u < active;
+            const uint32_t o = off + (on ? upper : 0u);
+#pragma unroll
+            for (int c = 0; c < 3; ++c) J[2 * g + u][c] = __builtin_nontemporal_load(lane_address(tile + (3 * (4 * g + u) + c) * plane, o));
+        }
+    v16f t = zero16();
+#pragma unroll
+    for (int g = 0; g < D / 8; ++g)
+#pragma unroll
+        for (int u = 0; u < 2; ++u) {
+            const bool on = 4 * g + 2 * h + u < active && j <= last;
+            const f2v a = J[2 * g + u][0], b = J[2 * g + u][1], c = J[2 * g + u][2];
+            const float t0 = a.x * v[0] + a.y * v[1] + b.x * v[2], t1 = b.y * v[0] + c.x * v[1] + c.y * v[2];
+            t[4 * g + 2 * u] = on ? t0 : 0.f;
+            t[4 * g + 2 * u + 1] = on ? t1 : 0.f;
+        }
+    return t;
+}
+
+template <int D, int K>
+struct SdfPairSmem {
+    SdfWeights<D, K, true, 2> w;
+    alignas(16) unsigned char tiles[2 * kPairs][kTilesPerWave * kBlockTile];
+};
+
+template <int D, int K>
+__device__ __forceinline__ void sdf_first_order(const SdfArgs& a, const SdfWeights<D, K, true, 2>& w, unsigned char* tile_mem,
+                                                int slot, int lane, v16f (*G1)[1], v16f (*G2)[2], v4f* GL) {
+    constexpr int KS1 = D / 16;
+    const int j = lane & 31, h = lane >> 5;
+    float* Xt = reinterpret_cast<float*>(tile_mem);
+    float* Zt = Xt + 32 * kLd64;
+    static_assert((32 * kLd64 + 32 * kLd16) * 4 <= kTilesPerWave * kBlockTile, "fp32 tiles fit the wave's memory");
+    const int64_t tiles = (a.n + 31) / 32;
+    const int64_t stride = (int64_t)gridDim.x * kPairs;
+    for (int64_t tile = (int64_t)blockIdx.x * kPairs + slot; tile < tiles; tile += stride) {
+        const int64_t i = tile * 32 + j;
+        const bool valid = i < a.n;
+        v16f x0[1] = {load_levels_tile<D>(a.enc, a.n, tile * 32, a.active_levels, j, h)};
+        v16f dK[1] = {zero16()};
+        uint32_t m1 = 0u, m_last = 0u;
+        if (valid) {
+            // read here for the last time in the step: non-temporal loads
+            typedef float f4v __attribute__((ext_vector_type(4)));
+            const f4v* row = lane_address(reinterpret_cast<const f4v*>(a.d_y) + tile * 128, 64u * j + 16u * h);
+            const f4v a_ = __builtin_nontemporal_load(row), b_ = __builtin_nontemporal_load(row + 2);
+            dK[0][0] = a_.x; dK[0][1] = a_.y; dK[0][2] = a_.z; dK[0][3] = a_.w;
+            dK[0][4] = b_.x; dK[0][5] = b_.y; dK[0][6] = b_.z; dK[0][7] = b_.w;
+            const uint32_t* words = a.masks + tile * 64;
+            m1 = *lane_address(words, 8u * j + 4u * h);
+            m_last = K == 3 ? *lane_address(words + 2 * a.n, 8u * j + 4u * h) : m1;
+        }
+        v16f a1[2], a2[2], d2[2], d1[2], de[1];
+        Split<1, 2> px, pk;      // x0: input of the first layer, factor of its weight gradient
+        Split<2, 2> p1, pd;      // a1 likewise for the second layer
+        split(x0, px);
+        matvec_split<2, KS1, 2, 2>(w.H1f, px, a1, lane);
+        relu<2>(a1);
+        if (K == 3) {
+            split(a1, p1);
+            matvec_split<2, 4, 2, 2>(w.H2f, p1, a2, lane);
+            relu<2>(a2);
+        }
+        wave_lds_fence();
+        stage16<kLd16>(Zt, dK[0], j, h);
+        stage<2, kLd64>(Xt, K == 3 ? a2 : a1, j, h);
+        wave_lds_fence();
+        outer_accumulate16<2, kLd16, kLd64>(GL, Zt, Xt, lane);
+        split(dK, pk);
+        matvec_split<2, 1, 2, 2>(w.HLt, pk, d2, lane);
+        apply_mask<2>(d2, m_last);
+        if (K == 3) {
+            split(d2, pd);
+            outer_accumulate_points<2, 2>(G2, pd, p1, tile_mem, lane);
+            matvec_split<2, 4, 2, 2>(w.H2t, pd, d1, lane);
+            apply_mask<2>(d1, m1);
+        } else {
+            d1[0] = d2[0]; d1[1] = d2[1];
+        }
+        split(d1, pd);
+        outer_accumulate_points<2, 1>(G1, pd, px, tile_mem, lane);
+        matvec_split<1, 4, 2, 2>(w.H1t, pd, de, lane);
+        if (a.stream_q) store_levels_tile<D, true>(a.d_enc, a.n, tile * 32, valid, de[0], j, h);      // as for q in the forward kernel
+        else store_levels_tile<D, false>(a.d_enc, a.n, tile * 32, valid, de[0], j, h);
+        if (a.d_pos) {
+            float dp[3];
+            contract_jac_tile<D>(a.jac, a.n, tile * 32, a.active_levels, j, h, de[0], dp);
+#pragma unroll
+            for (int c = 0; c < 3; ++c) dp[c] += __shfl_xor(dp[c], 32);
+            if (valid && h == 0) {
+                a.d_pos[3 * i + 0] += dp[0]; a.d_pos[3 * i + 1] += dp[1]; a.d_pos[3 * i + 2] += dp[2];
+            }
+        }
+    }
+}
+
+template <int D, int K>
+__device__ __forceinline__ void sdf_second_order(const SdfArgs& a, const SdfWeights<D, K, true, 2>& w, unsigned char* tile_mem,
+                                                 int slot, int lane, v16f (*G1)[1], v16f (*G2)[2], v4f* GL) {
+    constexpr int KS1 = D / 16;
+    const int j = lane & 31, h = lane >> 5;
+    v16f tsum[2] = {zero16(), zero16()};
+    const int64_t tiles = (a.n + 31) / 32;
+    const int64_t stride = (int64_t)gridDim.x * kPairs;
+    for (int64_t tile = (int64_t)blockIdx.x * kPairs + slot; tile < tiles; tile += stride) {
+        const int64_t i = tile * 32 + j;
+        const bool valid = i < a.n;
+        uint32_t m1 = 0u, m_last = 0u;
+        float nb3[3] = {0.f, 0.f, 0.f};
+        if (valid) {
+            const uint32_t* words = a.masks + tile * 64;
+            m1 = *lane_address(words, 8u * j + 4u * h);
+            m_last = K == 3 ? *lane_address(words + 2 * a.n, 8u * j + 4u * h) : m1;
+            const float* nb = lane_address(a.d_normal + tile * 96, 12u * j);
+            nb3[0] = nb[0]; nb3[1] = nb[1]; nb3[2] = nb[2];
+        }
+        // The t sweep first: of its vectors only t_0 outlives the product with S_{K-1}, and S_{K-1} does not outlive the
+        // product that turns it into S_1 (working registers: 104 at most beside the 128 of the sums).
+        v16f t0[1] = {apply_jac_tile<D>(a.jac, a.n, tile * 32, a.active_levels, j, h, nb3)};
+        v16f s1[2], t1[2], t2[2];
+        Split<1, 2> pt;
+        Split<2, 2> ps, pd;
+        split(t0, pt);
+        __builtin_amdgcn_sched_barrier(0);
+        matvec_split<2, KS1, 2, 2>(w.H1f, pt, t1, lane);
+        apply_mask<2>(t1, m1);
+        if (K == 3) {
+            split(t1, pd);
+            __builtin_amdgcn_sched_barrier(0);
+            matvec_split<2, 4, 2, 2>(w.H2f, pd, t2, lane);
+            apply_mask<2>(t2, m_last);
+            tsum[0] += t2[0]; tsum[1] += t2[1];
+            __builtin_amdgcn_sched_barrier(0);
+            last_row_masked(w.HLrow0, again(m_last), h, ps);
+            outer_accumulate_points<2, 2>(G2, ps, pd, tile_mem, lane);
+            matvec_split<2, 4, 2, 2>(w.H2t, ps, s1, lane);
+            apply_mask<2>(s1, again(m1));
+            split(s1, ps);
+        } else {
+            tsum[0] += t1[0]; tsum[1] += t1[1];
+            last_row_masked(w.HLrow0, m_last, h, ps);
+        }
+        outer_accumulate_points<2, 1>(G1, ps, pt, tile_mem, lane);
+    }
+    // S_K is the unit row selecting the SDF output: row 0 of the last matrix's gradient gets the sum of t_{K-1} over
+    // points, through one outer product with a one-hot factor
+    float* Xt = reinterpret_cast<float*>(tile_mem);
+    float* Zt = Xt + 32 * kLd64;
+    v16f onehot = zero16();
+    if (h == 0) onehot[0] = 1.f;
+    wave_lds_fence();
+    stage16<kLd16>(Zt, onehot, j, h);
+    stage<2, kLd64>(Xt, tsum, j, h);
+    wave_lds_fence();
+    outer_accumulate16<2, kLd16, kLd64>(GL, Zt, Xt, lane);
+}
+
+template <int D, int K>
+__global__ __launch_bounds__(kPairThreads) void sdf_bwd_pair_kernel(SdfArgs a) {
+    __shared__ SdfPairSmem<D, K> sm;
+    load_weights<D, K, true, kPairThreads, 2>(sm.w, a);
+    const int lane = threadIdx.x & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);   // the same for all lanes: keeps tile indices and addresses scalar
+    const int slot = wave % kPairs;
+    const bool second = wave >= kPairs;
+    v16f G1[2][1], G2[2][2];
+    v4f GL[4];                 // gradient of the last matrix [16][64]: four blocks of 16 columns
+#pragma unroll
+    for (int mb = 0; mb < 2; ++mb) {
+        G1[mb][0] = zero16();
+        G2[mb][0] = zero16(); G2[mb][1] = zero16();
+    }
+#pragma unroll
+    for (int cb = 0; cb < 4; ++cb) GL[cb] = v4f{0.f, 0.f, 0.f, 0.f};
+    if (second) sdf_second_order<D, K>(a, sm.w, sm.tiles[wave], slot, lane, G1, G2, GL);
+    else sdf_first_order<D, K>(a, sm.w, sm.tiles[wave], slot, lane, G1, G2, GL);
+    __syncthreads();
+    // ---- the waves of the second order leave their sums in LDS, their partners add their own, and the block's sums go
+    // to global memory in the gradients' own order
+    float* scratch = reinterpret_cast<float*>(&sm);
+    constexpr int kVecs = K == 3 ? 7 : 3;
+    static_assert(sizeof(sm) >= kPairs * kVecs * 1024 * sizeof(float), "scratch for the block sum");
+    v16f gl;                   // the four 16-column blocks of GL side by side
+#pragma unroll
+    for (int cb = 0; cb < 4; ++cb)
+#pragma unroll
+        for (int v = 0; v < 4; ++v) gl[4 * cb + v] = GL[cb][v];
+    const v16f* all[kVecs];
+    all[0] = &G1[0][0]; all[1] = &G1[1][0]; all[2] = &gl;
+    if constexpr (K == 3) { all[3] = &G2[0][0]; all[4] = &G2[0][1]; all[5] = &G2[1][0]; all[6] = &G2[1][1]; }
+    float* own = scratch + slot * kVecs * 1024 + lane;
+    if (second) {
+#pragma unroll
+        for (int k = 0; k < kVecs; ++k)
+#pragma unroll
+            for (int r = 0; r < 16; ++r) own[(k * 16 + r) * 64] = (*all[k])[r];
+    }
+    __syncthreads();
+    if (!second) {
+#pragma unroll
+        for (int k = 0; k < kVecs; ++k)
+#pragma unroll
+            for (int r = 0; r < 16; ++r) own[(k * 16 + r) * 64] += (*all[k])[r];
+    }
+    __syncthreads();
+    constexpr int kOf1 = 64 * D, kOf2 = K == 3 ? 64 * 64 : 0, kOfL = 16 * 64;
+    constexpr int kChunks = (kOf1 + kOf2 + kOfL) / kPairThreads;
+    static_assert((kOf1 + kOf2 + kOfL) % kPairThreads == 0, "whole chunks");
+    for (int k = 0; k < kChunks; ++k) {
+        const int x = rotated_chunk<kChunks>(k) * kPairThreads + threadIdx.x;
+        if (x < kOf1) {
+            atomicAdd(a.dH[0] + x, block_element_points<kPairs, kVecs, 1>(scratch, 0, x / D, x % D));
+        } else if (x < kOf1 + kOf2) {
+            const int e = x - kOf1;
+            atomicAdd(a.dH[1] + e, block_element_points<kPairs, kVecs, 2>(scratch, 3, e >> 6, e & 63));
+        } else {
+            const int e = x - kOf1 - kOf2;
+            atomicAdd(a.dH[K - 1] + e, block_element16<kPairs, kVecs>(scratch, 2, e >> 6, e & 63));
+        }
+    }
+}
+
 template <int D, int K>
 int run_fwd(const SdfArgs& a, hipStream_t st) {
     const int64_t tiles = (a.n + 31) / 32;
@@ -598,13 +927,12 @@ int run_fwd(const SdfArgs& a, hipStream_t st) {
 template <int D, int K>
 int run_bwd(const SdfArgs& a, hipStream_t st) {
     const int64_t tiles = (a.n + 31) / 32;
-    const int64_t want = (tiles + kWaves - 1) / kWaves;
-    if (a.masks) {
-        const int blocks = persistent_blocks((const void*)sdf_bwd_kernel<D, K, true>, kThreads, want);
-        hipLaunchKernelGGL((sdf_bwd_kernel<D, K, true>), dim3(blocks), dim3(kThreads), 0, st, a);
+    if (a.masks && a.n < kPairMaxPoints) {
+        const int blocks = persistent_blocks((const void*)sdf_bwd_pair_kernel<D, K>, kPairThreads, (tiles + kPairs - 1) / kPairs);
+        hipLaunchKernelGGL((sdf_bwd_pair_kernel<D, K>), dim3(blocks), dim3(kPairThreads), 0, st, a);
     } else {
-        const int blocks = persistent_blocks((const void*)sdf_bwd_kernel<D, K, false>, kThreads, want);
-        hipLaunchKernelGGL((sdf_bwd_kernel<D, K, false>), dim3(blocks), dim3(kThreads), 0, st, a);
+        const int blocks = persistent_blocks((const void*)sdf_bwd_kernel<D, K>, kThreads, (tiles + kWaves - 1) / kWaves);
+        hipLaunchKernelGGL((sdf_bwd_kernel<D, K>), dim3(blocks), dim3(kThreads), 0, st, a);
     }
     return check_launch("sdf backward");
 }
