@@ -117,8 +117,8 @@ int neus2_sdf_fwd_grad(const neus2_config* cfg, const float* enc, const float* j
 
 /* The SDF network with more matrices than neus2_sdf_fwd_grad / neus2_sdf_mlp_bwd hold fused (the
  * deeper networks of the paper's Fig. 7, "speed-up of our 2nd-order derivative ... across MLP
- * layer numbers"): the same quantities, computed layer by layer, one launch per matrix and
- * direction, the per-point vectors passing through a workspace.
+ * layer numbers"): the same quantities, computed in runs of up to six layers a launch (two with
+ * weight gradients), the per-point vectors passing through a workspace between runs.
  *   n_mats K = 2..NEUS2_DEEP_MAX_MATS matrices: H[0] [64][enc_dim], H[1..K-2] [64][64],
  *   H[K-1] [16][64] (row-major, device; the array of pointers is host memory); enc_dim 16 or 32.
  *   enc [device, (enc_dim/2)*n*2], jac [device, (enc_dim/2)*3*n*2], q, d_enc like enc; layouts as

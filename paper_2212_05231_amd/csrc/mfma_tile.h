@@ -560,33 +560,4 @@ __device__ __forceinline__ float block_element_points(const float* __restrict__ 
     return block_element<WAVES, V, XB>(scratch, first, tile_position(o), tile_position(i));
 }
 
-// Sum V register vectors over the block's WAVES waves such that every wave ends up with a share of
-// the totals: wave w holds, in registers 16/WAVES * w .. 16/WAVES * (w+1) - 1 of every vector, the
-// block's sums (its other registers keep its own partial sums).  All waves then flush their share
-// in parallel.  scratch: WAVES * V * 1024 floats of LDS nobody reads any more; one barrier inside,
-// and the caller has put one before (the scratch overlays memory other waves may still be using).
-// Every thread of the block must call it.
-template <int WAVES, int V>
-__device__ __forceinline__ void block_sum_shared(float* __restrict__ scratch, v16f* (&vec)[V], int wave, int lane) {
-    static_assert(16 % WAVES == 0, "registers are dealt out evenly");
-    constexpr int kShare = 16 / WAVES;
-#pragma unroll
-    for (int k = 0; k < V; ++k)
-#pragma unroll
-        for (int r = 0; r < 16; ++r) scratch[((wave * V + k) * 16 + r) * 64 + lane] = (*vec[k])[r];
-    __syncthreads();
-#pragma unroll
-    for (int k = 0; k < V; ++k)
-#pragma unroll
-        for (int q = 0; q < kShare; ++q) {
-            float sum = 0.f;
-#pragma unroll
-            for (int w = 0; w < WAVES; ++w) sum += scratch[((w * V + k) * 16 + wave * kShare + q) * 64 + lane];
-            // written through a loop over constant register numbers: the share's first register depends on the wave
-#pragma unroll
-            for (int r = 0; r < 16; ++r)
-                if (r == wave * kShare + q) (*vec[k])[r] = sum;
-        }
-}
-
 }  // namespace neus2

@@ -154,6 +154,19 @@ __device__ __forceinline__ void store_levels(float* __restrict__ dst, int64_t n,
         }
 }
 
+// the levels below active only (an array of a narrower encoding has no more)
+__device__ __forceinline__ void store_levels_active(float* __restrict__ dst, int64_t n, int64_t i, bool valid, int active, int h,
+                                                    const v16f& x) {
+#pragma unroll
+    for (int g = 0; g < 4; ++g)
+#pragma unroll
+        for (int u = 0; u < 2; ++u) {
+            const int level = 4 * g + 2 * h + u;
+            if (valid && level < active)
+                reinterpret_cast<float2*>(dst)[(int64_t)level * n + i] = make_float2(x[4 * g + 2 * u], x[4 * g + 2 * u + 1]);
+        }
+}
+
 // out_a = sum over this lane's features of x_k * J[k][a]   (J = de/dx; per level three planes [n] of
 // pairs: (J00,J01), (J02,J10), (J11,J12))
 template <int D>
@@ -939,236 +952,297 @@ int run_bwd(const SdfArgs& a, hipStream_t st) {
 
 // ------------------------------------------------------------------------------------------
 // Networks deeper than the fused kernels hold (up to eight hidden layers of 64: the depths of the
-// paper's Fig. 7), layer by layer.  The fused kernels keep every matrix in LDS and every weight
-// gradient in registers, which stops at two hidden layers; here ONE matrix is in LDS per launch
-// and the per-point vectors pass from launch to launch through a workspace in HBM, each lane
-// writing the 32 registers it holds as 128 consecutive bytes (vector v of point tile t, lane l:
-// floats ((t * 64 + l) * 32 ...)).  Every matrix is used as 64 x 64 (the first one's missing
-// columns and the last one's missing rows are zeros), so one kernel serves every layer.
-//   forward launch l:  a_l = G_l H_l a_{l-1}  (six-product arithmetic, writes the mask word)
-//                      t_l = G_l H_l t_{l-1}  (with WITH_T; t_0 = (de/dx) dL/dn)
-//   reverse launch l:  dH_l += delta_l a_{l-1}^T + S_l^T t_{l-1}^T   (with GRAD)
-//                      S_{l-1} = (H_l^T S_l) G_{l-1},  delta_{l-1} = G_{l-1} H_l^T delta_l
+// paper's Fig. 7), in runs of consecutive layers: a launch keeps the matrices of its run in LDS (six of three terms at
+// most) and a tile's vectors in registers from layer to layer; between launches they pass through a workspace in HBM.
+// One layer a launch instead, each lane writing its 32 registers as 128 consecutive bytes, moved 4.2 GB where 2.2 are
+// needed, every access instruction in 64 cache lines: eight hidden layers at 2^17 points, forward and backward, took
+// 1243 us, now 617.  Bound by the vectors that the backward call stores and reads back.
+// Every matrix is used as 64 x 64 (the first one's missing columns and the last one's missing rows are zeros), so one
+// kernel serves every layer.
+//   forward run:   a_l = G_l H_l a_{l-1}  (six-product arithmetic, writes the mask words)
+//                  t_l = G_l H_l t_{l-1}  (WITH_T; t_0 = (de/dx) dL/dn)
+//   reverse run:   S_{l-1} = (H_l^T S_l) G_{l-1}, down to dd/de and the normal
+//   gradient run:  dH_l += delta_l a_{l-1}^T + S_l^T t_{l-1}^T
+//                  S_{l-1} as above, delta_{l-1} = G_{l-1} H_l^T delta_l
 // with S_K = the unit row of the SDF output and delta_K = dL/d(d,g): Theorem 1 and Eqs. 7-8 as in
-// the fused kernels, Definition 1's vectors one layer at a time.
+// the fused kernels, Definition 1's vectors.
+constexpr int kDeepThreads = 512;                  // two wavefronts per SIMD: one's memory waits under the other's products
+constexpr int kDeepWaves = kDeepThreads / 64;
+constexpr int kDeepRun = 6;                        // layers a run holds at most
+constexpr int kDeepGradRun = 2;                    // of a gradient run: their sums take 64 registers a layer
+
+// The workspace: vectors of 32 floats per lane, two lanes a point, in the order [tile][register quad][lane][4], so that
+// an access instruction covers 1 KB on end: a_0, t_0, a_1, t_1, ..., four vectors that runs hand on, then the mask words
+// [layer][tile * 64 + lane].  (a_0 is the encoding itself and t_0 has 32 registers' upper half empty: left unwritten.)
 struct DeepArgs {
-    const float* W; int out_dim, in_dim;       // H_l [out_dim][in_dim], row-major
-    int64_t n; int levels;                     // points; levels of the encoding (input width / 2)
-    bool first, last;                          // l == 1, l == K
+    const float* H[NEUS2_DEEP_MAX_MATS];
+    int n_mats, enc_dim;
+    int first, count;                      // layers first .. first + count - 1 (numbered from 0); reverse kinds start at the last
+    int64_t n, vec;                        // points; floats of a workspace vector
+    float* ws;
     const float* enc; const float* jac; const float* d_normal; const float* d_y;
-    const float* a_in; const float* t_in; const float* s_in; const float* d_in;     // lane layout
-    float* a_out; float* t_out; float* s_out; float* d_out;                         // lane layout
-    float* a0_out; float* t0_out;              // forward, first layer: its inputs in lane layout, for the reverse launch
-    uint32_t* mask_out; const uint32_t* mask_in;   // one word per lane: [tile * 64 + lane]
-    float* y; float* q; float* normal; float* d_enc; float* dW;
+    float* y; float* q; float* normal; float* d_enc;
+    float* dH[NEUS2_DEEP_MAX_MATS];
+
+    __device__ __forceinline__ int in_dim(int l) const { return l == 0 ? enc_dim : 64; }
+    __device__ __forceinline__ int out_dim(int l) const { return l == n_mats - 1 ? 16 : 64; }
+    __device__ __forceinline__ float* a_vec(int l) const { return ws + 2 * l * vec; }
+    __device__ __forceinline__ float* t_vec(int l) const { return ws + (2 * l + 1) * vec; }
+    __device__ __forceinline__ float* passed(int k) const { return ws + (2 * n_mats + k) * vec; }
+    __device__ __forceinline__ uint32_t* masks(int l, int64_t tile) const {
+        return reinterpret_cast<uint32_t*>(ws + (2 * n_mats + 4) * vec) + ((int64_t)l * ((n + 31) / 32) + tile) * 64;
+    }
 };
 
-__device__ __forceinline__ void load_lane(const float* __restrict__ base, int64_t tile, int lane, v16f* v) {
-    const float4* p = reinterpret_cast<const float4*>(base + (tile * 64 + lane) * 32);
+template <int NB>
+__device__ __forceinline__ void load_lane(const float* base, int64_t tile, int lane, v16f* v) {
+    const float4* p = reinterpret_cast<const float4*>(base) + tile * 512 + lane;
 #pragma unroll
-    for (int b = 0; b < 2; ++b)
+    for (int b = 0; b < 2; ++b) {
+        if (b >= NB) { v[b] = zero16(); continue; }
 #pragma unroll
         for (int k = 0; k < 4; ++k) {
-            const float4 f = p[4 * b + k];
+            const float4 f = p[64 * (4 * b + k)];
             v[b][4 * k] = f.x; v[b][4 * k + 1] = f.y; v[b][4 * k + 2] = f.z; v[b][4 * k + 3] = f.w;
         }
+    }
 }
 
-__device__ __forceinline__ void store_lane(float* __restrict__ base, int64_t tile, int lane, const v16f* v) {
-    float4* p = reinterpret_cast<float4*>(base + (tile * 64 + lane) * 32);
+template <int NB>
+__device__ __forceinline__ void store_lane(float* base, int64_t tile, int lane, const v16f* v) {
+    float4* p = reinterpret_cast<float4*>(base) + tile * 512 + lane;
 #pragma unroll
-    for (int b = 0; b < 2; ++b)
+    for (int b = 0; b < NB; ++b)
 #pragma unroll
-        for (int k = 0; k < 4; ++k) p[4 * b + k] = make_float4(v[b][4 * k], v[b][4 * k + 1], v[b][4 * k + 2], v[b][4 * k + 3]);
+        for (int k = 0; k < 4; ++k) p[64 * (4 * b + k)] = make_float4(v[b][4 * k], v[b][4 * k + 1], v[b][4 * k + 2], v[b][4 * k + 3]);
+}
+
+// The matrices of layers l0, l0 + step, ... (COUNT at most, count of them) side by side in LDS; ROW_FASTEST: transposed.
+// All are fetched before the first is stored.
+template <int P, int COUNT, bool TRANSPOSED>
+__device__ __forceinline__ void deep_matrices(const DeepArgs& a, int l0, int step, int count, unsigned char* mats) {
+    typedef SplitMatrix<4, P> M;
+    typename M::template Fill<64, kDeepThreads, TRANSPOSED> f[COUNT];
+#pragma unroll
+    for (int k = 0; k < COUNT; ++k) {
+        if (k >= count) break;
+        const int l = l0 + k * step, od = a.out_dim(l), id = a.in_dim(l);
+        const float* __restrict__ W = a.H[l];
+        f[k].load(threadIdx.x, [&](int r, int c) {
+            const int o = TRANSPOSED ? c : r, i = TRANSPOSED ? r : c;
+            return o < od && i < id ? W[o * id + i] : 0.f;
+        });
+    }
+#pragma unroll
+    for (int k = 0; k < COUNT; ++k) {
+        if (k >= count) break;
+        f[k].store(mats + k * 64 * M::kLd, threadIdx.x);
+    }
+    __syncthreads();
 }
 
 template <bool WITH_T>
-__global__ __launch_bounds__(kThreads) void deep_forward_kernel(DeepArgs a) {
-    typedef SplitMatrix<4, 3> M;
-    __shared__ alignas(16) unsigned char Wf[64 * M::kLd];
-    {
-        typename M::template Fill<64, kThreads, false> f;
-        const float* __restrict__ W = a.W;
-        const int od = a.out_dim, id = a.in_dim;
-        f.load(threadIdx.x, [&](int o, int i) { return (o < od && i < id) ? W[o * id + i] : 0.f; });
-        f.store(Wf, threadIdx.x);
-        __syncthreads();
-    }
+__global__ __launch_bounds__(kDeepThreads) void deep_forward_kernel(DeepArgs a) {
+    constexpr int kMatrix = 64 * SplitMatrix<4, 3>::kLd;
+    __shared__ alignas(16) unsigned char mats[kDeepRun * kMatrix];
+    deep_matrices<3, kDeepRun, false>(a, a.first, 1, a.count, mats);
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int j = lane & 31, h = lane >> 5;
     const int64_t tiles = (a.n + 31) / 32;
-    for (int64_t tile = (int64_t)blockIdx.x * kWaves + wave; tile < tiles; tile += (int64_t)gridDim.x * kWaves) {
+    for (int64_t tile = (int64_t)blockIdx.x * kDeepWaves + wave; tile < tiles; tile += (int64_t)gridDim.x * kDeepWaves) {
         const int64_t i = tile * 32 + j;
         const bool valid = i < a.n;
-        v16f x[2], z[2];
-        if (a.first) {
-            x[0] = load_levels<32>(a.enc, a.n, i, valid, a.levels, h);
+        v16f x[2], t[2];
+        if (a.first == 0) {
+            x[0] = load_levels<32>(a.enc, a.n, i, valid, a.enc_dim / 2, h);
             x[1] = zero16();
-            if (a.a0_out) store_lane(a.a0_out, tile, lane, x);
-        } else {
-            load_lane(a.a_in, tile, lane, x);
-        }
-        Split<2, 3> px;
-        split(x, px);
-        matvec_split<2, 4, 3, 3>(Wf, px, z, lane);
-        uint32_t m = 0xffffffffu;
-        if (a.last) {
-            store_rows16(a.y, i, valid, h, z[0]);
-        } else {
-            m = relu_mask<2>(z);
-            store_lane(a.a_out, tile, lane, z);
-            a.mask_out[tile * 64 + lane] = m;
-        }
-        if (WITH_T) {
-            v16f t[2], tz[2];
-            if (a.first) {
+            if (WITH_T) {
                 float nb3[3] = {0.f, 0.f, 0.f};
                 if (valid) { nb3[0] = a.d_normal[3 * i]; nb3[1] = a.d_normal[3 * i + 1]; nb3[2] = a.d_normal[3 * i + 2]; }
-                t[0] = apply_jac<32>(a.jac, a.n, i, valid, a.levels, h, nb3);
+                t[0] = apply_jac<32>(a.jac, a.n, i, valid, a.enc_dim / 2, h, nb3);
                 t[1] = zero16();
-                store_lane(a.t0_out, tile, lane, t);
-            } else {
-                load_lane(a.t_in, tile, lane, t);
+                store_lane<1>(a.t_vec(0), tile, lane, t);
             }
-            Split<2, 2> pt;
-            split(t, pt);
-            matvec_split<2, 4, 3, 2>(Wf, pt, tz, lane);
-            apply_mask<2>(tz, m);
-            store_lane(a.t_out, tile, lane, tz);
+        } else {
+            load_lane<2>(a.a_vec(a.first), tile, lane, x);
+            if (WITH_T) load_lane<2>(a.t_vec(a.first), tile, lane, t);
+        }
+#pragma unroll 1
+        for (int k = 0; k < a.count; ++k) {
+            const int l = a.first + k;
+            const unsigned char* W = mats + k * kMatrix;
+            v16f z[2];
+            Split<2, 3> px;
+            split(x, px);
+            matvec_split<2, 4, 3, 3>(W, px, z, lane);
+            uint32_t m = 0xffffffffu;
+            if (l == a.n_mats - 1) {
+                store_rows16(a.y, i, valid, h, z[0]);
+            } else {
+                m = relu_mask<2>(z);
+                if (WITH_T || k == a.count - 1) store_lane<2>(a.a_vec(l + 1), tile, lane, z);
+                a.masks(l, tile)[lane] = m;
+            }
+            x[0] = z[0]; x[1] = z[1];
+            if (WITH_T) {
+                Split<2, 2> pt;
+                split(t, pt);
+                matvec_split<2, 4, 3, 2>(W, pt, t, lane);
+                apply_mask<2>(t, m);
+                store_lane<2>(a.t_vec(l + 1), tile, lane, t);
+            }
         }
     }
 }
 
-// add the registers [r0, r0 + count) of this wave's accumulator into dst[rows][cols] (row-major,
-// ld = cols) with atomics; r0 is the same for all lanes
-template <int ZB, int XB>
-__device__ __forceinline__ void flush_grad(float* __restrict__ dst, int rows, int cols, v16f (*G)[XB], int j, int h,
-                                           int r0, int count) {
-#pragma unroll
-    for (int mb = 0; mb < ZB; ++mb)
-#pragma unroll
-        for (int nb = 0; nb < XB; ++nb)
-#pragma unroll
-            for (int r = 0; r < 16; ++r) {
-                if (r < r0 || r >= r0 + count) continue;
-                const int o = 32 * mb + neuron_of(r, h), i = 32 * nb + j;
-                if (o < rows && i < cols) atomicAdd(dst + o * cols + i, G[mb][nb][r]);
-            }
-}
-
-struct DeepRevSmem {
-    alignas(16) unsigned char Wt[64 * SplitMatrix<4, 3>::kLd];
-    float tiles[kWaves][2][kTileWords];
-};
-
-// P: terms per factor of the transposed products (3 where the result is dd/de, which is compared at
-// forward tolerance; 2 in the backward call)
-template <int P, bool GRAD>
-__global__ __launch_bounds__(kThreads) void deep_reverse_kernel(DeepArgs a) {
-    typedef SplitMatrix<4, P> M;
-    __shared__ DeepRevSmem sm;
-    {
-        typename M::template Fill<64, kThreads, true> f;
-        const float* __restrict__ W = a.W;
-        const int od = a.out_dim, id = a.in_dim;
-        f.load(threadIdx.x, [&](int i, int o) { return (o < od && i < id) ? W[o * id + i] : 0.f; });
-        f.store(sm.Wt, threadIdx.x);
-        __syncthreads();
-    }
+// dd/de and the normal (Eq. 2): S downwards, three terms per factor (compared at forward tolerance)
+__global__ __launch_bounds__(kDeepThreads) void deep_reverse_kernel(DeepArgs a) {
+    constexpr int kMatrix = 64 * SplitMatrix<4, 3>::kLd;
+    __shared__ alignas(16) unsigned char mats[kDeepRun * kMatrix];
+    deep_matrices<3, kDeepRun, true>(a, a.first, -1, a.count, mats);
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int j = lane & 31, h = lane >> 5;
-    uint32_t* Zs = reinterpret_cast<uint32_t*>(sm.tiles[wave][0]);
-    uint32_t* Xs = reinterpret_cast<uint32_t*>(sm.tiles[wave][1]);
-    v16f G[2][2];
-#pragma unroll
-    for (int mb = 0; mb < 2; ++mb) { G[mb][0] = zero16(); G[mb][1] = zero16(); }
     const int64_t tiles = (a.n + 31) / 32;
-    for (int64_t tile = (int64_t)blockIdx.x * kWaves + wave; tile < tiles; tile += (int64_t)gridDim.x * kWaves) {
+    for (int64_t tile = (int64_t)blockIdx.x * kDeepWaves + wave; tile < tiles; tile += (int64_t)gridDim.x * kDeepWaves) {
         const int64_t i = tile * 32 + j;
         const bool valid = i < a.n;
-        v16f s[2], d[2];
-        if (a.last) {
-            // S_K: the unit row of output 0; delta_K: the adjoint of the 16 outputs
-            s[0] = zero16(); s[1] = zero16(); d[1] = zero16();
+        v16f s[2];
+        if (a.first == a.n_mats - 1) {
+            s[0] = zero16(); s[1] = zero16();
             if (h == 0 && valid) s[0][0] = 1.f;
-            if (GRAD) d[0] = load_rows16(a.d_y, i, valid, h);
         } else {
-            load_lane(a.s_in, tile, lane, s);
-            if (GRAD) load_lane(a.d_in, tile, lane, d);
+            load_lane<2>(a.passed(0), tile, lane, s);
         }
-        Split<2, P> ps;
-        Split<2, 2> pd;
-        split(s, ps);
-        if (GRAD) {
-            v16f ap[2], tp[2];
-            load_lane(a.a_in, tile, lane, ap);
-            load_lane(a.t_in, tile, lane, tp);
-            Split<2, 2> pa, pt;
-            split(d, pd);
-            split(ap, pa);
-            split(tp, pt);
-            stage_split(Zs, pd, j, h);
-            stage_split(Xs, pa, j, h);
-            wave_lds_fence();
-            outer_accumulate_split<2, 2>(G, Zs, Xs, lane);
-            wave_lds_fence();
-            stage_split(Zs, ps, j, h);
-            stage_split(Xs, pt, j, h);
-            wave_lds_fence();
-            outer_accumulate_split<2, 2>(G, Zs, Xs, lane);
-            wave_lds_fence();
-        }
-        const uint32_t m = a.first ? 0xffffffffu : a.mask_in[tile * 64 + lane];
-        v16f s2[2], d2[2];
-        matvec_split<2, 4, P, P>(sm.Wt, ps, s2, lane);
-        if (a.first) {
-            // dd/de and the normal (Eq. 2); the levels of this lane are 4g + 2h + u
-            if (a.q) {
-#pragma unroll
-                for (int g = 0; g < 4; ++g)
-#pragma unroll
-                    for (int u = 0; u < 2; ++u) {
-                        const int level = 4 * g + 2 * h + u;
-                        if (valid && level < a.levels)
-                            reinterpret_cast<float2*>(a.q)[(int64_t)level * a.n + i] = make_float2(s2[0][4 * g + 2 * u], s2[0][4 * g + 2 * u + 1]);
-                    }
+#pragma unroll 1
+        for (int k = 0; k < a.count; ++k) {
+            const int l = a.first - k;
+            const unsigned char* W = mats + k * kMatrix;
+            const uint32_t m = l > 0 ? a.masks(l - 1, tile)[lane] : 0u;
+            Split<2, 3> ps;
+            split(s, ps);
+            if (l > 0) {
+                matvec_split<2, 4, 3, 3>(W, ps, s, lane);
+                apply_mask<2>(s, m);
+                if (k == a.count - 1) store_lane<2>(a.passed(0), tile, lane, s);
+            } else {
+                v16f de[1];
+                matvec_split<1, 4, 3, 3>(W, ps, de, lane);
+                store_levels_active(a.q, a.n, i, valid, a.enc_dim / 2, h, de[0]);
                 float nrm[3];
-                contract_jac<32>(a.jac, a.n, i, valid, a.levels, h, s2[0], nrm);
+                contract_jac<32>(a.jac, a.n, i, valid, a.enc_dim / 2, h, de[0], nrm);
 #pragma unroll
                 for (int c = 0; c < 3; ++c) nrm[c] += __shfl_xor(nrm[c], 32);
                 if (valid && h == 0) { a.normal[3 * i] = nrm[0]; a.normal[3 * i + 1] = nrm[1]; a.normal[3 * i + 2] = nrm[2]; }
             }
-        } else {
-            apply_mask<2>(s2, m);
-            store_lane(a.s_out, tile, lane, s2);
         }
-        if (GRAD) {
-            matvec_split<2, 4, P, 2>(sm.Wt, pd, d2, lane);
-            if (a.first) {
+    }
+}
+
+// Both orders of a layer are the same work on other vectors (delta and a; S and t), so a wavefront takes one order of a
+// tile at a time and keeps the weight gradients of LAYERS layers, both orders' together, in registers.
+template <int LAYERS>
+struct DeepGradSmem {
+    alignas(16) unsigned char mats[LAYERS * 64 * SplitMatrix<4, 2>::kLd];
+    alignas(16) unsigned char tiles[kDeepWaves][kTilesPerWave * kBlockTile];
+};
+
+template <int LAYERS>
+__global__ __launch_bounds__(kDeepThreads) void deep_gradient_kernel(DeepArgs a) {
+    constexpr int kMatrix = 64 * SplitMatrix<4, 2>::kLd;
+    __shared__ DeepGradSmem<LAYERS> sm;
+    deep_matrices<2, LAYERS, true>(a, a.first, -1, LAYERS, sm.mats);
+    const int lane = threadIdx.x & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int j = lane & 31, h = lane >> 5;
+    unsigned char* tile_mem = sm.tiles[wave];
+    v16f G[LAYERS][2][2];
 #pragma unroll
-                for (int g = 0; g < 4; ++g)
+    for (int k = 0; k < LAYERS; ++k)
 #pragma unroll
-                    for (int u = 0; u < 2; ++u) {
-                        const int level = 4 * g + 2 * h + u;
-                        if (valid && level < a.levels)
-                            reinterpret_cast<float2*>(a.d_enc)[(int64_t)level * a.n + i] = make_float2(d2[0][4 * g + 2 * u], d2[0][4 * g + 2 * u + 1]);
-                    }
+        for (int mb = 0; mb < 2; ++mb) { G[k][mb][0] = zero16(); G[k][mb][1] = zero16(); }
+    const int64_t items = 2 * ((a.n + 31) / 32);
+    for (int64_t item = (int64_t)blockIdx.x * kDeepWaves + wave; item < items; item += (int64_t)gridDim.x * kDeepWaves) {
+        const int64_t tile = item >> 1;
+        const bool second = item & 1;
+        const int64_t i = tile * 32 + j;
+        const bool valid = i < a.n;
+        v16f z[2];
+        if (a.first == a.n_mats - 1) {
+            // S_K: the unit row of output 0; delta_K: the adjoint of the 16 outputs
+            z[1] = zero16();
+            if (second) {
+                z[0] = zero16();
+                if (h == 0 && valid) z[0][0] = 1.f;
             } else {
-                apply_mask<2>(d2, m);
-                store_lane(a.d_out, tile, lane, d2);
+                z[0] = load_rows16(a.d_y, i, valid, h);
+            }
+        } else {
+            load_lane<2>(a.passed(second), tile, lane, z);
+        }
+#pragma unroll
+        for (int k = 0; k < LAYERS; ++k) {
+            const int l = a.first - k;
+            v16f x[2];
+            uint32_t m = 0u;
+            if (l > 0) {
+                load_lane<2>(second ? a.t_vec(l) : a.a_vec(l), tile, lane, x);
+                m = a.masks(l - 1, tile)[lane];
+            } else if (second) {
+                load_lane<1>(a.t_vec(0), tile, lane, x);
+            } else {
+                x[0] = load_levels<32>(a.enc, a.n, i, valid, a.enc_dim / 2, h);
+                x[1] = zero16();
+            }
+            Split<2, 2> pz, px;
+            split(z, pz);
+            split(x, px);
+            outer_accumulate_points<2, 2>(G[k], pz, px, tile_mem, lane);
+            if (l > 0) {
+                matvec_split<2, 4, 2, 2>(sm.mats + k * kMatrix, pz, z, lane);
+                apply_mask<2>(z, m);
+                if (k == LAYERS - 1) store_lane<2>(a.passed(second), tile, lane, z);
+            } else if (!second) {
+                v16f de[1];
+                matvec_split<1, 4, 2, 2>(sm.mats + k * kMatrix, pz, de, lane);
+                store_levels_active(a.d_enc, a.n, i, valid, a.enc_dim / 2, h, de[0]);
             }
         }
     }
-    if (GRAD) {
-        __syncthreads();
-        float* scratch = reinterpret_cast<float*>(&sm);
-        static_assert(sizeof(sm) >= kWaves * 4 * 1024 * sizeof(float), "scratch for the block sum");
-        v16f* all[4] = {&G[0][0], &G[0][1], &G[1][0], &G[1][1]};
-        block_sum_shared<kWaves, 4>(scratch, all, wave, lane);
-        constexpr int kShare = 16 / kWaves;
-        flush_grad<2, 2>(a.dW, a.out_dim, a.in_dim, G, j, h, wave * kShare, kShare);
+    // ---- half of the waves leave their sums in LDS, the other half adds its own, and the block's sums go to global
+    // memory in the gradients' own order
+    __syncthreads();
+    float* scratch = reinterpret_cast<float*>(&sm);
+    constexpr int kVecs = 4 * LAYERS, kSlots = kDeepWaves / 2;
+    static_assert(sizeof(sm) >= kSlots * kVecs * 1024 * sizeof(float), "scratch for the block sum");
+    float* own = scratch + (wave % kSlots) * kVecs * 1024 + lane;
+    const v16f* all[kVecs];
+#pragma unroll
+    for (int k = 0; k < LAYERS; ++k)
+#pragma unroll
+        for (int b = 0; b < 4; ++b) all[4 * k + b] = &G[k][b >> 1][b & 1];
+    if (wave >= kSlots) {
+#pragma unroll
+        for (int k = 0; k < kVecs; ++k)
+#pragma unroll
+            for (int r = 0; r < 16; ++r) own[(k * 16 + r) * 64] = (*all[k])[r];
+    }
+    __syncthreads();
+    if (wave < kSlots) {
+#pragma unroll
+        for (int k = 0; k < kVecs; ++k)
+#pragma unroll
+            for (int r = 0; r < 16; ++r) own[(k * 16 + r) * 64] += (*all[k])[r];
+    }
+    __syncthreads();
+    for (int k = 0; k < LAYERS; ++k) {
+        const int l = a.first - k, id = a.in_dim(l), count = a.out_dim(l) * id;       // a multiple of kDeepThreads
+        const int shift = id == 64 ? 6 : id == 32 ? 5 : 4;
+        for (int c = 0; c < count; c += kDeepThreads) {
+            const int e = (c + (int)blockIdx.x / 8 * kDeepThreads) % count + threadIdx.x;   // workgroups start at different places
+            atomicAdd(a.dH[l] + e, block_element_points<kSlots, kVecs, 2>(scratch, 4 * k, e >> shift, e & (id - 1)));
+        }
     }
 }
 
@@ -1195,10 +1269,7 @@ int launch_sdf_fwd(const neus2_config* cfg, const float* enc, const float* jac, 
     return fail(NEUS2_ERR_UNSUPPORTED, "sdf network: input width %d with %d matrices has no kernel", D, K);
 }
 
-// Workspace of the layer-by-layer path: per point 32 floats per lane-layout vector (two lanes a
-// point), for a_0..a_{K-1} and t_0..t_{K-1} (the backward call keeps them all for its reverse
-// launches), two pairs of vectors that the reverse launches hand on, and a mask word per lane and
-// hidden layer.
+// Workspace of the deeper networks: see DeepArgs.
 static int64_t deep_vector_floats(int64_t n) { return ((n + 31) / 32) * 64 * 32; }
 
 int64_t sdf_deep_workspace_bytes(int n_mats, int64_t n) {
@@ -1208,32 +1279,27 @@ int64_t sdf_deep_workspace_bytes(int n_mats, int64_t n) {
 
 namespace {
 
-struct DeepLayout {
-    float* a[NEUS2_DEEP_MAX_MATS]; float* t[NEUS2_DEEP_MAX_MATS]; float* pass[4]; uint32_t* mask[NEUS2_DEEP_MAX_MATS];
-};
-
-DeepLayout deep_layout(void* workspace, int n_mats, int64_t n) {
-    DeepLayout L;
-    float* p = reinterpret_cast<float*>(workspace);
-    const int64_t vec = deep_vector_floats(n);
-    for (int l = 0; l < n_mats; ++l) { L.a[l] = p; p += vec; L.t[l] = p; p += vec; }
-    for (int k = 0; k < 4; ++k) { L.pass[k] = p; p += vec; }
-    uint32_t* w = reinterpret_cast<uint32_t*>(p);
-    for (int l = 0; l < n_mats; ++l) { L.mask[l] = w; w += ((n + 31) / 32) * 64; }
-    return L;
+DeepArgs deep_args(int n_mats, int enc_dim, const float* enc, const float* jac, const float* const* H, int64_t n, void* workspace) {
+    DeepArgs a = {};
+    for (int l = 0; l < n_mats; ++l) a.H[l] = H[l];
+    a.n_mats = n_mats; a.enc_dim = enc_dim; a.n = n; a.vec = deep_vector_floats(n);
+    a.ws = reinterpret_cast<float*>(workspace);
+    a.enc = enc; a.jac = jac;
+    return a;
 }
 
-int deep_dims(int n_mats, int enc_dim, int l, int& out_dim, int& in_dim) {
-    in_dim = l == 0 ? enc_dim : 64;
-    out_dim = l == n_mats - 1 ? 16 : 64;
-    return 0;
-}
-
+// items: pieces of work of a wavefront
 template <typename Kernel>
-void deep_launch(Kernel kernel, const DeepArgs& a, hipStream_t st) {
-    const int64_t want = ((a.n + 31) / 32 + kWaves - 1) / kWaves;
-    const int blocks = persistent_blocks((const void*)kernel, kThreads, want);
-    hipLaunchKernelGGL(kernel, dim3(blocks), dim3(kThreads), 0, st, a);
+void deep_launch(Kernel kernel, const DeepArgs& a, int64_t items, hipStream_t st) {
+    const int blocks = persistent_blocks((const void*)kernel, kDeepThreads, (items + kDeepWaves - 1) / kDeepWaves);
+    hipLaunchKernelGGL(kernel, dim3(blocks), dim3(kDeepThreads), 0, st, a);
+}
+
+// layers 0 .. n - 1 in as few runs as possible, of sizes that differ by one at most: [start[r], start[r + 1])
+int deep_runs(int n, int* start) {
+    const int runs = (n + kDeepRun - 1) / kDeepRun;
+    for (int r = 0; r <= runs; ++r) start[r] = r * n / runs;
+    return runs;
 }
 
 }  // namespace
@@ -1241,53 +1307,42 @@ void deep_launch(Kernel kernel, const DeepArgs& a, hipStream_t st) {
 int launch_sdf_deep_fwd(int n_mats, int enc_dim, const float* enc, const float* jac, const float* const* H, int64_t n,
                         float* y, float* q, float* normal, void* workspace, hipStream_t st) {
     if (n == 0) return NEUS2_OK;
-    const DeepLayout L = deep_layout(workspace, n_mats, n);
-    for (int l = 0; l < n_mats; ++l) {                           // forward launches: a_1 .. a_{K-1}, y
-        DeepArgs a = {};
-        a.W = H[l]; deep_dims(n_mats, enc_dim, l, a.out_dim, a.in_dim);
-        a.n = n; a.levels = enc_dim / 2; a.first = l == 0; a.last = l == n_mats - 1;
-        a.enc = enc; a.a_in = L.a[l]; a.a_out = L.a[(l + 1) % n_mats]; a.mask_out = L.mask[l]; a.y = y;
-        deep_launch(deep_forward_kernel<false>, a, st);
+    DeepArgs a = deep_args(n_mats, enc_dim, enc, jac, H, n, workspace);
+    a.y = y; a.q = q; a.normal = normal;
+    const int64_t tiles = (n + 31) / 32;
+    int start[NEUS2_DEEP_MAX_MATS + 1];
+    const int runs = deep_runs(n_mats, start);
+    for (int r = 0; r < runs; ++r) {                             // a_1 .. a_{K-1}, y
+        a.first = start[r]; a.count = start[r + 1] - start[r];
+        deep_launch(deep_forward_kernel<false>, a, tiles, st);
     }
-    for (int l = n_mats - 1; l >= 0; --l) {                      // reverse launches: S_{K-1} .. S_1, dd/de
-        DeepArgs a = {};
-        a.W = H[l]; deep_dims(n_mats, enc_dim, l, a.out_dim, a.in_dim);
-        a.n = n; a.levels = enc_dim / 2; a.first = l == 0; a.last = l == n_mats - 1;
-        a.s_in = L.pass[l & 1]; a.s_out = L.pass[(l & 1) ^ 1];
-        a.mask_in = l > 0 ? L.mask[l - 1] : nullptr;
-        a.jac = jac; a.q = q; a.normal = normal;
-        deep_launch(deep_reverse_kernel<3, false>, a, st);
+    for (int r = runs - 1; r >= 0; --r) {                        // S_{K-1} .. S_1, dd/de
+        a.first = start[r + 1] - 1; a.count = start[r + 1] - start[r];
+        deep_launch(deep_reverse_kernel, a, tiles, st);
     }
-    return check_launch("sdf forward (layer by layer)");
+    return check_launch("sdf forward (deeper network)");
 }
 
 int launch_sdf_deep_bwd(int n_mats, int enc_dim, const float* enc, const float* jac, const float* const* H,
                         const float* d_y, const float* d_normal, int64_t n, float* const* dH, float* d_enc,
                         void* workspace, hipStream_t st) {
     if (n == 0) return NEUS2_OK;
-    const DeepLayout L = deep_layout(workspace, n_mats, n);
-    for (int l = 0; l + 1 < n_mats; ++l) {                       // a_l and t_l of every hidden layer
-        DeepArgs a = {};
-        a.W = H[l]; deep_dims(n_mats, enc_dim, l, a.out_dim, a.in_dim);
-        a.n = n; a.levels = enc_dim / 2; a.first = l == 0; a.last = false;
-        a.enc = enc; a.jac = jac; a.d_normal = d_normal;
-        a.a0_out = L.a[0]; a.t0_out = L.t[0];
-        a.a_in = L.a[l]; a.t_in = L.t[l]; a.a_out = L.a[l + 1]; a.t_out = L.t[l + 1]; a.mask_out = L.mask[l];
-        deep_launch(deep_forward_kernel<true>, a, st);
+    DeepArgs a = deep_args(n_mats, enc_dim, enc, jac, H, n, workspace);
+    a.d_y = d_y; a.d_normal = d_normal; a.d_enc = d_enc;
+    for (int l = 0; l < n_mats; ++l) a.dH[l] = dH[l];
+    const int64_t tiles = (n + 31) / 32;
+    int start[NEUS2_DEEP_MAX_MATS + 1];
+    const int runs = deep_runs(n_mats - 1, start);
+    for (int r = 0; r < runs; ++r) {                             // a_l and t_l of every hidden layer
+        a.first = start[r]; a.count = start[r + 1] - start[r];
+        deep_launch(deep_forward_kernel<true>, a, tiles, st);
     }
-    for (int l = n_mats - 1; l >= 0; --l) {
-        DeepArgs a = {};
-        a.W = H[l]; deep_dims(n_mats, enc_dim, l, a.out_dim, a.in_dim);
-        a.n = n; a.levels = enc_dim / 2; a.first = l == 0; a.last = l == n_mats - 1;
-        a.d_y = d_y;
-        a.s_in = L.pass[l & 1]; a.s_out = L.pass[(l & 1) ^ 1];
-        a.d_in = L.pass[2 + (l & 1)]; a.d_out = L.pass[2 + ((l & 1) ^ 1)];
-        a.a_in = L.a[l]; a.t_in = L.t[l];                        // a_{l-1}, t_{l-1} in the paper's numbering
-        a.mask_in = l > 0 ? L.mask[l - 1] : nullptr;
-        a.d_enc = d_enc; a.dW = dH[l];
-        deep_launch(deep_reverse_kernel<2, true>, a, st);
+    for (int l = n_mats - 1; l >= 0; l -= kDeepGradRun) {
+        a.first = l;
+        if (l > 0) deep_launch(deep_gradient_kernel<kDeepGradRun>, a, 2 * tiles, st);
+        else deep_launch(deep_gradient_kernel<1>, a, 2 * tiles, st);
     }
-    return check_launch("sdf backward (layer by layer)");
+    return check_launch("sdf backward (deeper network)");
 }
 
 int launch_sdf_bwd(const neus2_config* cfg, const float* enc, const float* jac, const float* const* H,

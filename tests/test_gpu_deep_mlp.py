@@ -1,5 +1,5 @@
-"""The layer-by-layer SDF network (neus2_sdf_deep_fwd_grad / neus2_sdf_deep_bwd: one launch per
-matrix and direction, up to eight hidden layers, the depths of the paper's Fig. 7) against the
+"""The deeper SDF network (neus2_sdf_deep_fwd_grad / neus2_sdf_deep_bwd: a run of layers per launch and
+direction, up to eight hidden layers, the depths of the paper's Fig. 7) against the
 float64 oracle: (d,g), dd/de and the normal at forward tolerance; every weight gradient, first
 order plus the second-order term of Theorem 1, and dL/de at gradient tolerance.  At the depths the
 fused kernels hold as well the two paths are also compared with each other."""
@@ -143,3 +143,10 @@ def test_layer_by_layer_calls_reject_what_they_do_not_support():
         nb.sdf_deep_fwd_grad(32, buf, buf, H, n, buf, buf, buf, small)            # workspace too small
     with pytest.raises(RuntimeError):
         nb.sdf_deep_fwd_grad(24, buf, buf, H, n, buf, buf, buf, buf)              # input width
+
+
+@pytest.mark.parametrize("enc_dim,hidden,n", [(32, 5, 31), (16, 6, 33), (32, 7, 64), (16, 1, 1)])
+def test_runs_of_layers_at_their_edges(enc_dim, hidden, n):
+    """Six matrices fill a run, seven make two; an even number of matrices leaves no single layer for the last gradient
+    launch; tiles of 32 points that are not full, just begun and exactly full."""
+    test_layer_by_layer_network_against_the_oracle(enc_dim, hidden, n)
