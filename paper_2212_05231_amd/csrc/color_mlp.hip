@@ -44,10 +44,11 @@ __device__ __forceinline__ int external_column(int c) {
 // forward kernel and where the backward kernel recomputes it, uses three terms per factor and six
 // products: as accurate as fp32 arithmetic, and the same arithmetic in both kernels, so the ReLU
 // masks agree.  The adjoint sweep of the backward kernel uses two terms and three products.
-template <bool BWD>
+// PF: terms of the matrices of the forward direction (two in the backward kernel that is handed the masks).
+template <bool BWD, int PF = 3>
 struct ColorWeights {
-    typedef SplitMatrix<3, 3> M1f;     // [64][40 -> 48]
-    typedef SplitMatrix<4, 3> M2f;     // [64][64]
+    typedef SplitMatrix<3, PF> M1f;    // [64][40 -> 48]
+    typedef SplitMatrix<4, PF> M2f;    // [64][64]
     typedef SplitMatrix<4, 2> M1t;     // [first 32 input columns][64]
     typedef SplitMatrix<4, 2> M2t;
     typedef SplitMatrix<1, 2> M3t;     // [64][3 -> 16]
@@ -63,9 +64,9 @@ struct ColorWeights {
 
 // Every matrix is fetched from global memory before the first is written to LDS, so the fetches
 // are in flight together; the copies cover every slot a product reads, so nothing is cleared.
-template <bool BWD>
-__device__ void load_weights(ColorWeights<BWD>& w, const ColorArgs& a) {
-    typedef ColorWeights<BWD> W;
+template <bool BWD, int THREADS, int PF = 3>
+__device__ void load_weights(ColorWeights<BWD, PF>& w, const ColorArgs& a) {
+    typedef ColorWeights<BWD, PF> W;
     const int tid = threadIdx.x;
     const float* __restrict__ W1 = a.W[0];
     const float* __restrict__ W2 = a.W[1];
@@ -74,11 +75,11 @@ __device__ void load_weights(ColorWeights<BWD>& w, const ColorArgs& a) {
         const int e = c < 40 ? external_column(c) : -1;
         return e >= 0 ? W1[o * 38 + e] : 0.f;
     };
-    typename W::M1f::template Fill<64, kThreads, false> f1;
-    typename W::M2f::template Fill<64, kThreads, false> f2;
-    typename W::M1t::template Fill<BWD ? 32 : 0, kThreads, true> t1;
-    typename W::M2t::template Fill<BWD ? 64 : 0, kThreads, true> t2;
-    typename W::M3t::template Fill<BWD ? 64 : 0, kThreads, true> t3;
+    typename W::M1f::template Fill<64, THREADS, false> f1;
+    typename W::M2f::template Fill<64, THREADS, false> f2;
+    typename W::M1t::template Fill<BWD ? 32 : 0, THREADS, true> t1;
+    typename W::M2t::template Fill<BWD ? 64 : 0, THREADS, true> t2;
+    typename W::M3t::template Fill<BWD ? 64 : 0, THREADS, true> t3;
     f1.load(tid, first);
     f2.load(tid, [&](int o, int i) { return W2[o * 64 + i]; });
     float last = 0.f;
@@ -127,7 +128,6 @@ struct ColorRaw {
     float dir[3], p[3], nr[3];
     float d_rgb[3], rgb[3], d_sdf;
     float dn[2];               // backward: this lane's part of d_normal as it comes in (h = 0: n0; h = 1: n1, n2)
-    uint32_t m1, m2;           // backward with masks from the forward kernel
 };
 
 template <bool BWD>
@@ -146,7 +146,6 @@ __device__ __forceinline__ ColorRaw load_raw(const ColorArgs& a, int64_t i, bool
         if (BWD) { r.d_rgb[c] = a.d_rgb[3 * i + c]; r.rgb[c] = a.rgb_in[3 * i + c]; }
     }
     if (BWD && a.d_sdf) r.d_sdf = a.d_sdf[i];
-    if (BWD && a.masks) { r.m1 = __builtin_nontemporal_load(a.masks + mask_word(0, a.n, i, h)); r.m2 = __builtin_nontemporal_load(a.masks + mask_word(1, a.n, i, h)); }
     if (BWD) {
         r.dn[0] = a.d_normal[3 * i + (h ? 1 : 0)];
         if (h) r.dn[1] = a.d_normal[3 * i + 2];
@@ -179,24 +178,21 @@ __device__ __forceinline__ float sigmoid(float u) { return 1.f / (1.f + __expf(-
 
 // Both hidden layers; leaves the split input and first hidden layer behind for the backward
 // pass's weight gradients.
-template <bool BWD, bool GIVEN>
-__device__ __forceinline__ void forward_tile(const ColorWeights<BWD>& w, const v16f* cin, Split<2, GIVEN ? 2 : 3>& pc,
-                                             Split<2, GIVEN ? 2 : 3>& p1, v16f* a2, uint32_t& m1, uint32_t& m2, int lane) {
-    constexpr int PF = GIVEN ? 2 : 3;
+template <bool BWD>
+__device__ __forceinline__ void forward_tile(const ColorWeights<BWD>& w, const v16f* cin, Split<2, 3>& pc, Split<2, 3>& p1,
+                                             v16f* a2, uint32_t& m1, uint32_t& m2, int lane) {
     v16f a1[2];
     split(cin, pc);
-    matvec_split<2, 3, 3, PF>(w.W1f, pc, a1, lane);
-    if (GIVEN) apply_mask<2>(a1, m1);
-    else m1 = relu_mask<2>(a1);
+    matvec_split<2, 3, 3, 3>(w.W1f, pc, a1, lane);
+    m1 = relu_mask<2>(a1);
     split(a1, p1);
-    matvec_split<2, 4, 3, PF>(w.W2f, p1, a2, lane);
-    if (GIVEN) apply_mask<2>(a2, m2);
-    else m2 = relu_mask<2>(a2);
+    matvec_split<2, 4, 3, 3>(w.W2f, p1, a2, lane);
+    m2 = relu_mask<2>(a2);
 }
 
 __global__ __launch_bounds__(kThreads, 2) void color_fwd_kernel(ColorArgs a) {
     __shared__ ColorWeights<false> w;
-    load_weights<false>(w, a);
+    load_weights<false, kThreads>(w, a);
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);   // the same for all lanes: keeps tile indices and addresses scalar
     const int j = lane & 31, h = lane >> 5;
@@ -215,7 +211,7 @@ __global__ __launch_bounds__(kThreads, 2) void color_fwd_kernel(ColorArgs a) {
             const int64_t in = (tile + stride) * 32 + j;
             next = load_raw<false>(a, in, tile + stride < tiles && in < a.n, h);
         }
-        forward_tile<false, false>(w, cin, pc, p1, a2, m1, m2, lane);
+        forward_tile<false>(w, cin, pc, p1, a2, m1, m2, lane);
         if (a.masks && valid) {
             a.masks[mask_word(0, a.n, i, h)] = m1;
             a.masks[mask_word(1, a.n, i, h)] = m2;
@@ -248,15 +244,12 @@ struct ColorBwdSmem {
     float tiles[kWaves][2][kTileWords];
 };
 
-// GIVEN: the masks come from the forward kernel (a.masks).  The forward pass is then recomputed
-// only for its values, which enter weight gradients and further products at gradient tolerance:
-// two terms and three products like the rest of this kernel.  Without them it is recomputed in
-// the forward kernel's own arithmetic, which yields the same masks bit for bit.
-template <bool GIVEN>
+// Without masks from the forward kernel: the forward pass is recomputed in that kernel's own arithmetic, which yields the
+// same masks bit for bit.  One wavefront per SIMD with all 512 registers.
 __global__ __launch_bounds__(kThreads) void color_bwd_kernel(ColorArgs a) {
     __shared__ ColorBwdSmem sm;
     ColorWeights<true>& w = sm.w;
-    load_weights<true>(w, a);
+    load_weights<true, kThreads>(w, a);
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);   // the same for all lanes: keeps tile indices and addresses scalar
     const int j = lane & 31, h = lane >> 5;
@@ -282,15 +275,15 @@ __global__ __launch_bounds__(kThreads) void color_bwd_kernel(ColorArgs a) {
         const bool valid = i < a.n;
         v16f cin[2], a2[2];
         const ColorRaw cur = next;
-        uint32_t m1 = cur.m1, m2 = cur.m2;
+        uint32_t m1, m2;
         build_input(cur, valid, h, cin);
         {
             const int64_t in = (tile + stride) * 32 + j;
             next = load_raw<true>(a, in, tile + stride < tiles && in < a.n, h);
         }
         // ---- forward pass again
-        Split<2, GIVEN ? 2 : 3> pc, p1;
-        forward_tile<true, GIVEN>(w, cin, pc, p1, a2, m1, m2, lane);
+        Split<2, 3> pc, p1;
+        forward_tile<true>(w, cin, pc, p1, a2, m1, m2, lane);
         // adjoint of the pre-sigmoid output, from the colour the forward pass stored
         v16f d3[1] = {zero16()};
         if (valid && h == 0) {
@@ -370,6 +363,229 @@ __global__ __launch_bounds__(kThreads) void color_bwd_kernel(ColorArgs a) {
     }
 }
 
+// ------------------------------------------------------------------------------------------
+// With the masks from the forward kernel the forward pass is recomputed only for its values, which enter weight gradients
+// and further products at gradient tolerance: two terms and three products throughout.  The masks also take the adjoint
+// sweep out of the forward pass's wake, so two wavefronts share a tile: one recomputes the activations and makes the
+// gradients of the last two matrices, the other takes the adjoints (the first product, 6 of 164 matrix instructions, is made
+// by both) down to the inputs and makes the first matrix's.  Each needs 256 registers at most: eight wavefronts a
+// workgroup, waves w and w + 4 on one SIMD, one's waits for LDS, memory and matrix results filled by the other.  One
+// wavefront per SIMD with 512 registers waited on its own chain: 2^18 points 71 -> 61 us, 2^20 points 232 -> 197, 32576
+// points 20.6 -> 18.2.
+// (Eight wavefronts that each do all of a tile spilled 68 registers: 78 and 261 us.)
+constexpr int kPairThreads = 512;
+constexpr int kPairs = kPairThreads / 128;        // tiles a workgroup works on
+
+struct ColorPairSmem {
+    ColorWeights<true, 2> w;
+    alignas(16) unsigned char tiles[2 * kPairs][kTilesPerWave * kBlockTile];
+};
+
+// What both wavefronts read of a tile's point
+struct ColorPoint {
+    ColorRaw r;
+    uint32_t m1, m2;
+    v16f d3[1];                // adjoint of the pre-sigmoid output
+};
+
+__device__ __forceinline__ ColorPoint load_point(const ColorArgs& a, int64_t tile, bool valid, int j, int h) {
+    ColorPoint p = {};
+    p.d3[0] = zero16();
+    if (!valid) return p;
+    const uint32_t* words = a.masks + tile * 64;
+    p.m1 = *lane_address(words, 8u * j + 4u * h);
+    p.m2 = *lane_address(words + 2 * a.n, 8u * j + 4u * h);
+    // n is at most 2^28: a 32-bit division (the 64-bit one costs over a hundred instructions)
+    const int64_t ray = a.sample_ray ? *lane_address(a.sample_ray + tile * 32, 4u * j)
+                                     : (int32_t)((uint32_t)(tile * 32 + j) / (uint32_t)a.spr);
+    const float4* row = lane_address(reinterpret_cast<const float4*>(a.y) + tile * 128, 64u * j + 16u * h);
+    p.r.ya = row[0];
+    p.r.yb = row[2];
+    const float* pos = lane_address(a.pos + tile * 96, 12u * j);
+    const float* nr = lane_address(a.normal + tile * 96, 12u * j);
+    const float* rgb = lane_address(a.rgb_in + tile * 96, 12u * j);
+    const float* d_rgb = lane_address(a.d_rgb + tile * 96, 12u * j);
+#pragma unroll
+    for (int c = 0; c < 3; ++c) {
+        p.r.dir[c] = a.dirs[3 * ray + c];
+        p.r.p[c] = pos[c];
+        p.r.nr[c] = nr[c];
+        p.d3[0][c] = h == 0 ? d_rgb[c] * rgb[c] * (1.f - rgb[c]) : 0.f;
+    }
+    return p;
+}
+
+// activations, gradients of the second and the last matrix
+__device__ __forceinline__ void color_upper_layers(const ColorArgs& a, const ColorWeights<true, 2>& w, unsigned char* mem, int slot, int lane,
+                                                   v16f (*G2)[2], v4f* G3) {
+    const int j = lane & 31, h = lane >> 5;
+    float* Xt = reinterpret_cast<float*>(mem);
+    float* Zt = Xt + 32 * kLd64;
+    static_assert((32 * kLd64 + 32 * kLd16) * 4 <= kTilesPerWave * kBlockTile, "fp32 tiles fit the wave's memory");
+    const int64_t tiles = (a.n + 31) / 32;
+    const int64_t stride = (int64_t)gridDim.x * kPairs;
+    for (int64_t tile = (int64_t)blockIdx.x * kPairs + slot; tile < tiles; tile += stride) {
+        const bool valid = tile * 32 + j < a.n;
+        const ColorPoint p = load_point(a, tile, valid, j, h);
+        Split<2, 2> p1, pd;
+        Split<1, 2> p3;
+        v16f a1[2], a2[2], d2[2];
+        {
+            v16f cin[2];
+            Split<2, 2> pc;
+            build_input(p.r, valid, h, cin);
+            split(cin, pc);
+            matvec_split<2, 3, 2, 2>(w.W1f, pc, a1, lane);
+        }
+        apply_mask<2>(a1, p.m1);
+        split(a1, p1);
+        matvec_split<2, 4, 2, 2>(w.W2f, p1, a2, lane);
+        apply_mask<2>(a2, p.m2);
+        wave_lds_fence();
+        stage16<kLd16>(Zt, p.d3[0], j, h);
+        stage<2, kLd64>(Xt, a2, j, h);
+        wave_lds_fence();
+        outer_accumulate16<2, kLd16, kLd64>(G3, Zt, Xt, lane);
+        split(p.d3, p3);
+        matvec_split<2, 1, 2, 2>(w.W3t, p3, d2, lane);
+        apply_mask<2>(d2, again(p.m2));
+        split(d2, pd);
+        outer_accumulate_points<2, 2>(G2, pd, p1, mem, lane);
+    }
+}
+
+// adjoints, gradient of the first matrix: columns 0..31 in G1, 32..39 in G1n by blocks of 16 rows
+__device__ __forceinline__ void color_first_layer(const ColorArgs& a, const ColorWeights<true, 2>& w, unsigned char* mem, int slot, int lane,
+                                                  v16f (*G)[2], v4f* G1n) {
+    const int j = lane & 31, h = lane >> 5;
+    v16f G1[2][1] = {{G[0][0]}, {G[1][0]}};
+    const int64_t tiles = (a.n + 31) / 32;
+    const int64_t stride = (int64_t)gridDim.x * kPairs;
+    for (int64_t tile = (int64_t)blockIdx.x * kPairs + slot; tile < tiles; tile += stride) {
+        const bool valid = tile * 32 + j < a.n;
+        const ColorPoint p = load_point(a, tile, valid, j, h);
+        float* dn = lane_address(a.d_normal + tile * 96, 12u * j + 4u * h);       // h = 0: n0; h = 1: n1, n2
+        float dn0 = 0.f, dn1 = 0.f, d_sdf = 0.f;
+        if (valid) {
+            dn0 = dn[0];
+            if (h) dn1 = dn[1];
+            else if (a.d_sdf) d_sdf = *lane_address(a.d_sdf + tile * 32, 4u * j);
+        }
+        Split<2, 2> pd, pc;
+        Split<1, 2> p3, pc0;
+        v16f d2[2], d1[2], dcin[1];
+        split(p.d3, p3);
+        matvec_split<2, 1, 2, 2>(w.W3t, p3, d2, lane);
+        apply_mask<2>(d2, p.m2);
+        split(d2, pd);
+        matvec_split<2, 4, 2, 2>(w.W2t, pd, d1, lane);
+        apply_mask<2>(d1, p.m1);
+        split(d1, pd);
+        {
+            v16f cin[2];
+            build_input(p.r, valid, h, cin);
+            split(cin, pc);
+        }
+#pragma unroll
+        for (int term = 0; term < 2; ++term)
+#pragma unroll
+            for (int k = 0; k < 8; ++k) pc0.t[term][0][k] = pc.t[term][0][k];
+        // the inputs' first block goes to tile 0, the adjoints' two to tiles 1 and 2, which stay as they are
+        outer_accumulate_points<2, 1>(G1, pd, pc0, mem, lane);
+        stage_narrow_block(mem, pc, 1, j, h);
+        wave_lds_fence();
+        const bf8 xh = read_half_block(mem, 0, 0, lane), xm = read_half_block(mem, 1, 0, lane);
+#pragma unroll
+        for (int rb = 0; rb < 4; ++rb) {
+            const unsigned char* zt = mem + (1 + (rb >> 1)) * kBlockTile;
+            const bf8 zh = read_half_block(zt, 0, rb & 1, lane), zm = read_half_block(zt, 1, rb & 1, lane);
+            G1n[rb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(zh, xh, G1n[rb], 0, 0, 0);
+            G1n[rb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(zh, xm, G1n[rb], 0, 0, 0);
+            G1n[rb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(zm, xh, G1n[rb], 0, 0, 0);
+        }
+        wave_lds_fence();
+        matvec_split<1, 4, 2, 2>(w.W1t, pd, dcin, lane);
+        if (valid) {
+            // block 0, registers 0..7: dL/d(d,g) columns 4h..4h+3 and 8+4h..8+4h+3
+            float4* row = lane_address(reinterpret_cast<float4*>(a.d_y) + tile * 128, 64u * j + 16u * h);
+            row[0] = make_float4(dcin[0][0] + d_sdf, dcin[0][1], dcin[0][2], dcin[0][3]);
+            row[2] = make_float4(dcin[0][4], dcin[0][5], dcin[0][6], dcin[0][7]);
+            // registers 8..11: h = 0 -> x0 x1 x2 n0 ; h = 1 -> n1 n2
+            dn[0] = dn0 + (h ? dcin[0][8] : dcin[0][11]);
+            if (h) {
+                dn[1] = dn1 + dcin[0][9];
+            } else if (a.d_pos) {
+                float* dp = lane_address(a.d_pos + tile * 96, 12u * j);
+                dp[0] = dcin[0][8]; dp[1] = dcin[0][9]; dp[2] = dcin[0][10];
+            }
+        }
+        held(dcin[0]);
+    }
+    G[0][0] = G1[0][0];
+    G[1][0] = G1[1][0];
+}
+
+__global__ __launch_bounds__(kPairThreads) void color_bwd_pair_kernel(ColorArgs a) {
+    __shared__ ColorPairSmem sm;
+    load_weights<true, kPairThreads, 2>(sm.w, a);
+    const int lane = threadIdx.x & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);   // the same for all lanes: keeps tile indices and addresses scalar
+    const int slot = wave % kPairs;
+    float* scratch = reinterpret_cast<float*>(&sm);
+    constexpr int kVecs = 8;
+    static_assert(sizeof(sm) >= kPairs * kVecs * 1024 * sizeof(float), "scratch for the block sum");
+    float* own = scratch + slot * kVecs * 1024 + lane;
+    // each wave of a pair leaves its own vectors in the pair's scratch
+    auto leave = [&](int k, const v16f& v) {
+#pragma unroll
+        for (int r = 0; r < 16; ++r) own[(k * 16 + r) * 64] = v[r];
+    };
+    auto side_by_side = [](const v4f* G) {
+        v16f v;
+#pragma unroll
+        for (int b = 0; b < 4; ++b)
+#pragma unroll
+            for (int e = 0; e < 4; ++e) v[4 * b + e] = G[b][e];
+        return v;
+    };
+    const v4f zero4 = {0.f, 0.f, 0.f, 0.f};
+    v16f G[2][2] = {{zero16(), zero16()}, {zero16(), zero16()}};        // second matrix, or (column 0) the first
+    v4f N[4] = {zero4, zero4, zero4, zero4};
+    if (wave < kPairs) color_upper_layers(a, sm.w, sm.tiles[wave], slot, lane, G, N);
+    else color_first_layer(a, sm.w, sm.tiles[wave], slot, lane, G, N);
+    __syncthreads();
+    if (wave < kPairs) {
+        leave(3, side_by_side(N));
+        leave(4, G[0][0]); leave(5, G[0][1]); leave(6, G[1][0]); leave(7, G[1][1]);
+    } else {
+        leave(0, G[0][0]); leave(1, G[1][0]); leave(2, side_by_side(N));
+    }
+    __syncthreads();
+    // the block's sums go to global memory in the gradients' own order
+    constexpr int kOf1 = 64 * 38, kOf2 = 64 * 64, kOf3 = 3 * 64;
+    constexpr int kChunks = (kOf1 + kOf2 + kOf3 + kPairThreads - 1) / kPairThreads;
+    for (int k = 0; k < kChunks; ++k) {
+        const int x = rotated_chunk<kChunks>(k) * kPairThreads + threadIdx.x;
+        if (x < kOf1) {
+            const int o = x / 38, c = internal_column(x - 38 * o);
+            float sum;
+            if (c < 32) {
+                sum = block_element_points<kPairs, kVecs, 1>(scratch, 0, o, c);
+            } else {
+                const int row = tile_position(o), col = tile_position(c - 32);      // row 16 rb + 4 (lane / 16) + v, column lane % 16
+                sum = block_total<kPairs, kVecs>(scratch, 2, 4 * (row >> 4) + (row & 3), 16 * ((row >> 2) & 3) + col);
+            }
+            atomicAdd(a.dW[0] + x, sum);
+        } else if (x < kOf1 + kOf2) {
+            const int e = x - kOf1;
+            atomicAdd(a.dW[1] + e, block_element_points<kPairs, kVecs, 2>(scratch, 4, e >> 6, e & 63));
+        } else if (x < kOf1 + kOf2 + kOf3) {
+            const int e = x - kOf1 - kOf2;
+            atomicAdd(a.dW[2] + e, block_element16<kPairs, kVecs>(scratch, 3, e >> 6, e & 63));
+        }
+    }
+}
+
 int check_common(const neus2_config* cfg, const float* pos, const float* normal, const float* dirs,
                  const int32_t* sample_ray, const float* y, const float* const* W, int64_t n) {
     NEUS2_TRY(check_config(cfg));
@@ -429,13 +645,13 @@ int neus2_color_bwd(const neus2_config* cfg, const float* pos, const float* norm
     a.pos = pos; a.normal = normal; a.dirs = dirs; a.sample_ray = sample_ray; a.y = y; a.n = n; a.spr = cfg->samples_per_ray;
     a.rgb_in = rgb; a.d_rgb = d_rgb; a.d_sdf = d_sdf; a.d_y = d_y; a.d_normal = d_normal; a.d_pos = d_pos;
     for (int l = 0; l < 3; ++l) { a.W[l] = W[l]; a.dW[l] = dW[l]; }
-    const int64_t want = ((n + 31) / 32 + kWaves - 1) / kWaves;
+    const int64_t tiles = (n + 31) / 32;
     if (masks) {
-        const int blocks = persistent_blocks((const void*)color_bwd_kernel<true>, kThreads, want);
-        hipLaunchKernelGGL(color_bwd_kernel<true>, dim3(blocks), dim3(kThreads), 0, (hipStream_t)stream, a);
+        const int blocks = persistent_blocks((const void*)color_bwd_pair_kernel, kPairThreads, (tiles + kPairs - 1) / kPairs);
+        hipLaunchKernelGGL(color_bwd_pair_kernel, dim3(blocks), dim3(kPairThreads), 0, (hipStream_t)stream, a);
     } else {
-        const int blocks = persistent_blocks((const void*)color_bwd_kernel<false>, kThreads, want);
-        hipLaunchKernelGGL(color_bwd_kernel<false>, dim3(blocks), dim3(kThreads), 0, (hipStream_t)stream, a);
+        const int blocks = persistent_blocks((const void*)color_bwd_kernel, kThreads, (tiles + kWaves - 1) / kWaves);
+        hipLaunchKernelGGL(color_bwd_kernel, dim3(blocks), dim3(kThreads), 0, (hipStream_t)stream, a);
     }
     return check_launch("colour backward");
 }

@@ -36,6 +36,8 @@
 
 #include <hip/hip_runtime.h>
 
+#include <type_traits>
+
 namespace neus2 {
 
 typedef float v16f __attribute__((ext_vector_type(16)));
@@ -98,6 +100,12 @@ __device__ __forceinline__ void relu(v16f* z) {
         }
 }
 
+// Put behind the reads of a matrix result of which some registers are never read (padding rows): they stay taken up to here.
+// The compiler may otherwise give one of them to an instruction written in asm text while the matrix instruction is still
+// to write it: it makes its own instructions wait for that, not those in asm text (seen: a row number overwritten by the
+// padding rows of the product before).
+__device__ __forceinline__ void held(const v16f& x) { asm volatile("" : : "v"(x)); }
+
 template <int NB>
 __device__ __forceinline__ void apply_mask(v16f* z, uint32_t m) {
 #pragma unroll
@@ -135,6 +143,28 @@ __device__ __forceinline__ void wave_lds_fence() {
     __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
     __builtin_amdgcn_wave_barrier();
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
+// ---- for kernels that are short of registers --------------------------------------------------------
+// A uniform address (scalar registers) plus a 32-bit byte offset of the lane.
+template <typename V>
+__device__ __forceinline__ V* lane_address(V* base, uint32_t bytes) {
+    typedef std::conditional_t<std::is_const_v<V>, const char, char> Byte;
+    return reinterpret_cast<V*>(reinterpret_cast<Byte*>(base) + bytes);
+}
+
+// The same word in another register, as far as the compiler can tell: what is worked out from it is not worked out ahead
+// of the loop or shared with an earlier use, and so holds no register in between (expanded masks: 32 of them).
+__device__ __forceinline__ uint32_t again(uint32_t x) {
+    uint32_t r;
+    asm volatile("v_mov_b32 %0, %1" : "=v"(r) : "v"(x));
+    return r;
+}
+
+__device__ __forceinline__ int64_t again(int64_t x) {             // x is uniform
+    int64_t r;
+    asm volatile("s_mov_b64 %0, %1" : "=s"(r) : "s"(x));
+    return r;
 }
 
 // ---- split vectors ---------------------------------------------------------------------------
@@ -304,6 +334,30 @@ __device__ __forceinline__ bf8 read_block(const unsigned char* __restrict__ tile
     const v4s lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) v4s*)(first));
     const v4s hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) v4s*)(second));
     return __builtin_bit_cast(bf8, __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7));
+}
+
+// operand of v_mfma_f32_16x16x32_bf16 from the same tiles: columns 16 half + lane % 16, the eight points 8 (lane / 16) ..
+// (A[l%16][8*(l/16) + s], B[8*(l/16) + s][l%16]; register v of lane l holds D[4*(l/16) + v][l%16])
+__device__ __forceinline__ bf8 read_half_block(const unsigned char* __restrict__ tile, int term, int half, int lane) {
+    typedef short v4s __attribute__((ext_vector_type(4)));
+    const int piece = 2 * half + ((lane >> 1) & 1), swizzle = (lane >> 2) & 2;
+    const unsigned char* at = tile + term * (kBlockTile / 2) + (8 * (lane >> 4) + ((lane >> 2) & 3)) * 64 + (lane & 1) * 8;
+    const unsigned char* first = at + ((piece ^ swizzle) << 4);
+    const unsigned char* second = at + 4 * 64 + ((piece ^ swizzle ^ 1) << 4);
+    const v4s lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) v4s*)(first));
+    const v4s hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) v4s*)(second));
+    return __builtin_bit_cast(bf8, __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7));
+}
+
+// stage_block for a block of which only registers 0..3 count (8 neurons): the upper pieces are left alone
+template <int NB, int P>
+__device__ __forceinline__ void stage_narrow_block(unsigned char* __restrict__ tile, const Split<NB, P>& x, int b, int j, int h) {
+    const int swizzle = (j & 2) | ((j >> 2) & 1);
+#pragma unroll
+    for (int term = 0; term < 2; ++term) {
+        const u32x4 v = {x.t[term][b][0], x.t[term][b][1], 0u, 0u};
+        *reinterpret_cast<u32x4*>(tile + j * 64 + term * (kBlockTile / 2) + ((h ^ swizzle) << 4)) = v;
+    }
 }
 
 // G[mb][nb] += sum over the tile's 32 points of z[32 mb + .] (x) x[32 nb + .], two terms and three products, rows and

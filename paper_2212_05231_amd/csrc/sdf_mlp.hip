@@ -361,6 +361,7 @@ __global__ __launch_bounds__(kFwdThreads) void sdf_fwd_kernel(SdfArgs a) {
         }
         matvec_split<1, 4, 3, 3>(w.HLf, pv, yv, lane);
         store_rows16(a.y, i, valid, h, yv[0]);
+        held(yv[0]);
         if (a.masks && valid) {
             a.masks[mask_word(0, a.n, i, h)] = m1;
             if (K == 3) a.masks[mask_word(1, a.n, i, h)] = m_last;
@@ -380,6 +381,7 @@ __global__ __launch_bounds__(kFwdThreads) void sdf_fwd_kernel(SdfArgs a) {
         // 2^18 points the cached store is the faster one)
         if (a.stream_q) store_levels<D, true>(a.q, a.n, i, valid, qv[0], h);
         else store_levels<D>(a.q, a.n, i, valid, qv[0], h);
+        if (D < 32) held(qv[0]);
         float nrm[3];
         contract_jac_regs<D>(J, qv[0], nrm);
 #pragma unroll
@@ -607,26 +609,6 @@ constexpr int kPairs = kPairThreads / 128;        // tiles a workgroup works on
 // them.  The largest lane offset is 48 n bytes (upper lane half, Jacobian), so n stays below 2^26 here.
 constexpr int64_t kPairMaxPoints = (int64_t)1 << 26;
 
-template <typename V>
-__device__ __forceinline__ V* lane_address(V* base, uint32_t bytes) {
-    typedef std::conditional_t<std::is_const_v<V>, const char, char> Byte;
-    return reinterpret_cast<V*>(reinterpret_cast<Byte*>(base) + bytes);
-}
-
-// The same word in another register, as far as the compiler can tell: what is worked out from it is not worked out ahead
-// of the loop or shared with an earlier use, and so holds no register in between (expanded masks: 32 of them).
-__device__ __forceinline__ uint32_t again(uint32_t x) {
-    uint32_t r;
-    asm volatile("v_mov_b32 %0, %1" : "=v"(r) : "v"(x));
-    return r;
-}
-
-__device__ __forceinline__ int64_t again(int64_t x) {             // x is uniform
-    int64_t r;
-    asm volatile("s_mov_b64 %0, %1" : "=s"(r) : "s"(x));
-    return r;
-}
-
 typedef float f2v __attribute__((ext_vector_type(2)));
 
 // Levels 4 g + 2 h + u of the tile's points as in load_levels, store_levels and load_jac, first: the tile's first point.
@@ -790,6 +772,7 @@ __device__ __forceinline__ void sdf_first_order(const SdfArgs& a, const SdfWeigh
         matvec_split<1, 4, 2, 2>(w.H1t, pd, de, lane);
         if (a.stream_q) store_levels_tile<D, true>(a.d_enc, a.n, tile * 32, valid, de[0], j, h);      // as for q in the forward kernel
         else store_levels_tile<D, false>(a.d_enc, a.n, tile * 32, valid, de[0], j, h);
+        if (D < 32) held(de[0]);
         if (a.d_pos) {
             float dp[3];
             contract_jac_tile<D>(a.jac, a.n, tile * 32, a.active_levels, j, h, de[0], dp);
