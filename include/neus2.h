@@ -115,6 +115,12 @@ int neus2_sdf_fwd_grad(const neus2_config* cfg, const float* enc, const float* j
                        const float* const* H, int64_t n, float* y, float* q, float* normal,
                        uint32_t* masks, void* stream);
 
+/* The SDF value alone: sdf[i] [device, n] = y[16 i] of neus2_hash_encode followed by
+ * neus2_sdf_fwd_grad, bit for bit, without the Jacobian, dd/de and the normals.  enc [device,
+ * n_levels*n*2] is scratch: the features of the active levels afterwards. */
+int neus2_sdf_values(const neus2_config* cfg, const float* pos, const void* tables, const float* const* H, int64_t n,
+                     float* enc, float* sdf, void* stream);
+
 /* The SDF network with more matrices than neus2_sdf_fwd_grad / neus2_sdf_mlp_bwd hold fused (the
  * deeper networks of the paper's Fig. 7, "speed-up of our 2nd-order derivative ... across MLP
  * layer numbers"): the same quantities, computed in runs of up to six layers a launch (two with
@@ -382,8 +388,8 @@ int neus2_train_step(const neus2_config* cfg, const neus2_step_buffers* buf, int
 
 /* Sample points of m candidate cells: pos[i] = (cell coordinate + jitter[i]) / G.
  *   cells [device, m int32] Morton numbers (taken modulo G^3), jitter [device, m*3] in [0,1),
- *   pos [device, m*3].  The caller evaluates the SDF there (neus2_hash_encode,
- *   neus2_sdf_fwd_grad) and hands it to neus2_occupancy_update. */
+ *   pos [device, m*3].  The caller evaluates the SDF there (neus2_sdf_values, or
+ *   neus2_hash_encode and neus2_sdf_fwd_grad) and hands it to neus2_occupancy_update. */
 int neus2_occupancy_points(int log2_res, const int32_t* cells, const float* jitter, int64_t m,
                            float* pos, void* stream);
 

@@ -59,6 +59,7 @@ _SIGNATURES = {
     "neus2_workspace_bytes": (C.c_int64, [C.POINTER(Neus2Config), C.c_int64]),
     "neus2_hash_encode": (C.c_int, [C.POINTER(Neus2Config), _P, _P, C.c_int64, _P, _P, _P, _P]),
     "neus2_sdf_fwd_grad": (C.c_int, [C.POINTER(Neus2Config), _P, _P, _P, C.c_int64, _P, _P, _P, _P, _P]),
+    "neus2_sdf_values": (C.c_int, [C.POINTER(Neus2Config), _P, _P, _P, C.c_int64, _P, _P, _P]),
     "neus2_color_fwd": (C.c_int, [C.POINTER(Neus2Config), _P, _P, _P, _P, _P, _P, C.c_int64, _P, _P, _P]),
     "neus2_color_bwd": (C.c_int, [C.POINTER(Neus2Config), _P, _P, _P, _P, _P, _P, _P, _P, _P, C.c_int64, _P, _P, _P, _P, _P, _P]),
     "neus2_render_loss_bwd_ragged": (C.c_int, [C.POINTER(Neus2Config), _P, _P, _P, _P, _P, _P, C.c_int64, C.c_int64, _P, _P, _P,
@@ -168,6 +169,10 @@ def hash_encode(c, pos, tables, enc, jac, dbg_idx=None):
 def sdf_fwd_grad(c, enc, jac, H, n, y, q, normal, masks=None):
     _check(lib().neus2_sdf_fwd_grad(C.byref(c), _ptr(enc), _ptr(jac), _ptr_array(H), n, _ptr(y), _ptr(q),
                                     _ptr(normal), _ptr(masks), _stream()))
+
+
+def sdf_values(c, pos, tables, H, n, enc, sdf):
+    _check(lib().neus2_sdf_values(C.byref(c), _ptr(pos), _ptr(tables), _ptr_array(H), n, _ptr(enc), _ptr(sdf), _stream()))
 
 
 def color_fwd(c, pos, normal, dirs, y, W, n, rgb, sample_ray=None, masks=None):

@@ -229,6 +229,19 @@ int neus2_sdf_fwd_grad(const neus2_config* cfg, const float* enc, const float* j
     return launch_sdf_fwd(cfg, enc, jac, H, n, y, q, normal, masks, (hipStream_t)stream);
 }
 
+int neus2_sdf_values(const neus2_config* cfg, const float* pos, const void* tables, const float* const* H, int64_t n,
+                     float* enc, float* sdf, void* stream) {
+    NEUS2_TRY(check_config(cfg));
+    NEUS2_TRY(check_count(n, "n"));
+    NEUS2_TRY(check_ptr(pos, "pos"));
+    NEUS2_TRY(check_ptr(tables, "tables"));
+    NEUS2_TRY(check_mats((const void* const*)H, cfg->n_sdf_mats, "H"));
+    NEUS2_TRY(check_ptr(enc, "enc"));
+    NEUS2_TRY(check_ptr(sdf, "sdf"));
+    NEUS2_TRY(launch_encode(cfg, pos, tables, n, enc, nullptr, nullptr, (hipStream_t)stream, nullptr, nullptr, true));
+    return launch_sdf_values(cfg, enc, H, n, sdf, (hipStream_t)stream);
+}
+
 static int check_deep(int n_mats, int enc_dim, int64_t n, const void* workspace, int64_t workspace_bytes) {
     if (n_mats < 2 || n_mats > NEUS2_DEEP_MAX_MATS)
         return fail(NEUS2_ERR_UNSUPPORTED, "layer-by-layer sdf network: %d matrices (2..%d are built)", n_mats, NEUS2_DEEP_MAX_MATS);

@@ -51,6 +51,7 @@ struct ZeroRegions {
 };
 
 // internal launchers (each validates nothing; the extern "C" wrappers do)
+// jac == nullptr: the features alone
 int launch_encode(const neus2_config* cfg, const float* pos, const void* tables, int64_t n,
                   float* enc, float* jac, uint32_t* dbg_idx, hipStream_t st, const ZeroRegions* zero = nullptr,
                   float* hess = nullptr, bool active_only = false);
@@ -83,6 +84,7 @@ int launch_sdf_deep_bwd(int n_mats, int enc_dim, const float* enc, const float* 
                         void* workspace, hipStream_t st);
 int launch_sdf_fwd(const neus2_config* cfg, const float* enc, const float* jac,
                    const float* const* H, int64_t n, float* y, float* q, float* normal, uint32_t* masks, hipStream_t st);
+int launch_sdf_values(const neus2_config* cfg, const float* enc, const float* const* H, int64_t n, float* sdf, hipStream_t st);
 int launch_sdf_bwd(const neus2_config* cfg, const float* enc, const float* jac,
                    const float* const* H, const float* d_y, const float* d_normal, int64_t n,
                    float* const* dH, float* d_enc, float* d_pos, const uint32_t* masks, hipStream_t st);

@@ -1,8 +1,7 @@
 """Host side of the occupancy grid (supplement Sec. E.3 "Ray Marching Acceleration"): owns the
 grid's device buffers, draws the candidate cells of an update, and strings the library calls
 together.  All arithmetic on the grid and on the rays runs in the library's kernels
-(`neus2_occupancy_points`, `neus2_hash_encode`, `neus2_sdf_fwd_grad`, `neus2_occupancy_update`,
-`neus2_march_rays`); this module only decides WHICH cells are looked at and WHEN.
+(`neus2_occupancy_points`, `neus2_sdf_values`, `neus2_occupancy_update`, `neus2_march_rays`); this module only decides WHICH cells are looked at and WHEN.
 
 The paper refreshes the grid "periodically" as the publication it cites does; that
 publication's schedule is what `candidates` follows: during the first updates every cell is a
@@ -34,9 +33,7 @@ class OccupancyGrid:
         self._all, self.last_cells = None, None
         self.jitter = torch.zeros(self.m_max, 3, **f32)
         self.pos = torch.zeros(self.m_max, 3, **f32)
-        self.enc, self.jac = torch.zeros(L * self.m_max * F, **f32), torch.zeros(L * self.m_max * F * 3, **f32)
-        self.y, self.q = torch.zeros(self.m_max, 16, **f32), torch.zeros(L * self.m_max * F, **f32)
-        self.normal = torch.zeros(self.m_max, 3, **f32)
+        self.enc, self.sdf = torch.zeros(L * self.m_max * F, **f32), torch.zeros(max(self.m_max, 4), **f32)
 
     def _bits(self):
         """bool [n_cells] on the grid's device, unpacked from the bitfield."""
@@ -77,9 +74,8 @@ class OccupancyGrid:
             jitter.clamp_(max=1.0 - 2.0 ** -24)
             pos_m = self.pos[:m]
             nb.occupancy_points(self.log2_res, cells, jitter, pos_m)
-            nb.hash_encode(step.c, pos_m, step.tables, self.enc, self.jac)
-            nb.sdf_fwd_grad(step.c, self.enc, self.jac, step.H, m, self.y, self.q, self.normal)
-        nb.occupancy_update(self.log2_res, self.density, cells if m else None, self.y if m else None, 16, m,
+            nb.sdf_values(step.c, pos_m, step.tables, step.H, m, self.enc, self.sdf)
+        nb.occupancy_update(self.log2_res, self.density, cells if m else None, self.sdf if m else None, 1, m,
                             float(step.cfg.s), self.decay, self.threshold, self.bitfield, s_dev=step.s_dev)
         self.last_cells = cells
         self.updates += 1

@@ -95,3 +95,31 @@ def test_scatter_on_both_sides_of_the_list_and_record_sizes(n, table_bits, dtype
         assert error <= (1e-5 if with_lists and n >= 1 << 16 else 1e-6)
         found.append(d_pos.cpu().numpy())
     assert all(rel(f, found[0]) <= 1e-5 for f in found)
+
+
+@pytest.mark.parametrize("n,hidden,table,active,levels", [(1, 2, "f16", 16, 16), (31, 1, "f32", 16, 16), (33, 2, "f32", 5, 16),
+                                                         (4097, 2, "f16", 16, 16), (1000, 1, "f16", 8, 8)])
+def test_sdf_values_equal_the_forward_calls(n, hidden, table, active, levels):
+    """The value-only path does the same arithmetic: the same bits as the encoding and the forward kernel; nothing behind
+    the n values is written."""
+    import dataclasses
+    rng = np.random.default_rng(n + hidden)
+    cfg = wl.make_config(2 if levels == 16 else 1)
+    cfg = dataclasses.replace(cfg, table_dtype=table, active_levels=active, sdf_dims=[2 * levels] + [64] * hidden + [16])
+    assert cfg.n_levels == levels
+    c = nb.make_config(cfg)
+    pos = cuda(rng.uniform(size=(n, 3)).astype(np.float32))
+    tables = cuda(rng.normal(size=(levels, cfg.table_size, 2)).astype(np.float32) * 0.1)
+    if table == "f16":
+        tables = tables.half()
+    H = [cuda((rng.normal(size=(o_, i)) * (2.0 / i) ** 0.5).astype(np.float32)) for i, o_ in zip(cfg.sdf_dims, cfg.sdf_dims[1:])]
+    enc, jac, q = torch.empty(levels * n * 2, device="cuda"), torch.empty(levels * n * 6, device="cuda"), torch.empty(levels * n * 2, device="cuda")
+    y, normal = torch.empty(n, 16, device="cuda"), torch.empty(n, 3, device="cuda")
+    nb.hash_encode(c, pos, tables, enc, jac)
+    nb.sdf_fwd_grad(c, enc, jac, H, n, y, q, normal)
+    sdf, behind = guarded((n,))
+    scratch = torch.full((levels * n * 2,), float("nan"), device="cuda")
+    nb.sdf_values(c, pos, tables, H, n, scratch, sdf)
+    assert torch.equal(sdf, y[:, 0]) and float(y[:, 0].abs().max()) > 0
+    assert torch.equal(scratch[: 2 * n * active], enc[: 2 * n * active])
+    assert torch.all(torch.signbit(behind)) and torch.all(behind == 0)
