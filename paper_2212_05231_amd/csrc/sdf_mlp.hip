@@ -316,13 +316,124 @@ __device__ __forceinline__ void store_rows16(float* __restrict__ dst, int64_t i,
 }
 
 // ------------------------------------------------------------------------------------------
-// The forward kernel runs 512 threads per workgroup: its 90 KB of matrices are shared by eight
-// wavefronts, two per SIMD, so that one wavefront's waits for memory and LDS are filled by the
-// other (vector and matrix instructions of a SIMD do not run side by side, but stalls do overlap).
-constexpr int kFwdThreads = 512;
+// The forward kernel runs 1024 threads per workgroup: its 90 KB of matrices are shared by sixteen wavefronts, four per
+// SIMD with 128 registers each, so that one wavefront's waits for memory, LDS and matrix results are filled by the others.
+// Nothing is requested ahead: two wavefronts per SIMD that prefetched the next encoding and this tile's Jacobian (221
+// registers) took 60 us at 2^18 points and 199 at 2^20, four take 51 and 168 (4.5 TB/s: its streams are 732 bytes a point),
+// at 32576 points 15.7 and 12.8.
+constexpr int kFwdThreads = 1024;
 constexpr int kFwdWaves = kFwdThreads / 64;
+constexpr int kValueThreads = 512;
+constexpr int kValueWaves = kValueThreads / 64;
 
-template <int D, int K>
+// Accesses of a tile: a uniform address (scalar registers: array, tile, level) plus a 32-bit byte offset of the lane.  Written
+// with one 64-bit index per lane, the compiler kept two dozen addresses in vector registers through the whole loop and spilled
+// them.  The largest lane offset is 48 n bytes (upper lane half, Jacobian), so n stays below 2^26 here.
+constexpr int64_t kTileMaxPoints = (int64_t)1 << 26;
+
+typedef float f2v __attribute__((ext_vector_type(2)));
+
+// Levels 4 g + 2 h + u of the tile's points as in load_levels, store_levels and load_jac, first: the tile's first point.
+// Loads are unconditional: a lane without a point reads the tile's last one, a level beyond the active ones is read in
+// the lower lane half's place (in bounds: the arrays hold every level), and what does not count is replaced by zeros
+// afterwards.  A branch per level instead kept 48 zeroed registers alive across the loads.
+__device__ __forceinline__ int last_point(int64_t n, int64_t first) { return n - first < 32 ? (int)(n - first) - 1 : 31; }
+
+template <int D>
+__device__ __forceinline__ v16f load_levels_tile(const float* __restrict__ src, int64_t n, int64_t first, int active, int j, int h) {
+    v16f x = zero16();
+    const f2v* tile = reinterpret_cast<const f2v*>(src) + first;
+    const int64_t plane = again(n);
+    const int last = last_point(n, first);
+    const uint32_t off = 8u * (uint32_t)min(j, last), upper = again(h ? 16u * (uint32_t)n : 0u);
+#pragma unroll
+    for (int g = 0; g < D / 8; ++g)
+#pragma unroll
+        for (int u = 0; u < 2; ++u) {
+            const bool on = 4 * g + 2 * h + u < active;
+            const f2v v = *lane_address(tile + (4 * g + u) * plane, off + (on ? upper : 0u));
+            x[4 * g + 2 * u] = on && j <= last ? v.x : 0.f;
+            x[4 * g + 2 * u + 1] = on && j <= last ? v.y : 0.f;
+        }
+    return x;
+}
+
+template <int D, bool STREAM>
+__device__ __forceinline__ void store_levels_tile(float* __restrict__ dst, int64_t n, int64_t first, bool valid, const v16f& x, int j, int h) {
+    if (!valid) return;
+    f2v* tile = reinterpret_cast<f2v*>(dst) + first;
+    const int64_t plane = again(n);
+    const uint32_t off = again(8u * ((uint32_t)j + 2u * (uint32_t)h * (uint32_t)n));
+#pragma unroll
+    for (int g = 0; g < D / 8; ++g)
+#pragma unroll
+        for (int u = 0; u < 2; ++u) {
+            const f2v v = {x[4 * g + 2 * u], x[4 * g + 2 * u + 1]};
+            if (STREAM) __builtin_nontemporal_store(v, lane_address(tile + (4 * g + u) * plane, off));
+            else *lane_address(tile + (4 * g + u) * plane, off) = v;
+        }
+}
+
+// (de/dx)^T dL/de of the tile's points: this lane's levels
+template <int D, bool STREAM>
+__device__ __forceinline__ void contract_jac_tile(const float* __restrict__ jac, int64_t n, int64_t first, int active, int j, int h,
+                                                  const v16f& x, float out[3]) {
+    out[0] = out[1] = out[2] = 0.f;
+    const f2v* tile = reinterpret_cast<const f2v*>(jac) + first;
+    const int64_t plane = again(n);
+    const int last = last_point(n, first);
+    const uint32_t off = 8u * (uint32_t)min(j, last), upper = again(h ? 48u * (uint32_t)n : 0u);
+#pragma unroll
+    for (int g = 0; g < D / 8; ++g)
+#pragma unroll
+        for (int u = 0; u < 2; ++u) {
+            const bool on = 4 * g + 2 * h + u < active;
+            f2v J[3];
+#pragma unroll
+            for (int c = 0; c < 3; ++c) {
+                const f2v* p = lane_address(tile + (3 * (4 * g + u) + c) * plane, off + (on ? upper : 0u));
+                J[c] = STREAM ? __builtin_nontemporal_load(p) : *p;
+            }
+            const float x0 = x[4 * g + 2 * u], x1 = x[4 * g + 2 * u + 1];
+            out[0] += on ? x0 * J[0].x + x1 * J[1].y : 0.f;
+            out[1] += on ? x0 * J[0].y + x1 * J[2].x : 0.f;
+            out[2] += on ? x0 * J[1].x + x1 * J[2].y : 0.f;
+        }
+}
+
+// t_0 = (de/dx) dL/dn of the tile's points
+template <int D>
+__device__ __forceinline__ v16f apply_jac_tile(const float* __restrict__ jac, int64_t n, int64_t first, int active, int j, int h, const float v[3]) {
+    f2v J[D / 4][3];           // (J00,J01) (J02,J10) (J11,J12) per level of this lane
+    const f2v* tile = reinterpret_cast<const f2v*>(jac) + first;
+    const int64_t plane = again(n);
+    const int last = last_point(n, first);
+    const uint32_t off = 8u * (uint32_t)min(j, last), upper = again(h ? 48u * (uint32_t)n : 0u);
+#pragma unroll
+    for (int g = 0; g < D / 8; ++g)
+#pragma unroll
+        for (int u = 0; u < 2; ++u) {
+            const bool on = 4 * g + 2 * h + u < active;
+            const uint32_t o = off + (on ? upper : 0u);
+#pragma unroll
+            for (int c = 0; c < 3; ++c) J[2 * g + u][c] = __builtin_nontemporal_load(lane_address(tile + (3 * (4 * g + u) + c) * plane, o));
+        }
+    v16f t = zero16();
+#pragma unroll
+    for (int g = 0; g < D / 8; ++g)
+#pragma unroll
+        for (int u = 0; u < 2; ++u) {
+            const bool on = 4 * g + 2 * h + u < active && j <= last;
+            const f2v a = J[2 * g + u][0], b = J[2 * g + u][1], c = J[2 * g + u][2];
+            const float t0 = a.x * v[0] + a.y * v[1] + b.x * v[2], t1 = b.y * v[0] + c.x * v[1] + c.y * v[2];
+            t[4 * g + 2 * u] = on ? t0 : 0.f;
+            t[4 * g + 2 * u + 1] = on ? t1 : 0.f;
+        }
+    return t;
+}
+
+// WIDE: from kTileMaxPoints points on
+template <int D, int K, bool WIDE>
 __global__ __launch_bounds__(kFwdThreads) void sdf_fwd_kernel(SdfArgs a) {
     __shared__ SdfWeights<D, K, false> w;
     load_weights<D, K, false, kFwdThreads>(w, a);
@@ -332,19 +443,12 @@ __global__ __launch_bounds__(kFwdThreads) void sdf_fwd_kernel(SdfArgs a) {
     const int j = lane & 31, h = lane >> 5;
     const int64_t tiles = (a.n + 31) / 32;
     const int64_t stride = (int64_t)gridDim.x * kFwdWaves;
-    int64_t tile = (int64_t)blockIdx.x * kFwdWaves + wave;
-    // the encoding of the NEXT tile and the Jacobian of THIS tile are requested before the
-    // matrix work of this tile starts, so that HBM latency hides behind it
-    v16f x_next = load_levels<D>(a.enc, a.n, tile * 32 + j, tile < tiles && tile * 32 + j < a.n, a.active_levels, h);
-    for (; tile < tiles; tile += stride) {
-        const int64_t i = tile * 32 + j;
-        const bool valid = i < a.n;
-        v16f x0[1] = {x_next};
-        const JacRegs<D> J = load_jac<D>(a.jac, a.n, i, valid, a.active_levels, h);
-        {
-            const int64_t in = (tile + stride) * 32 + j;
-            x_next = load_levels<D>(a.enc, a.n, in, tile + stride < tiles && in < a.n, a.active_levels, h);
-        }
+    // tiles go to the workgroups first and then to their wavefronts: a small batch has every compute unit at work
+    for (int64_t tile = (int64_t)wave * gridDim.x + blockIdx.x; tile < tiles; tile += stride) {
+        const bool valid = tile * 32 + j < a.n;
+        v16f x0[1];
+        if (WIDE) x0[0] = load_levels<D>(a.enc, a.n, tile * 32 + j, valid, a.active_levels, h);
+        else x0[0] = load_levels_tile<D>(a.enc, a.n, tile * 32, a.active_levels, j, h);
         v16f a1[2], yv[1];
         Split<1, 3> px;
         Split<2, 3> pv;
@@ -360,12 +464,17 @@ __global__ __launch_bounds__(kFwdThreads) void sdf_fwd_kernel(SdfArgs a) {
             split(a2, pv);
         }
         matvec_split<1, 4, 3, 3>(w.HLf, pv, yv, lane);
-        store_rows16(a.y, i, valid, h, yv[0]);
-        held(yv[0]);
-        if (a.masks && valid) {
-            a.masks[mask_word(0, a.n, i, h)] = m1;
-            if (K == 3) a.masks[mask_word(1, a.n, i, h)] = m_last;
+        if (valid) {
+            float4* row = lane_address(reinterpret_cast<float4*>(a.y) + tile * 128, 64u * j + 16u * h);
+            row[0] = make_float4(yv[0][0], yv[0][1], yv[0][2], yv[0][3]);
+            row[2] = make_float4(yv[0][4], yv[0][5], yv[0][6], yv[0][7]);
+            if (a.masks) {
+                uint32_t* words = a.masks + tile * 64;
+                *lane_address(words, 8u * j + 4u * h) = m1;
+                if (K == 3) *lane_address(words + 2 * a.n, 8u * j + 4u * h) = m_last;
+            }
         }
+        held(yv[0]);
         // reverse sweep for dd/de
         v16f s1[2];
         last_row_masked(w.HLrow0, m_last, h, pv);
@@ -379,15 +488,18 @@ __global__ __launch_bounds__(kFwdThreads) void sdf_fwd_kernel(SdfArgs a) {
         // dd/de is read next by the scatter-add, four kernels later: for a batch whose per-point arrays
         // exceed the caches it is written with non-temporal stores (25 us of the step at 2^20 points; at
         // 2^18 points the cached store is the faster one)
-        if (a.stream_q) store_levels<D, true>(a.q, a.n, i, valid, qv[0], h);
-        else store_levels<D>(a.q, a.n, i, valid, qv[0], h);
+        if (WIDE) store_levels<D, true>(a.q, a.n, tile * 32 + j, valid, qv[0], h);
+        else if (a.stream_q) store_levels_tile<D, true>(a.q, a.n, tile * 32, valid, qv[0], j, h);
+        else store_levels_tile<D, false>(a.q, a.n, tile * 32, valid, qv[0], j, h);
         if (D < 32) held(qv[0]);
         float nrm[3];
-        contract_jac_regs<D>(J, qv[0], nrm);
+        if (WIDE) contract_jac<D>(a.jac, a.n, tile * 32 + j, valid, a.active_levels, h, qv[0], nrm);
+        else contract_jac_tile<D, true>(a.jac, a.n, tile * 32, a.active_levels, j, h, qv[0], nrm);
 #pragma unroll
         for (int c = 0; c < 3; ++c) nrm[c] += __shfl_xor(nrm[c], 32);
         if (valid && h == 0) {
-            a.normal[3 * i + 0] = nrm[0]; a.normal[3 * i + 1] = nrm[1]; a.normal[3 * i + 2] = nrm[2];
+            float* out = lane_address(a.normal + tile * 96, 12u * j);
+            out[0] = nrm[0]; out[1] = nrm[1]; out[2] = nrm[2];
         }
     }
 }
@@ -406,13 +518,13 @@ struct SdfValueWeights {
 };
 
 template <int D, int K>
-__global__ __launch_bounds__(kFwdThreads, 4) void sdf_value_kernel(SdfArgs a) {
+__global__ __launch_bounds__(kValueThreads, 4) void sdf_value_kernel(SdfArgs a) {
     typedef SdfValueWeights<D, K> W;
     __shared__ W w;
     {
-        typename W::M1::template Fill<64, kFwdThreads, false> f1;
-        typename W::M2::template Fill<K == 3 ? 64 : 0, kFwdThreads, false> f2;
-        typename W::M2::template Fill<32, kFwdThreads, false> fl;
+        typename W::M1::template Fill<64, kValueThreads, false> f1;
+        typename W::M2::template Fill<K == 3 ? 64 : 0, kValueThreads, false> f2;
+        typename W::M2::template Fill<32, kValueThreads, false> fl;
         const float* __restrict__ H1 = a.H[0];
         const float* __restrict__ H2 = a.H[1];
         const float* __restrict__ HL = a.H[K - 1];
@@ -428,7 +540,7 @@ __global__ __launch_bounds__(kFwdThreads, 4) void sdf_value_kernel(SdfArgs a) {
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int j = lane & 31, h = lane >> 5;
     const int64_t tiles = (a.n + 31) / 32;
-    for (int64_t tile = (int64_t)blockIdx.x * kFwdWaves + wave; tile < tiles; tile += (int64_t)gridDim.x * kFwdWaves) {
+    for (int64_t tile = (int64_t)blockIdx.x * kValueWaves + wave; tile < tiles; tile += (int64_t)gridDim.x * kValueWaves) {
         const int64_t i = tile * 32 + j;
         const bool valid = i < a.n;
         v16f x0[1] = {load_levels<D>(a.enc, a.n, i, valid, a.active_levels, h)};
@@ -662,109 +774,6 @@ __global__ __launch_bounds__(kThreads) void sdf_bwd_kernel(SdfArgs a) {
 constexpr int kPairThreads = 512;
 constexpr int kPairs = kPairThreads / 128;        // tiles a workgroup works on
 
-// Accesses of a tile: a uniform address (scalar registers: array, tile, level) plus a 32-bit byte offset of the lane.  Written
-// with one 64-bit index per lane, the compiler kept two dozen addresses in vector registers through the whole loop and spilled
-// them.  The largest lane offset is 48 n bytes (upper lane half, Jacobian), so n stays below 2^26 here.
-constexpr int64_t kPairMaxPoints = (int64_t)1 << 26;
-
-typedef float f2v __attribute__((ext_vector_type(2)));
-
-// Levels 4 g + 2 h + u of the tile's points as in load_levels, store_levels and load_jac, first: the tile's first point.
-// Loads are unconditional: a lane without a point reads the tile's last one, a level beyond the active ones is read in
-// the lower lane half's place (in bounds: the arrays hold every level), and what does not count is replaced by zeros
-// afterwards.  A branch per level instead kept 48 zeroed registers alive across the loads.
-__device__ __forceinline__ int last_point(int64_t n, int64_t first) { return n - first < 32 ? (int)(n - first) - 1 : 31; }
-
-template <int D>
-__device__ __forceinline__ v16f load_levels_tile(const float* __restrict__ src, int64_t n, int64_t first, int active, int j, int h) {
-    v16f x = zero16();
-    const f2v* tile = reinterpret_cast<const f2v*>(src) + first;
-    const int64_t plane = again(n);
-    const int last = last_point(n, first);
-    const uint32_t off = 8u * (uint32_t)min(j, last), upper = again(h ? 16u * (uint32_t)n : 0u);
-#pragma unroll
-    for (int g = 0; g < D / 8; ++g)
-#pragma unroll
-        for (int u = 0; u < 2; ++u) {
-            const bool on = 4 * g + 2 * h + u < active;
-            const f2v v = *lane_address(tile + (4 * g + u) * plane, off + (on ? upper : 0u));
-            x[4 * g + 2 * u] = on && j <= last ? v.x : 0.f;
-            x[4 * g + 2 * u + 1] = on && j <= last ? v.y : 0.f;
-        }
-    return x;
-}
-
-template <int D, bool STREAM>
-__device__ __forceinline__ void store_levels_tile(float* __restrict__ dst, int64_t n, int64_t first, bool valid, const v16f& x, int j, int h) {
-    if (!valid) return;
-    f2v* tile = reinterpret_cast<f2v*>(dst) + first;
-    const int64_t plane = again(n);
-    const uint32_t off = again(8u * ((uint32_t)j + 2u * (uint32_t)h * (uint32_t)n));
-#pragma unroll
-    for (int g = 0; g < D / 8; ++g)
-#pragma unroll
-        for (int u = 0; u < 2; ++u) {
-            const f2v v = {x[4 * g + 2 * u], x[4 * g + 2 * u + 1]};
-            if (STREAM) __builtin_nontemporal_store(v, lane_address(tile + (4 * g + u) * plane, off));
-            else *lane_address(tile + (4 * g + u) * plane, off) = v;
-        }
-}
-
-// (de/dx)^T dL/de of the tile's points: this lane's levels
-template <int D>
-__device__ __forceinline__ void contract_jac_tile(const float* __restrict__ jac, int64_t n, int64_t first, int active, int j, int h,
-                                                  const v16f& x, float out[3]) {
-    out[0] = out[1] = out[2] = 0.f;
-    const f2v* tile = reinterpret_cast<const f2v*>(jac) + first;
-    const int64_t plane = again(n);
-    const int last = last_point(n, first);
-    const uint32_t off = 8u * (uint32_t)min(j, last), upper = again(h ? 48u * (uint32_t)n : 0u);
-#pragma unroll
-    for (int g = 0; g < D / 8; ++g)
-#pragma unroll
-        for (int u = 0; u < 2; ++u) {
-            const bool on = 4 * g + 2 * h + u < active;
-            f2v J[3];
-#pragma unroll
-            for (int c = 0; c < 3; ++c) J[c] = *lane_address(tile + (3 * (4 * g + u) + c) * plane, off + (on ? upper : 0u));
-            const float x0 = x[4 * g + 2 * u], x1 = x[4 * g + 2 * u + 1];
-            out[0] += on ? x0 * J[0].x + x1 * J[1].y : 0.f;
-            out[1] += on ? x0 * J[0].y + x1 * J[2].x : 0.f;
-            out[2] += on ? x0 * J[1].x + x1 * J[2].y : 0.f;
-        }
-}
-
-// t_0 = (de/dx) dL/dn of the tile's points
-template <int D>
-__device__ __forceinline__ v16f apply_jac_tile(const float* __restrict__ jac, int64_t n, int64_t first, int active, int j, int h, const float v[3]) {
-    f2v J[D / 4][3];           // (J00,J01) (J02,J10) (J11,J12) per level of this lane
-    const f2v* tile = reinterpret_cast<const f2v*>(jac) + first;
-    const int64_t plane = again(n);
-    const int last = last_point(n, first);
-    const uint32_t off = 8u * (uint32_t)min(j, last), upper = again(h ? 48u * (uint32_t)n : 0u);
-#pragma unroll
-    for (int g = 0; g < D / 8; ++g)
-#pragma unroll
-        for (int u = 0; u < 2; ++u) {
-            const bool on = 4 * g + 2 * h + u < active;
-            const uint32_t o = off + (on ? upper : 0u);
-#pragma unroll
-            for (int c = 0; c < 3; ++c) J[2 * g + u][c] = __builtin_nontemporal_load(lane_address(tile + (3 * (4 * g + u) + c) * plane, o));
-        }
-    v16f t = zero16();
-#pragma unroll
-    for (int g = 0; g < D / 8; ++g)
-#pragma unroll
-        for (int u = 0; u < 2; ++u) {
-            const bool on = 4 * g + 2 * h + u < active && j <= last;
-            const f2v a = J[2 * g + u][0], b = J[2 * g + u][1], c = J[2 * g + u][2];
-            const float t0 = a.x * v[0] + a.y * v[1] + b.x * v[2], t1 = b.y * v[0] + c.x * v[1] + c.y * v[2];
-            t[4 * g + 2 * u] = on ? t0 : 0.f;
-            t[4 * g + 2 * u + 1] = on ? t1 : 0.f;
-        }
-    return t;
-}
-
 template <int D, int K>
 struct SdfPairSmem {
     SdfWeights<D, K, true, 2> w;
@@ -833,7 +842,7 @@ __device__ __forceinline__ void sdf_first_order(const SdfArgs& a, const SdfWeigh
         if (D < 32) held(de[0]);
         if (a.d_pos) {
             float dp[3];
-            contract_jac_tile<D>(a.jac, a.n, tile * 32, a.active_levels, j, h, de[0], dp);
+            contract_jac_tile<D, false>(a.jac, a.n, tile * 32, a.active_levels, j, h, de[0], dp);
 #pragma unroll
             for (int c = 0; c < 3; ++c) dp[c] += __shfl_xor(dp[c], 32);
             if (valid && h == 0) {
@@ -972,24 +981,24 @@ __global__ __launch_bounds__(kPairThreads) void sdf_bwd_pair_kernel(SdfArgs a) {
 template <int D, int K>
 int run_fwd(const SdfArgs& a, hipStream_t st) {
     const int64_t tiles = (a.n + 31) / 32;
-    const int64_t want = (tiles + kFwdWaves - 1) / kFwdWaves;
-    const int blocks = persistent_blocks((const void*)sdf_fwd_kernel<D, K>, kFwdThreads, want);
-    hipLaunchKernelGGL((sdf_fwd_kernel<D, K>), dim3(blocks), dim3(kFwdThreads), 0, st, a);
+    const auto kernel = a.n < kTileMaxPoints ? sdf_fwd_kernel<D, K, false> : sdf_fwd_kernel<D, K, true>;
+    const int blocks = persistent_blocks((const void*)kernel, kFwdThreads, tiles);
+    hipLaunchKernelGGL(kernel, dim3(blocks), dim3(kFwdThreads), 0, st, a);
     return check_launch("sdf forward");
 }
 
 template <int D, int K>
 int run_values(const SdfArgs& a, hipStream_t st) {
     const int64_t tiles = (a.n + 31) / 32;
-    const int blocks = persistent_blocks((const void*)sdf_value_kernel<D, K>, kFwdThreads, (tiles + kFwdWaves - 1) / kFwdWaves);
-    hipLaunchKernelGGL((sdf_value_kernel<D, K>), dim3(blocks), dim3(kFwdThreads), 0, st, a);
+    const int blocks = persistent_blocks((const void*)sdf_value_kernel<D, K>, kValueThreads, (tiles + kValueWaves - 1) / kValueWaves);
+    hipLaunchKernelGGL((sdf_value_kernel<D, K>), dim3(blocks), dim3(kValueThreads), 0, st, a);
     return check_launch("sdf values");
 }
 
 template <int D, int K>
 int run_bwd(const SdfArgs& a, hipStream_t st) {
     const int64_t tiles = (a.n + 31) / 32;
-    if (a.masks && a.n < kPairMaxPoints) {
+    if (a.masks && a.n < kTileMaxPoints) {
         const int blocks = persistent_blocks((const void*)sdf_bwd_pair_kernel<D, K>, kPairThreads, (tiles + kPairs - 1) / kPairs);
         hipLaunchKernelGGL((sdf_bwd_pair_kernel<D, K>), dim3(blocks), dim3(kPairThreads), 0, st, a);
     } else {
