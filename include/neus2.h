@@ -393,6 +393,10 @@ int neus2_train_step(const neus2_config* cfg, const neus2_step_buffers* buf, int
 int neus2_occupancy_points(int log2_res, const int32_t* cells, const float* jitter, int64_t m,
                            float* pos, void* stream);
 
+/* The cells whose bit is set: cells [device, G^3 int32] their Morton numbers in ascending order, counts [device,
+ * 1 + ceil(G^3 / 8192) int32] scratch with their number in counts[0]. */
+int neus2_occupancy_list(int log2_res, const uint32_t* bitfield, int32_t* counts, int32_t* cells, void* stream);
+
 /* One refresh: density *= decay for every cell; density[cells[i]] = max(., phi_s(sdf[i*sdf_stride]))
  * (a cell named twice keeps the larger; cell numbers outside the grid and non-finite values
  * are skipped); then bit c = density[c] > threshold for every cell.

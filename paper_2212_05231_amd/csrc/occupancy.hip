@@ -84,6 +84,50 @@ __global__ __launch_bounds__(kThreads) void bits_kernel(const float* __restrict_
     if (i < count && (lane & 31) == 0) bitfield[i >> 5] = (uint32_t)(mask >> lane);
 }
 
+// The numbers of the cells whose bit is set, ascending.  A thread takes a word of 32 cells, a workgroup kThreads of them:
+// first every workgroup's count, then each adds up the counts in front of it (2048 at most) and writes its part of the list.
+// counts[0] = their total, counts[1 + b] = those of workgroup b.  Bound by launch latency: the bitfield is 2 MB at most.
+// (Unpacking the bits to a byte a cell and compacting those took five passes over 2 to 16 bytes a cell.)
+__global__ __launch_bounds__(kThreads) void count_cells_kernel(const uint32_t* __restrict__ bitfield, int words, int32_t* __restrict__ counts) {
+    __shared__ int part[kThreads / 64];
+    const int w = blockIdx.x * kThreads + threadIdx.x;
+    int v = w < words ? __popc(bitfield[w]) : 0;
+#pragma unroll
+    for (int step = 32; step > 0; step >>= 1) v += __shfl_xor(v, step);
+    if ((threadIdx.x & 63) == 0) part[threadIdx.x >> 6] = v;
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        int sum = 0;
+        for (int k = 0; k < kThreads / 64; ++k) sum += part[k];
+        counts[1 + blockIdx.x] = sum;
+    }
+}
+
+__global__ __launch_bounds__(kThreads) void list_cells_kernel(const uint32_t* __restrict__ bitfield, int words, int32_t* __restrict__ counts,
+                                                              int32_t* __restrict__ cells) {
+    __shared__ int before[kThreads / 64], own[kThreads / 64];
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int w = blockIdx.x * kThreads + threadIdx.x;
+    uint32_t bits = w < words ? bitfield[w] : 0u;
+    int front = 0;
+    for (int b = threadIdx.x; b < (int)blockIdx.x; b += kThreads) front += counts[1 + b];
+#pragma unroll
+    for (int step = 32; step > 0; step >>= 1) front += __shfl_xor(front, step);
+    const int count = __popc(bits);
+    int upto = count;
+#pragma unroll
+    for (int step = 1; step < 64; step <<= 1) {
+        const int up = __shfl_up(upto, step);
+        if (lane >= step) upto += up;
+    }
+    if (lane == 63) { before[wave] = front; own[wave] = upto; }
+    __syncthreads();
+    int at = upto - count;
+    for (int k = 0; k < kThreads / 64; ++k) at += before[k] + (k < wave ? own[k] : 0);
+    if (blockIdx.x == gridDim.x - 1 && threadIdx.x == kThreads - 1) counts[0] = at + count;
+    for (; bits; bits &= bits - 1u) cells[at++] = 32 * w + (__ffs(bits) - 1);
+}
+
 // ---- marching ---------------------------------------------------------------------------------
 
 struct Chord {
@@ -233,6 +277,20 @@ extern "C" int neus2_occupancy_points(int log2_res, const int32_t* cells, const 
     hipStream_t st = static_cast<hipStream_t>(stream);
     cell_points_kernel<<<(unsigned)((m + kThreads - 1) / kThreads), kThreads, 0, st>>>(log2_res, cells, jitter, m, pos);
     return check_launch("cell_points_kernel");
+}
+
+extern "C" int neus2_occupancy_list(int log2_res, const uint32_t* bitfield, int32_t* counts, int32_t* cells, void* stream) {
+    NEUS2_TRY(check_grid(log2_res));
+    NEUS2_TRY(check_ptr(bitfield, "bitfield"));
+    NEUS2_TRY(check_ptr(counts, "counts"));
+    NEUS2_TRY(check_ptr(cells, "cells"));
+    hipStream_t st = static_cast<hipStream_t>(stream);
+    const int words = 1 << (3 * log2_res - 5);
+    const unsigned blocks = (unsigned)((words + kThreads - 1) / kThreads);
+    count_cells_kernel<<<blocks, kThreads, 0, st>>>(bitfield, words, counts);
+    NEUS2_TRY(check_launch("count_cells_kernel"));
+    list_cells_kernel<<<blocks, kThreads, 0, st>>>(bitfield, words, counts, cells);
+    return check_launch("list_cells_kernel");
 }
 
 extern "C" int neus2_occupancy_update(int log2_res, float* density, const int32_t* cells, const float* sdf,

@@ -1,7 +1,8 @@
 """Host side of the occupancy grid (supplement Sec. E.3 "Ray Marching Acceleration"): owns the
 grid's device buffers, draws the candidate cells of an update, and strings the library calls
 together.  All arithmetic on the grid and on the rays runs in the library's kernels
-(`neus2_occupancy_points`, `neus2_sdf_values`, `neus2_occupancy_update`, `neus2_march_rays`); this module only decides WHICH cells are looked at and WHEN.
+(`neus2_occupancy_list`, `neus2_occupancy_points`, `neus2_sdf_values`, `neus2_occupancy_update`,
+`neus2_march_rays`); this module only decides WHICH cells are looked at and WHEN.
 
 The paper refreshes the grid "periodically" as the publication it cites does; that
 publication's schedule is what `candidates` follows: during the first updates every cell is a
@@ -31,6 +32,8 @@ class OccupancyGrid:
         L, F = cfg.n_levels, cfg.n_features
         f32 = dict(dtype=torch.float32, device=device)
         self._all, self.last_cells = None, None
+        self._occupied = torch.empty(self.n_cells, dtype=torch.int32, device=device)
+        self._counts = torch.empty(1 + (self.n_cells + 8191) // 8192, dtype=torch.int32, device=device)
         self.jitter = torch.zeros(self.m_max, 3, **f32)
         self.pos = torch.zeros(self.m_max, 3, **f32)
         self.enc, self.sdf = torch.zeros(L * self.m_max * F, **f32), torch.zeros(max(self.m_max, 4), **f32)
@@ -52,12 +55,15 @@ class OccupancyGrid:
                 self._all = torch.arange(self.n_cells, dtype=torch.int32, device=dev)
             return self._all
         m = int(self.n_cells * self.later_fraction)
-        uniform = torch.randint(0, self.n_cells, (m // 2,), generator=gen, device=dev, dtype=torch.int32)
-        occupied = torch.nonzero(self._bits()).reshape(-1).to(torch.int32)
-        if occupied.numel() == 0:
-            return uniform
-        pick = torch.randint(0, occupied.numel(), (m - m // 2,), generator=gen, device=dev)
-        return torch.cat([uniform, occupied[pick]])
+        cells = torch.empty(m, dtype=torch.int32, device=dev)
+        torch.randint(0, self.n_cells, (m // 2,), generator=gen, dtype=torch.int32, device=dev, out=cells[: m // 2])
+        nb.occupancy_list(self.log2_res, self.bitfield, self._counts, self._occupied)
+        occupied = int(self._counts[0].item())
+        if occupied == 0:
+            return cells[: m // 2]
+        pick = torch.randint(0, occupied, (m - m // 2,), generator=gen, device=dev)
+        torch.index_select(self._occupied, 0, pick, out=cells[m // 2:])
+        return cells
 
     def update(self, gen=None, cells=None) -> int:
         """One refresh from the current SDF; the candidate cells and the point inside each are

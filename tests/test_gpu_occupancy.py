@@ -253,3 +253,16 @@ def test_training_loop_with_marched_samples():
     assert last < 0.35 * first
     assert out["surface_found"] > 0.95 and out["depth_error"] < 0.06
     assert 0.05 < out["occupied_fraction"] < 0.95 and out["samples_last"] > 2048
+
+
+@pytest.mark.parametrize("log2_res,share", [(2, 0.5), (3, 0.0), (4, 1.0), (5, 0.03), (6, 0.6), (8, 0.01)])
+def test_list_of_the_occupied_cells(log2_res, share):
+    """Grids smaller than a workgroup's part, of several parts and of the largest number of them; empty and full ones."""
+    cells = 1 << (3 * log2_res)
+    bits = np.random.default_rng(log2_res).random(cells) < share
+    words = cuda(oc.pack_bits(bits).view(np.int32), torch.int32)
+    listed, counts = torch.full((cells + 8,), -7, dtype=torch.int32, device="cuda"), torch.empty(1 + (cells + 8191) // 8192, dtype=torch.int32, device="cuda")
+    nb.occupancy_list(log2_res, words, counts, listed)
+    expected = np.flatnonzero(bits)
+    assert int(counts[0]) == len(expected)
+    assert np.array_equal(listed.cpu().numpy()[: len(expected)], expected) and bool((listed[len(expected):] == -7).all())
