@@ -57,12 +57,15 @@ class OccupancyGrid:
         m = int(self.n_cells * self.later_fraction)
         cells = torch.empty(m, dtype=torch.int32, device=dev)
         torch.randint(0, self.n_cells, (m // 2,), generator=gen, dtype=torch.int32, device=dev, out=cells[: m // 2])
-        nb.occupancy_list(self.log2_res, self.bitfield, self._counts, self._occupied)
-        occupied = int(self._counts[0].item())
-        if occupied == 0:
+        if dev.type == "cuda":
+            nb.occupancy_list(self.log2_res, self.bitfield, self._counts, self._occupied)
+            occupied = self._occupied[: int(self._counts[0].item())]
+        else:                                          # the schedule alone, without the library's kernels
+            occupied = torch.nonzero(self._bits()).reshape(-1).to(torch.int32)
+        if occupied.numel() == 0:
             return cells[: m // 2]
-        pick = torch.randint(0, occupied, (m - m // 2,), generator=gen, device=dev)
-        torch.index_select(self._occupied, 0, pick, out=cells[m // 2:])
+        pick = torch.randint(0, occupied.numel(), (m - m // 2,), generator=gen, device=dev)
+        torch.index_select(occupied, 0, pick, out=cells[m // 2:])
         return cells
 
     def update(self, gen=None, cells=None) -> int:
