@@ -519,7 +519,6 @@ __device__ __forceinline__ void color_first_layer(const ColorArgs& a, const Colo
                 dp[0] = dcin[0][8]; dp[1] = dcin[0][9]; dp[2] = dcin[0][10];
             }
         }
-        held(dcin[0]);
     }
     G[0][0] = G1[0][0];
     G[1][0] = G1[1][0];

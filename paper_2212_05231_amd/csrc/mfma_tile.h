@@ -60,6 +60,21 @@ __device__ __forceinline__ v16f zero16() {
 // neuron (within its block of 32) that register r of lane half h holds
 __device__ __forceinline__ constexpr int neuron_of(int r, int h) { return 8 * (r >> 2) + 4 * h + (r & 3); }
 
+// A constant in a scalar register whose value the compiler does not know.  Every asm statement of these files is empty, a
+// barrier to the optimiser only: between a matrix instruction and what touches its registers (also the ones nobody reads)
+// the compiler keeps the wait states the hardware needs, but it does not look for registers written in asm text.
+template <uint32_t V>
+__device__ __forceinline__ uint32_t opaque() {
+    uint32_t r = V;
+    asm("" : "+s"(r));
+    return r;
+}
+
+// all ones if the bit is set, else zero; one: opaque<1>()
+__device__ __forceinline__ uint32_t mask_bit(uint32_t m, int bit, uint32_t one) {
+    return (uint32_t)__builtin_amdgcn_sbfe((int)m, (uint32_t)bit, one);
+}
+
 // ReLU in place; returns the mask bits of this lane's 16*NB neurons (bit 16*b + r).
 // The mask is 1 only for strictly positive pre-activations (Definition 1 of the paper).
 // Neither direction uses a compare instruction: the result of a compare is a lane mask in a
@@ -67,22 +82,20 @@ __device__ __forceinline__ constexpr int neuron_of(int r, int h) { return 8 * (r
 // lanes and fetches back for every use.  A float is positive exactly when its bit pattern is a
 // positive integer, so the ReLU is an integer maximum with 0 on the pattern, the mask bit the
 // unsigned minimum of the result with 1, and a one-bit sign-extending field extract turns a mask
-// bit back into an all-ones or all-zeros word to AND with.  The mask instructions are written out
-// because the compiler rewrites the equivalent C expressions into compares and selects; the
-// instruction that first touches a result of a matrix instruction (the maximum, the AND) is left to
-// the compiler, which knows the wait states a matrix result needs and does not look into asm text.
+// bit back into an all-ones or all-zeros word to AND with.  The compiler would rewrite both into compares
+// and selects if it knew that the minimum's bound and the field's width are 1, so they are opaque().
 template <int NB>
 __device__ __forceinline__ uint32_t relu_mask(v16f* z) {
     uint32_t m = 0;
+    const uint32_t one = opaque<1u>();
 #pragma unroll
     for (int b = 0; b < NB; ++b)
 #pragma unroll
         for (int r = 0; r < 16; ++r) {
             const float zf = z[b][r];       // a copy: a bit cast of the vector element itself reads element 0
             const int zi = max(__builtin_bit_cast(int, zf), 0);
-            uint32_t on;
-            asm("v_min_u32 %0, 1, %1" : "=v"(on) : "v"(zi));
-            asm("v_lshl_or_b32 %0, %1, %2, %0" : "+v"(m) : "v"(on), "n"(16 * b + r));
+            m |= min((uint32_t)zi, one) << (16 * b + r);
+            asm("" : "+v"(m));           // bit by bit: summed as a tree the bits take more registers
             z[b][r] = __builtin_bit_cast(float, zi);
         }
     return m;
@@ -100,22 +113,15 @@ __device__ __forceinline__ void relu(v16f* z) {
         }
 }
 
-// Put behind the reads of a matrix result of which some registers are never read (padding rows): they stay taken up to here.
-// The compiler may otherwise give one of them to an instruction written in asm text while the matrix instruction is still
-// to write it: it makes its own instructions wait for that, not those in asm text (seen: a row number overwritten by the
-// padding rows of the product before).
-__device__ __forceinline__ void held(const v16f& x) { asm volatile("" : : "v"(x)); }
-
 template <int NB>
 __device__ __forceinline__ void apply_mask(v16f* z, uint32_t m) {
+    const uint32_t one = opaque<1u>();
 #pragma unroll
     for (int b = 0; b < NB; ++b)
 #pragma unroll
         for (int r = 0; r < 16; ++r) {
-            uint32_t keep;
-            asm("v_bfe_i32 %0, %1, %2, 1" : "=v"(keep) : "v"(m), "n"(16 * b + r));
             const float zf = z[b][r];
-            z[b][r] = __builtin_bit_cast(float, __builtin_bit_cast(uint32_t, zf) & keep);
+            z[b][r] = __builtin_bit_cast(float, __builtin_bit_cast(uint32_t, zf) & mask_bit(m, 16 * b + r, one));
         }
 }
 
@@ -156,15 +162,13 @@ __device__ __forceinline__ V* lane_address(V* base, uint32_t bytes) {
 // The same word in another register, as far as the compiler can tell: what is worked out from it is not worked out ahead
 // of the loop or shared with an earlier use, and so holds no register in between (expanded masks: 32 of them).
 __device__ __forceinline__ uint32_t again(uint32_t x) {
-    uint32_t r;
-    asm volatile("v_mov_b32 %0, %1" : "=v"(r) : "v"(x));
-    return r;
+    asm volatile("" : "+v"(x));
+    return x;
 }
 
 __device__ __forceinline__ int64_t again(int64_t x) {             // x is uniform
-    int64_t r;
-    asm volatile("s_mov_b64 %0, %1" : "=s"(r) : "s"(x));
-    return r;
+    asm volatile("" : "+s"(x));
+    return x;
 }
 
 // ---- split vectors ---------------------------------------------------------------------------
@@ -181,22 +185,13 @@ struct Split {
 // other element), also exact (checked on the chip over all exponents).  The selector words are kept
 // in registers: written as literals the compiler turns (-1, 0) into the inline constant -1.0, which
 // the instruction reads as (0, -1).  A non-finite neighbour turns the remainder into NaN (0 * inf).
-// (The asm statement is one instruction, not an empty one: the compiler counts every asm statement as
-// an instruction when it works out the wait states between a matrix instruction and its reader.)
-template <uint32_t V>
-__device__ __forceinline__ uint32_t in_register() {
-    uint32_t r;
-    asm("s_mov_b32 %0, %1" : "=s"(r) : "n"(V));
-    return r;
-}
-
 template <int NB, int P>
 __device__ __forceinline__ void split(const v16f* v, Split<NB, P>& out) {
     typedef __bf16 bf2 __attribute__((ext_vector_type(2)));
     typedef float f2 __attribute__((ext_vector_type(2)));
     static_assert(P == 2 || P == 3, "two or three terms");
-    const bf2 minus_low = __builtin_bit_cast(bf2, in_register<0x0000bf80u>());
-    const bf2 minus_high = __builtin_bit_cast(bf2, in_register<0xbf800000u>());
+    const bf2 minus_low = __builtin_bit_cast(bf2, opaque<0x0000bf80u>());
+    const bf2 minus_high = __builtin_bit_cast(bf2, opaque<0xbf800000u>());
 #pragma unroll
     for (int b = 0; b < NB; ++b)
 #pragma unroll

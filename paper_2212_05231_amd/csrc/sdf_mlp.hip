@@ -277,13 +277,12 @@ __device__ __forceinline__ v16f apply_jac_regs(const JacRegs<D>& J, const float 
 // word p holds registers 2p and 2p + 1).  The same values as splitting the masked row.
 template <int P>
 __device__ __forceinline__ void last_row_masked(const uint32_t (*row0)[3][16], uint32_t m, int h, Split<2, P>& out) {
+    const uint32_t one = opaque<1u>();
     uint32_t keep[16];
 #pragma unroll
     for (int k = 0; k < 16; ++k) {
         const int bit = 16 * (k >> 3) + 2 * (k & 7);
-        uint32_t lo, hi;
-        asm("v_bfe_i32 %0, %1, %2, 1" : "=v"(lo) : "v"(m), "n"(bit));
-        asm("v_bfe_i32 %0, %1, %2, 1" : "=v"(hi) : "v"(m), "n"(bit + 1));
+        const uint32_t lo = mask_bit(m, bit, one), hi = mask_bit(m, bit + 1, one);
         keep[k] = (lo & 0xffffu) | (hi & 0xffff0000u);
     }
 #pragma unroll
@@ -474,7 +473,6 @@ __global__ __launch_bounds__(kFwdThreads) void sdf_fwd_kernel(SdfArgs a) {
                 if (K == 3) *lane_address(words + 2 * a.n, 8u * j + 4u * h) = m_last;
             }
         }
-        held(yv[0]);
         // reverse sweep for dd/de
         v16f s1[2];
         last_row_masked(w.HLrow0, m_last, h, pv);
@@ -491,7 +489,6 @@ __global__ __launch_bounds__(kFwdThreads) void sdf_fwd_kernel(SdfArgs a) {
         if (WIDE) store_levels<D, true>(a.q, a.n, tile * 32 + j, valid, qv[0], h);
         else if (a.stream_q) store_levels_tile<D, true>(a.q, a.n, tile * 32, valid, qv[0], j, h);
         else store_levels_tile<D, false>(a.q, a.n, tile * 32, valid, qv[0], j, h);
-        if (D < 32) held(qv[0]);
         float nrm[3];
         if (WIDE) contract_jac<D>(a.jac, a.n, tile * 32 + j, valid, a.active_levels, h, qv[0], nrm);
         else contract_jac_tile<D, true>(a.jac, a.n, tile * 32, a.active_levels, j, h, qv[0], nrm);
@@ -558,7 +555,6 @@ __global__ __launch_bounds__(kValueThreads, 4) void sdf_value_kernel(SdfArgs a) 
         }
         matvec_split<1, 4, 3, 3>(w.HL, pv, yv, lane);
         if (valid && h == 0) a.y[i] = yv[0][0];
-        held(yv[0]);
     }
 }
 
@@ -839,7 +835,6 @@ __device__ __forceinline__ void sdf_first_order(const SdfArgs& a, const SdfWeigh
         matvec_split<1, 4, 2, 2>(w.H1t, pd, de, lane);
         if (a.stream_q) store_levels_tile<D, true>(a.d_enc, a.n, tile * 32, valid, de[0], j, h);      // as for q in the forward kernel
         else store_levels_tile<D, false>(a.d_enc, a.n, tile * 32, valid, de[0], j, h);
-        if (D < 32) held(de[0]);
         if (a.d_pos) {
             float dp[3];
             contract_jac_tile<D, false>(a.jac, a.n, tile * 32, a.active_levels, j, h, de[0], dp);
