@@ -88,8 +88,9 @@ int neus2_version(void);
 int neus2_validate_config(const neus2_config* cfg /*[host]*/);
 
 /* Bytes of scratch the scatter-add wants for n points (0 if it would not use any; -1 on a bad
- * descriptor).  The workspace is optional everywhere: without it (NULL, or too small) the
- * scatter-add falls back to its atomic kernel, same results. */
+ * descriptor); never less for more points, so one made for n serves every smaller batch.  The
+ * workspace is optional everywhere: without it (NULL, or too small) the scatter-add falls back to
+ * its atomic kernel, same results. */
 int64_t neus2_workspace_bytes(const neus2_config* cfg /*[host]*/, int64_t n);
 
 /* Multi-resolution hash encoding (Sec. 3 "InstantNGP", Sec. 4.1) and its Jacobian de/dx,
@@ -247,7 +248,7 @@ int neus2_hash_scatter_bwd(const neus2_config* cfg, const float* pos, const void
  * buffer of NEUS2_STATIC_SCRATCH_BYTES that is part of the library's device image (every GPU the
  * library is used on holds one until the process ends).  The call allocates nothing, on the
  * device or through any library.  A batch whose lists do not fit (neus2_workspace_bytes minus
- * the 24 * n_levels * n bytes of its position-gradient part is the need; about 140 000 points
+ * the 24 * n_levels * n bytes of its position-gradient part is at least the need; about 140 000 points
  * with 16 levels of 2^19 slots, more with fewer hashed levels) is rejected with
  * NEUS2_ERR_SHAPE and nothing is launched.  All calls on one GPU share the buffer: calls that
  * overlap in time on one GPU (different streams or threads) race; order them. */

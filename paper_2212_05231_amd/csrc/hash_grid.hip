@@ -1321,12 +1321,15 @@ float* scatter_hessian_region(const neus2_config* cfg, int64_t n, void* workspac
     return reinterpret_cast<float*>(reinterpret_cast<char*>(workspace) + (owner_workspace_need(plan, n) + 255) / 256 * 256);
 }
 
+// A workspace made for n points serves every smaller batch too (a step runs on the samples that the ray marcher found):
+// from kNarrowMinPoints on, where the records get shorter, it also holds the wide records of the batches just below.
 int64_t scatter_workspace_bytes(const neus2_config* cfg, int64_t n) {
     if (n < kOwnerMinPoints) return 0;
     bool ok = false;
     const OwnerPlan plan = make_owner_plan(cfg, n, ok);
     if (!ok) return 0;
-    return (owner_workspace_need(plan, n) + 255) / 256 * 256 + (int64_t)cfg->n_levels * n * 24;
+    const int64_t bytes = (owner_workspace_need(plan, n) + 255) / 256 * 256 + (int64_t)cfg->n_levels * n * 24;
+    return n < kNarrowMinPoints ? bytes : std::max(bytes, scatter_workspace_bytes(cfg, kNarrowMinPoints - 1));
 }
 
 int64_t scatter_records_bytes(const neus2_config* cfg, int64_t n) {

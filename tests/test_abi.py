@@ -150,3 +150,15 @@ def test_workload_generators_are_seeded_and_in_range():
     assert wl.make_config(2).res == [16, 22, 30, 42, 58, 80, 111, 153, 212, 294, 406, 561, 776, 1072, 1482, 2048]
     assert wl.make_config(1).res == [16, 24, 36, 54, 81, 121, 182, 273]
     assert wl.make_config(4).dense[:7] == [1, 1, 1, 1, 1, 1, 0]
+
+
+@pytest.mark.parametrize("k,active,frozen", [(1, 8, 0), (2, 16, 0), (2, 3, 0), (2, 16, 6), (4, 16, 0), (4, 8, 2)])
+def test_workspace_of_a_batch_serves_every_smaller_one(k, active, frozen):
+    """A step sizes its workspace once and runs on as many samples as the ray marcher found."""
+    cfg = wl.make_config(k)
+    cfg.active_levels, cfg.frozen_levels = active, frozen
+    c = nb.make_config(cfg)
+    edges = [7 << 12, 1 << 16, 1 << 17, 1 << 20]
+    counts = sorted({n + d for n in edges for d in (-1, 0, 1)} | set(range(20011, 130000, 1499)))
+    sizes = [nb.workspace_bytes(c, n) for n in counts]
+    assert sizes[-1] > 0 and all(a <= b for a, b in zip(sizes, sizes[1:])), list(zip(counts, sizes))

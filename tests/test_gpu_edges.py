@@ -97,6 +97,28 @@ def test_scatter_on_both_sides_of_the_list_and_record_sizes(n, table_bits, dtype
     assert all(rel(f, found[0]) <= 1e-5 for f in found)
 
 
+@pytest.mark.parametrize("capacity", [1 << 16, 70000])
+@pytest.mark.parametrize("n", [7 << 12, (1 << 16) - 1])
+def test_lists_for_every_batch_a_workspace_was_made_for(n, capacity):
+    """A workspace made for more points: a smaller batch goes through the lists too (the cursors in its header count their
+    records), with both gradients as without a workspace."""
+    rng = np.random.default_rng(n)
+    cfg = wl.make_config(2)
+    c, L, T = nb.make_config(cfg), cfg.n_levels, cfg.table_size
+    tab = cuda(wl.make_params(cfg, 3)["tables"])
+    pos = cuda(wl.make_rays(n // 64 + 1, 64, n)["pos"][:n])
+    q, d_enc = (cuda(rng.normal(size=(L, n, 2)).astype(np.float32)) for _ in range(2))
+    d_normal = cuda((rng.normal(size=(n, 3)) * 1e-2).astype(np.float32))
+    found = []
+    for ws in (torch.zeros(nb.workspace_bytes(c, capacity) // 4, dtype=torch.int32, device="cuda"), None):
+        got, d_pos = torch.zeros(L, T, 2, device="cuda"), torch.zeros(n, 3, device="cuda")
+        nb.hash_scatter_bwd(c, pos, tab, q, d_enc, d_normal, n, got, d_pos=d_pos, workspace=ws)
+        found.append((got.cpu(), d_pos.cpu()))
+        assert ws is None or bool(ws.any())
+    for a, b in zip(*found):
+        assert rel(a, b) <= 1e-6                       # ten roundings of binary32 on either side
+
+
 @pytest.mark.parametrize("n,hidden,table,active,levels", [(1, 2, "f16", 16, 16), (31, 1, "f32", 16, 16), (33, 2, "f32", 5, 16),
                                                          (4097, 2, "f16", 16, 16), (1000, 1, "f16", 8, 8)])
 def test_sdf_values_equal_the_forward_calls(n, hidden, table, active, levels):
