@@ -152,9 +152,11 @@ __device__ __forceinline__ void wave_lds_fence() {
 }
 
 // ---- for kernels that are short of registers --------------------------------------------------------
-// A uniform address (scalar registers) plus a 32-bit byte offset of the lane.
-template <typename V>
-__device__ __forceinline__ V* lane_address(V* base, uint32_t bytes) {
+// A uniform address (scalar registers) plus a byte offset of the lane: 32 bits, which the access instruction adds by itself,
+// or 64 for arrays that 32 do not span.
+template <typename V, typename Offset>
+__device__ __forceinline__ V* lane_address(V* base, Offset bytes) {
+    static_assert(std::is_unsigned_v<Offset>, "a byte offset");
     typedef std::conditional_t<std::is_const_v<V>, const char, char> Byte;
     return reinterpret_cast<V*>(reinterpret_cast<Byte*>(base) + bytes);
 }
@@ -162,6 +164,11 @@ __device__ __forceinline__ V* lane_address(V* base, uint32_t bytes) {
 // The same word in another register, as far as the compiler can tell: what is worked out from it is not worked out ahead
 // of the loop or shared with an earlier use, and so holds no register in between (expanded masks: 32 of them).
 __device__ __forceinline__ uint32_t again(uint32_t x) {
+    asm volatile("" : "+v"(x));
+    return x;
+}
+
+__device__ __forceinline__ uint64_t again(uint64_t x) {
     asm volatile("" : "+v"(x));
     return x;
 }

@@ -325,10 +325,14 @@ constexpr int kFwdWaves = kFwdThreads / 64;
 constexpr int kValueThreads = 512;
 constexpr int kValueWaves = kValueThreads / 64;
 
-// Accesses of a tile: a uniform address (scalar registers: array, tile, level) plus a 32-bit byte offset of the lane.  Written
+// Accesses of a tile: a uniform address (scalar registers: array, tile, level) plus a byte offset of the lane.  Written
 // with one 64-bit index per lane, the compiler kept two dozen addresses in vector registers through the whole loop and spilled
-// them.  The largest lane offset is 48 n bytes (upper lane half, Jacobian), so n stays below 2^26 here.
+// them.  The largest lane offset is 48 n bytes (upper lane half, Jacobian): 32 bits below kTileMaxPoints, 64 (WIDE) from there on,
+// where an access takes an addition of its own: 2^26 points forward 12.1 ms narrow, 13.2 wide, backward 19.0 and 18.9.
 constexpr int64_t kTileMaxPoints = (int64_t)1 << 26;
+
+template <bool WIDE>
+using LaneOffset = std::conditional_t<WIDE, uint64_t, uint32_t>;
 
 typedef float f2v __attribute__((ext_vector_type(2)));
 
@@ -338,31 +342,33 @@ typedef float f2v __attribute__((ext_vector_type(2)));
 // afterwards.  A branch per level instead kept 48 zeroed registers alive across the loads.
 __device__ __forceinline__ int last_point(int64_t n, int64_t first) { return n - first < 32 ? (int)(n - first) - 1 : 31; }
 
-template <int D>
+template <int D, bool WIDE>
 __device__ __forceinline__ v16f load_levels_tile(const float* __restrict__ src, int64_t n, int64_t first, int active, int j, int h) {
     v16f x = zero16();
     const f2v* tile = reinterpret_cast<const f2v*>(src) + first;
+    typedef LaneOffset<WIDE> Offset;
     const int64_t plane = again(n);
     const int last = last_point(n, first);
-    const uint32_t off = 8u * (uint32_t)min(j, last), upper = again(h ? 16u * (uint32_t)n : 0u);
+    const Offset off = (Offset)8 * min(j, last), upper = again(h ? (Offset)16 * (Offset)n : (Offset)0);
 #pragma unroll
     for (int g = 0; g < D / 8; ++g)
 #pragma unroll
         for (int u = 0; u < 2; ++u) {
             const bool on = 4 * g + 2 * h + u < active;
-            const f2v v = *lane_address(tile + (4 * g + u) * plane, off + (on ? upper : 0u));
+            const f2v v = *lane_address(tile + (4 * g + u) * plane, off + (on ? upper : (Offset)0));
             x[4 * g + 2 * u] = on && j <= last ? v.x : 0.f;
             x[4 * g + 2 * u + 1] = on && j <= last ? v.y : 0.f;
         }
     return x;
 }
 
-template <int D, bool STREAM>
+template <int D, bool WIDE, bool STREAM>
 __device__ __forceinline__ void store_levels_tile(float* __restrict__ dst, int64_t n, int64_t first, bool valid, const v16f& x, int j, int h) {
     if (!valid) return;
     f2v* tile = reinterpret_cast<f2v*>(dst) + first;
+    typedef LaneOffset<WIDE> Offset;
     const int64_t plane = again(n);
-    const uint32_t off = again(8u * ((uint32_t)j + 2u * (uint32_t)h * (uint32_t)n));
+    const Offset off = again((Offset)8 * ((Offset)j + (Offset)2 * (Offset)h * (Offset)n));
 #pragma unroll
     for (int g = 0; g < D / 8; ++g)
 #pragma unroll
@@ -374,14 +380,15 @@ __device__ __forceinline__ void store_levels_tile(float* __restrict__ dst, int64
 }
 
 // (de/dx)^T dL/de of the tile's points: this lane's levels
-template <int D, bool STREAM>
+template <int D, bool WIDE, bool STREAM>
 __device__ __forceinline__ void contract_jac_tile(const float* __restrict__ jac, int64_t n, int64_t first, int active, int j, int h,
                                                   const v16f& x, float out[3]) {
     out[0] = out[1] = out[2] = 0.f;
     const f2v* tile = reinterpret_cast<const f2v*>(jac) + first;
+    typedef LaneOffset<WIDE> Offset;
     const int64_t plane = again(n);
     const int last = last_point(n, first);
-    const uint32_t off = 8u * (uint32_t)min(j, last), upper = again(h ? 48u * (uint32_t)n : 0u);
+    const Offset off = (Offset)8 * min(j, last), upper = again(h ? (Offset)48 * (Offset)n : (Offset)0);
 #pragma unroll
     for (int g = 0; g < D / 8; ++g)
 #pragma unroll
@@ -390,7 +397,7 @@ __device__ __forceinline__ void contract_jac_tile(const float* __restrict__ jac,
             f2v J[3];
 #pragma unroll
             for (int c = 0; c < 3; ++c) {
-                const f2v* p = lane_address(tile + (3 * (4 * g + u) + c) * plane, off + (on ? upper : 0u));
+                const f2v* p = lane_address(tile + (3 * (4 * g + u) + c) * plane, off + (on ? upper : (Offset)0));
                 J[c] = STREAM ? __builtin_nontemporal_load(p) : *p;
             }
             const float x0 = x[4 * g + 2 * u], x1 = x[4 * g + 2 * u + 1];
@@ -401,19 +408,21 @@ __device__ __forceinline__ void contract_jac_tile(const float* __restrict__ jac,
 }
 
 // t_0 = (de/dx) dL/dn of the tile's points
-template <int D>
-__device__ __forceinline__ v16f apply_jac_tile(const float* __restrict__ jac, int64_t n, int64_t first, int active, int j, int h, const float v[3]) {
+template <int D, bool WIDE>
+__device__ __forceinline__ v16f apply_jac_tile(const float* __restrict__ jac, int64_t n, int64_t first, int active, int j, int h,
+                                               const float v[3]) {
     f2v J[D / 4][3];           // (J00,J01) (J02,J10) (J11,J12) per level of this lane
     const f2v* tile = reinterpret_cast<const f2v*>(jac) + first;
+    typedef LaneOffset<WIDE> Offset;
     const int64_t plane = again(n);
     const int last = last_point(n, first);
-    const uint32_t off = 8u * (uint32_t)min(j, last), upper = again(h ? 48u * (uint32_t)n : 0u);
+    const Offset off = (Offset)8 * min(j, last), upper = again(h ? (Offset)48 * (Offset)n : (Offset)0);
 #pragma unroll
     for (int g = 0; g < D / 8; ++g)
 #pragma unroll
         for (int u = 0; u < 2; ++u) {
             const bool on = 4 * g + 2 * h + u < active;
-            const uint32_t o = off + (on ? upper : 0u);
+            const Offset o = off + (on ? upper : (Offset)0);
 #pragma unroll
             for (int c = 0; c < 3; ++c) J[2 * g + u][c] = __builtin_nontemporal_load(lane_address(tile + (3 * (4 * g + u) + c) * plane, o));
         }
@@ -445,9 +454,7 @@ __global__ __launch_bounds__(kFwdThreads) void sdf_fwd_kernel(SdfArgs a) {
     // tiles go to the workgroups first and then to their wavefronts: a small batch has every compute unit at work
     for (int64_t tile = (int64_t)wave * gridDim.x + blockIdx.x; tile < tiles; tile += stride) {
         const bool valid = tile * 32 + j < a.n;
-        v16f x0[1];
-        if (WIDE) x0[0] = load_levels<D>(a.enc, a.n, tile * 32 + j, valid, a.active_levels, h);
-        else x0[0] = load_levels_tile<D>(a.enc, a.n, tile * 32, a.active_levels, j, h);
+        v16f x0[1] = {load_levels_tile<D, WIDE>(a.enc, a.n, tile * 32, a.active_levels, j, h)};
         v16f a1[2], yv[1];
         Split<1, 3> px;
         Split<2, 3> pv;
@@ -486,12 +493,10 @@ __global__ __launch_bounds__(kFwdThreads) void sdf_fwd_kernel(SdfArgs a) {
         // dd/de is read next by the scatter-add, four kernels later: for a batch whose per-point arrays
         // exceed the caches it is written with non-temporal stores (25 us of the step at 2^20 points; at
         // 2^18 points the cached store is the faster one)
-        if (WIDE) store_levels<D, true>(a.q, a.n, tile * 32 + j, valid, qv[0], h);
-        else if (a.stream_q) store_levels_tile<D, true>(a.q, a.n, tile * 32, valid, qv[0], j, h);
-        else store_levels_tile<D, false>(a.q, a.n, tile * 32, valid, qv[0], j, h);
+        if (a.stream_q) store_levels_tile<D, WIDE, true>(a.q, a.n, tile * 32, valid, qv[0], j, h);
+        else store_levels_tile<D, WIDE, false>(a.q, a.n, tile * 32, valid, qv[0], j, h);
         float nrm[3];
-        if (WIDE) contract_jac<D>(a.jac, a.n, tile * 32 + j, valid, a.active_levels, h, qv[0], nrm);
-        else contract_jac_tile<D, true>(a.jac, a.n, tile * 32, a.active_levels, j, h, qv[0], nrm);
+        contract_jac_tile<D, WIDE, true>(a.jac, a.n, tile * 32, a.active_levels, j, h, qv[0], nrm);
 #pragma unroll
         for (int c = 0; c < 3; ++c) nrm[c] += __shfl_xor(nrm[c], 32);
         if (valid && h == 0) {
@@ -776,7 +781,7 @@ struct SdfPairSmem {
     alignas(16) unsigned char tiles[2 * kPairs][kTilesPerWave * kBlockTile];
 };
 
-template <int D, int K>
+template <int D, int K, bool WIDE>
 __device__ __forceinline__ void sdf_first_order(const SdfArgs& a, const SdfWeights<D, K, true, 2>& w, unsigned char* tile_mem,
                                                 int slot, int lane, v16f (*G1)[1], v16f (*G2)[2], v4f* GL) {
     constexpr int KS1 = D / 16;
@@ -789,7 +794,7 @@ __device__ __forceinline__ void sdf_first_order(const SdfArgs& a, const SdfWeigh
     for (int64_t tile = (int64_t)blockIdx.x * kPairs + slot; tile < tiles; tile += stride) {
         const int64_t i = tile * 32 + j;
         const bool valid = i < a.n;
-        v16f x0[1] = {load_levels_tile<D>(a.enc, a.n, tile * 32, a.active_levels, j, h)};
+        v16f x0[1] = {load_levels_tile<D, WIDE>(a.enc, a.n, tile * 32, a.active_levels, j, h)};
         v16f dK[1] = {zero16()};
         uint32_t m1 = 0u, m_last = 0u;
         if (valid) {
@@ -833,11 +838,11 @@ __device__ __forceinline__ void sdf_first_order(const SdfArgs& a, const SdfWeigh
         split(d1, pd);
         outer_accumulate_points<2, 1>(G1, pd, px, tile_mem, lane);
         matvec_split<1, 4, 2, 2>(w.H1t, pd, de, lane);
-        if (a.stream_q) store_levels_tile<D, true>(a.d_enc, a.n, tile * 32, valid, de[0], j, h);      // as for q in the forward kernel
-        else store_levels_tile<D, false>(a.d_enc, a.n, tile * 32, valid, de[0], j, h);
+        if (a.stream_q) store_levels_tile<D, WIDE, true>(a.d_enc, a.n, tile * 32, valid, de[0], j, h);      // as for q in the forward kernel
+        else store_levels_tile<D, WIDE, false>(a.d_enc, a.n, tile * 32, valid, de[0], j, h);
         if (a.d_pos) {
             float dp[3];
-            contract_jac_tile<D, false>(a.jac, a.n, tile * 32, a.active_levels, j, h, de[0], dp);
+            contract_jac_tile<D, WIDE, false>(a.jac, a.n, tile * 32, a.active_levels, j, h, de[0], dp);
 #pragma unroll
             for (int c = 0; c < 3; ++c) dp[c] += __shfl_xor(dp[c], 32);
             if (valid && h == 0) {
@@ -847,7 +852,7 @@ __device__ __forceinline__ void sdf_first_order(const SdfArgs& a, const SdfWeigh
     }
 }
 
-template <int D, int K>
+template <int D, int K, bool WIDE>
 __device__ __forceinline__ void sdf_second_order(const SdfArgs& a, const SdfWeights<D, K, true, 2>& w, unsigned char* tile_mem,
                                                  int slot, int lane, v16f (*G1)[1], v16f (*G2)[2], v4f* GL) {
     constexpr int KS1 = D / 16;
@@ -869,7 +874,7 @@ __device__ __forceinline__ void sdf_second_order(const SdfArgs& a, const SdfWeig
         }
         // The t sweep first: of its vectors only t_0 outlives the product with S_{K-1}, and S_{K-1} does not outlive the
         // product that turns it into S_1 (working registers: 104 at most beside the 128 of the sums).
-        v16f t0[1] = {apply_jac_tile<D>(a.jac, a.n, tile * 32, a.active_levels, j, h, nb3)};
+        v16f t0[1] = {apply_jac_tile<D, WIDE>(a.jac, a.n, tile * 32, a.active_levels, j, h, nb3)};
         v16f s1[2], t1[2], t2[2];
         Split<1, 2> pt;
         Split<2, 2> ps, pd;
@@ -908,7 +913,7 @@ __device__ __forceinline__ void sdf_second_order(const SdfArgs& a, const SdfWeig
     outer_accumulate16<2, kLd16, kLd64>(GL, Zt, Xt, lane);
 }
 
-template <int D, int K>
+template <int D, int K, bool WIDE>
 __global__ __launch_bounds__(kPairThreads) void sdf_bwd_pair_kernel(SdfArgs a) {
     __shared__ SdfPairSmem<D, K> sm;
     load_weights<D, K, true, kPairThreads, 2>(sm.w, a);
@@ -925,8 +930,8 @@ __global__ __launch_bounds__(kPairThreads) void sdf_bwd_pair_kernel(SdfArgs a) {
     }
 #pragma unroll
     for (int cb = 0; cb < 4; ++cb) GL[cb] = v4f{0.f, 0.f, 0.f, 0.f};
-    if (second) sdf_second_order<D, K>(a, sm.w, sm.tiles[wave], slot, lane, G1, G2, GL);
-    else sdf_first_order<D, K>(a, sm.w, sm.tiles[wave], slot, lane, G1, G2, GL);
+    if (second) sdf_second_order<D, K, WIDE>(a, sm.w, sm.tiles[wave], slot, lane, G1, G2, GL);
+    else sdf_first_order<D, K, WIDE>(a, sm.w, sm.tiles[wave], slot, lane, G1, G2, GL);
     __syncthreads();
     // ---- the waves of the second order leave their sums in LDS, their partners add their own, and the block's sums go
     // to global memory in the gradients' own order
@@ -993,9 +998,10 @@ int run_values(const SdfArgs& a, hipStream_t st) {
 template <int D, int K>
 int run_bwd(const SdfArgs& a, hipStream_t st) {
     const int64_t tiles = (a.n + 31) / 32;
-    if (a.masks && a.n < kTileMaxPoints) {
-        const int blocks = persistent_blocks((const void*)sdf_bwd_pair_kernel<D, K>, kPairThreads, (tiles + kPairs - 1) / kPairs);
-        hipLaunchKernelGGL((sdf_bwd_pair_kernel<D, K>), dim3(blocks), dim3(kPairThreads), 0, st, a);
+    if (a.masks) {
+        const auto kernel = a.n < kTileMaxPoints ? sdf_bwd_pair_kernel<D, K, false> : sdf_bwd_pair_kernel<D, K, true>;
+        const int blocks = persistent_blocks((const void*)kernel, kPairThreads, (tiles + kPairs - 1) / kPairs);
+        hipLaunchKernelGGL(kernel, dim3(blocks), dim3(kPairThreads), 0, st, a);
     } else {
         const int blocks = persistent_blocks((const void*)sdf_bwd_kernel<D, K>, kThreads, (tiles + kWaves - 1) / kWaves);
         hipLaunchKernelGGL((sdf_bwd_kernel<D, K>), dim3(blocks), dim3(kThreads), 0, st, a);

@@ -189,3 +189,45 @@ def test_sdf_forward_over_tiles_and_levels(n, hidden, levels, active):
     assert rel(normal[agree].cpu(), nrm[agree].cpu()) <= 1e-5
     for behind in (behind_y, behind_q, behind_n):
         assert torch.all(torch.signbit(behind)) and torch.all(behind == 0)
+
+
+@pytest.mark.parametrize("levels,hidden", [(16, 2), (8, 1)])
+def test_networks_from_2_26_points_on(levels, hidden):
+    """Where a lane's byte offsets need 64 bits: the same bits per point, forward and backward, as the same points give in a
+    small batch; the backward call goes by the masks it is given (here the forward call's with some bits cleared)."""
+    import dataclasses
+    n, m = (1 << 26) + 5, 3000
+    if torch.cuda.mem_get_info()[0] < 1.2 * 4 * n * (levels * 12 + 45):
+        pytest.skip("not enough free device memory")
+    cfg = wl.make_config(2 if levels == 16 else 1)
+    cfg = dataclasses.replace(cfg, sdf_dims=[2 * levels] + [64] * hidden + [16])
+    c, gen = nb.make_config(cfg), torch.Generator(device="cuda").manual_seed(levels)
+    randn = lambda *shape: torch.randn(*shape, device="cuda", generator=gen)
+    H = [randn(o_, i) * (2.0 / i) ** 0.5 for i, o_ in zip(cfg.sdf_dims, cfg.sdf_dims[1:])]
+    chosen = torch.cat([torch.arange(1000), torch.arange(n // 2, n // 2 + 1000), torch.arange(n - 1000, n)]).cuda()
+
+    def call(enc, jac, d_y, d_normal, points, cleared):
+        count = enc.shape[1]
+        empty = lambda *shape: torch.empty(*shape, device="cuda")
+        y, q, normal, d_enc = empty(count, 16), empty(levels, count, 2), empty(count, 3), empty(levels, count, 2)
+        masks, dH = torch.empty(2, count, 2, dtype=torch.int32, device="cuda"), [torch.zeros_like(h) for h in H]
+        nb.sdf_fwd_grad(c, enc, jac, H, count, y, q, normal, masks=masks)
+        kept = [masks[:hidden, points].clone()]
+        masks[:hidden, points] &= cleared
+        nb.sdf_mlp_bwd(c, enc, jac, H, d_y, d_normal, count, dH, d_enc, masks=masks)
+        return kept + [y[points], normal[points], q[:, points], d_enc[:, points]], dH
+
+    small = [randn(m, 16), randn(m, 3)]
+    cleared = torch.randint(-2 ** 31, 2 ** 31, (hidden, m, 2), device="cuda", generator=gen, dtype=torch.int64).to(torch.int32)
+    enc, jac = randn(levels, n, 2), randn(levels, 3, n, 2)
+    d_y, d_normal = torch.zeros(n, 16, device="cuda"), torch.zeros(n, 3, device="cuda")
+    d_y[chosen], d_normal[chosen] = small[0], small[1]
+    got, dH = call(enc, jac, d_y, d_normal, chosen, cleared)
+    few = (enc[:, chosen].contiguous(), jac[:, :, chosen].contiguous())
+    del enc, jac, d_y, d_normal
+    want, dH_few = call(*few, *small, torch.arange(m, device="cuda"), cleared)
+    torch.cuda.empty_cache()
+    for a, b in zip(got, want):
+        assert torch.equal(a, b) and bool(a.any())
+    for a, b in zip(dH, dH_few):
+        assert rel(a.cpu(), b.cpu()) <= 1e-5                     # the same terms in another order
