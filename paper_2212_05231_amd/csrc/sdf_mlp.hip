@@ -770,6 +770,9 @@ __global__ __launch_bounds__(kThreads) void sdf_bwd_kernel(SdfArgs a) {
 // its copy of the weight gradients: 256 registers instead of 512, eight wavefronts a workgroup, two per SIMD (waves w and
 // w + 4 share a SIMD, so every SIMD holds one of each), and one's waits for LDS, memory and matrix results are filled by
 // the other.  The chains are about equally long: 114 and 96 matrix instructions of 32 clocks.
+// Everything that depends on the lane alone (its offsets into LDS and into the arrays) is worked out again for every tile:
+// kept through the loop those values took 31 registers that were not there, and fetching them back from memory was 20 % of
+// the time (2^18 points 105 -> 84 us, 2^20 points 318 -> 270).
 // Everything here is at gradient tolerance: two terms and three products, a plain ReLU for the recomputed
 // activations (where its sign differs from the given mask the value is within rounding of zero).
 constexpr int kPairThreads = 512;
@@ -783,15 +786,15 @@ struct SdfPairSmem {
 
 template <int D, int K, bool WIDE>
 __device__ __forceinline__ void sdf_first_order(const SdfArgs& a, const SdfWeights<D, K, true, 2>& w, unsigned char* tile_mem,
-                                                int slot, int lane, v16f (*G1)[1], v16f (*G2)[2], v4f* GL) {
+                                                int slot, int lane_in, v16f (*G1)[1], v16f (*G2)[2], v4f* GL) {
     constexpr int KS1 = D / 16;
-    const int j = lane & 31, h = lane >> 5;
     float* Xt = reinterpret_cast<float*>(tile_mem);
     float* Zt = Xt + 32 * kLd64;
     static_assert((32 * kLd64 + 32 * kLd16) * 4 <= kTilesPerWave * kBlockTile, "fp32 tiles fit the wave's memory");
     const int64_t tiles = (a.n + 31) / 32;
     const int64_t stride = (int64_t)gridDim.x * kPairs;
     for (int64_t tile = (int64_t)blockIdx.x * kPairs + slot; tile < tiles; tile += stride) {
+        const int lane = (int)again((uint32_t)lane_in), j = lane & 31, h = lane >> 5;
         const int64_t i = tile * 32 + j;
         const bool valid = i < a.n;
         v16f x0[1] = {load_levels_tile<D, WIDE>(a.enc, a.n, tile * 32, a.active_levels, j, h)};
@@ -854,13 +857,13 @@ __device__ __forceinline__ void sdf_first_order(const SdfArgs& a, const SdfWeigh
 
 template <int D, int K, bool WIDE>
 __device__ __forceinline__ void sdf_second_order(const SdfArgs& a, const SdfWeights<D, K, true, 2>& w, unsigned char* tile_mem,
-                                                 int slot, int lane, v16f (*G1)[1], v16f (*G2)[2], v4f* GL) {
+                                                 int slot, int lane_in, v16f (*G1)[1], v16f (*G2)[2], v4f* GL) {
     constexpr int KS1 = D / 16;
-    const int j = lane & 31, h = lane >> 5;
     v16f tsum[2] = {zero16(), zero16()};
     const int64_t tiles = (a.n + 31) / 32;
     const int64_t stride = (int64_t)gridDim.x * kPairs;
     for (int64_t tile = (int64_t)blockIdx.x * kPairs + slot; tile < tiles; tile += stride) {
+        const int lane = (int)again((uint32_t)lane_in), j = lane & 31, h = lane >> 5;
         const int64_t i = tile * 32 + j;
         const bool valid = i < a.n;
         uint32_t m1 = 0u, m_last = 0u;
@@ -873,7 +876,7 @@ __device__ __forceinline__ void sdf_second_order(const SdfArgs& a, const SdfWeig
             nb3[0] = nb[0]; nb3[1] = nb[1]; nb3[2] = nb[2];
         }
         // The t sweep first: of its vectors only t_0 outlives the product with S_{K-1}, and S_{K-1} does not outlive the
-        // product that turns it into S_1 (working registers: 104 at most beside the 128 of the sums).
+        // product that turns it into S_1.
         v16f t0[1] = {apply_jac_tile<D, WIDE>(a.jac, a.n, tile * 32, a.active_levels, j, h, nb3)};
         v16f s1[2], t1[2], t2[2];
         Split<1, 2> pt;
@@ -904,6 +907,7 @@ __device__ __forceinline__ void sdf_second_order(const SdfArgs& a, const SdfWeig
     // points, through one outer product with a one-hot factor
     float* Xt = reinterpret_cast<float*>(tile_mem);
     float* Zt = Xt + 32 * kLd64;
+    const int lane = lane_in, j = lane & 31, h = lane >> 5;
     v16f onehot = zero16();
     if (h == 0) onehot[0] = 1.f;
     wave_lds_fence();
@@ -1055,7 +1059,7 @@ struct DeepArgs {
 
 template <int NB>
 __device__ __forceinline__ void load_lane(const float* base, int64_t tile, int lane, v16f* v) {
-    const float4* p = reinterpret_cast<const float4*>(base) + tile * 512 + lane;
+    const float4* p = lane_address(reinterpret_cast<const float4*>(base) + tile * 512, 16u * lane);
 #pragma unroll
     for (int b = 0; b < 2; ++b) {
         if (b >= NB) { v[b] = zero16(); continue; }
@@ -1069,7 +1073,7 @@ __device__ __forceinline__ void load_lane(const float* base, int64_t tile, int l
 
 template <int NB>
 __device__ __forceinline__ void store_lane(float* base, int64_t tile, int lane, const v16f* v) {
-    float4* p = reinterpret_cast<float4*>(base) + tile * 512 + lane;
+    float4* p = lane_address(reinterpret_cast<float4*>(base) + tile * 512, 16u * lane);
 #pragma unroll
     for (int b = 0; b < NB; ++b)
 #pragma unroll
@@ -1201,6 +1205,8 @@ __global__ __launch_bounds__(kDeepThreads) void deep_reverse_kernel(DeepArgs a) 
 
 // Both orders of a layer are the same work on other vectors (delta and a; S and t), so a wavefront takes one order of a
 // tile at a time and keeps the weight gradients of LAYERS layers, both orders' together, in registers.
+// What depends on the lane alone is worked out again for every layer: kept, it was 34 registers spilled (eight hidden layers
+// at 2^17 points, forward and backward: 622 -> 556 us).
 template <int LAYERS>
 struct DeepGradSmem {
     alignas(16) unsigned char mats[LAYERS * 64 * SplitMatrix<4, 2>::kLd];
@@ -1212,9 +1218,8 @@ __global__ __launch_bounds__(kDeepThreads) void deep_gradient_kernel(DeepArgs a)
     constexpr int kMatrix = 64 * SplitMatrix<4, 2>::kLd;
     __shared__ DeepGradSmem<LAYERS> sm;
     deep_matrices<2, LAYERS, true>(a, a.first, -1, LAYERS, sm.mats);
-    const int lane = threadIdx.x & 63;
+    const int lane_in = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const int j = lane & 31, h = lane >> 5;
     unsigned char* tile_mem = sm.tiles[wave];
     v16f G[LAYERS][2][2];
 #pragma unroll
@@ -1223,6 +1228,7 @@ __global__ __launch_bounds__(kDeepThreads) void deep_gradient_kernel(DeepArgs a)
         for (int mb = 0; mb < 2; ++mb) { G[k][mb][0] = zero16(); G[k][mb][1] = zero16(); }
     const int64_t items = 2 * ((a.n + 31) / 32);
     for (int64_t item = (int64_t)blockIdx.x * kDeepWaves + wave; item < items; item += (int64_t)gridDim.x * kDeepWaves) {
+        const int lane = (int)again((uint32_t)lane_in), j = lane & 31, h = lane >> 5;
         const int64_t tile = item >> 1;
         const bool second = item & 1;
         const int64_t i = tile * 32 + j;
@@ -1243,6 +1249,7 @@ __global__ __launch_bounds__(kDeepThreads) void deep_gradient_kernel(DeepArgs a)
 #pragma unroll
         for (int k = 0; k < LAYERS; ++k) {
             const int l = a.first - k;
+            const int lane = (int)again((uint32_t)lane_in), j = lane & 31, h = lane >> 5;
             v16f x[2];
             uint32_t m = 0u;
             if (l > 0) {
@@ -1275,7 +1282,7 @@ __global__ __launch_bounds__(kDeepThreads) void deep_gradient_kernel(DeepArgs a)
     float* scratch = reinterpret_cast<float*>(&sm);
     constexpr int kVecs = 4 * LAYERS, kSlots = kDeepWaves / 2;
     static_assert(sizeof(sm) >= kSlots * kVecs * 1024 * sizeof(float), "scratch for the block sum");
-    float* own = scratch + (wave % kSlots) * kVecs * 1024 + lane;
+    float* own = scratch + (wave % kSlots) * kVecs * 1024 + lane_in;
     const v16f* all[kVecs];
 #pragma unroll
     for (int k = 0; k < LAYERS; ++k)
