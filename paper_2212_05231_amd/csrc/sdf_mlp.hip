@@ -337,9 +337,10 @@ using LaneOffset = std::conditional_t<WIDE, uint64_t, uint32_t>;
 typedef float f2v __attribute__((ext_vector_type(2)));
 
 // Levels 4 g + 2 h + u of the tile's points as in load_levels, store_levels and load_jac, first: the tile's first point.
-// Loads are unconditional: a lane without a point reads the tile's last one, a level beyond the active ones is read in
-// the lower lane half's place (in bounds: the arrays hold every level), and what does not count is replaced by zeros
-// afterwards.  A branch per level instead kept 48 zeroed registers alive across the loads.
+// Loads are unconditional within the groups of four levels that a kernel reads: a lane without a point reads the tile's last
+// one, the upper lane half reads the lower half's level where its own is not active, and what does not count is replaced by
+// zeros afterwards.  So one level beyond the active ones is read at most (5, 9 or 13 of them; in bounds: the arrays hold every
+// level).  A branch per level instead kept 48 zeroed registers alive across the loads.
 __device__ __forceinline__ int last_point(int64_t n, int64_t first) { return n - first < 32 ? (int)(n - first) - 1 : 31; }
 
 template <int D, bool WIDE>
@@ -440,8 +441,8 @@ __device__ __forceinline__ v16f apply_jac_tile(const float* __restrict__ jac, in
     return t;
 }
 
-// WIDE: from kTileMaxPoints points on
-template <int D, int K, bool WIDE>
+// G: groups of four levels that are read (those with an active one); WIDE: from kTileMaxPoints points on
+template <int D, int K, int G, bool WIDE>
 __global__ __launch_bounds__(kFwdThreads) void sdf_fwd_kernel(SdfArgs a) {
     __shared__ SdfWeights<D, K, false> w;
     load_weights<D, K, false, kFwdThreads>(w, a);
@@ -454,7 +455,7 @@ __global__ __launch_bounds__(kFwdThreads) void sdf_fwd_kernel(SdfArgs a) {
     // tiles go to the workgroups first and then to their wavefronts: a small batch has every compute unit at work
     for (int64_t tile = (int64_t)wave * gridDim.x + blockIdx.x; tile < tiles; tile += stride) {
         const bool valid = tile * 32 + j < a.n;
-        v16f x0[1] = {load_levels_tile<D, WIDE>(a.enc, a.n, tile * 32, a.active_levels, j, h)};
+        v16f x0[1] = {load_levels_tile<8 * G, WIDE>(a.enc, a.n, tile * 32, a.active_levels, j, h)};
         v16f a1[2], yv[1];
         Split<1, 3> px;
         Split<2, 3> pv;
@@ -496,7 +497,7 @@ __global__ __launch_bounds__(kFwdThreads) void sdf_fwd_kernel(SdfArgs a) {
         if (a.stream_q) store_levels_tile<D, WIDE, true>(a.q, a.n, tile * 32, valid, qv[0], j, h);
         else store_levels_tile<D, WIDE, false>(a.q, a.n, tile * 32, valid, qv[0], j, h);
         float nrm[3];
-        contract_jac_tile<D, WIDE, true>(a.jac, a.n, tile * 32, a.active_levels, j, h, qv[0], nrm);
+        contract_jac_tile<8 * G, WIDE, true>(a.jac, a.n, tile * 32, a.active_levels, j, h, qv[0], nrm);
 #pragma unroll
         for (int c = 0; c < 3; ++c) nrm[c] += __shfl_xor(nrm[c], 32);
         if (valid && h == 0) {
@@ -784,7 +785,7 @@ struct SdfPairSmem {
     alignas(16) unsigned char tiles[2 * kPairs][kTilesPerWave * kBlockTile];
 };
 
-template <int D, int K, bool WIDE>
+template <int D, int K, int G, bool WIDE>
 __device__ __forceinline__ void sdf_first_order(const SdfArgs& a, const SdfWeights<D, K, true, 2>& w, unsigned char* tile_mem,
                                                 int slot, int lane_in, v16f (*G1)[1], v16f (*G2)[2], v4f* GL) {
     constexpr int KS1 = D / 16;
@@ -797,7 +798,7 @@ __device__ __forceinline__ void sdf_first_order(const SdfArgs& a, const SdfWeigh
         const int lane = (int)again((uint32_t)lane_in), j = lane & 31, h = lane >> 5;
         const int64_t i = tile * 32 + j;
         const bool valid = i < a.n;
-        v16f x0[1] = {load_levels_tile<D, WIDE>(a.enc, a.n, tile * 32, a.active_levels, j, h)};
+        v16f x0[1] = {load_levels_tile<8 * G, WIDE>(a.enc, a.n, tile * 32, a.active_levels, j, h)};
         v16f dK[1] = {zero16()};
         uint32_t m1 = 0u, m_last = 0u;
         if (valid) {
@@ -845,7 +846,7 @@ __device__ __forceinline__ void sdf_first_order(const SdfArgs& a, const SdfWeigh
         else store_levels_tile<D, WIDE, false>(a.d_enc, a.n, tile * 32, valid, de[0], j, h);
         if (a.d_pos) {
             float dp[3];
-            contract_jac_tile<D, WIDE, false>(a.jac, a.n, tile * 32, a.active_levels, j, h, de[0], dp);
+            contract_jac_tile<8 * G, WIDE, false>(a.jac, a.n, tile * 32, a.active_levels, j, h, de[0], dp);
 #pragma unroll
             for (int c = 0; c < 3; ++c) dp[c] += __shfl_xor(dp[c], 32);
             if (valid && h == 0) {
@@ -855,7 +856,7 @@ __device__ __forceinline__ void sdf_first_order(const SdfArgs& a, const SdfWeigh
     }
 }
 
-template <int D, int K, bool WIDE>
+template <int D, int K, int G, bool WIDE>
 __device__ __forceinline__ void sdf_second_order(const SdfArgs& a, const SdfWeights<D, K, true, 2>& w, unsigned char* tile_mem,
                                                  int slot, int lane_in, v16f (*G1)[1], v16f (*G2)[2], v4f* GL) {
     constexpr int KS1 = D / 16;
@@ -877,7 +878,7 @@ __device__ __forceinline__ void sdf_second_order(const SdfArgs& a, const SdfWeig
         }
         // The t sweep first: of its vectors only t_0 outlives the product with S_{K-1}, and S_{K-1} does not outlive the
         // product that turns it into S_1.
-        v16f t0[1] = {apply_jac_tile<D, WIDE>(a.jac, a.n, tile * 32, a.active_levels, j, h, nb3)};
+        v16f t0[1] = {apply_jac_tile<8 * G, WIDE>(a.jac, a.n, tile * 32, a.active_levels, j, h, nb3)};
         v16f s1[2], t1[2], t2[2];
         Split<1, 2> pt;
         Split<2, 2> ps, pd;
@@ -917,7 +918,7 @@ __device__ __forceinline__ void sdf_second_order(const SdfArgs& a, const SdfWeig
     outer_accumulate16<2, kLd16, kLd64>(GL, Zt, Xt, lane);
 }
 
-template <int D, int K, bool WIDE>
+template <int D, int K, int G, bool WIDE>
 __global__ __launch_bounds__(kPairThreads) void sdf_bwd_pair_kernel(SdfArgs a) {
     __shared__ SdfPairSmem<D, K> sm;
     load_weights<D, K, true, kPairThreads, 2>(sm.w, a);
@@ -934,8 +935,8 @@ __global__ __launch_bounds__(kPairThreads) void sdf_bwd_pair_kernel(SdfArgs a) {
     }
 #pragma unroll
     for (int cb = 0; cb < 4; ++cb) GL[cb] = v4f{0.f, 0.f, 0.f, 0.f};
-    if (second) sdf_second_order<D, K, WIDE>(a, sm.w, sm.tiles[wave], slot, lane, G1, G2, GL);
-    else sdf_first_order<D, K, WIDE>(a, sm.w, sm.tiles[wave], slot, lane, G1, G2, GL);
+    if (second) sdf_second_order<D, K, G, WIDE>(a, sm.w, sm.tiles[wave], slot, lane, G1, G2, GL);
+    else sdf_first_order<D, K, G, WIDE>(a, sm.w, sm.tiles[wave], slot, lane, G1, G2, GL);
     __syncthreads();
     // ---- the waves of the second order leave their sums in LDS, their partners add their own, and the block's sums go
     // to global memory in the gradients' own order
@@ -982,10 +983,32 @@ __global__ __launch_bounds__(kPairThreads) void sdf_bwd_pair_kernel(SdfArgs a) {
     }
 }
 
+typedef void (*SdfKernel)(SdfArgs);
+
+// The variant that reads the groups of levels with an active one, from kTileMaxPoints points on the one that reads all.  With
+// one variant for all, levels that the training step leaves unwritten were fetched (half of the levels active, 2^20 points,
+// forward and backward: 169 and 251 us, now 155 and 243); picking level 0 for them in scalar registers, or a branch round
+// every load, cost up to 6 % forward and 8 % backward with all levels active.
+template <int D, int K>
+SdfKernel fwd_kernel(const SdfArgs& a) {
+    if (a.n >= kTileMaxPoints) return sdf_fwd_kernel<D, K, D / 8, true>;
+    if (a.active_levels <= 4) return sdf_fwd_kernel<D, K, 1, false>;
+    if (D == 16 || a.active_levels <= 8) return sdf_fwd_kernel<D, K, 2, false>;
+    return a.active_levels <= 12 ? sdf_fwd_kernel<D, K, D == 32 ? 3 : 2, false> : sdf_fwd_kernel<D, K, D / 8, false>;
+}
+
+template <int D, int K>
+SdfKernel bwd_kernel(const SdfArgs& a) {
+    if (a.n >= kTileMaxPoints) return sdf_bwd_pair_kernel<D, K, D / 8, true>;
+    if (a.active_levels <= 4) return sdf_bwd_pair_kernel<D, K, 1, false>;
+    if (D == 16 || a.active_levels <= 8) return sdf_bwd_pair_kernel<D, K, 2, false>;
+    return a.active_levels <= 12 ? sdf_bwd_pair_kernel<D, K, D == 32 ? 3 : 2, false> : sdf_bwd_pair_kernel<D, K, D / 8, false>;
+}
+
 template <int D, int K>
 int run_fwd(const SdfArgs& a, hipStream_t st) {
     const int64_t tiles = (a.n + 31) / 32;
-    const auto kernel = a.n < kTileMaxPoints ? sdf_fwd_kernel<D, K, false> : sdf_fwd_kernel<D, K, true>;
+    const SdfKernel kernel = fwd_kernel<D, K>(a);
     const int blocks = persistent_blocks((const void*)kernel, kFwdThreads, tiles);
     hipLaunchKernelGGL(kernel, dim3(blocks), dim3(kFwdThreads), 0, st, a);
     return check_launch("sdf forward");
@@ -1003,7 +1026,7 @@ template <int D, int K>
 int run_bwd(const SdfArgs& a, hipStream_t st) {
     const int64_t tiles = (a.n + 31) / 32;
     if (a.masks) {
-        const auto kernel = a.n < kTileMaxPoints ? sdf_bwd_pair_kernel<D, K, false> : sdf_bwd_pair_kernel<D, K, true>;
+        const SdfKernel kernel = bwd_kernel<D, K>(a);
         const int blocks = persistent_blocks((const void*)kernel, kPairThreads, (tiles + kPairs - 1) / kPairs);
         hipLaunchKernelGGL(kernel, dim3(blocks), dim3(kPairThreads), 0, st, a);
     } else {

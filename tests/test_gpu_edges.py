@@ -191,6 +191,33 @@ def test_sdf_forward_over_tiles_and_levels(n, hidden, levels, active):
         assert torch.all(torch.signbit(behind)) and torch.all(behind == 0)
 
 
+@pytest.mark.parametrize("levels,hidden,active", [(16, 2, a) for a in (0, 1, 4, 5, 8, 9, 11, 12, 13)] + [(8, 2, 1), (8, 1, 4), (8, 2, 5), (16, 1, 8)])
+def test_networks_with_fewer_active_levels(levels, hidden, active):
+    """Each group of four levels has a variant of the network kernels: the same bits as with all levels active and zeros in
+    the others, whose arrays may hold anything here."""
+    import dataclasses
+    n = 32 * 9 + 5
+    cfg = wl.make_config(2 if levels == 16 else 1)
+    cfg = dataclasses.replace(cfg, sdf_dims=[2 * levels] + [64] * hidden + [16])
+    gen = torch.Generator(device="cuda").manual_seed(active)
+    randn = lambda *shape: torch.randn(*shape, device="cuda", generator=gen)
+    H = [randn(o_, i) * (2.0 / i) ** 0.5 for i, o_ in zip(cfg.sdf_dims, cfg.sdf_dims[1:])]
+    enc, jac, d_y, d_normal = randn(levels, n, 2), randn(levels, 3, n, 2), randn(n, 16), randn(n, 3)
+    found = []
+    for count, fill in ((active, float("nan")), (levels, 0.0)):
+        c = nb.make_config(dataclasses.replace(cfg, active_levels=count))
+        enc[active:], jac[active:] = fill, fill
+        y, q, normal, d_enc, d_pos = (torch.zeros(*s, device="cuda") for s in ((n, 16), (levels, n, 2), (n, 3), (levels, n, 2), (n, 3)))
+        masks, dH = torch.zeros(2, n, 2, dtype=torch.int32, device="cuda"), [torch.zeros_like(h) for h in H]
+        nb.sdf_fwd_grad(c, enc, jac, H, n, y, q, normal, masks=masks)
+        nb.sdf_mlp_bwd(c, enc, jac, H, d_y, d_normal, n, dH, d_enc, d_pos=d_pos, masks=masks)
+        found.append(([y, q, normal, masks, d_enc, d_pos], dH))
+    for a, b in zip(found[0][0], found[1][0]):
+        assert torch.equal(a, b)
+    for a, b in zip(found[0][1], found[1][1]):
+        assert float((a - b).abs().max()) <= 1e-5 * float(b.abs().max())    # ten workgroups' sums in any order
+
+
 @pytest.mark.parametrize("levels,hidden", [(16, 2), (8, 1)])
 def test_networks_from_2_26_points_on(levels, hidden):
     """Where a lane's byte offsets need 64 bits: the same bits per point, forward and backward, as the same points give in a
