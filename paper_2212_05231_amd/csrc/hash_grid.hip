@@ -511,9 +511,7 @@ __global__ __launch_bounds__(kBlock) void sum_levels_kernel(const float* __restr
 // owner task takes a segment of such a list; with more ranges they get row records like a hashed
 // level.  Workgroups take tasks from a counter, heaviest tasks first.
 constexpr int kOwnerThreads = 1024;
-// Below kOwnerMinPoints the atomic kernel is used: its time is proportional to the points (3.4 us per 1000 with 16
-// levels), the lists cost 45 us (T = 2^19) to 60 us (T = 2^21) before the first point.  Measured at 24 576 points:
-// atomics 87 us, lists 58 (T = 2^19), 86 and 79 (2^21), 45 and 46 (8 active levels); at 32 768: 112 and 61, 115 and 92, 57 and 49.
+// Below kOwnerMinPoints the atomic kernel is used, from kNarrowMinPoints on the lists; in between lists_pay() decides.
 constexpr int64_t kOwnerMinPoints = 7 << 12;
 // Below kNarrowMinPoints a row record keeps its four values as floats (20 bytes), from there on it shares an exponent
 // (12 bytes): below, the records are a small part of the time, and the values keep the atomic kernel's binary32 (gradient
@@ -1118,11 +1116,27 @@ __global__ __launch_bounds__(kOwnerThreads) void scatter_owner_kernel(GridDesc g
     }
 }
 
+// Lists or atomics between kOwnerMinPoints and kNarrowMinPoints.  The atomic kernel takes 10 us and 0.2 ns per point and level.
+// The lists take about 30 us, 10 more where levels of one or two ranges are among them (tasks that walk over all points), 3.4
+// per 256 listed ranges (LDS images cleared and flushed) and 0.05 ns per point and level.  Measured, lists and atomics in us:
+//   levels        28 672 points                  65 535 points
+//   0-15 of 16    73, 105 (T = 2^19) 98, 106 (2^21)    92, 227   143, 231
+//   0-7           58, 56             55, 58            77, 116    82, 120
+//   0-3           48, 35             45, 35            63, 68     63, 66
+//   0-1           35, 26             35, 28            57, 47     57, 49
+//   8-15          55, 61             80, 60            68, 125   114, 125
+//   12-15         45, 37             53, 37            58, 69     74, 70
+// Without a listed level the few tasks do not fill the chip (0-4 at 65 535 points: 98, 80).  The lists win already at 24 576
+// points with all 16 levels (58, 87).
+bool lists_pay(int64_t n, int levels, bool in_place, int64_t listed_ranges) {
+    return listed_ranges > 0 && n * (4 * levels - (in_place ? 5 : 0)) > 600000 + 340 * listed_ranges;
+}
+
 // Which levels get record lists, which point lists, how many ranges and point chunks.  Levels with
 // row records (hashed levels with several ranges, dense levels with more than kInPlaceRanges
 // ranges) come first, then the dense levels with point lists (kIndexedMinRanges..kInPlaceRanges
 // ranges), then the levels of one or two ranges, which take the in-place path.  ok = false if the
-// configuration does not fit the scheme (then the atomic kernel is used).
+// configuration does not fit the scheme or the batch is too small for it (then the atomic kernel is used).
 constexpr int kInPlaceRanges = 64;
 constexpr int kIndexedMinRanges = 3;
 constexpr int kSegPoints = 8192;          // list entries per task of a level with point lists
@@ -1139,12 +1153,15 @@ OwnerPlan make_owner_plan(const neus2_config* cfg, int64_t n, bool& ok) {
     double cost[NEUS2_MAX_LEVELS];
     // lists of row records over all levels (see `chunks` of a listed level below)
     int64_t listed_ranges = 0;
+    bool in_place = false;
     for (int l = cfg->frozen_levels; l < cfg->active_levels; ++l) {
         const int64_t r1 = (int64_t)cfg->res[l] + 1;
         const int64_t used = cfg->dense[l] ? r1 * r1 * r1 : T;
         const int ranges = (int)((used + kOwnerSlots - 1) / kOwnerSlots);
         if (ranges > (cfg->dense[l] ? kInPlaceRanges : 1)) listed_ranges += ranges;
+        else if (ranges < kIndexedMinRanges) in_place = true;
     }
+    if (n < kNarrowMinPoints && !lists_pay(n, cfg->active_levels - cfg->frozen_levels, in_place, listed_ranges)) ok = false;
     int listed_chunks = 1;
     if (listed_ranges > 0) listed_chunks = (int)std::min<int64_t>(4, std::max<int64_t>(1, (2 * compute_units() + listed_ranges - 1) / listed_ranges));
 
@@ -1368,8 +1385,7 @@ int launch_scatter(const neus2_config* cfg, const float* pos, const void* tables
     if (n == 0 || cfg->active_levels == 0) return NEUS2_OK;
     const GridDesc g = make_grid_desc(cfg);
     // Large batches with a workspace: LDS-owner kernel (no global atomics on the big levels);
-    // the position gradient, if wanted, comes from a gather pass of its own.  Below kOwnerMinPoints
-    // points the atomic kernel is cheaper.
+    // the position gradient, if wanted, comes from a gather pass of its own.
     if (n >= kOwnerMinPoints && workspace) {
         bool ok = false;
         const OwnerPlan plan = make_owner_plan(cfg, n, ok);

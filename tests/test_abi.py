@@ -162,3 +162,20 @@ def test_workspace_of_a_batch_serves_every_smaller_one(k, active, frozen):
     counts = sorted({n + d for n in edges for d in (-1, 0, 1)} | set(range(20011, 130000, 1499)))
     sizes = [nb.workspace_bytes(c, n) for n in counts]
     assert sizes[-1] > 0 and all(a <= b for a, b in zip(sizes, sizes[1:])), list(zip(counts, sizes))
+
+
+@pytest.mark.parametrize("log2_table,n,frozen,active,lists", [
+    (19, 28672, 0, 16, True), (19, 28672, 0, 4, False), (19, 28672, 12, 16, False), (19, 28672, 4, 16, True), (19, 65535, 0, 2, False),
+    (19, 65535, 0, 8, True), (19, 65535, 12, 16, True), (19, 65535, 0, 5, False), (19, 40000, 14, 16, False), (19, 40000, 8, 16, True),
+    (21, 28672, 8, 16, False), (21, 40000, 0, 10, True), (21, 40000, 12, 16, False), (21, 65535, 4, 16, True), (15, 28672, 0, 6, False),
+    (15, 28672, 8, 16, True), (15, 40000, 0, 3, False), (15, 65535, 0, 10, True), (19, 1 << 16, 0, 2, True), (21, 1 << 16, 14, 16, True)])
+def test_lists_only_where_they_are_the_faster_path(log2_table, n, frozen, active, lists):
+    """Between 28 672 and 65 535 points few levels, frozen ones and many short lists are left to the atomic kernel, which needs
+    no workspace: each of these was 10 % or more faster on the side given here (from 2^16 points on the lists always run)."""
+    cfg = wl.make_config(4 if log2_table == 21 else 2)
+    cfg.log2_table_size = log2_table
+    if log2_table == 15:
+        cfg.res = wl.level_resolutions(16, 16, 512)
+    cfg.dense = wl.dense_flags(cfg.res, cfg.table_size)
+    cfg.frozen_levels, cfg.active_levels = frozen, active
+    assert (nb.workspace_bytes(nb.make_config(cfg), n) > 0) == lists
