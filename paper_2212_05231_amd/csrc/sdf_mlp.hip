@@ -243,21 +243,6 @@ __device__ __forceinline__ JacRegs<D> load_jac(const float* __restrict__ jac, in
 }
 
 template <int D>
-__device__ __forceinline__ void contract_jac_regs(const JacRegs<D>& J, const v16f& x, float out[3]) {
-    out[0] = out[1] = out[2] = 0.f;
-#pragma unroll
-    for (int g = 0; g < D / 8; ++g)
-#pragma unroll
-        for (int u = 0; u < 2; ++u) {
-            const float2 a = J.v[2 * g + u][0], b = J.v[2 * g + u][1], c = J.v[2 * g + u][2];
-            const float x0 = x[4 * g + 2 * u], x1 = x[4 * g + 2 * u + 1];
-            out[0] += x0 * a.x + x1 * b.y;
-            out[1] += x0 * a.y + x1 * c.x;
-            out[2] += x0 * b.x + x1 * c.y;
-        }
-}
-
-template <int D>
 __device__ __forceinline__ v16f apply_jac_regs(const JacRegs<D>& J, const float v[3]) {
     v16f t = zero16();
 #pragma unroll
@@ -1058,8 +1043,9 @@ constexpr int kDeepRun = 6;                        // layers a run holds at most
 constexpr int kDeepGradRun = 2;                    // of a gradient run: their sums take 64 registers a layer
 
 // The workspace: vectors of 32 floats per lane, two lanes a point, in the order [tile][register quad][lane][4], so that
-// an access instruction covers 1 KB on end: a_0, t_0, a_1, t_1, ..., four vectors that runs hand on, then the mask words
-// [layer][tile * 64 + lane].  (a_0 is the encoding itself and t_0 has 32 registers' upper half empty: left unwritten.)
+// an access instruction covers 1 KB on end: t_0, a_1, t_1, ..., a_{K-1}, t_{K-1}, two vectors that runs hand on (one of each
+// order), then the mask words of the hidden layers [layer][tile * 64 + lane].  (a_0 is the encoding itself; the upper 16 of
+// t_0's 32 registers are empty and left unwritten.)
 struct DeepArgs {
     const float* H[NEUS2_DEEP_MAX_MATS];
     int n_mats, enc_dim;
@@ -1072,11 +1058,11 @@ struct DeepArgs {
 
     __device__ __forceinline__ int in_dim(int l) const { return l == 0 ? enc_dim : 64; }
     __device__ __forceinline__ int out_dim(int l) const { return l == n_mats - 1 ? 16 : 64; }
-    __device__ __forceinline__ float* a_vec(int l) const { return ws + 2 * l * vec; }
-    __device__ __forceinline__ float* t_vec(int l) const { return ws + (2 * l + 1) * vec; }
-    __device__ __forceinline__ float* passed(int k) const { return ws + (2 * n_mats + k) * vec; }
+    __device__ __forceinline__ float* a_vec(int l) const { return ws + (2 * l - 1) * vec; }          // l > 0
+    __device__ __forceinline__ float* t_vec(int l) const { return ws + 2 * l * vec; }
+    __device__ __forceinline__ float* passed(int k) const { return ws + (2 * n_mats - 1 + k) * vec; }
     __device__ __forceinline__ uint32_t* masks(int l, int64_t tile) const {
-        return reinterpret_cast<uint32_t*>(ws + (2 * n_mats + 4) * vec) + ((int64_t)l * ((n + 31) / 32) + tile) * 64;
+        return reinterpret_cast<uint32_t*>(ws + (2 * n_mats + 1) * vec) + ((int64_t)l * ((n + 31) / 32) + tile) * 64;
     }
 };
 
@@ -1375,7 +1361,7 @@ static int64_t deep_vector_floats(int64_t n) { return ((n + 31) / 32) * 64 * 32;
 
 int64_t sdf_deep_workspace_bytes(int n_mats, int64_t n) {
     const int64_t vec = deep_vector_floats(n) * 4, words = ((n + 31) / 32) * 64 * 4;
-    return (2 * (int64_t)n_mats + 4) * vec + (int64_t)n_mats * words;
+    return (2 * (int64_t)n_mats + 1) * vec + ((int64_t)n_mats - 1) * words;
 }
 
 namespace {

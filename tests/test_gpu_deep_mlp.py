@@ -150,3 +150,20 @@ def test_runs_of_layers_at_their_edges(enc_dim, hidden, n):
     """Six matrices fill a run, seven make two; an even number of matrices leaves no single layer for the last gradient
     launch; tiles of 32 points that are not full, just begun and exactly full."""
     test_layer_by_layer_network_against_the_oracle(enc_dim, hidden, n)
+
+
+@pytest.mark.parametrize("n_mats,enc_dim,n", [(2, 32, 1), (3, 16, 33), (7, 32, 64), (9, 32, 95)])
+def test_workspace_holds_what_is_used_and_no_more(n_mats, enc_dim, n):
+    """Two vectors of 32 floats per lane and layer (the encoding serves as the first one's), one per order handed on, a mask
+    word per lane and hidden layer; nothing behind the size asked for is written."""
+    lanes = (n + 31) // 32 * 64
+    size = nb.sdf_deep_workspace_bytes(n_mats, n)
+    assert size == 4 * lanes * (32 * (2 * n_mats + 1) + n_mats - 1)
+    rng = np.random.default_rng(n)
+    L, H = enc_dim // 2, [cuda(h) for h in make_net(rng, enc_dim, n_mats - 1)]
+    held = torch.full((size + 4096,), 0x5A, dtype=torch.uint8, device="cuda")
+    enc, jac, d_y, d_normal = (torch.randn(*s, device="cuda") for s in ((L, n, 2), (L, 3, n, 2), (n, 16), (n, 3)))
+    y, q, normal, d_enc = (torch.zeros(*s, device="cuda") for s in ((n, 16), (L, n, 2), (n, 3), (L, n, 2)))
+    nb.sdf_deep_fwd_grad(enc_dim, enc, jac, H, n, y, q, normal, held[:size])
+    nb.sdf_deep_bwd(enc_dim, enc, jac, H, d_y, d_normal, n, [torch.zeros_like(h) for h in H], d_enc, held[:size])
+    assert bool((held[size:] == 0x5A).all()) and bool((held[:size] != 0x5A).any())
