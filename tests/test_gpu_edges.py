@@ -258,3 +258,105 @@ def test_networks_from_2_26_points_on(levels, hidden):
         assert torch.equal(a, b) and bool(a.any())
     for a, b in zip(dH, dH_few):
         assert rel(a.cpu(), b.cpu()) <= 1e-5                     # the same terms in another order
+
+
+@pytest.mark.parametrize("n", [1, 31, 33, 1000])
+@pytest.mark.parametrize("given", [True, False])
+def test_color_backward_adjoints_and_nothing_behind_them(n, given):
+    """The adjoints of every input of the colour network, d_normal added to, d_sdf passed on; tiles that are not full."""
+    rng = np.random.default_rng(n + 7)
+    cfg = wl.make_config(2)
+    cfg.samples_per_ray = 1
+    c = nb.make_config(cfg)
+    W = [rng.normal(size=(cfg.color_dims[i + 1], cfg.color_dims[i])).astype(np.float32) * 0.3 for i in range(3)]
+    pos = rng.uniform(size=(n, 3)).astype(np.float32)
+    nrm, y, dn0 = (rng.normal(size=(n, k)).astype(np.float32) for k in (3, 16, 3))
+    dirs = rng.normal(size=(n, 3))
+    dirs = (dirs / np.linalg.norm(dirs, axis=1, keepdims=True)).astype(np.float32)
+    d_rgb, d_sdf = rng.normal(size=(n, 3)).astype(np.float32), rng.normal(size=n).astype(np.float32)
+    Wg, args = [cuda(w) for w in W], (cuda(pos), cuda(nrm), cuda(dirs), cuda(y))
+    rgb, kept = torch.empty(n, 3, device="cuda"), torch.zeros(2, n, 2, dtype=torch.int32, device="cuda")
+    nb.color_fwd(c, *args, Wg, n, rgb, masks=kept)
+    rgb_r, acts, masks = o.color_forward(W, o.color_input(pos, nrm.astype(np.float64), dirs, y.astype(np.float64), 1))
+    d_in = o.mlp_backward(W, acts, masks, d_rgb * rgb_r * (1 - rgb_r))[1]
+    want_dy = d_in[:, 22:38].copy()
+    want_dy[:, 0] += d_sdf
+    (d_y, behind_y), (d_normal, behind_n), (d_pos, behind_p) = guarded((n, 16)), guarded((n, 3)), guarded((n, 3))
+    d_normal += cuda(dn0)
+    nb.color_bwd(c, *args, Wg, rgb, cuda(d_rgb), cuda(d_sdf), n, [torch.zeros_like(w) for w in Wg], d_y, d_normal, d_pos,
+                 masks=kept if given else None)
+    for got, want in ((d_y, want_dy), (d_normal, dn0 + d_in[:, 3:6]), (d_pos, d_in[:, 0:3])):
+        assert rel(got.cpu().numpy(), want) <= GRAD_TOL
+    for behind in (behind_y, behind_n, behind_p):
+        assert torch.all(torch.signbit(behind)) and torch.all(behind == 0)
+
+
+@pytest.mark.parametrize("n,levels,hidden", [(1, 16, 2), (31, 8, 2), (33, 16, 1), (257 * 32 + 7, 16, 2)])
+def test_sdf_backward_with_and_without_masks_and_nothing_behind(n, levels, hidden):
+    """Both kernels of the SDF backward call on tiles that are not full, with the position gradient added to: two terms per
+    factor on one side, three on the other, 1e-4 of the norm apart at most."""
+    import dataclasses
+    cfg = wl.make_config(2 if levels == 16 else 1)
+    c = nb.make_config(dataclasses.replace(cfg, sdf_dims=[2 * levels] + [64] * hidden + [16]))
+    gen = torch.Generator(device="cuda").manual_seed(n)
+    randn = lambda *shape: torch.randn(*shape, device="cuda", generator=gen)
+    H = [randn(o_, i) * (2.0 / i) ** 0.5 for i, o_ in zip([2 * levels] + [64] * hidden, [64] * hidden + [16])]
+    enc, jac, d_y, d_normal = randn(levels, n, 2), randn(levels, 3, n, 2), randn(n, 16), randn(n, 3)
+    masks = torch.zeros(2, n, 2, dtype=torch.int32, device="cuda")
+    nb.sdf_fwd_grad(c, enc, jac, H, n, torch.empty(n, 16, device="cuda"), torch.empty_like(enc), torch.empty(n, 3, device="cuda"), masks=masks)
+    found, start = [], randn(n, 3)
+    for kept in (masks, None):
+        (d_enc, behind_e), (d_pos, behind_p) = guarded((levels, n, 2)), guarded((n, 3))
+        d_pos += start
+        dH, behind = zip(*[guarded(h.shape) for h in H])
+        nb.sdf_mlp_bwd(c, enc, jac, H, d_y, d_normal, n, list(dH), d_enc, d_pos=d_pos, masks=kept)
+        for guard in (behind_e, behind_p, *behind):
+            assert torch.all(torch.signbit(guard)) and torch.all(guard == 0)
+        found.append([d_enc, d_pos, *dH])
+    for a, b in zip(*found):
+        assert rel(a.cpu(), b.cpu()) <= GRAD_TOL and bool(a.any())
+
+
+@pytest.mark.parametrize("n_rays", [509, 1023])
+def test_step_position_gradient_through_wide_records(n_rays):
+    """A whole step below 2^16 points that wants the position gradient: its encode kernel clears the lists' header and leaves
+    the second derivatives behind 20-byte records.  Against the step without a workspace on all points and against the
+    oracle on a sample of rays (adjoints scale with 1/rays)."""
+    w = wl.make_workload(2, n_rays=n_rays)
+    cfg, params, batch = w["cfg"], w["params"], w["batch"]
+    params["tables"] = (params["tables"].astype(np.float64) * 2000.0).astype(params["tables"].dtype)
+    n, spr = batch["pos"].shape[0], cfg.samples_per_ray
+    assert 7 << 12 <= n < 1 << 16
+    found = []
+    for use_ws in (True, False):
+        step = nb.Step(cfg, params, n, want_pos_grad=True, use_workspace=use_ws)
+        step.set_batch(batch)
+        step.zero_grads()
+        step.train_step()
+        found.append((step.d_pos.cpu().numpy(), step.d_tables.cpu().numpy()))
+        assert not use_ws or bool(step.workspace[64:64 + 32 * 256].any())           # the cursors of the lists
+    assert rel(found[0][0], found[1][0]) <= 1e-5 and rel(found[0][1], found[1][1]) <= 1e-5
+    pick = np.sort(np.random.default_rng(n_rays).choice(n_rays, size=40, replace=False))
+    points = (pick[:, None] * spr + np.arange(spr)[None, :]).reshape(-1)
+    sub = {"pos": batch["pos"][points], "dirs": batch["dirs"][pick], "target": batch["target"][pick]}
+    ref = o.train_step(cfg, params, sub, want_pos_grad=True)
+    assert rel(found[0][0][points], ref["dpos"] * (len(pick) / n_rays)) <= GRAD_TOL
+
+
+def test_concentrated_batch_overflows_the_lists_of_wide_records():
+    """40 000 samples inside a cube of side 2e-3: their rows crowd into a few ranges of every hashed level, and the surplus of
+    those lists goes through global atomics.  A slot's sum of m values of either sign in binary32 is off by about
+    2^-24 sqrt(m) of itself, m at most 160 000 here: 2.4e-5."""
+    rng = np.random.default_rng(6)
+    cfg = wl.make_config(2)
+    c, L, T, n = nb.make_config(cfg), cfg.n_levels, cfg.table_size, 40000
+    pos = (0.37 + 2e-3 * rng.uniform(size=(n, 3))).astype(np.float32)
+    q, d_enc = (rng.normal(size=(n, 2 * L)).astype(np.float32) for _ in range(2))
+    d_normal = (rng.normal(size=(n, 3)) * 1e-2).astype(np.float32)
+    to_lm = lambda a: cuda(a.reshape(n, L, 2).transpose(1, 0, 2))
+    ws = torch.zeros(nb.workspace_bytes(c, n) // 4, dtype=torch.int32, device="cuda")
+    got = torch.zeros(L, T, 2, device="cuda")
+    nb.hash_scatter_bwd(c, cuda(pos), cuda(wl.make_params(cfg, 3)["tables"]), to_lm(q), to_lm(d_enc), cuda(d_normal), n, got, workspace=ws)
+    capacity = ((4 * n // (T >> 13)) * 3 // 2 + 1023) // 64 * 64
+    assert int(ws[64:64 + 32 * 256].max()) > capacity
+    assert rel(got.cpu().numpy(), o.table_gradient(cfg, pos, q, d_enc, d_normal)) <= 2.4e-5

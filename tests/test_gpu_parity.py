@@ -1167,7 +1167,7 @@ def test_full_size_sampled_rays(k):
 
 
 def test_dense_level_through_record_lists_and_its_range_crossings():
-    """Workload 4's descriptor at 2^16 points, the smallest batch that takes the LDS scatter: its
+    """Workload 4's descriptor at 2^16 points, the smallest batch whose row records are packed: its
     level of resolution 101 is dense with 130 ranges of 8192 slots, more than the in-place path
     takes, so its rows go through record lists; a row whose x+1 corner is the first slot of the
     next range is split (that corner goes straight to the gradient).  Every tensor of the step,
@@ -1332,7 +1332,7 @@ def test_whole_step_on_shapes_other_than_the_benchmark_ones(seed):
 
 def test_large_batch_position_gradient():
     """Batches of 2^16 points and more take the path that keeps the table gradient in LDS; the
-    position gradient then comes from a gather pass of its own.  Against the oracle on a sample
+    position gradient then comes from second derivatives that the encode kernel stored.  Against the oracle on a sample
     of rays (adjoints scale with 1/rays), and against the atomic path on all points."""
     w = wl.make_workload(2, n_rays=1024 + 3)
     cfg, params, batch = w["cfg"], w["params"], w["batch"]
