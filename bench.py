@@ -43,10 +43,10 @@ MFMA_BF16_PEAK_TFLOPS = 2500.0 # MI355X dense bf16 matrix rate: the network kern
 
 # the HIP kernels behind each timed call (names as rocprofv3 prints them)
 KERNELS_OF_CALL = {
-    "hash_encode": ["encode_kernel"], "sdf_fwd_grad": ["sdf_fwd_kernel"], "sdf_mlp_bwd": ["sdf_bwd_kernel"],
-    "sdf_bwd_2nd": ["sdf_bwd_kernel", "zero_kernel", "bin_rows_kernel", "scatter_owner_kernel", "pos_hessian_kernel", "sum_levels_kernel"],
+    "hash_encode": ["encode_kernel"], "sdf_fwd_grad": ["sdf_fwd_kernel"], "sdf_mlp_bwd": ["sdf_bwd_pair_kernel"],
+    "sdf_bwd_2nd": ["sdf_bwd_pair_kernel", "zero_kernel", "bin_rows_kernel", "scatter_owner_kernel", "pos_hessian_kernel", "sum_levels_kernel"],
     "hash_scatter_bwd": ["zero_kernel", "bin_rows_kernel", "scatter_owner_kernel"],
-    "adam_all": ["adam_tables_kernel"], "color_fwd": ["color_fwd_kernel"], "color_bwd": ["color_bwd_kernel"],
+    "adam_all": ["adam_tables_kernel"], "color_fwd": ["color_fwd_kernel"], "color_bwd": ["color_bwd_pair_kernel"],
     "render_loss_bwd": ["render_loss_kernel"], "loss": ["loss_kernel"],
 }
 
