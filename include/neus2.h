@@ -171,7 +171,8 @@ int neus2_color_fwd(const neus2_config* cfg, const float* pos, const float* norm
  *   and matrices.  The backward pass recomputes the hidden activations instead of reading them
  *   back.  Given the masks it does so at the accuracy its results are compared at (gradient
  *   tolerance, see "Arithmetic" above); without them it repeats the forward call's own
- *   arithmetic, which reproduces the masks bit for bit, at about 8 % more time. */
+ *   arithmetic, which reproduces the masks bit for bit, in a slower kernel (2^15 points 33 us
+ *   against 30, 2^18 points 80 against 63, 2^20 points 261 against 203). */
 int neus2_color_bwd(const neus2_config* cfg, const float* pos, const float* normal,
                     const float* dirs, const int32_t* sample_ray, const float* y,
                     const float* const* W, const float* rgb,

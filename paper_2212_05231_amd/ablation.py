@@ -11,8 +11,8 @@ and the gradient of the loss with respect to every matrix of f (which needs the 
 term of Theorem 1 because the loss depends on normal) and with respect to e.
 The library runs neus2_sdf_fwd_grad + neus2_loss + neus2_sdf_mlp_bwd (the fused kernels of the
 training step: 1 and 2 hidden layers of 64) or, for the figure's deeper networks (4 and 8 hidden
-layers), neus2_sdf_deep_fwd_grad + neus2_loss + neus2_sdf_deep_bwd (one launch per matrix and
-direction); PyTorch runs the same network with autograd.grad(create_graph=True) for q and
+layers), neus2_sdf_deep_fwd_grad + neus2_loss + neus2_sdf_deep_bwd (runs of a few layers a
+launch); PyTorch runs the same network with autograd.grad(create_graph=True) for q and
 .backward() for the rest.  Prints one line per case and a JSON summary; the gradients of the two
 sides are compared as a sanity check (the parity tests proper are against the float64 oracle).
 """

@@ -1027,7 +1027,8 @@ int run_bwd(const SdfArgs& a, hipStream_t st) {
 // most) and a tile's vectors in registers from layer to layer; between launches they pass through a workspace in HBM.
 // One layer a launch instead, each lane writing its 32 registers as 128 consecutive bytes, moved 4.2 GB where 2.2 are
 // needed, every access instruction in 64 cache lines: eight hidden layers at 2^17 points, forward and backward, took
-// 1243 us, now 617.  Bound by the vectors that the backward call stores and reads back.
+// 1243 us, runs of layers 617 and without spilled registers 556.  Bound by the vectors that the backward call stores and
+// reads back.
 // Every matrix is used as 64 x 64 (the first one's missing columns and the last one's missing rows are zeros), so one
 // kernel serves every layer.
 //   forward run:   a_l = G_l H_l a_{l-1}  (six-product arithmetic, writes the mask words)
