@@ -360,3 +360,29 @@ def test_concentrated_batch_overflows_the_lists_of_wide_records():
     capacity = ((4 * n // (T >> 13)) * 3 // 2 + 1023) // 64 * 64
     assert int(ws[64:64 + 32 * 256].max()) > capacity
     assert rel(got.cpu().numpy(), o.table_gradient(cfg, pos, q, d_enc, d_normal)) <= 2.4e-5
+
+
+@pytest.mark.parametrize("n,size_y,size_w", [(1, 1.0, 1.0), (31, 1e-20, 1.0), (33, 1e10, 1e-9), (257 * 128 + 5, 1.0, 1.0), (1000, 0.0, 1.0)])
+def test_colour_forward_without_masks(n, size_y, size_w):
+    """A forward pass that is not asked for masks takes scaled fp16 terms: the scale follows the point (features of any
+    size) and the matrix (one of zeros among them).  At most 64 products, each within 2^-22 of its size (two roundings of
+    2^-23 and the product of the low terms), random signs: 1e-6 of the norm, as the masked pass."""
+    rng = np.random.default_rng(n)
+    cfg = wl.make_config(2)
+    cfg.samples_per_ray = 1
+    W = [rng.normal(size=(cfg.color_dims[i + 1], cfg.color_dims[i])).astype(np.float32) * 0.3 for i in range(3)]
+    W[0] = (W[0] * size_w).astype(np.float32)
+    W[2] = (W[2] / max(size_y * size_w, 1.0)).astype(np.float32)
+    if size_y == 0.0:
+        W[1][:] = 0.0
+    pos, nrm = rng.uniform(size=(n, 3)).astype(np.float32), rng.normal(size=(n, 3)).astype(np.float32)
+    y = (rng.normal(size=(n, 16)) * size_y).astype(np.float32)
+    dirs = rng.normal(size=(n, 3))
+    dirs = (dirs / np.linalg.norm(dirs, axis=1, keepdims=True)).astype(np.float32)
+    rgb, behind = guarded((n, 3))
+    nb.color_fwd(nb.make_config(cfg), cuda(pos), cuda(nrm), cuda(dirs), cuda(y), [cuda(w) for w in W], n, rgb)
+    want, _, _ = o.color_forward(W, o.color_input(pos, nrm.astype(np.float64), dirs, y.astype(np.float64), 1))
+    got = rgb.cpu().numpy()
+    assert rel(got, want) <= 1e-6
+    assert np.ptp(want) > 1e-3 if size_y else np.all(got == 0.5)
+    assert torch.all(torch.signbit(behind)) and torch.all(behind == 0)
