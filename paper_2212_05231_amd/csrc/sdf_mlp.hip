@@ -1061,7 +1061,7 @@ int run_bwd(const SdfArgs& a, hipStream_t st) {
 // kernel serves every layer.
 //   forward run:   a_l = G_l H_l a_{l-1}  (six-product arithmetic, writes the mask words)
 //                  t_l = G_l H_l t_{l-1}  (WITH_T; t_0 = (de/dx) dL/dn)
-//   reverse run:   S_{l-1} = (H_l^T S_l) G_{l-1}, down to dd/de and the normal
+//   reverse:       S_{l-1} = (H_l^T S_l) G_{l-1}, down to dd/de and the normal, all layers in one launch
 //   gradient run:  dH_l += delta_l a_{l-1}^T + S_l^T t_{l-1}^T
 //                  S_{l-1} as above, delta_{l-1} = G_{l-1} H_l^T delta_l
 // with S_K = the unit row of the SDF output and delta_K = dL/d(d,g): Theorem 1 and Eqs. 7-8 as in
@@ -1078,7 +1078,7 @@ constexpr int kDeepGradRun = 2;                    // of a gradient run: their s
 struct DeepArgs {
     const float* H[NEUS2_DEEP_MAX_MATS];
     int n_mats, enc_dim;
-    int first, count;                      // layers first .. first + count - 1 (numbered from 0); reverse kinds start at the last
+    int first, count;                      // layers first .. first + count - 1 (numbered from 0); gradient runs start at the last
     int64_t n, vec;                        // points; floats of a workspace vector
     float* ws;
     const float* enc; const float* jac; const float* d_normal; const float* d_y;
@@ -1176,11 +1176,14 @@ __global__ __launch_bounds__(kDeepThreads) void deep_forward_kernel(DeepArgs a) 
             v16f z[2];
             Split<2, 3> px;
             split(x, px);
-            matvec_split<2, 4, 3, 3>(W, px, z, lane);
             uint32_t m = 0xffffffffu;
-            if (l == a.n_mats - 1) {
+            if (l == a.n_mats - 1) {                             // 16 outputs: one block of rows
+                matvec_split<1, 4, 3, 3>(W, px, z, lane);
                 store_rows16(a.y, i, valid, h, z[0]);
+                break;
             } else {
+                if (l == 0) matvec_split<2, 2, 3, 3, 4>(W, px, z, lane);      // 32 inputs at most
+                else matvec_split<2, 4, 3, 3>(W, px, z, lane);
                 m = relu_mask<2>(z);
                 if (WITH_T || k == a.count - 1) store_lane<2>(a.a_vec(l + 1), tile, lane, z);
                 a.masks(l, tile)[lane] = m;
@@ -1189,7 +1192,8 @@ __global__ __launch_bounds__(kDeepThreads) void deep_forward_kernel(DeepArgs a) 
             if (WITH_T) {
                 Split<2, 2> pt;
                 split(t, pt);
-                matvec_split<2, 4, 3, 2>(W, pt, t, lane);
+                if (l == 0) matvec_split<2, 2, 3, 2, 4>(W, pt, t, lane);
+                else matvec_split<2, 4, 3, 2>(W, pt, t, lane);
                 apply_mask<2>(t, m);
                 store_lane<2>(a.t_vec(l + 1), tile, lane, t);
             }
@@ -1197,47 +1201,89 @@ __global__ __launch_bounds__(kDeepThreads) void deep_forward_kernel(DeepArgs a) 
     }
 }
 
-// dd/de and the normal (Eq. 2): S downwards, three terms per factor (compared at forward tolerance)
-__global__ __launch_bounds__(kDeepThreads) void deep_reverse_kernel(DeepArgs a) {
-    constexpr int kMatrix = 64 * SplitMatrix<4, 3>::kLd;
-    __shared__ alignas(16) unsigned char mats[kDeepRun * kMatrix];
-    deep_matrices<3, kDeepRun, true>(a, a.first, -1, a.count, mats);
+// dd/de and the normal (Eq. 2): S downwards from row 0 of the last matrix, all layers in one launch: the transposed matrices of
+// eight layers fit LDS as two fp16 terms, scaled (they decide no mask and are as accurate as fp32), and a tile's vector stays in
+// registers.  Sixteen wavefronts share them, four per SIMD.  Six bf16 products in two runs of layers with a vector handed on
+// through the workspace took 88 us at eight hidden layers and 2^17 points, this takes 44 (two hidden layers: 24, 14).
+constexpr int kReverseThreads = 1024;
+constexpr int kReverseWaves = kReverseThreads / 64;
+constexpr int kReverseMats = NEUS2_DEEP_MAX_MATS - 1;
+
+struct DeepReverseSmem {
+    alignas(16) unsigned char mats[kReverseMats * 64 * SplitMatrix<4, 2>::kLd];
+    alignas(16) float row0[2][32];                          // [lane half][16 b + r]
+    alignas(16) float part[kReverseMats * kReverseWaves];
+};
+
+__global__ __launch_bounds__(kReverseThreads) void deep_reverse_kernel(DeepArgs a) {
+    constexpr int kMatrix = 64 * SplitMatrix<4, 2>::kLd;
+    __shared__ DeepReverseSmem sm;
+    int exponents = 0;                                      // sum over the matrices
+    {
+        typename SplitMatrix<4, 2>::template Fill<64, kReverseThreads, true> f[kReverseMats];
+        float largest[kReverseMats];
+        int exponent[kReverseMats];
+#pragma unroll
+        for (int l = 0; l < kReverseMats; ++l) {
+            largest[l] = 0.f;
+            if (l >= a.n_mats - 1) continue;
+            const int id = a.in_dim(l);
+            const float* __restrict__ W = a.H[l];
+            f[l].load(threadIdx.x, [&](int i, int o) { return i < id ? W[o * id + i] : 0.f; });
+        }
+        if (threadIdx.x < 64) {
+            const int k = threadIdx.x & 31;
+            sm.row0[threadIdx.x >> 5][k] = a.H[a.n_mats - 1][32 * (k >> 4) + neuron_of(k & 15, threadIdx.x >> 5)];
+        }
+#pragma unroll
+        for (int l = 0; l < kReverseMats; ++l)
+            if (l < a.n_mats - 1) largest[l] = f[l].largest(threadIdx.x);
+        workgroup_exponents<kReverseMats, kReverseWaves>(largest, sm.part, exponent);
+#pragma unroll
+        for (int l = 0; l < kReverseMats; ++l) {
+            if (l >= a.n_mats - 1) continue;
+            f[l].store_half(sm.mats + l * kMatrix, threadIdx.x, exponent[l]);
+            exponents += exponent[l];
+        }
+        __syncthreads();
+    }
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int j = lane & 31, h = lane >> 5;
     const int64_t tiles = (a.n + 31) / 32;
-    for (int64_t tile = (int64_t)blockIdx.x * kDeepWaves + wave; tile < tiles; tile += (int64_t)gridDim.x * kDeepWaves) {
+    for (int64_t tile = (int64_t)wave * gridDim.x + blockIdx.x; tile < tiles; tile += (int64_t)gridDim.x * kReverseWaves) {
         const int64_t i = tile * 32 + j;
         const bool valid = i < a.n;
         v16f s[2];
-        if (a.first == a.n_mats - 1) {
-            s[0] = zero16(); s[1] = zero16();
-            if (h == 0 && valid) s[0][0] = 1.f;
-        } else {
-            load_lane<2>(a.passed(0), tile, lane, s);
-        }
-#pragma unroll 1
-        for (int k = 0; k < a.count; ++k) {
-            const int l = a.first - k;
-            const unsigned char* W = mats + k * kMatrix;
-            const uint32_t m = l > 0 ? a.masks(l - 1, tile)[lane] : 0u;
-            Split<2, 3> ps;
-            split(s, ps);
-            if (l > 0) {
-                matvec_split<2, 4, 3, 3>(W, ps, s, lane);
-                apply_mask<2>(s, m);
-                if (k == a.count - 1) store_lane<2>(a.passed(0), tile, lane, s);
-            } else {
-                v16f de[1];
-                matvec_split<1, 4, 3, 3>(W, ps, de, lane);
-                store_levels_active(a.q, a.n, i, valid, a.enc_dim / 2, h, de[0]);
-                float nrm[3];
-                contract_jac<32>(a.jac, a.n, i, valid, a.enc_dim / 2, h, de[0], nrm);
 #pragma unroll
-                for (int c = 0; c < 3; ++c) nrm[c] += __shfl_xor(nrm[c], 32);
-                if (valid && h == 0) { a.normal[3 * i] = nrm[0]; a.normal[3 * i + 1] = nrm[1]; a.normal[3 * i + 2] = nrm[2]; }
-            }
+        for (int b = 0; b < 2; ++b)
+#pragma unroll
+            for (int r = 0; r < 16; ++r) s[b][r] = sm.row0[h][16 * b + r];
+        apply_mask<2>(s, a.masks(a.n_mats - 2, tile)[lane]);
+        int e = exponents;
+#pragma unroll 1
+        for (int l = a.n_mats - 2; l > 0; --l) {
+            const uint32_t m = a.masks(l - 1, tile)[lane];
+            HalfSplit<2> ps;
+            const int k = half_exponent<2>(s);
+            half_split(s, k, ps);
+            e += k;
+            matvec_half<2, 4>(sm.mats + l * kMatrix, ps, s, lane);
+            apply_mask<2>(s, m);
         }
+        HalfSplit<2> ps;
+        const int k = half_exponent<2>(s);
+        half_split(s, k, ps);
+        v16f de[1];
+        matvec_half<1, 4>(sm.mats, ps, de, lane);
+#pragma unroll
+        for (int r = 0; r < 16; ++r) de[0][r] = __builtin_amdgcn_ldexpf(de[0][r], -(e + k));
+        store_levels_active(a.q, a.n, i, valid, a.enc_dim / 2, h, de[0]);
+        float nrm[3];
+        contract_jac<32>(a.jac, a.n, i, valid, a.enc_dim / 2, h, de[0], nrm);
+#pragma unroll
+        for (int c = 0; c < 3; ++c) nrm[c] += __shfl_xor(nrm[c], 32);
+        if (valid && h == 0) { a.normal[3 * i] = nrm[0]; a.normal[3 * i + 1] = nrm[1]; a.normal[3 * i + 2] = nrm[2]; }
     }
 }
 
@@ -1432,10 +1478,8 @@ int launch_sdf_deep_fwd(int n_mats, int enc_dim, const float* enc, const float* 
         a.first = start[r]; a.count = start[r + 1] - start[r];
         deep_launch(deep_forward_kernel<false>, a, tiles, st);
     }
-    for (int r = runs - 1; r >= 0; --r) {                        // S_{K-1} .. S_1, dd/de
-        a.first = start[r + 1] - 1; a.count = start[r + 1] - start[r];
-        deep_launch(deep_reverse_kernel, a, tiles, st);
-    }
+    const int blocks = persistent_blocks((const void*)deep_reverse_kernel, kReverseThreads, tiles);
+    hipLaunchKernelGGL(deep_reverse_kernel, dim3(blocks), dim3(kReverseThreads), 0, st, a);      // S_{K-1} .. S_1, dd/de
     return check_launch("sdf forward (deeper network)");
 }
 
