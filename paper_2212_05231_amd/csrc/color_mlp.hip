@@ -412,6 +412,8 @@ __global__ __launch_bounds__(kThreads) void color_bwd_kernel(ColorArgs a) {
 // wavefront per SIMD with 512 registers waited on its own chain: 2^18 points 71 -> 61 us, 2^20 points 232 -> 197, 32576
 // points 20.6 -> 18.2.
 // (Eight wavefronts that each do all of a tile spilled 68 registers: 78 and 261 us.)
+// The last matrix's gradient as 4x4 products instead of 16x16 ones with 13 empty rows, 256 clocks of the matrix pipe a tile instead
+// of 1024 and on the longer of the two chains: 2^20 points 185 -> 171 us, 131072 points 38.6 -> 36.7, 32576 points 23.2 -> 22.5.
 constexpr int kPairThreads = 512;
 constexpr int kPairs = kPairThreads / 128;        // tiles a workgroup works on
 
@@ -454,13 +456,14 @@ __device__ __forceinline__ ColorPoint load_point(const ColorArgs& a, int64_t til
     return p;
 }
 
-// activations, gradients of the second and the last matrix
+// activations, gradients of the second and the last matrix (in N[0], see outer_accumulate4)
 __device__ __forceinline__ void color_upper_layers(const ColorArgs& a, const ColorWeights<true, 2>& w, unsigned char* mem, int slot, int lane,
-                                                   v16f (*G2)[2], v4f* G3) {
+                                                   v16f (*G2)[2], v4f* N) {
     const int j = lane & 31, h = lane >> 5;
     float* Xt = reinterpret_cast<float*>(mem);
     float* Zt = Xt + 32 * kLd64;
-    static_assert((32 * kLd64 + 32 * kLd16) * 4 <= kTilesPerWave * kBlockTile, "fp32 tiles fit the wave's memory");
+    v4f G3[2] = {N[0], N[1]};
+    static_assert((32 * kLd64 + 32 * 4) * 4 <= kTilesPerWave * kBlockTile, "fp32 tiles fit the wave's memory");
     const int64_t tiles = (a.n + 31) / 32;
     const int64_t stride = (int64_t)gridDim.x * kPairs;
     for (int64_t tile = (int64_t)blockIdx.x * kPairs + slot; tile < tiles; tile += stride) {
@@ -481,16 +484,17 @@ __device__ __forceinline__ void color_upper_layers(const ColorArgs& a, const Col
         matvec_split<2, 4, 2, 2>(w.W2f, p1, a2, lane);
         apply_mask<2>(a2, p.m2);
         wave_lds_fence();
-        stage16<kLd16>(Zt, p.d3[0], j, h);
+        if (h == 0) *reinterpret_cast<float4*>(Zt + 4 * j) = make_float4(p.d3[0][0], p.d3[0][1], p.d3[0][2], 0.f);
         stage<2, kLd64>(Xt, a2, j, h);
         wave_lds_fence();
-        outer_accumulate16<2, kLd16, kLd64>(G3, Zt, Xt, lane);
+        outer_accumulate4<kLd64>(G3, Zt, Xt, lane);
         split(p.d3, p3);
         matvec_split<2, 1, 2, 2>(w.W3t, p3, d2, lane);
         apply_mask<2>(d2, again(p.m2));
         split(d2, pd);
         outer_accumulate_points<2, 2>(G2, pd, p1, mem, lane);
     }
+    N[0] = G3[0] + G3[1];
 }
 
 // adjoints, gradient of the first matrix: columns 0..31 in G1, 32..39 in G1n by blocks of 16 rows
@@ -620,7 +624,7 @@ __global__ __launch_bounds__(kPairThreads) void color_bwd_pair_kernel(ColorArgs 
             atomicAdd(a.dW[1] + e, block_element_points<kPairs, kVecs, 2>(scratch, 4, e >> 6, e & 63));
         } else if (x < kOf1 + kOf2 + kOf3) {
             const int e = x - kOf1 - kOf2;
-            atomicAdd(a.dW[2] + e, block_element16<kPairs, kVecs>(scratch, 3, e >> 6, e & 63));
+            atomicAdd(a.dW[2] + e, block_total<kPairs, kVecs>(scratch, 3, e >> 6, e & 63));       // row: register, column: lane
         }
     }
 }

@@ -761,6 +761,25 @@ __device__ __forceinline__ void outer_accumulate16(v4f* G, const float* __restri
     }
 }
 
+// The same for a factor of four columns (the three colour adjoints and a zero) on v_mfma_f32_4x4x1_f32, sixteen products of 4x4
+// at once: one point an instruction, lane l's block l / 4 holds the four adjoints against neurons 4 (l / 4) .. + 3, so no row
+// is padding, 32 instructions of 8 clocks a tile instead of 32 of 32.  Zt: [32 points][4], Xt: [32 points][LDX] floats.
+//   D(4x4) += A(4x1) B(1x4) in each block; lane l holds A[l%4], B[l%4] of block l/4, register v of lane l D[v][l%4]
+// G[v] of lane l accumulates row v, column l of Z^T X; even and odd points apart (two chains).
+template <int LDX>
+__device__ __forceinline__ void outer_accumulate4(v4f (&G)[2], const float* __restrict__ Zt, const float* __restrict__ Xt, int lane) {
+    const float* z = Zt + (lane & 3);
+    const float* x = Xt + lane;
+#pragma unroll
+    for (int s = 0; s < 4; ++s) {
+        float a[8], b[8];
+#pragma unroll
+        for (int p = 0; p < 8; ++p) { a[p] = z[(8 * s + p) * 4]; b[p] = x[(8 * s + p) * LDX]; }
+#pragma unroll
+        for (int p = 0; p < 8; ++p) G[p & 1] = __builtin_amdgcn_mfma_f32_4x4x1f32(a[p], b[p], G[p & 1], 0, 0, 0);
+    }
+}
+
 // The end of a kernel that accumulates V register vectors (weight gradients) in each of its WAVES waves: every wave
 // writes its vectors to LDS (block_store, one barrier by the caller), then any thread reads the block's sum of one
 // element (block_total) and adds it to global memory.  The threads walk over the gradient in its own memory order, so
