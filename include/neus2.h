@@ -13,9 +13,9 @@
  *    enqueue work; they never synchronise.
  *  - Arithmetic: fp32 throughout.  The matrix products of the two networks take their fp32
  *    factors as sums of bf16 or fp16 terms on the 16-bit matrix cores with fp32 accumulation.
- *    What decides a ReLU mask: three bf16 terms, six term products; the other forward outputs:
- *    two fp16 terms, scaled by powers of two, three term products; both as accurate as an fp32
- *    product (about 2e-7 relative on the outputs).  Two bf16 terms (three term products) in the
+ *    Forward passes: three bf16 terms, six term products; where a call is not asked for the ReLU
+ *    masks, what decides none of them takes two fp16 terms, scaled by powers of two, three term
+ *    products; both as accurate as an fp32 product (about 2e-7 relative on the outputs).  Two bf16 terms (three term products) in the
  *    adjoint sweeps and weight gradients (about 1e-5 relative on the gradients).
  *  - n is the number of sample points; for ray workloads n = rays * samples_per_ray and a
  *    ray's samples are consecutive.

@@ -272,14 +272,17 @@ __device__ __forceinline__ void half_pair(float x0, float x1, float s, uint32_t 
     word[1] = __builtin_bit_cast(uint32_t, lo);
 }
 
-// two values as a word of each of two bf16 terms
-__device__ __forceinline__ void bf16_pair(float x0, float x1, uint32_t (&word)[2]) {
+// two values as a word of each of P bf16 terms
+template <int P>
+__device__ __forceinline__ void bf16_pair(float x0, float x1, uint32_t (&word)[P]) {
     typedef __bf16 bf2 __attribute__((ext_vector_type(2)));
     typedef float f2 __attribute__((ext_vector_type(2)));
-    word[0] = __builtin_bit_cast(uint32_t, __builtin_convertvector(f2{x0, x1}, bf2));
-    x0 -= __builtin_bit_cast(float, word[0] << 16);
-    x1 -= __builtin_bit_cast(float, word[0] & 0xffff0000u);
-    word[1] = __builtin_bit_cast(uint32_t, __builtin_convertvector(f2{x0, x1}, bf2));
+#pragma unroll
+    for (int term = 0; term < P; ++term) {
+        word[term] = __builtin_bit_cast(uint32_t, __builtin_convertvector(f2{x0, x1}, bf2));
+        x0 -= __builtin_bit_cast(float, word[term] << 16);
+        x1 -= __builtin_bit_cast(float, word[term] & 0xffff0000u);
+    }
 }
 
 // zero (opaque) keeps the compiler at one instruction per element and term: scale, subtract and round in a mixed-precision
@@ -698,6 +701,22 @@ __device__ __forceinline__ void matvec_half(const unsigned char* __restrict__ W,
     }
 #pragma unroll
     for (int mb = 0; mb < MB; ++mb) z[mb] = acc[mb];
+}
+
+// One spelling for kernels that exist with either kind of terms: returns k (0 of bf16 terms); 64 inputs
+__device__ __forceinline__ int split_scaled(const v16f* v, Split<2, 3>& out) { split(v, out); return 0; }
+__device__ __forceinline__ int split_scaled(const v16f* v, HalfSplit<2>& out) {
+    const int k = half_exponent<2>(v);
+    half_split(v, k, out);
+    return k;
+}
+template <int MB>
+__device__ __forceinline__ void matvec_scaled(const unsigned char* __restrict__ W, const Split<2, 3>& x, v16f* z, int lane) {
+    matvec_split<MB, 4, 3, 3>(W, x, z, lane);
+}
+template <int MB>
+__device__ __forceinline__ void matvec_scaled(const unsigned char* __restrict__ W, const HalfSplit<2>& x, v16f* z, int lane) {
+    matvec_half<MB, 4>(W, x, z, lane);
 }
 
 // Largest magnitude of COUNT matrices over a workgroup of WAVES waves, each thread bringing its own part: one barrier.

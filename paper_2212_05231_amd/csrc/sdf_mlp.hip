@@ -45,16 +45,16 @@ __device__ __forceinline__ int64_t mask_word(int layer, int64_t n, int64_t i, in
 // factor and six products: as accurate as fp32 arithmetic, and the same arithmetic in both
 // kernels, so the ReLU masks agree.  The adjoint, S and t sweeps of the backward kernel use
 // two terms and three products.
-// HLf, H1t, H2t of the forward kernel, which decide no mask, are fp16 terms, scaled (matvec_half).
+// HALF (a forward pass that is not asked for the masks): HLf, H1t, H2t, which decide none, are fp16 terms, scaled (matvec_half).
 // PF: terms of the matrices of the forward direction.
-template <int D, int K, bool BWD, int PF = 3>
+template <int D, int K, bool BWD, int PF = 3, bool HALF = false>
 struct SdfWeights {
-    static constexpr int KS1 = D / 16;
+    static constexpr int KS1 = D / 16, P = BWD || HALF ? 2 : 3;
     typedef SplitMatrix<KS1, PF> M1f;              // [64][D]
     typedef SplitMatrix<4, PF> M2f;                // [64][64]
-    typedef SplitMatrix<4, 2> MLf;                 // last matrix [16 -> 32][64]
-    typedef SplitMatrix<4, 2> M1t;                 // [D -> 32][64]
-    typedef SplitMatrix<4, 2> M2t;
+    typedef SplitMatrix<4, P> MLf;                 // last matrix [16 -> 32][64]
+    typedef SplitMatrix<4, P> M1t;                 // [D -> 32][64]
+    typedef SplitMatrix<4, P> M2t;
     typedef SplitMatrix<1, 2> MLt;                 // [64][16]
     alignas(16) unsigned char H1f[64 * M1f::kLd];
     alignas(16) unsigned char H1t[32 * M1t::kLd];
@@ -63,17 +63,17 @@ struct SdfWeights {
     alignas(16) unsigned char HLf[BWD ? 16 : 32 * MLf::kLd];
     alignas(16) unsigned char HLt[BWD ? 64 * MLt::kLd : 16];
     // Row 0 of the last matrix (the SDF output), already split and packed as a lane holds it
-    // (Split<2, 2>, forward HalfSplit<2>): [lane half][term][word 8 b + p]
-    alignas(16) uint32_t HLrow0[2][2][16];
-    alignas(16) float part[BWD ? 4 : 3 * 16];      // forward: sixteen waves
+    // (Split<2, P> or HalfSplit<2>): [lane half][term][word 8 b + p]
+    alignas(16) uint32_t HLrow0[2][P][16];
+    alignas(16) float part[HALF ? 3 * 16 : 4];     // sixteen waves
 };
 
 // Every matrix is fetched from global memory before the first is written to LDS, so the fetches
 // are in flight together; the copies cover every slot a product reads, so nothing is cleared.
-// exponent (forward): H1, H2 and the last matrix are 2^exponent times theirs where they are fp16 terms.
-template <int D, int K, bool BWD, int THREADS, int PF = 3>
-__device__ void load_weights(SdfWeights<D, K, BWD, PF>& w, const SdfArgs& a, int (&exponent)[3]) {
-    typedef SdfWeights<D, K, BWD, PF> W;
+// exponent (HALF): H1, H2 and the last matrix are 2^exponent times theirs where they are fp16 terms.
+template <int D, int K, bool BWD, int THREADS, int PF = 3, bool HALF = false>
+__device__ void load_weights(SdfWeights<D, K, BWD, PF, HALF>& w, const SdfArgs& a, int (&exponent)[3]) {
+    typedef SdfWeights<D, K, BWD, PF, HALF> W;
     const int tid = threadIdx.x;
     const float* __restrict__ H1 = a.H[0];
     const float* __restrict__ H2 = a.H[1];
@@ -98,7 +98,7 @@ __device__ void load_weights(SdfWeights<D, K, BWD, PF>& w, const SdfArgs& a, int
         row0[0] = HL[32 * b + neuron_of(2 * p, hh)];
         row0[1] = HL[32 * b + neuron_of(2 * p + 1, hh)];
     }
-    if constexpr (!BWD) {
+    if constexpr (HALF) {
         float largest[3] = {f1.largest(tid), K == 3 ? f2.largest(tid) : 0.f, fl.largest(tid)};
         workgroup_exponents<3, THREADS / 64>(largest, w.part, exponent);
         t1.store_half(w.H1t, tid, exponent[0]);
@@ -107,16 +107,17 @@ __device__ void load_weights(SdfWeights<D, K, BWD, PF>& w, const SdfArgs& a, int
     } else {
         t1.store(w.H1t, tid);
         t2.store(w.H2t, tid);
+        fl.store(w.HLf, tid);
         tl.store(w.HLt, tid);
     }
     f1.store(w.H1f, tid);
     f2.store(w.H2f, tid);
     if (tid < 32) {
-        uint32_t word[2];
-        if constexpr (BWD) bf16_pair(row0[0], row0[1], word);
-        else half_pair(row0[0], row0[1], __builtin_amdgcn_ldexpf(1.f, exponent[2]), word);
-        w.HLrow0[tid >> 4][0][tid & 15] = word[0];
-        w.HLrow0[tid >> 4][1][tid & 15] = word[1];
+        uint32_t word[W::P];
+        if constexpr (HALF) half_pair(row0[0], row0[1], __builtin_amdgcn_ldexpf(1.f, exponent[2]), word);
+        else bf16_pair<W::P>(row0[0], row0[1], word);
+#pragma unroll
+        for (int term = 0; term < W::P; ++term) w.HLrow0[tid >> 4][term][tid & 15] = word[term];
     }
     __syncthreads();
 }
@@ -265,8 +266,8 @@ __device__ __forceinline__ v16f apply_jac_regs(const JacRegs<D>& J, const float 
 // terms were split when the matrix was copied to LDS, and masking a packed pair is an AND with a
 // word that has ones in the halves whose mask bit is set (bit 16 b + r for register r of block b;
 // word p holds registers 2p and 2p + 1).  The same values as splitting the masked row.
-template <class Vector>                        // Split<2, 2> or HalfSplit<2>
-__device__ __forceinline__ void last_row_masked(const uint32_t (*row0)[2][16], uint32_t m, int h, Vector& out) {
+template <int P, class Vector>                 // Split<2, P> or HalfSplit<2>
+__device__ __forceinline__ void last_row_masked(const uint32_t (*row0)[P][16], uint32_t m, int h, Vector& out) {
     const uint32_t one = opaque<1u>();
     uint32_t keep[16];
 #pragma unroll
@@ -276,7 +277,7 @@ __device__ __forceinline__ void last_row_masked(const uint32_t (*row0)[2][16], u
         keep[k] = (lo & 0xffffu) | (hi & 0xffff0000u);
     }
 #pragma unroll
-    for (int term = 0; term < 2; ++term)
+    for (int term = 0; term < P; ++term)
 #pragma unroll
         for (int g = 0; g < 4; ++g) {
             const u32x4 words = *reinterpret_cast<const u32x4*>(&row0[h][term][4 * g]);
@@ -309,10 +310,11 @@ __device__ __forceinline__ void store_rows16(float* __restrict__ dst, int64_t i,
 // SIMD with 128 registers each, so that one wavefront's waits for memory, LDS and matrix results are filled by the others.
 // Nothing is requested ahead: two wavefronts per SIMD that prefetched the next encoding and this tile's Jacobian (221
 // registers) took 60 us at 2^18 points and 199 at 2^20, four took 51 and 168, at 32576 points 15.7 and 12.8.
-// The last layer and the reverse sweep, which decide no mask, take scaled fp16 terms, 48 instead of 96 matrix instructions: 2^18
-// points 45.4 -> 43.4 us, 2^20 points 177 -> 171 (another box than above; its streams of 732 bytes a point are 4.5 TB/s), 131072
-// points 26.3 -> 24.8.  The first layer leaves out the k-step of levels that are not read.  (fp16 terms in every layer: 41 and
-// 167, but then other masks than the kernels without given masks work out, or theirs would have to change as well.)
+// Asked for no masks (rendering), the last layer and the reverse sweep, which decide none, take scaled fp16 terms, 48 instead of 96
+// matrix instructions: 2^18 points 45.4 -> 43.4 us, 2^20 points 177 -> 171 (another box than above; its streams of 732 bytes a
+// point are 4.5 TB/s), 131072 points 26.3 -> 24.8.  Not in a training step: d and the normal are inputs of the colour network,
+// where another last bit decides one ReLU mask in 10^7 the other way.  The first layer leaves out the k-step of levels that are
+// not read.
 constexpr int kFwdThreads = 1024;
 constexpr int kFwdWaves = kFwdThreads / 64;
 constexpr int kValueThreads = 512;
@@ -434,13 +436,16 @@ __device__ __forceinline__ v16f apply_jac_tile(const float* __restrict__ jac, in
     return t;
 }
 
-// G: groups of four levels that are read (those with an active one); WIDE: from kTileMaxPoints points on
-template <int D, int K, int G, bool WIDE>
+// G: groups of four levels that are read (those with an active one); WIDE: from kTileMaxPoints points on; MASKS: writes the ReLU
+// masks
+template <int D, int K, int G, bool WIDE, bool MASKS>
 __global__ __launch_bounds__(kFwdThreads) void sdf_fwd_kernel(SdfArgs a) {
-    __shared__ SdfWeights<D, K, false> w;
-    int kw[3];
-    load_weights<D, K, false, kFwdThreads>(w, a, kw);
-    constexpr int KS1 = SdfWeights<D, K, false>::KS1;
+    typedef SdfWeights<D, K, false, 3, !MASKS> W;
+    typedef std::conditional_t<MASKS, Split<2, 3>, HalfSplit<2>> Vector;
+    __shared__ W w;
+    int kw[3] = {0, 0, 0};
+    load_weights<D, K, false, kFwdThreads, 3, !MASKS>(w, a, kw);
+    constexpr int KS1 = W::KS1;
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);   // the same for all lanes: keeps tile indices and addresses scalar
     const int j = lane & 31, h = lane >> 5;
@@ -452,7 +457,7 @@ __global__ __launch_bounds__(kFwdThreads) void sdf_fwd_kernel(SdfArgs a) {
         v16f x0[1] = {load_levels_tile<8 * G, WIDE>(a.enc, a.n, tile * 32, a.active_levels, j, h)};
         v16f a1[2], yv[1];
         Split<1, 3> px;
-        HalfSplit<2> pv;
+        Vector pv;
         split(x0, px);
         matvec_split<2, (8 * G + 15) / 16, 3, 3, KS1>(w.H1f, px, a1, lane);
         const uint32_t m1 = relu_mask<2>(a1);
@@ -463,18 +468,17 @@ __global__ __launch_bounds__(kFwdThreads) void sdf_fwd_kernel(SdfArgs a) {
             matvec_split<2, 4, 3, 3>(w.H2f, p1, a1, lane);
             m_last = relu_mask<2>(a1);
         }
-        // from here on no mask depends on the values: fp16 terms, the vector times 2^k
-        int k = half_exponent<2>(a1);
-        half_split(a1, k, pv);
-        matvec_half<1, 4>(w.HLf, pv, yv, lane);
+        // from here on no mask of this network depends on the values: fp16 terms, the vector times 2^k (k = 0 with masks)
+        int k = split_scaled(a1, pv);
+        matvec_scaled<1>(w.HLf, pv, yv, lane);
         if (valid) {
             float4* row = lane_address(reinterpret_cast<float4*>(a.y) + tile * 128, 64u * j + 16u * h);
             float y[8];
 #pragma unroll
-            for (int r = 0; r < 8; ++r) y[r] = __builtin_amdgcn_ldexpf(yv[0][r], -(k + kw[2]));
+            for (int r = 0; r < 8; ++r) y[r] = MASKS ? yv[0][r] : __builtin_amdgcn_ldexpf(yv[0][r], -(k + kw[2]));
             row[0] = make_float4(y[0], y[1], y[2], y[3]);
             row[2] = make_float4(y[4], y[5], y[6], y[7]);
-            if (a.masks) {
+            if (MASKS) {
                 uint32_t* words = a.masks + tile * 64;
                 *lane_address(words, 8u * j + 4u * h) = m1;
                 if (K == 3) *lane_address(words + 2 * a.n, 8u * j + 4u * h) = m_last;
@@ -485,16 +489,17 @@ __global__ __launch_bounds__(kFwdThreads) void sdf_fwd_kernel(SdfArgs a) {
         last_row_masked(w.HLrow0, m_last, h, pv);
         int e = kw[2] + kw[0];
         if (K == 3) {
-            matvec_half<2, 4>(w.H2t, pv, s1, lane);
+            matvec_scaled<2>(w.H2t, pv, s1, lane);
             apply_mask<2>(s1, m1);
-            k = half_exponent<2>(s1);
-            half_split(s1, k, pv);
+            k = split_scaled(s1, pv);
             e += kw[1] + k;
         }
         v16f qv[1];
-        matvec_half<1, 4>(w.H1t, pv, qv, lane);
+        matvec_scaled<1>(w.H1t, pv, qv, lane);
+        if (!MASKS) {
 #pragma unroll
-        for (int r = 0; r < D / 2; ++r) qv[0][r] = __builtin_amdgcn_ldexpf(qv[0][r], -e);
+            for (int r = 0; r < D / 2; ++r) qv[0][r] = __builtin_amdgcn_ldexpf(qv[0][r], -e);
+        }
         // dd/de is read next by the scatter-add, four kernels later: for a batch whose per-point arrays
         // exceed the caches it is written with non-temporal stores (25 us of the step at 2^20 points; at
         // 2^18 points the cached store is the faster one)
@@ -1002,12 +1007,12 @@ typedef void (*SdfKernel)(SdfArgs);
 // one variant for all, levels that the training step leaves unwritten were fetched (half of the levels active, 2^20 points,
 // forward and backward: 169 and 251 us, now 155 and 243); picking level 0 for them in scalar registers, or a branch round
 // every load, cost up to 6 % forward and 8 % backward with all levels active.
-template <int D, int K>
+template <int D, int K, bool MASKS>
 SdfKernel fwd_kernel(const SdfArgs& a) {
-    if (a.n >= kTileMaxPoints) return sdf_fwd_kernel<D, K, D / 8, true>;
-    if (a.active_levels <= 4) return sdf_fwd_kernel<D, K, 1, false>;
-    if (D == 16 || a.active_levels <= 8) return sdf_fwd_kernel<D, K, 2, false>;
-    return a.active_levels <= 12 ? sdf_fwd_kernel<D, K, D == 32 ? 3 : 2, false> : sdf_fwd_kernel<D, K, D / 8, false>;
+    if (a.n >= kTileMaxPoints) return sdf_fwd_kernel<D, K, D / 8, true, MASKS>;
+    if (a.active_levels <= 4) return sdf_fwd_kernel<D, K, 1, false, MASKS>;
+    if (D == 16 || a.active_levels <= 8) return sdf_fwd_kernel<D, K, 2, false, MASKS>;
+    return a.active_levels <= 12 ? sdf_fwd_kernel<D, K, D == 32 ? 3 : 2, false, MASKS> : sdf_fwd_kernel<D, K, D / 8, false, MASKS>;
 }
 
 template <int D, int K>
@@ -1021,7 +1026,7 @@ SdfKernel bwd_kernel(const SdfArgs& a) {
 template <int D, int K>
 int run_fwd(const SdfArgs& a, hipStream_t st) {
     const int64_t tiles = (a.n + 31) / 32;
-    const SdfKernel kernel = fwd_kernel<D, K>(a);
+    const SdfKernel kernel = a.masks ? fwd_kernel<D, K, true>(a) : fwd_kernel<D, K, false>(a);
     const int blocks = persistent_blocks((const void*)kernel, kFwdThreads, tiles);
     hipLaunchKernelGGL(kernel, dim3(blocks), dim3(kFwdThreads), 0, st, a);
     return check_launch("sdf forward");
