@@ -386,3 +386,60 @@ def test_colour_forward_without_masks(n, size_y, size_w):
     assert rel(got, want) <= 1e-6
     assert np.ptp(want) > 1e-3 if size_y else np.all(got == 0.5)
     assert torch.all(torch.signbit(behind)) and torch.all(behind == 0)
+
+
+def runs_of_one_cell(n, res, rng):
+    """Positions in runs of 1 to 40 neighbours that share a cell of a grid of `res` cells, as marched samples do."""
+    lengths = rng.integers(1, 41, size=n)
+    cell = np.repeat(rng.integers(0, res, size=(n, 3)), lengths, axis=0)[:n]
+    return ((cell + rng.uniform(0.05, 0.95, size=(n, 3))) / res).astype(np.float32)
+
+
+@pytest.mark.parametrize("n,log2_t,res,broken", [(65536, 15, [16, 30], False),      # in place: one range, and three point lists
+                                                 (65537, 14, [16, 22], True),         # in place: one and two ranges
+                                                 (70001, 19, [33, 70, 300], False),   # point lists, a hashed level of 64 ranges
+                                                 (66000, 13, [16, 64], False),        # a hashed level of one range: cells may share slots
+                                                 (524288 + 77, 21, [40, 900], False)])  # 256 ranges: 1024 points a binning workgroup
+def test_scatter_add_of_runs_in_one_cell(n, log2_t, res, broken):
+    """Runs of samples in one cell are summed before they reach the table; lists against 64-bit sums of the corner values.
+    Sums in doubles, one rounding to binary32 on a dense level (1e-6), 2^-18 of a record's largest value on a hashed one with lists (1e-5).
+    A non-finite adjoint reaches its own cell's entries and no others."""
+    import dataclasses
+    rng = np.random.default_rng(n)
+    dense = wl.dense_flags(res, 1 << log2_t)
+    levels = len(res)
+    cfg = dataclasses.replace(wl.make_config(2), log2_table_size=log2_t, res=res + [4] * (16 - levels), dense=dense + [1] * (16 - levels),
+                              active_levels=levels)
+    c = nb.make_config(cfg)
+    pos = runs_of_one_cell(n, res[0], rng)
+    gen = torch.Generator(device="cuda").manual_seed(n)
+    q, d_enc = (torch.randn(16, n, 2, device="cuda", generator=gen) for _ in range(2))
+    d_normal = torch.randn(n, 3, device="cuda", generator=gen) * 0.05
+    if broken:
+        d_enc[0, 1000, 1], d_enc[1, 2000, 0] = float("nan"), float("inf")
+    tables = torch.zeros(16, 1 << log2_t, 2, device="cuda", dtype=torch.float16)
+    d_tables, behind = guarded((16, 1 << log2_t, 2))
+    ws = torch.zeros(nb.workspace_bytes(c, n) // 4, dtype=torch.int32, device="cuda")
+    nb.hash_scatter_bwd(c, cuda(pos), tables, q, d_enc, d_normal, n, d_tables, workspace=ws)
+    assert bool(ws.any())
+    q, d_enc, d_normal = (t.cpu().numpy().astype(np.float64) for t in (q, d_enc, d_normal))
+    for level in range(levels):
+        p = o.grid_coords(pos, res[level])
+        cell = np.minimum(np.floor(p), res[level] - 1)
+        w = p - cell
+        want = np.zeros((1 << log2_t, 2))
+        for k in range(8):
+            f = [w[:, a] if (k >> a) & 1 else 1 - w[:, a] for a in range(3)]
+            s = [res[level] if (k >> a) & 1 else -res[level] for a in range(3)]
+            slope = s[0] * f[1] * f[2] * d_normal[:, 0] + f[0] * s[1] * f[2] * d_normal[:, 1] + f[0] * f[1] * s[2] * d_normal[:, 2]
+            value = (f[0] * f[1] * f[2])[:, None] * d_enc[level] + q[level] * slope[:, None]
+            corner = np.stack([cell[:, a] + ((k >> a) & 1) for a in range(3)], axis=1)
+            slot = o.vertex_index(corner, res[level], dense[level], 1 << log2_t)
+            for x in range(2):
+                want[:, x] += np.bincount(slot, weights=value[:, x], minlength=1 << log2_t)
+        got = d_tables[level].cpu().numpy().astype(np.float64)
+        finite = np.isfinite(want)
+        assert np.array_equal(finite, np.isfinite(got)) and int((~finite).sum()) == (8 if broken else 0)
+        tol = 1e-6 if dense[level] or (1 << log2_t) <= 8192 else 1e-5
+        assert rel(got[finite], want[finite]) <= tol, level
+    assert torch.all(torch.signbit(behind)) and torch.all(behind == 0)
