@@ -554,7 +554,7 @@ struct OwnerPlan {
 //   b: m0 0..17 | m1 low 14 bits 18..31
 //   c: m1 high 4 bits 0..3 | m2 4..21 | m3 high 10 bits 22..31
 // E = 127 marks a record whose values were not finite (or beyond 2^30): it decodes to NaN, so that a
-// broken gradient stays visible.  Magnitudes below 2^-96 are written as zero.
+// broken gradient stays visible.  Where all four are below 2^-96 they keep 2^-113 absolute.
 struct __attribute__((packed, aligned(4))) RowRecord {
     uint32_t a, b, c;
 };
@@ -566,30 +566,30 @@ constexpr uint32_t kCodeNext = 15u, kCodeSame = 14u;
 __device__ __forceinline__ int sext(uint32_t x, int off, int len) { return (int32_t)(x << (32 - off - len)) >> (32 - len); }
 
 __device__ __forceinline__ RowRecord pack_row(uint32_t slot, uint32_t code, const float4& v) {
-    const float big = fmaxf(fmaxf(fabsf(v.x), fabsf(v.y)), fmaxf(fabsf(v.z), fabsf(v.w)));   // NaN if any is
-    int e = __builtin_amdgcn_frexp_expf(big);      // big = f 2^e, 0.5 <= f < 1; 0 for big = 0
-    int E = e + kRecBias;
-    int m[4] = {0, 0, 0, 0};
-    if (!(big <= 1.0e9f)) {
-        E = 127;
-    } else if (E < 0 || big == 0.f) {
-        E = 0;
-    } else {
-        // in * 2^(17-e) rounded to nearest even, as the low bits of a float: adding 1.5 * 2^23 leaves
-        // the integer in the mantissa (two's complement in the low 18 bits); |in| < 2^e, so the only value
-        // out of range is +2^17 (a magnitude just below 2^e rounding up), which the unsigned minimum on
-        // the bit pattern (positive floats order like their patterns) brings back to 2^17 - 1.
-        const float in[4] = {v.x, v.y, v.z, v.w};
-        const float scale = __builtin_bit_cast(float, (uint32_t)(127 + kRecMant - e) << 23);
-        constexpr float kRound = 12582912.0f;                     // 1.5 * 2^23, pattern 0x4B400000
+    // The largest magnitude, as a bit pattern: magnitudes order like integers, and a NaN is larger than all of them (a
+    // floating-point maximum would leave it out).  All of it without a branch: the moves that merged the ways were a tenth of
+    // the kernel's vector instructions.
+    const float in[4] = {v.x, v.y, v.z, v.w};
+    uint32_t size[4];
 #pragma unroll
-        for (int k = 0; k < 4; ++k)
-            m[k] = (int)min(__builtin_bit_cast(uint32_t, fmaf(in[k], scale, kRound)), 0x4B400000u + ((1u << kRecMant) - 1u));
-    }
+    for (int k = 0; k < 4; ++k) size[k] = __builtin_bit_cast(uint32_t, in[k]) & 0x7FFFFFFFu;
+    const uint32_t big = max(max(size[0], size[1]), max(size[2], size[3]));
+    const int e = max(__builtin_amdgcn_frexp_expf(__builtin_bit_cast(float, big)), -kRecBias);      // 0 for 0, infinity and NaN
+    // in * 2^(17-e) rounded to nearest even, as the low bits of a float: adding 1.5 * 2^23 leaves
+    // the integer in the mantissa (two's complement in the low 18 bits); |in| < 2^e, so the only value
+    // out of range is +2^17 (a magnitude just below 2^e rounding up), which the unsigned minimum on
+    // the bit pattern (positive floats order like their patterns) brings back to 2^17 - 1.
+    const float scale = __builtin_bit_cast(float, (uint32_t)(127 + kRecMant - e) << 23);
+    constexpr float kRound = 12582912.0f;                     // 1.5 * 2^23, pattern 0x4B400000
+    uint32_t m[4];
+#pragma unroll
+    for (int k = 0; k < 4; ++k)
+        m[k] = min(__builtin_bit_cast(uint32_t, fmaf(in[k], scale, kRound)), 0x4B400000u + ((1u << kRecMant) - 1u));
+    const uint32_t E = big <= __builtin_bit_cast(uint32_t, 1.0e9f) ? (uint32_t)(e + kRecBias) : 127u;
     RowRecord r;
-    r.a = slot | (code << 13) | ((uint32_t)E << 17) | (((uint32_t)m[3] & 0xFFu) << 24);
-    r.b = ((uint32_t)m[0] & 0x3FFFFu) | (((uint32_t)m[1] & 0x3FFFu) << 18);
-    r.c = (((uint32_t)m[1] >> 14) & 0xFu) | (((uint32_t)m[2] & 0x3FFFFu) << 4) | ((((uint32_t)m[3] >> 8) & 0x3FFu) << 22);
+    r.a = slot | (code << 13) | (E << 17) | (m[3] << 24);
+    r.b = (m[0] & 0x3FFFFu) | (m[1] << 18);
+    r.c = ((m[1] >> 14) & 0xFu) | ((m[2] & 0x3FFFFu) << 4) | ((m[3] >> 8) << 22);
     return r;
 }
 
@@ -646,18 +646,55 @@ struct Records {
 
 // Records of one workgroup are first put in LDS in list order (range by range), then written
 // out by consecutive threads: runs of records of one list leave as whole cache lines instead
-// of one 16-byte piece per lane.
-constexpr int kBinThreads = 512;
-constexpr int kBinRecords = 4 * kBinThreads;
+// of one 12-byte piece per lane.
+// What bounds it: with the stores left out 125 of 254 us (2^20 points, ten levels of 256 ranges), with runs that lie end to end
+// 167: half of the time is the scattered runs.  So a batch whose runs would be short (512 points, more than kWideBinRanges
+// ranges: less than 16 records of 12 bytes, a cache line and a half) takes 1024 points a workgroup: 289 -> 237 us there.  With
+// longer runs smaller workgroups are the better ones (2^18 points, 64 ranges: 47 and 50 us).  The arithmetic runs at eight
+// wavefronts per SIMD, which 64 registers allow since the values are worked out after the places and packed without branches
+// (72 registers, three workgroups a compute unit: 2^18 points 67 us, with the levels' order as below).
+// Every workgroup starts at another level, and those of the point lists alternate between theirs: with all of them at the same
+// level their reservations queue up at a few cache lines, which take one atomic in 12 ns (2^18 points, 512 workgroups, ten levels:
+// 67 -> 55 us; four levels of point lists at 2^20 points 88 -> 72).
+constexpr int kWideBinRanges = 128;
 constexpr uint32_t kNoRecord = 0xFFFFFFFFu;
 
-template <typename Rec>
+// A staged record with its place in the entry's lists (kNoRecord if it went elsewhere) is written and read 16 bytes at a time
+// (a wide one 16 and 8): word by word its four writes to places all over the tile took 40 % of the kernel's LDS time.
+template <typename Rec, int RECORDS>
+struct Staged;
+template <int RECORDS>
+struct Staged<RowRecord, RECORDS> {
+    uint4 at[RECORDS];
+    __device__ __forceinline__ void put(int k, const RowRecord& r, uint32_t dest) { at[k] = make_uint4(r.a, r.b, r.c, dest); }
+    __device__ __forceinline__ uint32_t get(int k, RowRecord& r) const {
+        const uint4 w = at[k];
+        r = RowRecord{w.x, w.y, w.z};
+        return w.w;
+    }
+};
+template <int RECORDS>
+struct Staged<WideRecord, RECORDS> {
+    uint4 at[RECORDS];
+    uint2 rest[RECORDS];
+    __device__ __forceinline__ void put(int k, const WideRecord& r, uint32_t dest) {
+        at[k] = make_uint4(r.head, __float_as_uint(r.v[0]), __float_as_uint(r.v[1]), __float_as_uint(r.v[2]));
+        rest[k] = make_uint2(__float_as_uint(r.v[3]), dest);
+    }
+    __device__ __forceinline__ uint32_t get(int k, WideRecord& r) const {
+        const uint4 w = at[k];
+        const uint2 x = rest[k];
+        r.head = w.x;
+        r.v[0] = __uint_as_float(w.y); r.v[1] = __uint_as_float(w.z); r.v[2] = __uint_as_float(w.w); r.v[3] = __uint_as_float(x.x);
+        return x.y;
+    }
+};
+
+template <typename Rec, int THREADS>
 struct BinSmem {
-    uint32_t word[sizeof(Rec) / 4][kBinRecords];                  // the staged records, word by word
-    uint32_t dest[kBinRecords];          // record index within the entry's lists, kNoRecord if it went elsewhere
+    Staged<Rec, 4 * THREADS> staged;
     int cnt[kMaxRanges];                 // records of this workgroup per range
-    int base[kMaxRanges];                // first position of this workgroup in the list of the range
-    int first[kMaxRanges];               // first staged position of the range
+    int2 place[kMaxRanges];              // of a range: first staged position, first position of this workgroup in its list
     int total;
 };
 
@@ -681,15 +718,16 @@ __device__ __forceinline__ float2 corner_value(const Cell& c, int cr, const floa
 // corners (one or two for most points).  4 bytes per entry instead of 48 bytes of row records per
 // point, and the owner of a range no longer tests every point of the batch against its range.
 // A list that is full sends the point's corners in that range straight to the gradient.
+template <int THREADS>
 __device__ void bin_points(const GridDesc& g, const OwnerPlan& plan, const Records& rec, const float* __restrict__ pos,
                            const float* __restrict__ q, const float* __restrict__ d_enc,
-                           const float* __restrict__ d_normal, int64_t n, int point_blocks, int e,
+                           const float* __restrict__ d_normal, int64_t n, int point_block, int e,
                            float* __restrict__ d_tables, int* cnt, int* base) {
     const int level = plan.level[e];
     const int n_ranges = plan.ranges[e];
     const int capacity = plan.idx_capacity[e];
-    const int64_t i = (int64_t)(blockIdx.x % point_blocks) * kBinThreads + threadIdx.x;
-    for (int k = threadIdx.x; k < kMaxRanges; k += kBinThreads) cnt[k] = 0;
+    const int64_t i = (int64_t)point_block * THREADS + threadIdx.x;
+    for (int k = threadIdx.x; k < kMaxRanges; k += THREADS) cnt[k] = 0;
     __syncthreads();
     const bool valid = i < n;
     Cell c;
@@ -707,7 +745,7 @@ __device__ void bin_points(const GridDesc& g, const OwnerPlan& plan, const Recor
         }
     }
     __syncthreads();
-    for (int k = threadIdx.x; k < n_ranges; k += kBinThreads)
+    for (int k = threadIdx.x; k < n_ranges; k += THREADS)
         base[k] = cnt[k] ? atomicAdd(&rec.cursor[e * kMaxRanges + k], cnt[k]) : 0;
     __syncthreads();
     if (!valid) return;
@@ -735,44 +773,50 @@ __device__ void bin_points(const GridDesc& g, const OwnerPlan& plan, const Recor
     }
 }
 
-// A workgroup takes 512 points and walks over a share of the levels with row records (levels
-// grp, grp + level_groups, ...): position and dL/dn are fetched once, and the next level's dL/de and
+// A workgroup takes THREADS points and walks over a share of the levels with row records (levels
+// grp, grp + level_groups, ..., from another one on in every workgroup): position and dL/dn are fetched once, and the next level's dL/de and
 // dd/de are requested before the current level's records are made, so that only the first level of a
 // workgroup waits for memory.  Workgroups beyond the level groups handle the levels with point lists.
-template <typename Rec>
-__global__ __launch_bounds__(kBinThreads) void bin_rows_kernel(GridDesc g, OwnerPlan plan, Records rec,
+template <typename Rec, int THREADS>
+__global__ __launch_bounds__(THREADS, 8) void bin_rows_kernel(GridDesc g, OwnerPlan plan, Records rec,
                                                               const float* __restrict__ pos,
                                                               const float* __restrict__ q,
                                                               const float* __restrict__ d_enc,
                                                               const float* __restrict__ d_normal, int64_t n,
                                                               int point_blocks, int level_groups,
                                                               float* __restrict__ d_tables) {
-    __shared__ BinSmem<Rec> sm;
-    constexpr int kWords = sizeof(Rec) / 4;
-    const int grp = blockIdx.x / point_blocks;
-    if (grp >= level_groups) {                // uniform over the workgroup
-        bin_points(g, plan, rec, pos, q, d_enc, d_normal, n, point_blocks, plan.n_listed + grp - level_groups, d_tables, sm.cnt,
-                   sm.base);
+    __shared__ BinSmem<Rec, THREADS> sm;
+    const int row_blocks = point_blocks * level_groups;
+    const bool points = (int)blockIdx.x >= row_blocks;      // uniform over the workgroup
+    const int roles = points ? plan.n_indexed : level_groups, at = (int)blockIdx.x - (points ? row_blocks : 0);
+    const int grp = at % roles, point_block = at / roles;
+    if (points) {
+        bin_points<THREADS>(g, plan, rec, pos, q, d_enc, d_normal, n, point_block, plan.n_listed + grp, d_tables, sm.cnt, reinterpret_cast<int*>(sm.place));
         return;
     }
-    const int64_t i = (int64_t)(blockIdx.x % point_blocks) * kBinThreads + threadIdx.x;
+    const int turns = (plan.n_listed - grp + level_groups - 1) / level_groups;      // levels of this group
+    const int start = point_block % turns;
+    const int64_t i = (int64_t)point_block * THREADS + threadIdx.x;
     const bool valid = i < n;
     float px = 0.f, py = 0.f, pz = 0.f, dnx = 0.f, dny = 0.f, dnz = 0.f;
     float2 de_next = make_float2(0.f, 0.f), q_next = make_float2(0.f, 0.f);
     if (valid) {
         px = pos[3 * i + 0]; py = pos[3 * i + 1]; pz = pos[3 * i + 2];
         dnx = d_normal[3 * i + 0]; dny = d_normal[3 * i + 1]; dnz = d_normal[3 * i + 2];
-        const int64_t o = (int64_t)plan.level[grp] * n + i;
+        const int64_t o = (int64_t)plan.level[grp + level_groups * start] * n + i;
         de_next = reinterpret_cast<const float2*>(d_enc)[o];
         q_next = reinterpret_cast<const float2*>(q)[o];
     }
-    for (int e = grp; e < plan.n_listed; e += level_groups) {
+    for (int turn = 0, at_turn = start; turn < turns; ++turn) {
+        const int e = grp + level_groups * at_turn;
+        at_turn = at_turn + 1 < turns ? at_turn + 1 : 0;
+        const int e_next = grp + level_groups * at_turn;
         const int level = plan.level[e];
         const int n_ranges = plan.ranges[e];
         const int capacity = plan.capacity[e];
         const float2 de = de_next, qq = q_next;
-        if (valid && e + level_groups < plan.n_listed) {
-            const int64_t o = (int64_t)plan.level[e + level_groups] * n + i;
+        if (valid && turn + 1 < turns) {
+            const int64_t o = (int64_t)plan.level[e_next] * n + i;
             // last use of both arrays in the step: non-temporal loads
             typedef float f2v __attribute__((ext_vector_type(2)));
             const f2v a_ = __builtin_nontemporal_load(reinterpret_cast<const f2v*>(d_enc) + o);
@@ -780,68 +824,41 @@ __global__ __launch_bounds__(kBinThreads) void bin_rows_kernel(GridDesc g, Owner
             de_next = make_float2(a_.x, a_.y);
             q_next = make_float2(b_.x, b_.y);
         }
-        for (int k = threadIdx.x; k < kMaxRanges; k += kBinThreads) sm.cnt[k] = 0;
+        for (int k = threadIdx.x; k < kMaxRanges; k += THREADS) sm.cnt[k] = 0;
         __syncthreads();
 
-        uint32_t range[4];
-        Rec row_rec[4];
+        // Where the rows go first; their values when they are put in place, so that they hold no registers in between.
+        const int res = g.res[level];
+        const float fres = (float)res;
+        const bool dense = (g.dense_bits >> level) & 1u;
+        uint32_t s0[4];                           // slot of the row's first corner
+        uint32_t code = kCodeNext;                // how the second one follows
         int rank[4];
+        float w0 = 0.f, w1 = 0.f, w2 = 0.f;
         if (valid) {
-            const int res = g.res[level];
-            const float fres = (float)res;
-            const bool dense = (g.dense_bits >> level) & 1u;
             const uint32_t stride = (uint32_t)res + 1u;
             const float gx = grid_coord(px, fres), gy = grid_coord(py, fres), gz = grid_coord(pz, fres);
             const int cx = min((int)floorf(gx), res - 1);
             const int cy = min((int)floorf(gy), res - 1);
             const int cz = min((int)floorf(gz), res - 1);
-            const float w0 = gx - (float)cx, w1 = gy - (float)cy, w2 = gz - (float)cz;
-            const float nx = dnx * fres, ny = dny * fres, nz = dnz * fres;
+            w0 = gx - (float)cx; w1 = gy - (float)cy; w2 = gz - (float)cz;
             const uint32_t hy0 = (uint32_t)cy * kPrimeY, hz0 = (uint32_t)cz * kPrimeZ;
             // the trailing bits in which x and x + 1 differ: 2^(t+1) - 1, t = number of trailing ones of x
-            const uint32_t code_x = 31u - (uint32_t)__clz((int)((uint32_t)cx ^ ((uint32_t)cx + 1u)));
+            if (!dense) code = 31u - (uint32_t)__clz((int)((uint32_t)cx ^ ((uint32_t)cx + 1u)));
 #pragma unroll
             for (int row = 0; row < 4; ++row) {
                 const int dy = row & 1, dz = row >> 1;
-                const uint32_t rh = (hy0 + (dy ? kPrimeY : 0u)) ^ (hz0 + (dz ? kPrimeZ : 0u));
-                const float fy = dy ? w1 : 1.f - w1, fz = dz ? w2 : 1.f - w2;
-                const float sy = dy ? 1.f : -1.f, sz = dz ? 1.f : -1.f;
-                const float fyz = fy * fz;
-                const float dn_x = nx * fyz;
-                const float dn_yz = ny * (sy * fz) + nz * (fy * sz);
-                uint32_t s0, s1, code;
-                if (dense) {
-                    s0 = (uint32_t)cx + ((uint32_t)(cy + dy) + (uint32_t)(cz + dz) * stride) * stride;
-                    s1 = s0 + 1u;
-                    code = kCodeNext;
-                } else {
-                    s0 = ((uint32_t)cx ^ rh) & g.table_mask;
-                    s1 = ((uint32_t)(cx + 1) ^ rh) & g.table_mask;
-                    code = code_x;
-                }
-                const float f0 = 1.f - w0, f1 = w0;
-                const float dn0 = -dn_x + f0 * dn_yz, dn1 = dn_x + f1 * dn_yz;
-                const float wk0 = f0 * fyz, wk1 = f1 * fyz;
-                float4 val = make_float4(wk0 * de.x + qq.x * dn0, wk0 * de.y + qq.y * dn0, wk1 * de.x + qq.x * dn1, wk1 * de.y + qq.y * dn1);
-                range[row] = s0 >> kOwnerSlotBits;
-                // On a hashed level both corners share the range.  On a dense level the x+1 corner can be
-                // the first slot of the next range (1 row in 8192): it then goes straight to the gradient.
-                if ((s1 >> kOwnerSlotBits) != range[row]) {
-                    float* gt = d_tables + ((size_t)level * g.table_size + s1) * 2;
-                    atomicAdd(gt + 0, val.z);
-                    atomicAdd(gt + 1, val.w);
-                    val.z = 0.f; val.w = 0.f;
-                    code = kCodeSame;
-                }
-                make_record(row_rec[row], s0 & (kOwnerSlots - 1), code, val);
-                rank[row] = atomicAdd(&sm.cnt[range[row]], 1);
+                if (dense) s0[row] = (uint32_t)cx + ((uint32_t)(cy + dy) + (uint32_t)(cz + dz) * stride) * stride;
+                else s0[row] = ((uint32_t)cx ^ (hy0 + (dy ? kPrimeY : 0u)) ^ (hz0 + (dz ? kPrimeZ : 0u))) & g.table_mask;
+                rank[row] = atomicAdd(&sm.cnt[s0[row] >> kOwnerSlotBits], 1);
             }
         }
         __syncthreads();
         // one reservation per range in the global list, and the staged order: ranges one after another
-        for (int k = threadIdx.x; k < n_ranges; k += kBinThreads)
-            sm.base[k] = sm.cnt[k] ? atomicAdd(&rec.cursor[e * kMaxRanges + k], sm.cnt[k]) : 0;
-        if (threadIdx.x >= kBinThreads - 64) {               // the last wavefront: exclusive prefix sums of cnt
+        static_assert(kMaxRanges <= THREADS - 64, "a range a thread, beside the last wavefront");
+        int reserved = 0;
+        if (threadIdx.x < n_ranges && sm.cnt[threadIdx.x]) reserved = atomicAdd(&rec.cursor[e * kMaxRanges + threadIdx.x], sm.cnt[threadIdx.x]);
+        if (threadIdx.x >= THREADS - 64) {               // the last wavefront: exclusive prefix sums of cnt
             const int lane = threadIdx.x & 63;
             constexpr int kPer = kMaxRanges / 64;
             int c[kPer], sum = 0;
@@ -855,50 +872,65 @@ __global__ __launch_bounds__(kBinThreads) void bin_rows_kernel(GridDesc g, Owner
             }
             int at = incl - sum;
 #pragma unroll
-            for (int j = 0; j < kPer; ++j) { sm.first[kPer * lane + j] = at; at += c[j]; }
+            for (int j = 0; j < kPer; ++j) { sm.place[kPer * lane + j].x = at; at += c[j]; }
             if (lane == 63) sm.total = incl;
         }
+        if (threadIdx.x < n_ranges) sm.place[threadIdx.x].y = reserved;
         __syncthreads();
         if (valid) {
+            const float nx = dnx * fres, ny = dny * fres, nz = dnz * fres;
+            const float f0 = 1.f - w0, f1 = w0;
 #pragma unroll
             for (int row = 0; row < 4; ++row) {
-                const int r = (int)range[row];
-                const int in_list = sm.base[r] + rank[row];
-                const int at = sm.first[r] + rank[row];
-                struct Words { uint32_t w[kWords]; };
-                const Words words = __builtin_bit_cast(Words, row_rec[row]);
-#pragma unroll
-                for (int k = 0; k < kWords; ++k) sm.word[k][at] = words.w[k];
+                const int dy = row & 1, dz = row >> 1;
+                const float fy = dy ? w1 : 1.f - w1, fz = dz ? w2 : 1.f - w2;
+                const float sy = dy ? 1.f : -1.f, sz = dz ? 1.f : -1.f;
+                const float fyz = fy * fz;
+                const float dn_x = nx * fyz;
+                const float dn_yz = ny * (sy * fz) + nz * (fy * sz);
+                const float dn0 = -dn_x + f0 * dn_yz, dn1 = dn_x + f1 * dn_yz;
+                const float wk0 = f0 * fyz, wk1 = f1 * fyz;
+                float4 val = make_float4(wk0 * de.x + qq.x * dn0, wk0 * de.y + qq.y * dn0, wk1 * de.x + qq.x * dn1, wk1 * de.y + qq.y * dn1);
+                uint32_t row_code = code;
+                // On a hashed level both corners share the range.  On a dense level the x+1 corner can be
+                // the first slot of the next range (1 row in 8192): it then goes straight to the gradient.
+                if (dense && ((s0[row] + 1u) >> kOwnerSlotBits) != (s0[row] >> kOwnerSlotBits)) {
+                    float* gt = d_tables + ((size_t)level * g.table_size + s0[row] + 1u) * 2;
+                    atomicAdd(gt + 0, val.z);
+                    atomicAdd(gt + 1, val.w);
+                    val.z = 0.f; val.w = 0.f;
+                    row_code = kCodeSame;
+                }
+                Rec record;
+                make_record(record, s0[row] & (kOwnerSlots - 1), row_code, val);
+                const int r = (int)(s0[row] >> kOwnerSlotBits);
+                const int2 place = sm.place[r];
+                const int in_list = place.y + rank[row], at = place.x + rank[row];
                 if (in_list < capacity) {
-                    sm.dest[at] = (uint32_t)r * (uint32_t)capacity + (uint32_t)in_list;
+                    sm.staged.put(at, record, (uint32_t)r * (uint32_t)capacity + (uint32_t)in_list);
                 } else {                                                 // list full: straight to the global gradient
-                    sm.dest[at] = kNoRecord;
-                    uint32_t s0, s1;
+                    sm.staged.put(at, record, kNoRecord);
+                    uint32_t t0, t1;
                     float v[4];
-                    open_record(row_rec[row], s0, s1, v);
+                    open_record(record, t0, t1, v);
                     float* gt = d_tables + ((size_t)level * g.table_size + ((size_t)r << kOwnerSlotBits)) * 2;
-                    atomicAdd(gt + 2 * s0 + 0, v[0]);
-                    atomicAdd(gt + 2 * s0 + 1, v[1]);
-                    atomicAdd(gt + 2 * s1 + 0, v[2]);
-                    atomicAdd(gt + 2 * s1 + 1, v[3]);
+                    atomicAdd(gt + 2 * t0 + 0, v[0]);
+                    atomicAdd(gt + 2 * t0 + 1, v[1]);
+                    atomicAdd(gt + 2 * t1 + 0, v[2]);
+                    atomicAdd(gt + 2 * t1 + 1, v[3]);
                 }
             }
         }
         __syncthreads();
         const int total = sm.total;
         Rec* out = reinterpret_cast<Rec*>(rec.rows) + plan.list_base[e];
-        for (int at = threadIdx.x; at < total; at += kBinThreads) {
-            const uint32_t d = sm.dest[at];
-            if (d != kNoRecord) {
-                struct Words { uint32_t w[kWords]; } words;
-#pragma unroll
-                for (int k = 0; k < kWords; ++k) words.w[k] = sm.word[k][at];
-                out[d] = __builtin_bit_cast(Rec, words);            // (a non-temporal store here costs 0.2 ms: measured)
-            }
+        for (int at = threadIdx.x; at < total; at += THREADS) {
+            Rec r;
+            const uint32_t d = sm.staged.get(at, r);
+            if (d != kNoRecord) out[d] = r;                         // (a non-temporal store here costs 0.2 ms: measured)
         }
-        // the next round writes cnt only after the barrier that follows its clearing, base/first/total
-        // after the one behind its ranks, and the staged records after a third: every thread has left
-        // this loop by then
+        // the next round writes cnt only after this loop's barriers, place and total after the one behind its ranks, and
+        // the staged records after a third: every thread has left this loop by then
     }
 }
 
@@ -1451,12 +1483,18 @@ int launch_scatter(const neus2_config* cfg, const float* pos, const void* tables
             if (!header_cleared)                                                                 // task counter and cursors
                 NEUS2_TRY(launch_zero(reinterpret_cast<float*>(ws), kWorkspaceHeader / 4, st));
             if (plan.n_listed + plan.n_indexed > 0) {
-                const int pbs = (int)((n + kBinThreads - 1) / kBinThreads);
-                // enough workgroups to fill the chip several times over; each walks over its share of the levels
-                int groups = (8 * compute_units() + pbs - 1) / pbs;
+                // 1024 points a workgroup where 512 leave eight records a run (see kWideBinRanges) and the chip stays full
+                int most = 0;
+                for (int e = 0; e < plan.n_listed; ++e) most = std::max(most, (int)plan.ranges[e]);
+                const int threads = !wide && most > kWideBinRanges && n >= (int64_t)2048 * compute_units() ? 1024 : 512;
+                const int pbs = (int)((n + threads - 1) / threads);
+                // Enough workgroups to fill the chip once (2048 threads a compute unit); each walks over its share of the levels.
+                // Twice as many: 2^18 points 47 -> 53 us, 2^19 points 87 -> 95.
+                int groups = (4 * compute_units() + pbs - 1) / pbs;
                 if (groups > plan.n_listed) groups = plan.n_listed;
                 if (groups < 1 && plan.n_listed > 0) groups = 1;
-                hipLaunchKernelGGL(wide ? bin_rows_kernel<WideRecord> : bin_rows_kernel<RowRecord>, dim3(pbs * (groups + plan.n_indexed)), dim3(kBinThreads), 0, st, g, plan,
+                auto* const kernel = wide ? bin_rows_kernel<WideRecord, 512> : threads == 512 ? bin_rows_kernel<RowRecord, 512> : bin_rows_kernel<RowRecord, 1024>;
+                hipLaunchKernelGGL(kernel, dim3(pbs * (groups + plan.n_indexed)), dim3(threads), 0, st, g, plan,
                                    rec, pos, q, d_enc, d_normal, n, pbs, groups, d_tables);
             }
             const int wgs = compute_units();
