@@ -409,6 +409,19 @@ int neus2_occupancy_update(int log2_res, float* density, const int32_t* cells, c
                            int64_t sdf_stride, int64_t m, const float* s_dev, float s, float decay,
                            float threshold, uint32_t* bitfield, void* stream);
 
+/* The two calls of a refresh whose candidates come in random order, for log2_res >= 5: the same points and the same
+ * refresh, with the candidates put in order of 512 blocks of consecutive Morton numbers (roughly in order inside a block,
+ * which is not fixed), so that neighbours in the list are neighbours in space.
+ *   counts [device, 1024 int32] scratch that the first call fills and the second reads (any contents before);
+ *   cells_out [device, m int32], jitter_out and pos [device, m*3]: candidates, their jitter and their points in that
+ *   order (jitter no larger than 1 - 2^-24); cells_out and jitter_out must not overlap cells and jitter, pos
+ *   may take the place of jitter.  The second call takes cells_out as `cells`, and the SDF at pos, one value after the other. */
+int neus2_occupancy_points_ordered(int log2_res, const int32_t* cells, const float* jitter, int64_t m, int32_t* counts,
+                                   int32_t* cells_out, float* jitter_out, float* pos, void* stream);
+int neus2_occupancy_update_ordered(int log2_res, float* density, const int32_t* cells, const float* sdf, int64_t m,
+                                   const int32_t* counts, const float* s_dev, float s, float decay, float threshold,
+                                   uint32_t* bitfield, void* stream);
+
 /* Ray marching through the grid.  Ray r (origins, dirs [device, rays*3], unit-cube coordinates;
  * jitter [device, rays] in [0,1)) is clipped against [0,1]^3 (slab test, t_near >= 0); its
  * samples are the lattice points t_k = t_0 + k dt, t_0 = t_near + jitter dt, 0 <= k < max_steps,

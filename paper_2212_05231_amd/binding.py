@@ -89,6 +89,8 @@ _SIGNATURES = {
     "neus2_pose_update": (C.c_int, [_P, _P, _P, _P, _P, _P, C.c_float, C.c_float, C.c_float, C.c_float, C.c_int, C.c_int, _P]),
     "neus2_occupancy_points": (C.c_int, [C.c_int, _P, _P, C.c_int64, _P, _P]),
     "neus2_occupancy_list": (C.c_int, [C.c_int, _P, _P, _P, _P]),
+    "neus2_occupancy_points_ordered": (C.c_int, [C.c_int, _P, _P, C.c_int64, _P, _P, _P, _P, _P]),
+    "neus2_occupancy_update_ordered": (C.c_int, [C.c_int, _P, _P, _P, C.c_int64, _P, _P, C.c_float, C.c_float, C.c_float, _P, _P]),
     "neus2_occupancy_update": (C.c_int, [C.c_int, _P, _P, _P, C.c_int64, C.c_int64, _P, C.c_float, C.c_float, C.c_float, _P, _P]),
     "neus2_march_rays": (C.c_int, [C.c_int, _P, _P, _P, _P, C.c_int64, C.c_float, C.c_int32, C.c_int64, _P, _P, _P, _P, _P]),
     "neus2_train_step": (C.c_int, [C.POINTER(Neus2Config), C.POINTER(Neus2StepBuffers), C.c_int64, _P]),
@@ -307,6 +309,16 @@ def pose_update(param, m, v, prev, Mb, pose, lr, beta1, beta2, eps, t, apply=Tru
 
 def occupancy_points(log2_res, cells, jitter, pos):
     _check(lib().neus2_occupancy_points(log2_res, _ptr(cells), _ptr(jitter), cells.shape[0], _ptr(pos), _stream()))
+
+
+def occupancy_points_ordered(log2_res, cells, jitter, counts, cells_out, jitter_out, pos):
+    _check(lib().neus2_occupancy_points_ordered(log2_res, _ptr(cells), _ptr(jitter), cells.shape[0], _ptr(counts), _ptr(cells_out),
+                                                _ptr(jitter_out), _ptr(pos), _stream()))
+
+
+def occupancy_update_ordered(log2_res, density, cells, sdf, m, counts, s, decay, threshold, bitfield, s_dev=None):
+    _check(lib().neus2_occupancy_update_ordered(log2_res, _ptr(density), _ptr(cells), _ptr(sdf), m, _ptr(counts), _ptr(s_dev),
+                                                s, decay, threshold, _ptr(bitfield), _stream()))
 
 
 def occupancy_list(log2_res, bitfield, counts, cells):

@@ -7,6 +7,8 @@
 // arithmetic.  Every operation that feeds it is a single rounded operation in a fixed order
 // (no fused multiply-add anywhere in this file), so that the kept set can be reproduced bit for
 // bit by any IEEE implementation.
+#include <algorithm>
+
 #include "common.h"
 
 #pragma clang fp contract(off)
@@ -56,6 +58,11 @@ __global__ __launch_bounds__(kThreads) void decay_kernel(float* __restrict__ den
     }
 }
 
+__device__ __forceinline__ float logistic_density(float sdf, float s) {
+    const float e = expf(-s * fabsf(sdf));
+    return s * e / ((1.0f + e) * (1.0f + e));
+}
+
 // density[cell] = max(density[cell], phi_s(sdf)).  Densities are never negative, so their bit
 // patterns order like unsigned integers and one integer atomic maximum does it.
 __global__ __launch_bounds__(kThreads) void raise_kernel(float* __restrict__ density, int64_t count,
@@ -67,8 +74,7 @@ __global__ __launch_bounds__(kThreads) void raise_kernel(float* __restrict__ den
     const int64_t c = cells[i];
     if (c < 0 || c >= count) return;
     const float s = s_dev ? s_dev[0] : s_fixed;
-    const float e = expf(-s * fabsf(sdf[i * stride]));
-    const float phi = s * e / ((1.0f + e) * (1.0f + e));
+    const float phi = logistic_density(sdf[i * stride], s);
     if (!(phi > 0.0f) || phi > 3.0e38f) return;                 // NaN, zero, overflow: nothing to raise
     atomicMax(reinterpret_cast<unsigned int*>(density) + c, __float_as_uint(phi));
 }
@@ -125,7 +131,240 @@ __global__ __launch_bounds__(kThreads) void list_cells_kernel(const uint32_t* __
     int at = upto - count;
     for (int k = 0; k < kThreads / 64; ++k) at += before[k] + (k < wave ? own[k] : 0);
     if (blockIdx.x == gridDim.x - 1 && threadIdx.x == kThreads - 1) counts[0] = at + count;
-    for (; bits; bits &= bits - 1u) cells[at++] = 32 * w + (__ffs(bits) - 1);
+    // two words at a time, a lane a bit: stores of consecutive lanes side by side (a lane a word was 11 us at 128^3 cells)
+    const int half = lane >> 5, bit = lane & 31;
+#pragma unroll 4
+    for (int k = 0; k < 64; k += 2) {
+        const uint32_t word = (uint32_t)__shfl((int)bits, k + half);
+        const int first = __shfl(at, k + half);
+        if ((word >> bit) & 1u) cells[first + __popc(word & ((1u << bit) - 1u))] = 32 * (w - lane + k + half) + bit;
+    }
+}
+
+// ---- candidates in order of where they lie -----------------------------------------------------
+//
+// Drawn candidates come in random order: the gathers of the encoding then find nothing of a neighbour's in a cache, on
+// the coarse levels either, and every atomic maximum is a request of its own.  Three kernels put them in order: counts
+// and places by kBuckets blocks of consecutive Morton numbers (a block is a cube of cells), then the order inside every
+// kSortItems of them.  A workgroup lays its candidates out in LDS and writes them with consecutive threads, so runs of one
+// bucket leave together (a random store a candidate would touch a line each): 512 buckets are eight candidates a run.
+// 2^20 candidates of a 128^3 grid: 7 + 15 + 12 us, for which the encoding takes 259 instead of 324 (the levels finer than the
+// grid are left: their cells are nobody else's, and four cache lines a point and level are what the L2s can deliver) and the
+// refresh of the cells 8 instead of 52.
+constexpr int kBuckets = 512;
+constexpr int kSortThreads = 1024;
+constexpr int kSortItems = 4 * kSortThreads;
+constexpr int kSortEach = kSortItems / kSortThreads;
+
+__device__ __forceinline__ uint32_t bucket_of(int log2_res, int32_t cell) {      // log2_res >= 3
+    return ((uint32_t)cell & ((1u << (3 * log2_res)) - 1u)) >> (3 * log2_res - 9);
+}
+
+// Exclusive prefix sums of a value a thread, by the whole workgroup.
+__device__ __forceinline__ int bucket_scan(int v, int* wave_total) {
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    int upto = v;
+#pragma unroll
+    for (int step = 1; step < 64; step <<= 1) {
+        const int up = __shfl_up(upto, step);
+        if (lane >= step) upto += up;
+    }
+    if (lane == 63) wave_total[wave] = upto;
+    __syncthreads();
+    for (int k = 0; k < wave; ++k) upto += wave_total[k];
+    return upto - v;
+}
+
+// counts[b] += the candidates of bucket b
+__global__ __launch_bounds__(kSortThreads) void count_buckets_kernel(int log2_res, const int32_t* __restrict__ cells, int64_t m,
+                                                                     int32_t* __restrict__ counts) {
+    __shared__ int hist[kBuckets];
+    if (threadIdx.x < kBuckets) hist[threadIdx.x] = 0;
+    __syncthreads();
+    const int64_t first = (int64_t)blockIdx.x * kSortItems + threadIdx.x;
+#pragma unroll
+    for (int k = 0; k < kSortEach; ++k) {
+        const int64_t i = first + k * kSortThreads;
+        if (i < m) atomicAdd(&hist[bucket_of(log2_res, cells[i])], 1);
+    }
+    __syncthreads();
+    if (threadIdx.x < kBuckets && hist[threadIdx.x] > 0) atomicAdd(counts + threadIdx.x, hist[threadIdx.x]);
+}
+
+struct SortItems {
+    int cell[kSortItems];
+    float jitter[3][kSortItems];
+};
+
+// counts[0 .. kBuckets) as counted, counts[kBuckets ..) cursors that start at zero.
+__global__ __launch_bounds__(kSortThreads) void place_cells_kernel(int log2_res, const int32_t* __restrict__ cells, const float* __restrict__ jitter,
+                                                                   int64_t m, int32_t* __restrict__ counts, int32_t* __restrict__ cells_out,
+                                                                   float* __restrict__ jitter_out) {
+    __shared__ int hist[kBuckets];               // candidates of this workgroup, then the place of its first one minus its place in LDS
+    __shared__ int front[kBuckets];              // places in LDS
+    __shared__ int totals[2][kSortThreads / 64];
+    __shared__ SortItems items;
+    const int t = threadIdx.x;
+    if (t < kBuckets) hist[t] = 0;
+    __syncthreads();
+    const int64_t base = (int64_t)blockIdx.x * kSortItems;
+    const int here = (int)min((int64_t)kSortItems, m - base);
+    int cell[kSortEach], rank[kSortEach];
+    float j[kSortEach][3];
+#pragma unroll
+    for (int k = 0; k < kSortEach; ++k) {
+        const int i = k * kSortThreads + t;
+        if (i >= here) continue;
+        cell[k] = cells[base + i];
+#pragma unroll
+        for (int a = 0; a < 3; ++a) j[k][a] = fminf(jitter[3 * (base + i) + a], 0x1.fffffep-1f);
+        rank[k] = atomicAdd(&hist[bucket_of(log2_res, cell[k])], 1);
+    }
+    __syncthreads();
+    const int start = bucket_scan(t < kBuckets ? counts[t] : 0, totals[0]);
+    const int own = t < kBuckets ? hist[t] : 0;
+    const int place = bucket_scan(own, totals[1]);
+    if (t < kBuckets) {
+        front[t] = place;
+        hist[t] = start + (own > 0 ? atomicAdd(counts + kBuckets + t, own) : 0) - place;
+    }
+    __syncthreads();
+#pragma unroll
+    for (int k = 0; k < kSortEach; ++k) {
+        if (k * kSortThreads + t >= here) continue;
+        const int at = front[bucket_of(log2_res, cell[k])] + rank[k];
+        items.cell[at] = cell[k];
+#pragma unroll
+        for (int a = 0; a < 3; ++a) items.jitter[a][at] = j[k][a];
+    }
+    __syncthreads();
+#pragma unroll
+    for (int k = 0; k < kSortEach; ++k) {
+        const int i = k * kSortThreads + t;
+        if (i >= here) continue;
+        const int c = items.cell[i];
+        const int64_t dst = (int64_t)hist[bucket_of(log2_res, c)] + i;
+        if (dst < 0 || dst >= m) continue;                     // cells changed between the two kernels: stay inside
+        cells_out[dst] = c;
+#pragma unroll
+        for (int a = 0; a < 3; ++a) jitter_out[3 * dst + a] = items.jitter[a][i];
+    }
+}
+
+// The candidates of a workgroup, consecutive ones of the list, in order of kSortThreads equal pieces of the numbers they
+// span (about eight cells a piece at 2^20 candidates of a 128^3 grid), in place, and their points.  Neighbouring lanes of
+// the encoding then share cells and cache lines on levels up to the grid's resolution, also hashed ones.
+__global__ __launch_bounds__(kSortThreads) void order_cells_kernel(int log2_res, int64_t m, int32_t* __restrict__ cells, float* __restrict__ jitter,
+                                                                   float* __restrict__ pos) {
+    __shared__ int hist[kSortThreads];
+    __shared__ int totals[kSortThreads / 64];
+    __shared__ uint32_t low, high;
+    __shared__ SortItems items;
+    const int t = threadIdx.x;
+    const uint32_t mask = (1u << (3 * log2_res)) - 1u;
+    hist[t] = 0;
+    if (t == 0) { low = mask; high = 0u; }
+    __syncthreads();
+    const int64_t base = (int64_t)blockIdx.x * kSortItems;
+    const int here = (int)min((int64_t)kSortItems, m - base);
+    int cell[kSortEach], rank[kSortEach];
+    float j[kSortEach][3];
+    uint32_t least = mask, most = 0u;
+#pragma unroll
+    for (int k = 0; k < kSortEach; ++k) {
+        const int i = k * kSortThreads + t;
+        if (i >= here) continue;
+        cell[k] = cells[base + i];
+#pragma unroll
+        for (int a = 0; a < 3; ++a) j[k][a] = jitter[3 * (base + i) + a];
+        const uint32_t code = (uint32_t)cell[k] & mask;
+        least = min(least, code);
+        most = max(most, code);
+    }
+#pragma unroll
+    for (int step = 32; step > 0; step >>= 1) {
+        least = min(least, (uint32_t)__shfl_xor((int)least, step));
+        most = max(most, (uint32_t)__shfl_xor((int)most, step));
+    }
+    if ((t & 63) == 0) { atomicMin(&low, least); atomicMax(&high, most); }
+    __syncthreads();
+    // pieces are aligned, so none holds cells of two buckets: at most kSortThreads + 1 of them by the first guess
+    int shift = max(0, 22 - __clz((int)((high - low) | 1u)));
+    if ((high >> shift) - (low >> shift) >= kSortThreads) ++shift;
+    const uint32_t first = low >> shift;
+#pragma unroll
+    for (int k = 0; k < kSortEach; ++k)
+        if (k * kSortThreads + t < here) rank[k] = atomicAdd(&hist[(((uint32_t)cell[k] & mask) >> shift) - first], 1);
+    __syncthreads();
+    const int place = bucket_scan(hist[t], totals);
+    hist[t] = place;
+    __syncthreads();
+#pragma unroll
+    for (int k = 0; k < kSortEach; ++k) {
+        if (k * kSortThreads + t >= here) continue;
+        const int at = hist[(((uint32_t)cell[k] & mask) >> shift) - first] + rank[k];
+        items.cell[at] = cell[k];
+#pragma unroll
+        for (int a = 0; a < 3; ++a) items.jitter[a][at] = j[k][a];
+    }
+    __syncthreads();
+    const float inv = 1.0f / (float)(1 << log2_res);           // a power of two: exact
+#pragma unroll
+    for (int k = 0; k < kSortEach; ++k) {
+        const int i = k * kSortThreads + t;
+        if (i >= here) continue;
+        const int c = items.cell[i];
+        const uint32_t code = (uint32_t)c & mask;
+        cells[base + i] = c;
+#pragma unroll
+        for (int a = 0; a < 3; ++a) {
+            const float ja = items.jitter[a][i];
+            jitter[3 * (base + i) + a] = ja;
+            pos[3 * (base + i) + a] = ((float)gather3(code >> a) + ja) * inv;
+        }
+    }
+}
+
+// Decay, raise and threshold in one pass over the cells, for candidates in order of their buckets: a workgroup owns
+// `own_cells` consecutive cells (a bucket, or a part of one: it then reads the whole bucket), takes the maxima of its
+// candidates in LDS and writes each density and bit once.  Atomic maxima in memory were 42 us at 2^20 candidates (a
+// request each, whatever their order), decay and bits another pass over the cells each.
+constexpr int kOwnCells = 4096;
+
+__global__ __launch_bounds__(kSortThreads) void update_cells_kernel(int log2_res, float* __restrict__ density, const int32_t* __restrict__ cells,
+                                                                    const float* __restrict__ sdf, int64_t m, const int32_t* __restrict__ counts,
+                                                                    const float* __restrict__ s_dev, float s_fixed, float decay, float threshold,
+                                                                    uint32_t* __restrict__ bitfield, int own_cells) {
+    __shared__ uint32_t top[kOwnCells];
+    __shared__ int totals[kSortThreads / 64];
+    __shared__ int span[2];
+    const int t = threadIdx.x;
+    for (int c = t; c < own_cells; c += kSortThreads) top[c] = 0u;
+    const uint32_t first = blockIdx.x * (uint32_t)own_cells;
+    const int bucket = (int)bucket_of(log2_res, (int32_t)first);
+    const int count = t < kBuckets ? counts[t] : 0;
+    const int start = bucket_scan(count, totals);
+    if (t == bucket) { span[0] = start; span[1] = start + count; }
+    __syncthreads();
+    const float s = s_dev ? s_dev[0] : s_fixed;
+    const int64_t end = min((int64_t)span[1], m);
+    for (int64_t i = max(span[0], 0) + t; i < end; i += kSortThreads) {
+        const uint32_t c = (uint32_t)cells[i] - first;
+        if (c >= (uint32_t)own_cells) continue;                // another part of the bucket, or outside the grid
+        const float phi = logistic_density(sdf[i], s);
+        if (!(phi > 0.0f) || phi > 3.0e38f) continue;           // NaN, zero, overflow: nothing to raise
+        atomicMax(&top[c], __float_as_uint(phi));
+    }
+    __syncthreads();
+    for (int c = t; c < own_cells; c += kSortThreads) {         // own_cells is a multiple of 64: whole wavefronts
+        const float old = density[first + c] * decay;
+        // the bit patterns of values that are never negative order like unsigned integers
+        const float v = __uint_as_float(max(__float_as_uint(old), top[c]));
+        density[first + c] = v;
+        const uint64_t mask = __ballot(v > threshold);
+        const int lane = t & 63;
+        if ((lane & 31) == 0) bitfield[(first + c) >> 5] = (uint32_t)(mask >> lane);
+    }
 }
 
 // ---- marching ---------------------------------------------------------------------------------
@@ -293,22 +532,71 @@ extern "C" int neus2_occupancy_list(int log2_res, const uint32_t* bitfield, int3
     return check_launch("list_cells_kernel");
 }
 
+static int check_sorted(int log2_res, int64_t m) {
+    NEUS2_TRY(check_grid(log2_res));
+    NEUS2_TRY(check_m(m, "m"));
+    if (log2_res < 5) return fail(NEUS2_ERR_SHAPE, "log2_res %d: candidates are put in order from 5 on", log2_res);
+    return NEUS2_OK;
+}
+
+extern "C" int neus2_occupancy_points_ordered(int log2_res, const int32_t* cells, const float* jitter, int64_t m, int32_t* counts,
+                                              int32_t* cells_out, float* jitter_out, float* pos, void* stream) {
+    NEUS2_TRY(check_sorted(log2_res, m));
+    NEUS2_TRY(check_ptr(cells, "cells"));
+    NEUS2_TRY(check_ptr(jitter, "jitter"));
+    NEUS2_TRY(check_ptr(counts, "counts"));
+    NEUS2_TRY(check_ptr(cells_out, "cells_out"));
+    NEUS2_TRY(check_ptr(jitter_out, "jitter_out"));
+    NEUS2_TRY(check_ptr(pos, "pos"));
+    hipStream_t st = static_cast<hipStream_t>(stream);
+    NEUS2_TRY(launch_zero(reinterpret_cast<float*>(counts), 2 * kBuckets, st));
+    if (m == 0) return NEUS2_OK;
+    const unsigned blocks = (unsigned)((m + kSortItems - 1) / kSortItems);
+    count_buckets_kernel<<<blocks, kSortThreads, 0, st>>>(log2_res, cells, m, counts);
+    NEUS2_TRY(check_launch("count_buckets_kernel"));
+    place_cells_kernel<<<blocks, kSortThreads, 0, st>>>(log2_res, cells, jitter, m, counts, cells_out, jitter_out);
+    NEUS2_TRY(check_launch("place_cells_kernel"));
+    order_cells_kernel<<<blocks, kSortThreads, 0, st>>>(log2_res, m, cells_out, jitter_out, pos);
+    return check_launch("order_cells_kernel");
+}
+
+static int check_refresh(const float* density, const uint32_t* bitfield, const float* s_dev, float s, float decay, float threshold) {
+    NEUS2_TRY(check_ptr(density, "density"));
+    NEUS2_TRY(check_ptr(bitfield, "bitfield"));
+    NEUS2_TRY(check_ptr(s_dev, "s_dev", false));
+    if (!(decay >= 0.0f && decay <= 1.0f)) return fail(NEUS2_ERR_CONFIG, "decay %g outside [0,1]", (double)decay);
+    if (!(threshold >= 0.0f)) return fail(NEUS2_ERR_CONFIG, "threshold %g is negative or NaN", (double)threshold);
+    if (!s_dev && !(s > 0.0f)) return fail(NEUS2_ERR_CONFIG, "s %g is not positive", (double)s);
+    return NEUS2_OK;
+}
+
+extern "C" int neus2_occupancy_update_ordered(int log2_res, float* density, const int32_t* cells, const float* sdf, int64_t m,
+                                              const int32_t* counts, const float* s_dev, float s, float decay, float threshold,
+                                              uint32_t* bitfield, void* stream) {
+    NEUS2_TRY(check_sorted(log2_res, m));
+    NEUS2_TRY(check_refresh(density, bitfield, s_dev, s, decay, threshold));
+    NEUS2_TRY(check_ptr(cells, "cells"));
+    NEUS2_TRY(check_ptr(sdf, "sdf"));
+    NEUS2_TRY(check_ptr(counts, "counts"));
+    hipStream_t st = static_cast<hipStream_t>(stream);
+    const int total = 1 << (3 * log2_res);
+    const int own = std::min(kOwnCells, total / kBuckets);
+    update_cells_kernel<<<total / own, kSortThreads, 0, st>>>(log2_res, density, cells, sdf, m, counts, s_dev, s, decay, threshold,
+                                                              bitfield, own);
+    return check_launch("update_cells_kernel");
+}
+
 extern "C" int neus2_occupancy_update(int log2_res, float* density, const int32_t* cells, const float* sdf,
                                       int64_t sdf_stride, int64_t m, const float* s_dev, float s, float decay,
                                       float threshold, uint32_t* bitfield, void* stream) {
     NEUS2_TRY(check_grid(log2_res));
     NEUS2_TRY(check_m(m, "m"));
-    NEUS2_TRY(check_ptr(density, "density"));
-    NEUS2_TRY(check_ptr(bitfield, "bitfield"));
-    NEUS2_TRY(check_ptr(s_dev, "s_dev", false));
     if (m > 0) {
         NEUS2_TRY(check_ptr(cells, "cells"));
         NEUS2_TRY(check_ptr(sdf, "sdf"));
         if (sdf_stride < 1) return fail(NEUS2_ERR_SHAPE, "sdf_stride %lld < 1", (long long)sdf_stride);
     }
-    if (!(decay >= 0.0f && decay <= 1.0f)) return fail(NEUS2_ERR_CONFIG, "decay %g outside [0,1]", (double)decay);
-    if (!(threshold >= 0.0f)) return fail(NEUS2_ERR_CONFIG, "threshold %g is negative or NaN", (double)threshold);
-    if (!s_dev && !(s > 0.0f)) return fail(NEUS2_ERR_CONFIG, "s %g is not positive", (double)s);
+    NEUS2_TRY(check_refresh(density, bitfield, s_dev, s, decay, threshold));
     hipStream_t st = static_cast<hipStream_t>(stream);
     const int64_t count = (int64_t)1 << (3 * log2_res);
     decay_kernel<<<(unsigned)((count / 4 + kThreads - 1) / kThreads), kThreads, 0, st>>>(

@@ -266,3 +266,68 @@ def test_list_of_the_occupied_cells(log2_res, share):
     expected = np.flatnonzero(bits)
     assert int(counts[0]) == len(expected)
     assert np.array_equal(listed.cpu().numpy()[: len(expected)], expected) and bool((listed[len(expected):] == -7).all())
+
+
+@pytest.mark.parametrize("log2_res,m,where", [(5, 1, "all"), (5, 4095, "all"), (5, 70001, "one"), (6, 4096, "all"), (6, 131072, "few"),
+                                              (7, 4097, "few"), (7, 300001, "all"), (8, 5000, "all"), (8, 40000, "one")])
+def test_ordered_refresh_is_the_plain_one(log2_res, m, where):
+    """Candidates put in order of their blocks are the same candidates at the same points, block by block, and the refresh
+    from them equals the one from the list as drawn to the last bit: parts of a workgroup, one block for all candidates,
+    cells outside the grid, SDF values that are not finite, a last block cut into several workgroups (log2_res 8)."""
+    gen = torch.Generator(device="cuda").manual_seed(100 * log2_res + m % 97)
+    total = 1 << (3 * log2_res)
+    high = {"all": total, "few": total // 16, "one": 65}[where]
+    cells = torch.randint(total - high, total, (m,), generator=gen, device="cuda", dtype=torch.int32)
+    if m > 10:
+        cells[3], cells[7] = -5, total + 11
+    jitter = torch.rand(m, 3, generator=gen, device="cuda").clamp_(max=1.0 - 2.0 ** -24)
+    guard = 777.0
+    plain = torch.empty(m, 3, device="cuda")
+    out_cells = torch.full((m + 64,), -99, dtype=torch.int32, device="cuda")
+    out_jitter, out_pos = (torch.full((m + 64, 3), guard, device="cuda") for _ in range(2))
+    counts = torch.full((1024,), 12345, dtype=torch.int32, device="cuda")
+    density = torch.rand(total, generator=gen, device="cuda")
+    bits_a, bits_b = (torch.zeros(total // 32, dtype=torch.int32, device="cuda") for _ in range(2))
+    nb.occupancy_points(log2_res, cells, jitter, plain)
+    nb.occupancy_points_ordered(log2_res, cells, jitter, counts, out_cells, out_jitter, out_pos)
+    assert (out_cells[m:] == -99).all() and (out_jitter[m:] == guard).all() and (out_pos[m:] == guard).all()
+
+    def rows(c, j, p):
+        r = np.concatenate([c.cpu().numpy().reshape(-1, 1).view(np.uint32), j.cpu().numpy().view(np.uint32), p.cpu().numpy().view(np.uint32)], axis=1)
+        return r[np.lexsort(r.T)]
+    assert np.array_equal(rows(cells, jitter, plain), rows(out_cells[:m], out_jitter[:m], out_pos[:m]))
+    block = (out_cells[:m].to(torch.int64) & (total - 1)) >> (3 * log2_res - 9)
+    assert bool((block[1:] >= block[:-1]).all())
+
+    def sdf_at(pos):                                         # the same value for the same point, some of them not finite
+        v = (pos[:, 0] * 3.0 + pos[:, 1] - pos[:, 2]) * 0.1
+        v = torch.where((pos[:, 0] * 64).floor() % 7 == 0, torch.full_like(v, float("nan")), v)
+        return torch.where((pos[:, 1] * 64).floor() % 5 == 0, torch.full_like(v, float("inf")), v).contiguous()
+    density_b = density.clone()
+    nb.occupancy_update(log2_res, density, cells, sdf_at(plain), 1, m, 30.0, 0.95, 0.6, bits_a)
+    nb.occupancy_update_ordered(log2_res, density_b, out_cells, sdf_at(out_pos[:m]), m, counts, 30.0, 0.95, 0.6, bits_b)
+    assert torch.equal(density, density_b) and torch.equal(bits_a, bits_b)
+
+
+@pytest.mark.parametrize("log2_res", [5, 6])
+def test_refresh_of_drawn_candidates_in_either_order(log2_res, monkeypatch):
+    """The same draws give the same grid whether the candidates are put in order or not, over several refreshes, and what
+    the grid object keeps of them belongs together."""
+    from paper_2212_05231_amd import occupancy
+    w = wl.make_workload(2, n_rays=8)
+    cfg, params = w["cfg"], w["params"]
+    params["tables"] = (params["tables"].astype(np.float64) * 3000.0).astype(params["tables"].dtype)
+    grids = []
+    for first in (0, 1 << 40):
+        monkeypatch.setattr(occupancy, "ORDER_FROM", first)
+        grid = occupancy.OccupancyGrid(nb.Step(cfg, params, 64, n_rays=1), log2_res=log2_res, decay=0.9, threshold=4.0, warm_updates=1)
+        gen = torch.Generator(device="cuda").manual_seed(5)
+        kept = [(grid.update(gen), grid.last_cells, grid.last_cells.clone()) for _ in range(3)]
+        assert all(torch.equal(a, b) for _, a, b in kept)     # a later refresh leaves an earlier one's list alone
+        m = kept[-1][0]
+        pos = torch.empty(m, 3, device="cuda")
+        nb.occupancy_points(log2_res, grid.last_cells, grid.jitter[:m].contiguous(), pos)
+        assert torch.equal(pos, grid.pos[:m])
+        grids.append(grid)
+    assert torch.equal(grids[0].density, grids[1].density) and torch.equal(grids[0].bitfield, grids[1].bitfield)
+    assert torch.equal(grids[0].last_cells.sort().values, grids[1].last_cells.sort().values)
