@@ -2,7 +2,7 @@
 grid's device buffers, draws the candidate cells of an update, and strings the library calls
 together.  All arithmetic on the grid and on the rays runs in the library's kernels
 (`neus2_occupancy_list`, `neus2_occupancy_points`, `neus2_sdf_values`, `neus2_occupancy_update`,
-`neus2_march_rays`); this module only decides WHICH cells are looked at and WHEN.
+the `_ordered` forms of the points and the update, `neus2_march_rays`); this module only decides WHICH cells are looked at and WHEN.
 
 The paper refreshes the grid "periodically" as the publication it cites does; that
 publication's schedule is what `candidates` follows: during the first updates every cell is a
