@@ -113,7 +113,7 @@ def algorithmic_cost(cfg, n):
     # products and weight gradients), on v_mfma_f32_32x32x16_bf16 (32768 flop for a tile of 32 points),
     # including recomputation (three products where the forward kernels hand over their masks, as here) and the
     # padding of narrow layers.  Instruction counts per tile follow the
-    # kernels' structure; the backward kernels add 32 narrow fp32 instructions (2048 flop each).
+    # kernels' structure; the backward kernels add 32 narrow fp32 instructions (2048 flop each, 512 in the colour network's).
     ks1, k3 = sd[0] // 16, 1 if K == 3 else 0
     issued = {
         "sdf_fwd_grad": 6 * (2 * ks1 + 8 * k3 + 4 + 8 * k3 + 4),
@@ -125,7 +125,7 @@ def algorithmic_cost(cfg, n):
         out[k] = {kk: vv * n for kk, vv in v.items()}
     for k, mf in issued.items():
         if k in out:
-            out[k]["issued_flops"] = (mf * 32768 + (32 * 2048 if k.endswith("bwd") else 0)) * n // 32
+            out[k]["issued_flops"] = (mf * 32768 + (32 * {"sdf_mlp_bwd": 2048, "color_bwd": 512}.get(k, 0))) * n // 32
     # parameters a point can address: a dense level uses (res+1)^3 of its T slots; the levels beyond the
     # active ones have never had a gradient and the step leaves them out (NEUS2_ADAM_ACTIVE_LEVELS)
     n_tab = sum(((r + 1) ** 3 if d else cfg.table_size) for r, d in list(zip(cfg.res, cfg.dense))[:cfg.active_levels]) * F
