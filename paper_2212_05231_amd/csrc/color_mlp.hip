@@ -44,8 +44,7 @@ __device__ __forceinline__ int external_column(int c) {
 // forward kernel and where the backward kernel recomputes it, uses three terms per factor and six
 // products: as accurate as fp32 arithmetic, and the same arithmetic in both kernels, so the ReLU
 // masks agree.  The adjoint sweep of the backward kernel uses two terms and three products.
-// A forward pass that is not asked for the masks (rendering) takes two fp16 terms, scaled: as accurate, half the products.
-// PF: terms of the matrices of the forward direction (two in that pass and in the backward kernel that is handed the masks).
+// PF: terms of the matrices of the forward direction (two in the backward kernel that is handed the masks).
 template <bool BWD, int PF = 3>
 struct ColorWeights {
     typedef SplitMatrix<3, PF> M1f;    // [64][40 -> 48]
@@ -61,14 +60,12 @@ struct ColorWeights {
     alignas(16) unsigned char W1t[BWD ? 32 * M1t::kLd : 16];
     alignas(16) unsigned char W2t[BWD ? 64 * M2t::kLd : 16];
     alignas(16) unsigned char W3t[BWD ? 64 * M3t::kLd : 16];
-    alignas(16) float part[BWD ? 4 : 2 * kWaves];
 };
 
 // Every matrix is fetched from global memory before the first is written to LDS, so the fetches
 // are in flight together; the copies cover every slot a product reads, so nothing is cleared.
-// exponent: the first two matrices are 2^exponent times theirs where they are fp16 terms (!BWD, PF = 2).
 template <bool BWD, int THREADS, int PF = 3>
-__device__ void load_weights(ColorWeights<BWD, PF>& w, const ColorArgs& a, int (&exponent)[2]) {
+__device__ void load_weights(ColorWeights<BWD, PF>& w, const ColorArgs& a) {
     typedef ColorWeights<BWD, PF> W;
     const int tid = threadIdx.x;
     const float* __restrict__ W1 = a.W[0];
@@ -91,15 +88,8 @@ __device__ void load_weights(ColorWeights<BWD, PF>& w, const ColorArgs& a, int (
     t1.load(tid, [&](int c, int o) { return first(o, c); });
     t2.load(tid, [&](int i, int o) { return W2[o * 64 + i]; });
     t3.load(tid, [&](int i, int o) { return o < 3 ? W3[o * 64 + i] : 0.f; });
-    if constexpr (!BWD && PF == 2) {
-        float largest[2] = {f1.largest(tid), f2.largest(tid)};
-        workgroup_exponents<2, THREADS / 64>(largest, w.part, exponent);
-        f1.store_half(w.W1f, tid, exponent[0]);
-        f2.store_half(w.W2f, tid, exponent[1]);
-    } else {
-        f1.store(w.W1f, tid);
-        f2.store(w.W2f, tid);
-    }
+    f1.store(w.W1f, tid);
+    f2.store(w.W2f, tid);
     if (!BWD && tid < 192) w.W3r[lh][lo][lk] = last;
     t1.store(w.W1t, tid);
     t2.store(w.W2t, tid);
@@ -200,29 +190,9 @@ __device__ __forceinline__ void forward_tile(const ColorWeights<BWD>& w, const v
     m2 = relu_mask<2>(a2);
 }
 
-// The same for a pass whose masks nobody wants: a2 comes out times 2^e.
-__device__ __forceinline__ void forward_tile_half(const ColorWeights<false, 2>& w, const int (&kw)[2], const v16f* cin, v16f* a2, int& e, int lane) {
-    HalfSplit<2> p;
-    int k = half_exponent<2>(cin);
-    half_split(cin, k, p);
-    e = k + kw[0] + kw[1];
-    matvec_half<2, 3>(w.W1f, p, a2, lane);
-    relu<2>(a2);
-    k = half_exponent<2>(a2);
-    half_split(a2, k, p);
-    e += k;
-    matvec_half<2, 4>(w.W2f, p, a2, lane);
-    relu<2>(a2);
-}
-
-// MASKS: writes the ReLU masks, in the arithmetic that the backward kernel without given masks repeats.  Without them fp16
-// terms: 2^20 points 79.5 -> 60 us, 2^18 points 23 -> 20.
-template <bool MASKS>
 __global__ __launch_bounds__(kThreads, 2) void color_fwd_kernel(ColorArgs a) {
-    constexpr int kTerms = MASKS ? 3 : 2;
-    __shared__ ColorWeights<false, kTerms> w;
-    int kw[2];
-    load_weights<false, kThreads, kTerms>(w, a, kw);
+    __shared__ ColorWeights<false> w;
+    load_weights<false, kThreads>(w, a);
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);   // the same for all lanes: keeps tile indices and addresses scalar
     const int j = lane & 31, h = lane >> 5;
@@ -234,22 +204,17 @@ __global__ __launch_bounds__(kThreads, 2) void color_fwd_kernel(ColorArgs a) {
         const int64_t i = tile * 32 + j;
         const bool valid = i < a.n;
         v16f cin[2], a2[2];
-        int e = 0;
+        uint32_t m1, m2;
+        Split<2, 3> pc, p1;
         build_input(next, valid, h, cin);
         {
             const int64_t in = (tile + stride) * 32 + j;
             next = load_raw<false>(a, in, tile + stride < tiles && in < a.n, h);
         }
-        if constexpr (MASKS) {
-            uint32_t m1, m2;
-            Split<2, 3> pc, p1;
-            forward_tile<false>(w, cin, pc, p1, a2, m1, m2, lane);
-            if (valid) {
-                a.masks[mask_word(0, a.n, i, h)] = m1;
-                a.masks[mask_word(1, a.n, i, h)] = m2;
-            }
-        } else {
-            forward_tile_half(w, kw, cin, a2, e, lane);
+        forward_tile<false>(w, cin, pc, p1, a2, m1, m2, lane);
+        if (a.masks && valid) {
+            a.masks[mask_word(0, a.n, i, h)] = m1;
+            a.masks[mask_word(1, a.n, i, h)] = m2;
         }
         // Last layer, three outputs: fp32 dot products of this lane's 32 activations with its part
         // of each row, and one cross-lane add for the other half of the point.  As a matrix product
@@ -265,10 +230,7 @@ __global__ __launch_bounds__(kThreads, 2) void color_fwd_kernel(ColorArgs a) {
                 u[o] += wv.x * act[r] + wv.y * act[r + 1] + wv.z * act[r + 2] + wv.w * act[r + 3];
             }
 #pragma unroll
-        for (int o = 0; o < 3; ++o) {
-            u[o] += __shfl_xor(u[o], 32);
-            if (!MASKS) u[o] = __builtin_amdgcn_ldexpf(u[o], -e);
-        }
+        for (int o = 0; o < 3; ++o) u[o] += __shfl_xor(u[o], 32);
         if (valid && h == 0) {
             a.rgb[3 * i + 0] = sigmoid(u[0]);
             a.rgb[3 * i + 1] = sigmoid(u[1]);
@@ -287,8 +249,7 @@ struct ColorBwdSmem {
 __global__ __launch_bounds__(kThreads) void color_bwd_kernel(ColorArgs a) {
     __shared__ ColorBwdSmem sm;
     ColorWeights<true>& w = sm.w;
-    int unused[2];
-    load_weights<true, kThreads>(w, a, unused);
+    load_weights<true, kThreads>(w, a);
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);   // the same for all lanes: keeps tile indices and addresses scalar
     const int j = lane & 31, h = lane >> 5;
@@ -569,8 +530,7 @@ __device__ __forceinline__ void color_first_layer(const ColorArgs& a, const Colo
 
 __global__ __launch_bounds__(kPairThreads) void color_bwd_pair_kernel(ColorArgs a) {
     __shared__ ColorPairSmem sm;
-    int unused[2];
-    load_weights<true, kPairThreads, 2>(sm.w, a, unused);
+    load_weights<true, kPairThreads, 2>(sm.w, a);
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);   // the same for all lanes: keeps tile indices and addresses scalar
     const int slot = wave % kPairs;
@@ -664,9 +624,8 @@ int neus2_color_fwd(const neus2_config* cfg, const float* pos, const float* norm
     a.pos = pos; a.normal = normal; a.dirs = dirs; a.sample_ray = sample_ray; a.y = y; a.rgb = rgb; a.n = n; a.masks = masks;
     a.spr = cfg->samples_per_ray;
     for (int l = 0; l < 3; ++l) a.W[l] = W[l];
-    void (*const kernel)(ColorArgs) = masks ? color_fwd_kernel<true> : color_fwd_kernel<false>;
-    const int blocks = persistent_blocks((const void*)kernel, kThreads, ((n + 31) / 32 + kWaves - 1) / kWaves);
-    hipLaunchKernelGGL(kernel, dim3(blocks), dim3(kThreads), 0, (hipStream_t)stream, a);
+    const int blocks = persistent_blocks((const void*)color_fwd_kernel, kThreads, ((n + 31) / 32 + kWaves - 1) / kWaves);
+    hipLaunchKernelGGL(color_fwd_kernel, dim3(blocks), dim3(kThreads), 0, (hipStream_t)stream, a);
     return check_launch("colour forward");
 }
 

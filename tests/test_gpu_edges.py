@@ -364,9 +364,8 @@ def test_concentrated_batch_overflows_the_lists_of_wide_records():
 
 @pytest.mark.parametrize("n,size_y,size_w", [(1, 1.0, 1.0), (31, 1e-20, 1.0), (33, 1e10, 1e-9), (257 * 128 + 5, 1.0, 1.0), (1000, 0.0, 1.0)])
 def test_colour_forward_without_masks(n, size_y, size_w):
-    """A forward pass that is not asked for masks takes scaled fp16 terms: the scale follows the point (features of any
-    size) and the matrix (one of zeros among them).  At most 64 products, each within 2^-22 of its size (two roundings of
-    2^-23 and the product of the low terms), random signs: 1e-6 of the norm, as the masked pass."""
+    """A forward pass that is not asked for masks, features and matrices of any size (one of zeros among them).  At most 64
+    products, each within 2^-22 of its size, random signs: 1e-6 of the norm, as the masked pass."""
     rng = np.random.default_rng(n)
     cfg = wl.make_config(2)
     cfg.samples_per_ray = 1
@@ -443,3 +442,71 @@ def test_scatter_add_of_runs_in_one_cell(n, log2_t, res, broken):
         tol = 1e-6 if dense[level] or (1 << log2_t) <= 8192 else 1e-5
         assert rel(got[finite], want[finite]) <= tol, level
     assert torch.all(torch.signbit(behind)) and torch.all(behind == 0)
+
+
+def colour_inputs(n, rng):
+    cfg = wl.make_config(2)
+    cfg.samples_per_ray = 1
+    W = [rng.normal(size=(cfg.color_dims[i + 1], cfg.color_dims[i])).astype(np.float32) * 0.3 for i in range(3)]
+    pos, nrm = rng.uniform(size=(n, 3)).astype(np.float32), rng.normal(size=(n, 3)).astype(np.float32)
+    y = rng.normal(size=(n, 16)).astype(np.float32)
+    dirs = rng.normal(size=(n, 3))
+    return nb.make_config(cfg), W, pos, nrm, (dirs / np.linalg.norm(dirs, axis=1, keepdims=True)).astype(np.float32), y
+
+
+def without_neuron_scales(rng, mats, low=-30, high=30):
+    """The same network with each hidden neuron scaled by a power of two: row of one matrix up, column of the next down."""
+    scaled = [m.copy() for m in mats]
+    for l in range(len(mats) - 1):
+        scale = np.ldexp(np.float32(1), rng.integers(low, high + 1, size=mats[l].shape[0])).astype(np.float32)
+        scaled[l] *= scale[:, None]
+        scaled[l + 1] /= scale[None, :]
+    return scaled
+
+
+@pytest.mark.parametrize("n", [33, 4099])
+def test_colour_calls_without_masks_decide_the_gates_alike(n):
+    """Points whose input makes one pre-activation of the first layer cancel to its rounding errors.  The forward call
+    without masks is the masked one to the last bit, and the backward call without masks takes the gates that the masked
+    forward call wrote: one gate the other way is a term of 0.3 / 8 of a point's adjoint and more, the two backward kernels
+    differ by 2e-5."""
+    rng = np.random.default_rng(n)
+    c, W, pos, nrm, dirs, y = colour_inputs(n, rng)
+    neuron = rng.integers(0, 64, size=n)
+    cin = o.color_input(pos, nrm.astype(np.float64), dirs, y.astype(np.float64), 1)
+    weights = W[0].astype(np.float64)[neuron]
+    last = weights[:, 37]
+    ok = np.abs(last) > 0.03
+    y[ok, 15] -= (np.sum(weights * cin, axis=1)[ok] / last[ok]).astype(np.float32)
+    cin = o.color_input(pos, nrm.astype(np.float64), dirs, y.astype(np.float64), 1)
+    z, size = np.sum(weights * cin, axis=1), np.sum(np.abs(weights * cin), axis=1)
+    assert np.mean(np.abs(z) < 2.0 ** -22 * size) > 0.5
+    args, Wg = (cuda(pos), cuda(nrm), cuda(dirs), cuda(y)), [cuda(w) for w in W]
+    kept = torch.zeros(2, n, 2, dtype=torch.int32, device="cuda")
+    rgb, plain = torch.empty(n, 3, device="cuda"), torch.empty(n, 3, device="cuda")
+    nb.color_fwd(c, *args, Wg, n, rgb, masks=kept)
+    nb.color_fwd(c, *args, Wg, n, plain)
+    assert torch.equal(rgb, plain)
+    d_rgb = cuda(rng.choice([-1.0, 1.0], size=(n, 3)).astype(np.float32))
+    got = []
+    for masks in (kept, None):
+        d_y, d_normal, d_pos = torch.empty(n, 16, device="cuda"), torch.zeros(n, 3, device="cuda"), torch.empty(n, 3, device="cuda")
+        nb.color_bwd(c, *args, Wg, rgb, d_rgb, None, n, [torch.zeros_like(w) for w in Wg], d_y, d_normal, d_pos, masks=masks)
+        got.append(torch.cat([d_y, d_normal, d_pos], dim=1).double())
+    norm = got[0].norm(dim=1)
+    off = (got[1] - got[0]).norm(dim=1) / norm.clamp_min(1e-3 * float(norm.mean()))
+    assert float(off.max()) <= 5e-3
+
+
+@pytest.mark.parametrize("masks", [False, True])
+def test_colour_forward_whatever_the_scale_of_a_neuron(masks):
+    """Factors of two between a neuron's weights and those that read it change no bit: every element keeps 24 bits of its
+    own, whatever its neighbours in the vector or the matrix are."""
+    n, rng = 1031, np.random.default_rng(7)
+    c, W, pos, nrm, dirs, y = colour_inputs(n, rng)
+    got = []
+    for mats in (W, without_neuron_scales(rng, W)):
+        got.append(torch.empty(n, 3, device="cuda"))
+        kept = torch.zeros(2, n, 2, dtype=torch.int32, device="cuda") if masks else None
+        nb.color_fwd(c, cuda(pos), cuda(nrm), cuda(dirs), cuda(y), [cuda(w) for w in mats], n, got[-1], masks=kept)
+    assert torch.equal(*got)
