@@ -12,11 +12,11 @@
  *  - `stream` is a hipStream_t passed as void* (NULL = the default stream).  Calls only
  *    enqueue work; they never synchronise.
  *  - Arithmetic: fp32 throughout.  The matrix products of the two networks take their fp32
- *    factors as sums of bf16 or fp16 terms on the 16-bit matrix cores with fp32 accumulation.
- *    Forward passes: three bf16 terms, six term products; where a call is not asked for the ReLU
- *    masks, what decides none of them takes two fp16 terms, scaled by powers of two, three term
- *    products; both as accurate as an fp32 product (about 2e-7 relative on the outputs).  Two bf16 terms (three term products) in the
- *    adjoint sweeps and weight gradients (about 1e-5 relative on the gradients).
+ *    factors as sums of bf16 terms on the bf16 matrix cores with fp32 accumulation: three terms
+ *    (six term products) wherever a result is a forward output or decides a ReLU mask, which is
+ *    as accurate as an fp32 product (about 2e-7 relative on the outputs); two terms (three term
+ *    products) in the adjoint sweeps and weight gradients (about 1e-5 relative on the gradients).
+ *    (dd/de and the normal of neus2_sdf_deep_fwd_grad: two fp16 terms, scaled, three products.)
  *  - n is the number of sample points; for ray workloads n = rays * samples_per_ray and a
  *    ray's samples are consecutive.
  *

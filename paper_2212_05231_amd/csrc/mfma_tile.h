@@ -703,22 +703,6 @@ __device__ __forceinline__ void matvec_half(const unsigned char* __restrict__ W,
     for (int mb = 0; mb < MB; ++mb) z[mb] = acc[mb];
 }
 
-// One spelling for kernels that exist with either kind of terms: returns k (0 of bf16 terms); 64 inputs
-__device__ __forceinline__ int split_scaled(const v16f* v, Split<2, 3>& out) { split(v, out); return 0; }
-__device__ __forceinline__ int split_scaled(const v16f* v, HalfSplit<2>& out) {
-    const int k = half_exponent<2>(v);
-    half_split(v, k, out);
-    return k;
-}
-template <int MB>
-__device__ __forceinline__ void matvec_scaled(const unsigned char* __restrict__ W, const Split<2, 3>& x, v16f* z, int lane) {
-    matvec_split<MB, 4, 3, 3>(W, x, z, lane);
-}
-template <int MB>
-__device__ __forceinline__ void matvec_scaled(const unsigned char* __restrict__ W, const HalfSplit<2>& x, v16f* z, int lane) {
-    matvec_half<MB, 4>(W, x, z, lane);
-}
-
 // Largest magnitude of COUNT matrices over a workgroup of WAVES waves, each thread bringing its own part: one barrier.
 // part: COUNT * WAVES floats of LDS that are not written again.
 template <int COUNT, int WAVES>

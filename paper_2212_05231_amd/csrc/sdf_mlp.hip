@@ -45,16 +45,15 @@ __device__ __forceinline__ int64_t mask_word(int layer, int64_t n, int64_t i, in
 // factor and six products: as accurate as fp32 arithmetic, and the same arithmetic in both
 // kernels, so the ReLU masks agree.  The adjoint, S and t sweeps of the backward kernel use
 // two terms and three products.
-// HALF (a forward pass that is not asked for the masks): HLf, H1t, H2t, which decide none, are fp16 terms, scaled (matvec_half).
 // PF: terms of the matrices of the forward direction.
-template <int D, int K, bool BWD, int PF = 3, bool HALF = false>
+template <int D, int K, bool BWD, int PF = 3>
 struct SdfWeights {
-    static constexpr int KS1 = D / 16, P = BWD || HALF ? 2 : 3;
+    static constexpr int KS1 = D / 16;
     typedef SplitMatrix<KS1, PF> M1f;              // [64][D]
     typedef SplitMatrix<4, PF> M2f;                // [64][64]
-    typedef SplitMatrix<4, P> MLf;                 // last matrix [16 -> 32][64]
-    typedef SplitMatrix<4, P> M1t;                 // [D -> 32][64]
-    typedef SplitMatrix<4, P> M2t;
+    typedef SplitMatrix<4, 3> MLf;                 // last matrix [16 -> 32][64]
+    typedef SplitMatrix<4, BWD ? 2 : 3> M1t;       // [D -> 32][64]
+    typedef SplitMatrix<4, BWD ? 2 : 3> M2t;
     typedef SplitMatrix<1, 2> MLt;                 // [64][16]
     alignas(16) unsigned char H1f[64 * M1f::kLd];
     alignas(16) unsigned char H1t[32 * M1t::kLd];
@@ -63,17 +62,15 @@ struct SdfWeights {
     alignas(16) unsigned char HLf[BWD ? 16 : 32 * MLf::kLd];
     alignas(16) unsigned char HLt[BWD ? 64 * MLt::kLd : 16];
     // Row 0 of the last matrix (the SDF output), already split and packed as a lane holds it
-    // (Split<2, P> or HalfSplit<2>): [lane half][term][word 8 b + p]
-    alignas(16) uint32_t HLrow0[2][P][16];
-    alignas(16) float part[HALF ? 3 * 16 : 4];     // sixteen waves
+    // (Split<2, 3>): [lane half][term][word 8 b + p]
+    alignas(16) uint32_t HLrow0[2][3][16];
 };
 
 // Every matrix is fetched from global memory before the first is written to LDS, so the fetches
 // are in flight together; the copies cover every slot a product reads, so nothing is cleared.
-// exponent (HALF): H1, H2 and the last matrix are 2^exponent times theirs where they are fp16 terms.
-template <int D, int K, bool BWD, int THREADS, int PF = 3, bool HALF = false>
-__device__ void load_weights(SdfWeights<D, K, BWD, PF, HALF>& w, const SdfArgs& a, int (&exponent)[3]) {
-    typedef SdfWeights<D, K, BWD, PF, HALF> W;
+template <int D, int K, bool BWD, int THREADS, int PF = 3>
+__device__ void load_weights(SdfWeights<D, K, BWD, PF>& w, const SdfArgs& a) {
+    typedef SdfWeights<D, K, BWD, PF> W;
     const int tid = threadIdx.x;
     const float* __restrict__ H1 = a.H[0];
     const float* __restrict__ H2 = a.H[1];
@@ -98,26 +95,23 @@ __device__ void load_weights(SdfWeights<D, K, BWD, PF, HALF>& w, const SdfArgs& 
         row0[0] = HL[32 * b + neuron_of(2 * p, hh)];
         row0[1] = HL[32 * b + neuron_of(2 * p + 1, hh)];
     }
-    if constexpr (HALF) {
-        float largest[3] = {f1.largest(tid), K == 3 ? f2.largest(tid) : 0.f, fl.largest(tid)};
-        workgroup_exponents<3, THREADS / 64>(largest, w.part, exponent);
-        t1.store_half(w.H1t, tid, exponent[0]);
-        t2.store_half(w.H2t, tid, exponent[1]);
-        fl.store_half(w.HLf, tid, exponent[2]);
-    } else {
-        t1.store(w.H1t, tid);
-        t2.store(w.H2t, tid);
-        fl.store(w.HLf, tid);
-        tl.store(w.HLt, tid);
-    }
     f1.store(w.H1f, tid);
+    t1.store(w.H1t, tid);
     f2.store(w.H2f, tid);
+    t2.store(w.H2t, tid);
+    fl.store(w.HLf, tid);
+    tl.store(w.HLt, tid);
     if (tid < 32) {
-        uint32_t word[W::P];
-        if constexpr (HALF) half_pair(row0[0], row0[1], __builtin_amdgcn_ldexpf(1.f, exponent[2]), word);
-        else bf16_pair<W::P>(row0[0], row0[1], word);
+        typedef __bf16 bf2 __attribute__((ext_vector_type(2)));
+        typedef float f2 __attribute__((ext_vector_type(2)));
+        float x0 = row0[0], x1 = row0[1];
 #pragma unroll
-        for (int term = 0; term < W::P; ++term) w.HLrow0[tid >> 4][term][tid & 15] = word[term];
+        for (int term = 0; term < 3; ++term) {
+            const uint32_t word = __builtin_bit_cast(uint32_t, __builtin_convertvector(f2{x0, x1}, bf2));
+            w.HLrow0[tid >> 4][term][tid & 15] = word;
+            x0 -= __builtin_bit_cast(float, word << 16);
+            x1 -= __builtin_bit_cast(float, word & 0xffff0000u);
+        }
     }
     __syncthreads();
 }
@@ -266,8 +260,8 @@ __device__ __forceinline__ v16f apply_jac_regs(const JacRegs<D>& J, const float 
 // terms were split when the matrix was copied to LDS, and masking a packed pair is an AND with a
 // word that has ones in the halves whose mask bit is set (bit 16 b + r for register r of block b;
 // word p holds registers 2p and 2p + 1).  The same values as splitting the masked row.
-template <int P, class Vector>                 // Split<2, P> or HalfSplit<2>
-__device__ __forceinline__ void last_row_masked(const uint32_t (*row0)[P][16], uint32_t m, int h, Vector& out) {
+template <int P>
+__device__ __forceinline__ void last_row_masked(const uint32_t (*row0)[3][16], uint32_t m, int h, Split<2, P>& out) {
     const uint32_t one = opaque<1u>();
     uint32_t keep[16];
 #pragma unroll
@@ -309,12 +303,8 @@ __device__ __forceinline__ void store_rows16(float* __restrict__ dst, int64_t i,
 // The forward kernel runs 1024 threads per workgroup: its 90 KB of matrices are shared by sixteen wavefronts, four per
 // SIMD with 128 registers each, so that one wavefront's waits for memory, LDS and matrix results are filled by the others.
 // Nothing is requested ahead: two wavefronts per SIMD that prefetched the next encoding and this tile's Jacobian (221
-// registers) took 60 us at 2^18 points and 199 at 2^20, four took 51 and 168, at 32576 points 15.7 and 12.8.
-// Asked for no masks (rendering), the last layer and the reverse sweep, which decide none, take scaled fp16 terms, 48 instead of 96
-// matrix instructions: 2^18 points 45.4 -> 43.4 us, 2^20 points 177 -> 171 (another box than above; its streams of 732 bytes a
-// point are 4.5 TB/s), 131072 points 26.3 -> 24.8.  Not in a training step: d and the normal are inputs of the colour network,
-// where another last bit decides one ReLU mask in 10^7 the other way.  The first layer leaves out the k-step of levels that are
-// not read.
+// registers) took 60 us at 2^18 points and 199 at 2^20, four take 51 and 168 (4.5 TB/s: its streams are 732 bytes a point),
+// at 32576 points 15.7 and 12.8.  The first layer leaves out the k-step of levels that are not read.
 constexpr int kFwdThreads = 1024;
 constexpr int kFwdWaves = kFwdThreads / 64;
 constexpr int kValueThreads = 512;
@@ -436,16 +426,12 @@ __device__ __forceinline__ v16f apply_jac_tile(const float* __restrict__ jac, in
     return t;
 }
 
-// G: groups of four levels that are read (those with an active one); WIDE: from kTileMaxPoints points on; MASKS: writes the ReLU
-// masks
-template <int D, int K, int G, bool WIDE, bool MASKS>
+// G: groups of four levels that are read (those with an active one); WIDE: from kTileMaxPoints points on
+template <int D, int K, int G, bool WIDE>
 __global__ __launch_bounds__(kFwdThreads) void sdf_fwd_kernel(SdfArgs a) {
-    typedef SdfWeights<D, K, false, 3, !MASKS> W;
-    typedef std::conditional_t<MASKS, Split<2, 3>, HalfSplit<2>> Vector;
-    __shared__ W w;
-    int kw[3] = {0, 0, 0};
-    load_weights<D, K, false, kFwdThreads, 3, !MASKS>(w, a, kw);
-    constexpr int KS1 = W::KS1;
+    __shared__ SdfWeights<D, K, false> w;
+    load_weights<D, K, false, kFwdThreads>(w, a);
+    constexpr int KS1 = SdfWeights<D, K, false>::KS1;
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);   // the same for all lanes: keeps tile indices and addresses scalar
     const int j = lane & 31, h = lane >> 5;
@@ -457,28 +443,24 @@ __global__ __launch_bounds__(kFwdThreads) void sdf_fwd_kernel(SdfArgs a) {
         v16f x0[1] = {load_levels_tile<8 * G, WIDE>(a.enc, a.n, tile * 32, a.active_levels, j, h)};
         v16f a1[2], yv[1];
         Split<1, 3> px;
-        Vector pv;
+        Split<2, 3> pv;
         split(x0, px);
         matvec_split<2, (8 * G + 15) / 16, 3, 3, KS1>(w.H1f, px, a1, lane);
         const uint32_t m1 = relu_mask<2>(a1);
         uint32_t m_last = m1;
+        split(a1, pv);
         if (K == 3) {
-            Split<2, 3> p1;
-            split(a1, p1);
-            matvec_split<2, 4, 3, 3>(w.H2f, p1, a1, lane);
-            m_last = relu_mask<2>(a1);
+            v16f a2[2];
+            matvec_split<2, 4, 3, 3>(w.H2f, pv, a2, lane);
+            m_last = relu_mask<2>(a2);
+            split(a2, pv);
         }
-        // from here on no mask of this network depends on the values: fp16 terms, the vector times 2^k (k = 0 with masks)
-        int k = split_scaled(a1, pv);
-        matvec_scaled<1>(w.HLf, pv, yv, lane);
+        matvec_split<1, 4, 3, 3>(w.HLf, pv, yv, lane);
         if (valid) {
             float4* row = lane_address(reinterpret_cast<float4*>(a.y) + tile * 128, 64u * j + 16u * h);
-            float y[8];
-#pragma unroll
-            for (int r = 0; r < 8; ++r) y[r] = MASKS ? yv[0][r] : __builtin_amdgcn_ldexpf(yv[0][r], -(k + kw[2]));
-            row[0] = make_float4(y[0], y[1], y[2], y[3]);
-            row[2] = make_float4(y[4], y[5], y[6], y[7]);
-            if (MASKS) {
+            row[0] = make_float4(yv[0][0], yv[0][1], yv[0][2], yv[0][3]);
+            row[2] = make_float4(yv[0][4], yv[0][5], yv[0][6], yv[0][7]);
+            if (a.masks) {
                 uint32_t* words = a.masks + tile * 64;
                 *lane_address(words, 8u * j + 4u * h) = m1;
                 if (K == 3) *lane_address(words + 2 * a.n, 8u * j + 4u * h) = m_last;
@@ -487,19 +469,13 @@ __global__ __launch_bounds__(kFwdThreads) void sdf_fwd_kernel(SdfArgs a) {
         // reverse sweep for dd/de
         v16f s1[2];
         last_row_masked(w.HLrow0, m_last, h, pv);
-        int e = kw[2] + kw[0];
         if (K == 3) {
-            matvec_scaled<2>(w.H2t, pv, s1, lane);
+            matvec_split<2, 4, 3, 3>(w.H2t, pv, s1, lane);
             apply_mask<2>(s1, m1);
-            k = split_scaled(s1, pv);
-            e += kw[1] + k;
+            split(s1, pv);
         }
         v16f qv[1];
-        matvec_scaled<1>(w.H1t, pv, qv, lane);
-        if (!MASKS) {
-#pragma unroll
-            for (int r = 0; r < D / 2; ++r) qv[0][r] = __builtin_amdgcn_ldexpf(qv[0][r], -e);
-        }
+        matvec_split<1, 4, 3, 3>(w.H1t, pv, qv, lane);
         // dd/de is read next by the scatter-add, four kernels later: for a batch whose per-point arrays
         // exceed the caches it is written with non-temporal stores (25 us of the step at 2^20 points; at
         // 2^18 points the cached store is the faster one)
@@ -519,27 +495,24 @@ __global__ __launch_bounds__(kFwdThreads) void sdf_fwd_kernel(SdfArgs a) {
 // ------------------------------------------------------------------------------------------
 // The SDF value alone (a refresh of the occupancy grid wants no normals): the forward kernel's arithmetic without its
 // reverse sweep, 128 bytes of input a point instead of 512 and 4 of output instead of 220.  Four wavefronts per SIMD.
-// 2^20 points: 72.8 us with bf16 terms in every layer, 68.8 with fp16 terms in the last; the forward kernel 171.
+// 2^20 points: 73 us, the forward kernel 177.
 template <int D, int K>
 struct SdfValueWeights {
     typedef SplitMatrix<D / 16, 3> M1;
     typedef SplitMatrix<4, 3> M2;
     alignas(16) unsigned char H1[64 * M1::kLd];
     alignas(16) unsigned char H2[K == 3 ? 64 * M2::kLd : 16];
-    typedef SplitMatrix<4, 2> ML;
-    alignas(16) unsigned char HL[32 * ML::kLd];
-    alignas(16) float part[kValueWaves];
+    alignas(16) unsigned char HL[32 * M2::kLd];
 };
 
 template <int D, int K>
 __global__ __launch_bounds__(kValueThreads, 4) void sdf_value_kernel(SdfArgs a) {
     typedef SdfValueWeights<D, K> W;
     __shared__ W w;
-    int kw[1];
     {
         typename W::M1::template Fill<64, kValueThreads, false> f1;
         typename W::M2::template Fill<K == 3 ? 64 : 0, kValueThreads, false> f2;
-        typename W::ML::template Fill<32, kValueThreads, false> fl;
+        typename W::M2::template Fill<32, kValueThreads, false> fl;
         const float* __restrict__ H1 = a.H[0];
         const float* __restrict__ H2 = a.H[1];
         const float* __restrict__ HL = a.H[K - 1];
@@ -548,9 +521,7 @@ __global__ __launch_bounds__(kValueThreads, 4) void sdf_value_kernel(SdfArgs a) 
         fl.load(threadIdx.x, [&](int o, int i) { return o < 16 ? HL[o * 64 + i] : 0.f; });
         f1.store(w.H1, threadIdx.x);
         f2.store(w.H2, threadIdx.x);
-        float largest[1] = {fl.largest(threadIdx.x)};
-        workgroup_exponents<1, kValueWaves>(largest, w.part, kw);
-        fl.store_half(w.HL, threadIdx.x, kw[0]);
+        fl.store(w.HL, threadIdx.x);
         __syncthreads();
     }
     const int lane = threadIdx.x & 63;
@@ -563,20 +534,18 @@ __global__ __launch_bounds__(kValueThreads, 4) void sdf_value_kernel(SdfArgs a) 
         v16f x0[1] = {load_levels<D>(a.enc, a.n, i, valid, a.active_levels, h)};
         v16f z[2], yv[1];
         Split<1, 3> px;
-        HalfSplit<2> pv;
+        Split<2, 3> pv;
         split(x0, px);
         matvec_split<2, D / 16, 3, 3>(w.H1, px, z, lane);
         relu<2>(z);
+        split(z, pv);
         if (K == 3) {
-            Split<2, 3> p1;
-            split(z, p1);
-            matvec_split<2, 4, 3, 3>(w.H2, p1, z, lane);
+            matvec_split<2, 4, 3, 3>(w.H2, pv, z, lane);
             relu<2>(z);
+            split(z, pv);
         }
-        const int k = half_exponent<2>(z);
-        half_split(z, k, pv);
-        matvec_half<1, 4>(w.HL, pv, yv, lane);
-        if (valid && h == 0) a.y[i] = __builtin_amdgcn_ldexpf(yv[0][0], -(k + kw[0]));
+        matvec_split<1, 4, 3, 3>(w.HL, pv, yv, lane);
+        if (valid && h == 0) a.y[i] = yv[0][0];
     }
 }
 
@@ -593,8 +562,7 @@ template <int D, int K>
 __global__ __launch_bounds__(kThreads) void sdf_bwd_kernel(SdfArgs a) {
     __shared__ SdfBwdSmem<D, K> sm;
     SdfWeights<D, K, true>& w = sm.w;
-    int unused[3];
-    load_weights<D, K, true, kThreads>(w, a, unused);
+    load_weights<D, K, true, kThreads>(w, a);
     constexpr int KS1 = SdfWeights<D, K, true>::KS1;
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);   // the same for all lanes: keeps tile indices and addresses scalar
@@ -938,8 +906,7 @@ __device__ __forceinline__ void sdf_second_order(const SdfArgs& a, const SdfWeig
 template <int D, int K, int G, bool WIDE>
 __global__ __launch_bounds__(kPairThreads) void sdf_bwd_pair_kernel(SdfArgs a) {
     __shared__ SdfPairSmem<D, K> sm;
-    int unused[3];
-    load_weights<D, K, true, kPairThreads, 2>(sm.w, a, unused);
+    load_weights<D, K, true, kPairThreads, 2>(sm.w, a);
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);   // the same for all lanes: keeps tile indices and addresses scalar
     const int slot = wave % kPairs;
@@ -1007,12 +974,12 @@ typedef void (*SdfKernel)(SdfArgs);
 // one variant for all, levels that the training step leaves unwritten were fetched (half of the levels active, 2^20 points,
 // forward and backward: 169 and 251 us, now 155 and 243); picking level 0 for them in scalar registers, or a branch round
 // every load, cost up to 6 % forward and 8 % backward with all levels active.
-template <int D, int K, bool MASKS>
+template <int D, int K>
 SdfKernel fwd_kernel(const SdfArgs& a) {
-    if (a.n >= kTileMaxPoints) return sdf_fwd_kernel<D, K, D / 8, true, MASKS>;
-    if (a.active_levels <= 4) return sdf_fwd_kernel<D, K, 1, false, MASKS>;
-    if (D == 16 || a.active_levels <= 8) return sdf_fwd_kernel<D, K, 2, false, MASKS>;
-    return a.active_levels <= 12 ? sdf_fwd_kernel<D, K, D == 32 ? 3 : 2, false, MASKS> : sdf_fwd_kernel<D, K, D / 8, false, MASKS>;
+    if (a.n >= kTileMaxPoints) return sdf_fwd_kernel<D, K, D / 8, true>;
+    if (a.active_levels <= 4) return sdf_fwd_kernel<D, K, 1, false>;
+    if (D == 16 || a.active_levels <= 8) return sdf_fwd_kernel<D, K, 2, false>;
+    return a.active_levels <= 12 ? sdf_fwd_kernel<D, K, D == 32 ? 3 : 2, false> : sdf_fwd_kernel<D, K, D / 8, false>;
 }
 
 template <int D, int K>
@@ -1026,7 +993,7 @@ SdfKernel bwd_kernel(const SdfArgs& a) {
 template <int D, int K>
 int run_fwd(const SdfArgs& a, hipStream_t st) {
     const int64_t tiles = (a.n + 31) / 32;
-    const SdfKernel kernel = a.masks ? fwd_kernel<D, K, true>(a) : fwd_kernel<D, K, false>(a);
+    const SdfKernel kernel = fwd_kernel<D, K>(a);
     const int blocks = persistent_blocks((const void*)kernel, kFwdThreads, tiles);
     hipLaunchKernelGGL(kernel, dim3(blocks), dim3(kFwdThreads), 0, st, a);
     return check_launch("sdf forward");
@@ -1066,7 +1033,7 @@ int run_bwd(const SdfArgs& a, hipStream_t st) {
 // kernel serves every layer.
 //   forward run:   a_l = G_l H_l a_{l-1}  (six-product arithmetic, writes the mask words)
 //                  t_l = G_l H_l t_{l-1}  (WITH_T; t_0 = (de/dx) dL/dn)
-//   reverse:       S_{l-1} = (H_l^T S_l) G_{l-1}, down to dd/de and the normal, all layers in one launch
+//   reverse run:   S_{l-1} = (H_l^T S_l) G_{l-1}, down to dd/de and the normal
 //   gradient run:  dH_l += delta_l a_{l-1}^T + S_l^T t_{l-1}^T
 //                  S_{l-1} as above, delta_{l-1} = G_{l-1} H_l^T delta_l
 // with S_K = the unit row of the SDF output and delta_K = dL/d(d,g): Theorem 1 and Eqs. 7-8 as in

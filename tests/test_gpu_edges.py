@@ -510,3 +510,50 @@ def test_colour_forward_whatever_the_scale_of_a_neuron(masks):
         kept = torch.zeros(2, n, 2, dtype=torch.int32, device="cuda") if masks else None
         nb.color_fwd(c, cuda(pos), cuda(nrm), cuda(dirs), cuda(y), [cuda(w) for w in mats], n, got[-1], masks=kept)
     assert torch.equal(*got)
+
+
+@pytest.mark.parametrize("levels,hidden,masks,row0", [(16, 2, False, -24), (16, 2, True, -24), (16, 1, False, 30), (8, 2, False, -24), (8, 1, False, -40)])
+def test_sdf_forward_whatever_the_scale_of_a_neuron(levels, hidden, masks, row0):
+    """As for the colours: hidden neurons scaled by powers of two change no bit of the values, dd/de and the normals, and
+    neither does the size of the SDF's row beside the fifteen feature rows (undone afterwards, exactly)."""
+    import dataclasses
+    n, rng = 1031, np.random.default_rng(levels + hidden)
+    cfg = wl.make_config(2 if levels == 16 else 1)
+    cfg = dataclasses.replace(cfg, sdf_dims=[2 * levels] + [64] * hidden + [16])
+    c = nb.make_config(cfg)
+    H = [(rng.normal(size=(o_, i)) * (2.0 / i) ** 0.5).astype(np.float32) for i, o_ in zip(cfg.sdf_dims, cfg.sdf_dims[1:])]
+    other = without_neuron_scales(rng, H)
+    other[-1][0] = np.ldexp(other[-1][0], row0)
+    pos, enc, jac = (cuda(rng.normal(size=k).astype(np.float32)) for k in ((n, 3), (levels, n, 2), (levels, 3, n, 2)))
+    pos.sigmoid_()
+    tables = cuda(rng.normal(size=(levels, cfg.table_size, 2)).astype(np.float32) * 0.1)
+    if cfg.table_dtype == "f16":
+        tables = tables.half()
+    found = []
+    for mats, back in ((H, 0), (other, -row0)):
+        y, q, normal, sdf = (torch.empty(*k, device="cuda") for k in ((n, 16), (levels, n, 2), (n, 3), (n,)))
+        kept = torch.zeros(2, n, 2, dtype=torch.int32, device="cuda") if masks else None
+        Hg = [cuda(m) for m in mats]
+        nb.sdf_fwd_grad(c, enc, jac, Hg, n, y, q, normal, masks=kept)
+        nb.sdf_values(c, pos, tables, Hg, n, torch.empty(levels * n * 2, device="cuda"), sdf)
+        found.append([y[:, 0] * 2.0 ** back, y[:, 1:], q * 2.0 ** back, normal * 2.0 ** back, sdf * 2.0 ** back])
+    for a, b in zip(*found):
+        assert torch.equal(a, b) and bool(a.any()) and bool(torch.isfinite(a).all())
+
+
+@pytest.mark.parametrize("levels,hidden", [(16, 2), (8, 1)])
+def test_sdf_forward_is_the_same_with_and_without_masks(levels, hidden):
+    """Whether the masks are wanted changes no bit of the results."""
+    import dataclasses
+    n = 257 * 32 + 7
+    cfg = wl.make_config(2 if levels == 16 else 1)
+    cfg = dataclasses.replace(cfg, sdf_dims=[2 * levels] + [64] * hidden + [16])
+    gen = torch.Generator(device="cuda").manual_seed(levels)
+    randn = lambda *shape: torch.randn(*shape, device="cuda", generator=gen)
+    H = [randn(o_, i) * (2.0 / i) ** 0.5 for i, o_ in zip(cfg.sdf_dims, cfg.sdf_dims[1:])]
+    enc, jac = randn(levels, n, 2), randn(levels, 3, n, 2)
+    found = []
+    for kept in (None, torch.zeros(2, n, 2, dtype=torch.int32, device="cuda")):
+        found.append([torch.empty(*k, device="cuda") for k in ((n, 16), (levels, n, 2), (n, 3))])
+        nb.sdf_fwd_grad(nb.make_config(cfg), enc, jac, H, n, *found[-1], masks=kept)
+    assert all(torch.equal(a, b) for a, b in zip(*found))
