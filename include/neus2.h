@@ -16,7 +16,6 @@
  *    (six term products) wherever a result is a forward output or decides a ReLU mask, which is
  *    as accurate as an fp32 product (about 2e-7 relative on the outputs); two terms (three term
  *    products) in the adjoint sweeps and weight gradients (about 1e-5 relative on the gradients).
- *    (dd/de and the normal of neus2_sdf_deep_fwd_grad: two fp16 terms, scaled, three products.)
  *  - n is the number of sample points; for ray workloads n = rays * samples_per_ray and a
  *    ray's samples are consecutive.
  *

@@ -221,88 +221,6 @@ __device__ __forceinline__ void split(const v16f* v, Split<NB, P>& out) {
         }
 }
 
-// ---- vectors as two fp16 terms ------------------------------------------------------------------
-// x 2^k = hi + lo, k chosen per point such that the vector's largest magnitude lies in [2^14, 2^15): 11 bits and the sign in
-// each term, so the remainder is at most 2^-23 of x (and 0 three times out of four) for every element down to 2^-17 of
-// the largest, and below 2^-39 of the largest for those that are smaller still.  Three products hi*hi, hi*lo, lo*hi then are as
-// accurate as an fp32 product, where bf16 terms take three per factor and six products: half the matrix instructions, half
-// the vector instructions of a split (2 to 2.5 an element against 5.5) and two thirds of the LDS words of the matrices.
-template <int NB>
-struct HalfSplit {
-    uint32_t t[2][NB][8];
-};
-
-typedef _Float16 h8 __attribute__((ext_vector_type(8)));
-
-// the value of the lane that holds the other half of the point, together with this lane's
-__device__ __forceinline__ float larger_of_halves(float x) {
-    const uint32_t w = __builtin_bit_cast(uint32_t, x);
-    const auto pair = __builtin_amdgcn_permlane32_swap(w, w, false, false);
-    const uint32_t a = pair[0], b = pair[1];
-    return fmaxf(__builtin_bit_cast(float, a), __builtin_bit_cast(float, b));
-}
-
-// x of the lane that the permutation CONTROL names (within 16 lanes)
-template <int CONTROL>
-__device__ __forceinline__ float permuted(float x) {
-    return __builtin_bit_cast(float, __builtin_amdgcn_mov_dpp(__builtin_bit_cast(int, x), CONTROL, 0xf, 0xf, true));
-}
-
-// k of a largest magnitude; what 2^k does not bring up to 2^14 (below 2^-112) counts as small.  0, infinity and NaN get some k
-// (an infinity becomes a NaN in the split: inf - inf).
-__device__ __forceinline__ int half_exponent(float largest) { return min(15 - __builtin_amdgcn_frexp_expf(largest), 126); }
-
-template <int NB>
-__device__ __forceinline__ int half_exponent(const v16f* v) {
-    float m = 0.f;
-#pragma unroll
-    for (int b = 0; b < NB; ++b)
-#pragma unroll
-        for (int r = 0; r < 16; r += 2) m = fmaxf(fmaxf(fabsf(v[b][r]), fabsf(v[b][r + 1])), m);
-    return half_exponent(larger_of_halves(m));
-}
-
-// two values times s as a word of each term
-__device__ __forceinline__ void half_pair(float x0, float x1, float s, uint32_t (&word)[2]) {
-    typedef _Float16 h2 __attribute__((ext_vector_type(2)));
-    x0 *= s; x1 *= s;
-    const h2 hi = {(_Float16)x0, (_Float16)x1};
-    const h2 lo = {(_Float16)(x0 - (float)hi[0]), (_Float16)(x1 - (float)hi[1])};
-    word[0] = __builtin_bit_cast(uint32_t, hi);
-    word[1] = __builtin_bit_cast(uint32_t, lo);
-}
-
-// two values as a word of each of P bf16 terms
-template <int P>
-__device__ __forceinline__ void bf16_pair(float x0, float x1, uint32_t (&word)[P]) {
-    typedef __bf16 bf2 __attribute__((ext_vector_type(2)));
-    typedef float f2 __attribute__((ext_vector_type(2)));
-#pragma unroll
-    for (int term = 0; term < P; ++term) {
-        word[term] = __builtin_bit_cast(uint32_t, __builtin_convertvector(f2{x0, x1}, bf2));
-        x0 -= __builtin_bit_cast(float, word[term] << 16);
-        x1 -= __builtin_bit_cast(float, word[term] & 0xffff0000u);
-    }
-}
-
-// zero (opaque) keeps the compiler at one instruction per element and term: scale, subtract and round in a mixed-precision
-// multiply-add that writes one half of the word.
-template <int NB>
-__device__ __forceinline__ void half_split(const v16f* v, int k, HalfSplit<NB>& out) {
-    typedef _Float16 h2 __attribute__((ext_vector_type(2)));
-    const float s = __builtin_amdgcn_ldexpf(1.f, k), zero = __builtin_bit_cast(float, opaque<0u>());
-#pragma unroll
-    for (int b = 0; b < NB; ++b)
-#pragma unroll
-        for (int p = 0; p < 8; ++p) {
-            const float x0 = v[b][2 * p], x1 = v[b][2 * p + 1];
-            const h2 hi = {(_Float16)__builtin_fmaf(x0, s, zero), (_Float16)__builtin_fmaf(x1, s, zero)};
-            const h2 lo = {(_Float16)__builtin_fmaf(x0, s, -(float)hi[0]), (_Float16)__builtin_fmaf(x1, s, -(float)hi[1])};
-            out.t[0][b][p] = __builtin_bit_cast(uint32_t, hi);
-            out.t[1][b][p] = __builtin_bit_cast(uint32_t, lo);
-        }
-}
-
 // Write the first two terms to a per-wave transposed tile, one word [hi | mid] per element.
 template <int NB, int P>
 __device__ __forceinline__ void stage_split(uint32_t* __restrict__ tile, const Split<NB, P>& x, int j, int h) {
@@ -523,39 +441,6 @@ struct SplitMatrix {
                 for (int s = 0; s < 8; ++s) v[k][s] = get(r, c0 + 8 * (s >> 2) + (s & 3));
             }
         }
-        __device__ __forceinline__ float largest(int tid) const {
-            float m = 0.f;
-#pragma unroll
-            for (int k = 0; k < kPer; ++k) {
-                if (kUnits % THREADS != 0 && tid + k * THREADS >= kUnits) break;
-#pragma unroll
-                for (int s = 0; s < 8; ++s) m = fmaxf(m, fabsf(v[k][s]));
-            }
-            return m;
-        }
-        // as two fp16 terms of the elements times 2^exponent
-        __device__ __forceinline__ void store_half(unsigned char* __restrict__ W, int tid, int exponent) const {
-            static_assert(PS == 2, "two terms");
-            const float scale = __builtin_amdgcn_ldexpf(1.f, exponent);
-#pragma unroll
-            for (int k = 0; k < kPer; ++k) {
-                const int unit = tid + k * THREADS;
-                if (kUnits % THREADS != 0 && unit >= kUnits) break;
-                int r, ug;
-                decode(unit, r, ug);
-                u32x4 hi, lo;
-#pragma unroll
-                for (int p = 0; p < 4; ++p) {
-                    uint32_t word[2];
-                    half_pair(v[k][2 * p], v[k][2 * p + 1], scale, word);
-                    hi[p] = word[0];
-                    lo[p] = word[1];
-                }
-                u32x4* dst = reinterpret_cast<u32x4*>(W + r * kLd + ug * (PS * 16));
-                dst[0] = hi;
-                dst[1] = lo;
-            }
-        }
         __device__ __forceinline__ void store(unsigned char* __restrict__ W, int tid) const {
             typedef __bf16 bf2 __attribute__((ext_vector_type(2)));
             typedef float f2 __attribute__((ext_vector_type(2)));
@@ -649,90 +534,6 @@ __device__ __forceinline__ void matvec_split(const unsigned char* __restrict__ W
     }
 #pragma unroll
     for (int mb = 0; mb < MB; ++mb) z[mb] = acc[mb];
-}
-
-// The same with two fp16 terms on both sides (SplitMatrix<KSTEPS, 2> filled by store_half): z comes out times 2^(k of x + k of
-// W).  The small products of an output block come first and hi*hi last, so that only the last KSTEPS additions round at the
-// size of the result (dd/de of the SDF network, relative error against 64 bits, median: 1.4e-7; the products of a k-step side
-// by side 1.8e-7; six products of bf16 terms side by side 1.9e-7).
-// Not for what decides a ReLU mask: there the bf16 terms stay, whose masks the backward kernels without given masks repeat.
-template <int MB, int KSTEPS, int NB>
-__device__ __forceinline__ void matvec_half(const unsigned char* __restrict__ W, const HalfSplit<NB>& x, v16f* z, int lane) {
-    static_assert(KSTEPS <= 2 * NB, "the vector is shorter than the matrix is wide");
-    constexpr int kLd = SplitMatrix<KSTEPS, 2>::kLd;
-    constexpr int kTotal = KSTEPS * MB;
-    const unsigned char* base = W + (lane & 31) * kLd + (lane >> 5) * 32;
-    auto address = [&](int t) -> const u32x4* {
-        return reinterpret_cast<const u32x4*>(base + 32 * (t / KSTEPS) * kLd + (t % KSTEPS) * 64);
-    };
-    u32x4 cur[2] = {address(0)[0], address(0)[1]};
-    v16f acc[MB];
-#pragma unroll
-    for (int mb = 0; mb < MB; ++mb) acc[mb] = zero16();
-    h8 hi[KSTEPS];
-#pragma unroll
-    for (int t = 0; t < kTotal; ++t) {
-        const int mb = t / KSTEPS, u = t % KSTEPS;
-        h8 b[2];
-#pragma unroll
-        for (int p = 0; p < 2; ++p) {
-            u32x4 v;
-#pragma unroll
-            for (int e = 0; e < 4; ++e) v[e] = x.t[p][u >> 1][4 * (u & 1) + e];
-            b[p] = __builtin_bit_cast(h8, v);
-        }
-        u32x4 nxt[2] = {cur[0], cur[1]};
-        if (t + 1 < kTotal) { nxt[0] = address(t + 1)[0]; nxt[1] = address(t + 1)[1]; }
-        hi[u] = __builtin_bit_cast(h8, cur[0]);
-        const h8 al = __builtin_bit_cast(h8, cur[1]);
-        acc[mb] = __builtin_amdgcn_mfma_f32_32x32x16_f16(al, b[0], acc[mb], 0, 0, 0);
-        acc[mb] = __builtin_amdgcn_mfma_f32_32x32x16_f16(hi[u], b[1], acc[mb], 0, 0, 0);
-        if (u == KSTEPS - 1) {
-#pragma unroll
-            for (int w = 0; w < KSTEPS; ++w) {
-                u32x4 v;
-#pragma unroll
-                for (int e = 0; e < 4; ++e) v[e] = x.t[0][w >> 1][4 * (w & 1) + e];
-                acc[mb] = __builtin_amdgcn_mfma_f32_32x32x16_f16(hi[w], __builtin_bit_cast(h8, v), acc[mb], 0, 0, 0);
-            }
-        }
-        cur[0] = nxt[0]; cur[1] = nxt[1];
-        __builtin_amdgcn_sched_barrier(0);
-    }
-#pragma unroll
-    for (int mb = 0; mb < MB; ++mb) z[mb] = acc[mb];
-}
-
-// Largest magnitude of COUNT matrices over a workgroup of WAVES waves, each thread bringing its own part: one barrier.
-// part: COUNT * WAVES floats of LDS that are not written again.
-template <int COUNT, int WAVES>
-__device__ __forceinline__ void workgroup_exponents(float (&largest)[COUNT], float* __restrict__ part, int (&exponent)[COUNT]) {
-#pragma unroll
-    for (int k = 0; k < COUNT; ++k) {
-        float m = largest[k];
-        // within a row of 16 lanes by lane permutations of the vector unit (pairs, quads, mirrored eights, mirrored rows), then
-        // across rows and halves: through LDS (ds_bpermute) the five steps were 0.4 us of the kernel's start
-        m = fmaxf(m, permuted<0xB1>(m));
-        m = fmaxf(m, permuted<0x4E>(m));
-        m = fmaxf(m, permuted<0x141>(m));
-        m = fmaxf(m, permuted<0x140>(m));
-        {
-            const uint32_t w = __builtin_bit_cast(uint32_t, m);
-            const auto pair = __builtin_amdgcn_permlane16_swap(w, w, false, false);
-            const uint32_t a = pair[0], b = pair[1];
-            m = fmaxf(__builtin_bit_cast(float, a), __builtin_bit_cast(float, b));
-        }
-        m = larger_of_halves(m);
-        if ((threadIdx.x & 63) == 0) part[k * WAVES + (threadIdx.x >> 6)] = m;
-    }
-    __syncthreads();
-#pragma unroll
-    for (int k = 0; k < COUNT; ++k) {
-        float m = 0.f;
-#pragma unroll
-        for (int w = 0; w < WAVES; ++w) m = fmaxf(m, part[k * WAVES + w]);
-        exponent[k] = __builtin_amdgcn_readfirstlane(half_exponent(m));
-    }
 }
 
 // Weight gradient of a factor Z with at most 16 columns (the 16-wide output adjoint, the 3

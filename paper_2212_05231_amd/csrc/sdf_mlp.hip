@@ -1050,7 +1050,7 @@ constexpr int kDeepGradRun = 2;                    // of a gradient run: their s
 struct DeepArgs {
     const float* H[NEUS2_DEEP_MAX_MATS];
     int n_mats, enc_dim;
-    int first, count;                      // layers first .. first + count - 1 (numbered from 0); gradient runs start at the last
+    int first, count;                      // layers first .. first + count - 1 (numbered from 0); reverse kinds start at the last
     int64_t n, vec;                        // points; floats of a workspace vector
     float* ws;
     const float* enc; const float* jac; const float* d_normal; const float* d_y;
@@ -1173,83 +1173,58 @@ __global__ __launch_bounds__(kDeepThreads) void deep_forward_kernel(DeepArgs a) 
     }
 }
 
-// dd/de and the normal (Eq. 2): S downwards from row 0 of the last matrix, all layers in one launch: the transposed matrices of
-// eight layers fit LDS as two fp16 terms, scaled (they decide no mask and are as accurate as fp32), and a tile's vector stays in
-// registers.  Sixteen wavefronts share them, four per SIMD.  Six bf16 products in two runs of layers with a vector handed on
-// through the workspace took 88 us at eight hidden layers and 2^17 points, this takes 44 (two hidden layers: 24, 14).
-constexpr int kReverseThreads = 1024;
-constexpr int kReverseWaves = kReverseThreads / 64;
-constexpr int kReverseMats = NEUS2_DEEP_MAX_MATS - 1;
-
+// dd/de and the normal (Eq. 2): S downwards from row 0 of the last matrix, three terms per factor (compared at forward tolerance),
+// the transposed matrices of a run in LDS.  Forward call at 2^17 points: eight hidden layers 152 -> 141 us against a product with
+// the last matrix too (two runs either way), six 119 -> 100 (one run instead of two), two 46 -> 40; sixteen wavefronts
+// instead of eight spill 8 registers: 138, 100 and 41.  (Two scaled fp16 terms, whose eight matrices fit LDS at once, took 107, 82 and 38
+// but lose the small elements of a vector or a matrix beside large ones.)
 struct DeepReverseSmem {
-    alignas(16) unsigned char mats[kReverseMats * 64 * SplitMatrix<4, 2>::kLd];
+    alignas(16) unsigned char mats[kDeepRun * 64 * SplitMatrix<4, 3>::kLd];
     alignas(16) float row0[2][32];                          // [lane half][16 b + r]
-    alignas(16) float part[kReverseMats * kReverseWaves];
 };
 
-__global__ __launch_bounds__(kReverseThreads) void deep_reverse_kernel(DeepArgs a) {
-    constexpr int kMatrix = 64 * SplitMatrix<4, 2>::kLd;
+__global__ __launch_bounds__(kDeepThreads) void deep_reverse_kernel(DeepArgs a) {
+    constexpr int kMatrix = 64 * SplitMatrix<4, 3>::kLd;
     __shared__ DeepReverseSmem sm;
-    int exponents = 0;                                      // sum over the matrices
-    {
-        typename SplitMatrix<4, 2>::template Fill<64, kReverseThreads, true> f[kReverseMats];
-        float largest[kReverseMats];
-        int exponent[kReverseMats];
-#pragma unroll
-        for (int l = 0; l < kReverseMats; ++l) {
-            largest[l] = 0.f;
-            if (l >= a.n_mats - 1) continue;
-            const int id = a.in_dim(l);
-            const float* __restrict__ W = a.H[l];
-            f[l].load(threadIdx.x, [&](int i, int o) { return i < id ? W[o * id + i] : 0.f; });
-        }
-        if (threadIdx.x < 64) {
-            const int k = threadIdx.x & 31;
-            sm.row0[threadIdx.x >> 5][k] = a.H[a.n_mats - 1][32 * (k >> 4) + neuron_of(k & 15, threadIdx.x >> 5)];
-        }
-#pragma unroll
-        for (int l = 0; l < kReverseMats; ++l)
-            if (l < a.n_mats - 1) largest[l] = f[l].largest(threadIdx.x);
-        workgroup_exponents<kReverseMats, kReverseWaves>(largest, sm.part, exponent);
-#pragma unroll
-        for (int l = 0; l < kReverseMats; ++l) {
-            if (l >= a.n_mats - 1) continue;
-            f[l].store_half(sm.mats + l * kMatrix, threadIdx.x, exponent[l]);
-            exponents += exponent[l];
-        }
-        __syncthreads();
+    const bool from_top = a.first == a.n_mats - 2;
+    if (from_top && threadIdx.x < 64) {
+        const int k = threadIdx.x & 31;
+        sm.row0[threadIdx.x >> 5][k] = a.H[a.n_mats - 1][32 * (k >> 4) + neuron_of(k & 15, threadIdx.x >> 5)];
     }
+    deep_matrices<3, kDeepRun, true>(a, a.first, -1, a.count, sm.mats);
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int j = lane & 31, h = lane >> 5;
     const int64_t tiles = (a.n + 31) / 32;
-    for (int64_t tile = (int64_t)wave * gridDim.x + blockIdx.x; tile < tiles; tile += (int64_t)gridDim.x * kReverseWaves) {
+    for (int64_t tile = (int64_t)wave * gridDim.x + blockIdx.x; tile < tiles; tile += (int64_t)gridDim.x * kDeepWaves) {
         const int64_t i = tile * 32 + j;
         const bool valid = i < a.n;
         v16f s[2];
+        if (from_top) {
 #pragma unroll
-        for (int b = 0; b < 2; ++b)
+            for (int b = 0; b < 2; ++b)
 #pragma unroll
-            for (int r = 0; r < 16; ++r) s[b][r] = sm.row0[h][16 * b + r];
-        apply_mask<2>(s, a.masks(a.n_mats - 2, tile)[lane]);
-        int e = exponents;
+                for (int r = 0; r < 16; ++r) s[b][r] = sm.row0[h][16 * b + r];
+            apply_mask<2>(s, a.masks(a.n_mats - 2, tile)[lane]);
+        } else {
+            load_lane<2>(a.passed(0), tile, lane, s);
+        }
+        Split<2, 3> ps;
+        const int products = a.first - a.count >= 0 ? a.count : a.count - 1;       // the first layer's has another end
 #pragma unroll 1
-        for (int l = a.n_mats - 2; l > 0; --l) {
-            const uint32_t m = a.masks(l - 1, tile)[lane];
-            HalfSplit<2> ps;
-            const int k = half_exponent<2>(s);
-            half_split(s, k, ps);
-            e += k;
-            matvec_half<2, 4>(sm.mats + l * kMatrix, ps, s, lane);
+        for (int k = 0; k < products; ++k) {
+            const uint32_t m = a.masks(a.first - k - 1, tile)[lane];
+            split(s, ps);
+            matvec_split<2, 4, 3, 3>(sm.mats + k * kMatrix, ps, s, lane);
             apply_mask<2>(s, m);
         }
-        HalfSplit<2> ps;
-        const int k = half_exponent<2>(s);
-        half_split(s, k, ps);
+        if (products == a.count) {
+            store_lane<2>(a.passed(0), tile, lane, s);
+            continue;
+        }
         v16f de[1];
-        matvec_half<1, 4>(sm.mats, ps, de, lane);
-#pragma unroll
-        for (int r = 0; r < 16; ++r) de[0][r] = __builtin_amdgcn_ldexpf(de[0][r], -(e + k));
+        split(s, ps);
+        matvec_split<1, 4, 3, 3>(sm.mats + products * kMatrix, ps, de, lane);
         store_levels_active(a.q, a.n, i, valid, a.enc_dim / 2, h, de[0]);
         float nrm[3];
         contract_jac<32>(a.jac, a.n, i, valid, a.enc_dim / 2, h, de[0], nrm);
@@ -1450,8 +1425,12 @@ int launch_sdf_deep_fwd(int n_mats, int enc_dim, const float* enc, const float* 
         a.first = start[r]; a.count = start[r + 1] - start[r];
         deep_launch(deep_forward_kernel<false>, a, tiles, st);
     }
-    const int blocks = persistent_blocks((const void*)deep_reverse_kernel, kReverseThreads, tiles);
-    hipLaunchKernelGGL(deep_reverse_kernel, dim3(blocks), dim3(kReverseThreads), 0, st, a);      // S_{K-1} .. S_1, dd/de
+    const int back = deep_runs(n_mats - 1, start);
+    for (int r = back - 1; r >= 0; --r) {                        // S_{K-1} .. S_1, dd/de
+        a.first = start[r + 1] - 1; a.count = start[r + 1] - start[r];
+        const int blocks = persistent_blocks((const void*)deep_reverse_kernel, kDeepThreads, tiles);
+        hipLaunchKernelGGL(deep_reverse_kernel, dim3(blocks), dim3(kDeepThreads), 0, st, a);
+    }
     return check_launch("sdf forward (deeper network)");
 }
 

@@ -167,3 +167,30 @@ def test_workspace_holds_what_is_used_and_no_more(n_mats, enc_dim, n):
     nb.sdf_deep_fwd_grad(enc_dim, enc, jac, H, n, y, q, normal, held[:size])
     nb.sdf_deep_bwd(enc_dim, enc, jac, H, d_y, d_normal, n, [torch.zeros_like(h) for h in H], d_enc, held[:size])
     assert bool((held[size:] == 0x5A).all()) and bool((held[:size] != 0x5A).any())
+
+
+@pytest.mark.parametrize("enc_dim,hidden", [(32, 1), (32, 5), (32, 6), (32, 7), (32, 8), (16, 8)])
+def test_forward_whatever_the_scale_of_a_neuron(enc_dim, hidden):
+    """Hidden neurons scaled by powers of two (a row up, the column that reads it down) and another size of the SDF's row
+    beside the feature rows change no bit of the values, dd/de and the normals (the row's size undone exactly): every element
+    keeps 24 bits of its own, in one run of layers and in two."""
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    rng = np.random.default_rng(enc_dim + hidden)
+    n, L = 32 * 16 + 5, enc_dim // 2
+    H = make_net(rng, enc_dim, hidden)
+    other = [h.copy() for h in H]
+    for l in range(hidden):
+        scale = np.ldexp(np.float32(1), rng.integers(-30, 31, size=64)).astype(np.float32)
+        other[l] *= scale[:, None]
+        other[l + 1] /= scale[None, :]
+    other[-1][0] = np.ldexp(other[-1][0], -24)
+    enc, jac = cuda(rng.normal(size=(L, n, 2))), cuda(rng.normal(size=(L, 3, n, 2)) * 0.3)
+    ws = torch.empty(nb.sdf_deep_workspace_bytes(len(H), n), dtype=torch.uint8, device="cuda")
+    found = []
+    for mats, back in ((H, 0), (other, 24)):
+        y, q, normal = torch.empty(n, 16, device="cuda"), torch.empty(L, n, 2, device="cuda"), torch.empty(n, 3, device="cuda")
+        nb.sdf_deep_fwd_grad(enc_dim, enc, jac, [cuda(m) for m in mats], n, y, q, normal, ws)
+        found.append([y[:, 0] * 2.0 ** back, y[:, 1:], q * 2.0 ** back, normal * 2.0 ** back])
+    for a, b in zip(*found):
+        assert torch.equal(a, b) and bool(a.any()) and bool(torch.isfinite(a).all())
