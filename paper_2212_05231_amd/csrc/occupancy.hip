@@ -329,12 +329,14 @@ __global__ __launch_bounds__(kSortThreads) void order_cells_kernel(int log2_res,
 // `own_cells` consecutive cells (a bucket, or a part of one: it then reads the whole bucket), takes the maxima of its
 // candidates in LDS and writes each density and bit once.  Atomic maxima in memory were 42 us at 2^20 candidates (a
 // request each, whatever their order), decay and bits another pass over the cells each.
+// Where the occupied cells lie in few buckets, half of the candidates are theirs: from `share` on a bucket's candidates are left to
+// crowded_cells_kernel, which spreads them over the chip.
 constexpr int kOwnCells = 4096;
 
 __global__ __launch_bounds__(kSortThreads) void update_cells_kernel(int log2_res, float* __restrict__ density, const int32_t* __restrict__ cells,
                                                                     const float* __restrict__ sdf, int64_t m, const int32_t* __restrict__ counts,
                                                                     const float* __restrict__ s_dev, float s_fixed, float decay, float threshold,
-                                                                    uint32_t* __restrict__ bitfield, int own_cells) {
+                                                                    uint32_t* __restrict__ bitfield, int own_cells, int64_t share) {
     __shared__ uint32_t top[kOwnCells];
     __shared__ int totals[kSortThreads / 64];
     __shared__ int span[2];
@@ -347,7 +349,7 @@ __global__ __launch_bounds__(kSortThreads) void update_cells_kernel(int log2_res
     if (t == bucket) { span[0] = start; span[1] = start + count; }
     __syncthreads();
     const float s = s_dev ? s_dev[0] : s_fixed;
-    const int64_t end = min((int64_t)span[1], m);
+    const int64_t end = min(min((int64_t)span[1], span[0] + share), m);
     for (int64_t i = max(span[0], 0) + t; i < end; i += kSortThreads) {
         const uint32_t c = (uint32_t)cells[i] - first;
         if (c >= (uint32_t)own_cells) continue;                // another part of the bucket, or outside the grid
@@ -365,6 +367,52 @@ __global__ __launch_bounds__(kSortThreads) void update_cells_kernel(int log2_res
         const int lane = t & 63;
         if ((lane & 31) == 0) bitfield[(first + c) >> 5] = (uint32_t)(mask >> lane);
     }
+}
+
+// What update_cells_kernel left of crowded buckets, after it: a workgroup takes the ones among kSortItems consecutive
+// candidates, which are one bucket's (share >= kSortItems), merges those of one cell in LDS and raises density and bit where
+// they are larger than what is there.  Exact: neither ever falls here, so the order does not matter.
+__global__ __launch_bounds__(kSortThreads) void crowded_cells_kernel(int log2_res, float* __restrict__ density, const int32_t* __restrict__ cells,
+                                                                     const float* __restrict__ sdf, int64_t m, const int32_t* __restrict__ counts,
+                                                                     const float* __restrict__ s_dev, float s_fixed, float threshold,
+                                                                     uint32_t* __restrict__ bitfield, int64_t share) {
+    constexpr int kSlots = 4096;
+    __shared__ int totals[kSortThreads / 64];
+    __shared__ int span[2];
+    __shared__ int owner[kSlots];
+    __shared__ uint32_t top[kSlots];
+    const int t = threadIdx.x;
+    const int64_t base = (int64_t)blockIdx.x * kSortItems;
+    if (t == 0) { span[0] = 0; span[1] = 0; }
+    const int count = t < kBuckets ? counts[t] : 0;
+    const int start = bucket_scan(count, totals);               // a barrier inside
+    const int64_t low = max((int64_t)start + share, base), high = min(min((int64_t)start + count, m), base + kSortItems);
+    if (t < kBuckets && low < high) { span[0] = (int)(low - base); span[1] = (int)(high - base); }
+    __syncthreads();
+    const int first = max(span[0], 0), last = span[1];
+    if (first >= last) return;                                  // the same for the workgroup
+    for (int k = t; k < kSlots; k += kSortThreads) { owner[k] = -1; top[k] = 0u; }
+    __syncthreads();
+    const int64_t total = (int64_t)1 << (3 * log2_res);
+    const float s = s_dev ? s_dev[0] : s_fixed;
+    auto raise = [&](int c, uint32_t bits) {
+        if (bits > __float_as_uint(density[c])) atomicMax(reinterpret_cast<unsigned int*>(density) + c, bits);
+        const uint32_t bit = 1u << (c & 31);
+        if (__uint_as_float(bits) > threshold && !(bitfield[c >> 5] & bit)) atomicOr(bitfield + (c >> 5), bit);
+    };
+    for (int k = first + t; k < last; k += kSortThreads) {
+        const int c = cells[base + k];
+        if (c < 0 || c >= total) continue;
+        const float phi = logistic_density(sdf[base + k], s);
+        if (!(phi > 0.0f) || phi > 3.0e38f) continue;           // NaN, zero, overflow: nothing to raise
+        const int slot = c & (kSlots - 1);
+        const int other = atomicCAS(&owner[slot], -1, c);
+        if (other == -1 || other == c) atomicMax(&top[slot], __float_as_uint(phi));
+        else raise(c, __float_as_uint(phi));                    // grids beyond 128^3: another cell has the slot
+    }
+    __syncthreads();
+    for (int k = t; k < kSlots; k += kSortThreads)
+        if (owner[k] >= 0) raise(owner[k], top[k]);
 }
 
 // ---- marching ---------------------------------------------------------------------------------
@@ -581,9 +629,15 @@ extern "C" int neus2_occupancy_update_ordered(int log2_res, float* density, cons
     hipStream_t st = static_cast<hipStream_t>(stream);
     const int total = 1 << (3 * log2_res);
     const int own = std::min(kOwnCells, total / kBuckets);
+    // two workgroups' worth, and four times the mean: evenly spread candidates and those of a shell stay below it
+    const int64_t share = std::max((int64_t)2 * kSortItems, 4 * (m / kBuckets));
     update_cells_kernel<<<total / own, kSortThreads, 0, st>>>(log2_res, density, cells, sdf, m, counts, s_dev, s, decay, threshold,
-                                                              bitfield, own);
-    return check_launch("update_cells_kernel");
+                                                              bitfield, own, share);
+    NEUS2_TRY(check_launch("update_cells_kernel"));
+    if (m <= share) return NEUS2_OK;
+    crowded_cells_kernel<<<(unsigned)((m + kSortItems - 1) / kSortItems), kSortThreads, 0, st>>>(
+        log2_res, density, cells, sdf, m, counts, s_dev, s, threshold, bitfield, share);
+    return check_launch("crowded_cells_kernel");
 }
 
 extern "C" int neus2_occupancy_update(int log2_res, float* density, const int32_t* cells, const float* sdf,

@@ -331,3 +331,42 @@ def test_refresh_of_drawn_candidates_in_either_order(log2_res, monkeypatch):
         grids.append(grid)
     assert torch.equal(grids[0].density, grids[1].density) and torch.equal(grids[0].bitfield, grids[1].bitfield)
     assert torch.equal(grids[0].last_cells.sort().values, grids[1].last_cells.sort().values)
+
+
+@pytest.mark.parametrize("log2_res,crowds,rest", [(5, [(0, 64, 8192)], 300), (5, [(511, 64, 8193)], 300), (6, [(17, 512, 70000), (18, 3, 9000), (40, 1, 12289)], 4096),
+                                                  (7, [(5, 4096, 300001)], 100000), (8, [(200, 32768, 100000), (201, 2, 20000)], 50000)])
+def test_ordered_refresh_of_crowded_blocks(log2_res, crowds, rest):
+    """Blocks (number, cells of it that are drawn, draws) with more candidates than one workgroup takes, at the edge of that
+    number and beyond, neighbours, blocks of more cells than a table in LDS, the lowest and the highest one: the same
+    densities and bits as from the list as drawn, cells without a candidate among them; nothing behind them is written."""
+    gen = torch.Generator(device="cuda").manual_seed(log2_res)
+    total = 1 << (3 * log2_res)
+    per = total // 512
+    randint = lambda high, count: torch.randint(0, high, (count,), generator=gen, device="cuda", dtype=torch.int32)
+    cells = torch.cat([block * per + (per - k if block > 256 else 0) + randint(k, count) for block, k, count in crowds] + [randint(total, rest)])
+    cells = cells[torch.randperm(cells.numel(), generator=gen, device="cuda")].contiguous()
+    m = cells.numel()
+    jitter = torch.rand(m, 3, generator=gen, device="cuda").clamp_(max=1.0 - 2.0 ** -24)
+    plain, out_pos, out_jitter = (torch.empty(m, 3, device="cuda") for _ in range(3))
+    out_cells, counts = torch.empty_like(cells), torch.empty(1024, dtype=torch.int32, device="cuda")
+    nb.occupancy_points(log2_res, cells, jitter, plain)
+    nb.occupancy_points_ordered(log2_res, cells, jitter, counts, out_cells, out_jitter, out_pos)
+
+    def sdf_at(pos):
+        v = ((pos * 4096.0).frac() - 0.5).sum(dim=1) * 0.05
+        return torch.where(v > 0.06, torch.full_like(v, float("nan")), v).contiguous()
+    guard = 16
+    start = torch.rand(total, generator=gen, device="cuda") * 8.0
+    found = []
+    for ordered in (False, True):
+        density = torch.cat([start, torch.full((guard,), 5.0, device="cuda")])
+        bits = torch.full((total // 32 + guard,), -1, dtype=torch.int32, device="cuda")
+        if ordered:
+            nb.occupancy_update_ordered(log2_res, density, out_cells, sdf_at(out_pos), m, counts, 30.0, 0.95, 6.5, bits)
+        else:
+            nb.occupancy_update(log2_res, density, cells, sdf_at(plain), 1, m, 30.0, 0.95, 6.5, bits)
+        found.append((density, bits))
+    assert torch.equal(found[0][0], found[1][0]) and torch.equal(found[0][1], found[1][1])
+    assert bool((found[1][0][total:] == 5.0).all()) and bool((found[1][1][total // 32:] == -1).all())
+    raised = found[1][0][:total] > start * 0.95
+    assert bool(raised.any()) and not bool(raised.all())
