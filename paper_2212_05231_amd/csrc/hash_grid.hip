@@ -1488,8 +1488,10 @@ int launch_scatter(const neus2_config* cfg, const float* pos, const void* tables
                 for (int e = 0; e < plan.n_listed; ++e) most = std::max(most, (int)plan.ranges[e]);
                 const int threads = !wide && most > kWideBinRanges && n >= (int64_t)2048 * compute_units() ? 1024 : 512;
                 const int pbs = (int)((n + threads - 1) / threads);
-                // Enough workgroups to fill the chip once (2048 threads a compute unit); each walks over its share of the levels.
-                // Twice as many: 2^18 points 47 -> 53 us, 2^19 points 87 -> 95.
+                // Four workgroups a compute unit; each walks over its share of the levels.  Of 512 threads they fill the chip once
+                // (twice as many: 2^18 points 47 -> 53 us, 2^19 points 87 -> 95).  Of 1024 threads they are two groups of levels
+                // below 2^20 points, the second at work while the first's end: the whole call at 640 000 points 354 us, with one
+                // group 366, at 896 000 468 and 479, at 2^19 315 both ways; with 512 threads a workgroup 386, 529 and 333.
                 int groups = (4 * compute_units() + pbs - 1) / pbs;
                 if (groups > plan.n_listed) groups = plan.n_listed;
                 if (groups < 1 && plan.n_listed > 0) groups = 1;
