@@ -114,7 +114,10 @@ def algorithmic_cost(cfg, n):
     # including recomputation (three products where the forward kernels hand over their masks, as here) and the
     # padding of narrow layers.  Instruction counts per tile follow the
     # kernels' structure; the backward kernels add 32 narrow fp32 instructions (2048 flop each, 512 in the colour network's).
-    ks1, k3 = sd[0] // 16, 1 if K == 3 else 0
+    # The first layer's products over the inputs take the k-steps of the groups of four levels that are read: those with
+    # an active level, all of them from 2^26 points on.
+    groups = min(max((cfg.active_levels + 3) // 4, 1), sd[0] // 8) if n < 1 << 26 else sd[0] // 8
+    ks1, k3 = (8 * groups + 15) // 16, 1 if K == 3 else 0
     issued = {
         "sdf_fwd_grad": 6 * (2 * ks1 + 8 * k3 + 4 + 8 * k3 + 4),
         "sdf_mlp_bwd": 3 * (2 * ks1 + 8 * k3) + 3 * (2 + 8 * k3 + 4 + 8 * k3 + 2 * ks1 + 8 * k3) + 3 * 2 * (4 * k3 + 2) * 2,
