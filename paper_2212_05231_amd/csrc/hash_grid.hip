@@ -653,10 +653,16 @@ struct Records {
 // longer runs smaller workgroups are the better ones (2^18 points, 64 ranges: 47 and 50 us).  The arithmetic runs at eight
 // wavefronts per SIMD, which 64 registers allow since the values are worked out after the places and packed without branches
 // (72 registers, three workgroups a compute unit: 2^18 points 67 us, with the levels' order as below).
-// Every workgroup starts at another level, and those of the point lists alternate between theirs: with all of them at the same
+// Otherwise (see kFewBinRecords) every workgroup starts at another level, and those of the point lists alternate between theirs: with all of them at the same
 // level their reservations queue up at a few cache lines, which take one atomic in 12 ns (2^18 points, 512 workgroups, ten levels:
 // 67 -> 55 us; four levels of point lists at 2^20 points 88 -> 72).
 constexpr int kWideBinRanges = 128;
+// Small batches over few ranges (ranges times points up to this) take the workgroups level group after level group, twice as many and
+// all from their first level on: with the levels alternating, the workgroups of a group come to one or two of the eight
+// XCDs (the group repeats every four or eight workgroups), and groups of unequal numbers of levels leave some idle.  Kernel, us,
+// alternating and in turn: 2^17 points 4 ranges 35.5 and 30.0, 2 ranges 43 and 36.8, 8 ranges 28.7 and 27.0; 2^16 points in an
+// eighth of the cube 4 ranges 26.9 and 19.1.  Whole call beyond: 2^18 points 8 ranges 144 and 148, 16 ranges 137 and 143.
+constexpr int64_t kFewBinRecords = (int64_t)1 << 20;
 constexpr uint32_t kNoRecord = 0xFFFFFFFFu;
 
 // A staged record with its place in the entry's lists (kNoRecord if it went elsewhere) is written and read 16 bytes at a time
@@ -774,7 +780,7 @@ __device__ void bin_points(const GridDesc& g, const OwnerPlan& plan, const Recor
 }
 
 // A workgroup takes THREADS points and walks over a share of the levels with row records (levels
-// grp, grp + level_groups, ..., from another one on in every workgroup): position and dL/dn are fetched once, and the next level's dL/de and
+// grp, grp + level_groups, ..., spread: from another one on in every workgroup): position and dL/dn are fetched once, and the next level's dL/de and
 // dd/de are requested before the current level's records are made, so that only the first level of a
 // workgroup waits for memory.  Workgroups beyond the level groups handle the levels with point lists.
 template <typename Rec, int THREADS>
@@ -783,19 +789,20 @@ __global__ __launch_bounds__(THREADS, 8) void bin_rows_kernel(GridDesc g, OwnerP
                                                               const float* __restrict__ q,
                                                               const float* __restrict__ d_enc,
                                                               const float* __restrict__ d_normal, int64_t n,
-                                                              int point_blocks, int level_groups,
+                                                              int point_blocks, int level_groups, int spread,
                                                               float* __restrict__ d_tables) {
     __shared__ BinSmem<Rec, THREADS> sm;
     const int row_blocks = point_blocks * level_groups;
     const bool points = (int)blockIdx.x >= row_blocks;      // uniform over the workgroup
     const int roles = points ? plan.n_indexed : level_groups, at = (int)blockIdx.x - (points ? row_blocks : 0);
-    const int grp = at % roles, point_block = at / roles;
+    const int side = spread ? roles : point_blocks, whole = at / side, rest = at - whole * side;
+    const int grp = spread ? rest : whole, point_block = spread ? whole : rest;
     if (points) {
         bin_points<THREADS>(g, plan, rec, pos, q, d_enc, d_normal, n, point_block, plan.n_listed + grp, d_tables, sm.cnt, reinterpret_cast<int*>(sm.place));
         return;
     }
     const int turns = (plan.n_listed - grp + level_groups - 1) / level_groups;      // levels of this group
-    const int start = point_block % turns;
+    const int start = spread ? point_block % turns : 0;
     const int64_t i = (int64_t)point_block * THREADS + threadIdx.x;
     const bool valid = i < n;
     float px = 0.f, py = 0.f, pz = 0.f, dnx = 0.f, dny = 0.f, dnz = 0.f;
@@ -1492,12 +1499,13 @@ int launch_scatter(const neus2_config* cfg, const float* pos, const void* tables
                 // (twice as many: 2^18 points 47 -> 53 us, 2^19 points 87 -> 95).  Of 1024 threads they are two groups of levels
                 // below 2^20 points, the second at work while the first's end: the whole call at 640 000 points 354 us, with one
                 // group 366, at 896 000 468 and 479, at 2^19 315 both ways; with 512 threads a workgroup 386, 529 and 333.
-                int groups = (4 * compute_units() + pbs - 1) / pbs;
+                const bool few = most > 0 && (int64_t)most * n <= kFewBinRecords;      // point lists alone: alternating
+                int groups = ((few ? 8 : 4) * compute_units() + pbs - 1) / pbs;
                 if (groups > plan.n_listed) groups = plan.n_listed;
                 if (groups < 1 && plan.n_listed > 0) groups = 1;
                 auto* const kernel = wide ? bin_rows_kernel<WideRecord, 512> : threads == 512 ? bin_rows_kernel<RowRecord, 512> : bin_rows_kernel<RowRecord, 1024>;
                 hipLaunchKernelGGL(kernel, dim3(pbs * (groups + plan.n_indexed)), dim3(threads), 0, st, g, plan,
-                                   rec, pos, q, d_enc, d_normal, n, pbs, groups, d_tables);
+                                   rec, pos, q, d_enc, d_normal, n, pbs, groups, (int)!few, d_tables);
             }
             const int wgs = compute_units();
             if (plan.n_tasks > 0)

@@ -444,6 +444,13 @@ def test_scatter_add_of_runs_in_one_cell(n, log2_t, res, broken):
     assert torch.all(torch.signbit(behind)) and torch.all(behind == 0)
 
 
+@pytest.mark.parametrize("n,log2_t", [(131072, 16), (131073, 16), (262144, 15), (262145, 15), (80001, 14)])
+def test_scatter_add_over_few_ranges(n, log2_t):
+    """Both orders of the binning workgroups, on either side of the number of records where one follows the other: several
+    hashed levels of two to eight ranges that the groups share out unevenly, point lists and in-place levels beside them."""
+    test_scatter_add_of_runs_in_one_cell(n, log2_t, [12, 24 if log2_t < 16 else 36, 50, 64, 90, 120, 200], False)
+
+
 def colour_inputs(n, rng):
     cfg = wl.make_config(2)
     cfg.samples_per_ray = 1
