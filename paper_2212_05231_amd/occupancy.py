@@ -14,7 +14,8 @@ from __future__ import annotations
 from . import binding as nb
 
 # From this many drawn candidates on they are put in order of where they lie, us a refresh (16 levels of 2^19 slots, 128^3
-# cells): 2^20 candidates 500 -> 425 (fp32 tables 622 -> 536), 2^19 290 -> 258, 2^18 190 -> 175; 2^17 of 64^3 cells 137 -> 137.
+# cells): 2^20 candidates 508 -> 438 (fp32 tables 623 -> 542), 2^19 295 -> 265, 2^18 192 -> 178; 2^17 138 -> 135, 2^17 of 64^3
+# cells 135 -> 131, two launches more for little.
 ORDER_FROM = 1 << 18
 
 
