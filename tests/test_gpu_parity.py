@@ -892,6 +892,21 @@ def test_step_whose_backward_kernels_work_the_masks_out_again(k, n_rays):
     print(check_step(cfg, step, ref, n))
 
 
+@pytest.mark.parametrize("k,n_rays", [(1, 3000), (2, 150), (3, 150)])
+def test_step_without_mask_buffers_is_the_step_with_them(k, n_rays):
+    """The masks a backward kernel works out again are those the forward kernel would have written: the forward results are
+    the same bits, and the adjoints, which depend on the masks and not on the recomputed activations, agree to the rounding
+    of two-term products (2^-16 each, random signs) where one mask the other way is 1e-3 of the norm of this many points."""
+    _, kept, _, _ = run_step(k, n_rays, scale_tables=2000.0)
+    _, none, _, _ = run_step(k, n_rays, scale_tables=2000.0, keep_masks=False)
+    assert kept.buffers.sdf_masks and none.buffers.sdf_masks is None
+    for name in ["y", "q", "normal"] + (["rgb", "C"] if kept.cfg.loss_kind else []):
+        assert torch.equal(getattr(kept, name), getattr(none, name)), name
+    assert rel(kept.d_enc.cpu().numpy(), none.d_enc.cpu().numpy().astype(np.float64)) <= 2e-5
+    for a, b in zip(kept.dH + (kept.dW if kept.cfg.loss_kind else []), none.dH + (none.dW if kept.cfg.loss_kind else [])):
+        assert rel(a.cpu().numpy(), b.cpu().numpy().astype(np.float64)) <= 5e-5
+
+
 def test_step_config2_with_order_one_tables_and_position_gradient():
     """Tables scaled so that SDF values, alphas and masks are non-degenerate."""
     cfg, step, ref, n = run_step(2, 64, want_pos=True, scale_tables=2000.0)
