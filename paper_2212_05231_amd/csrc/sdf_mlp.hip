@@ -1029,8 +1029,8 @@ int run_bwd(const SdfArgs& a, hipStream_t st) {
 // needed, every access instruction in 64 cache lines: eight hidden layers at 2^17 points, forward and backward, took
 // 1243 us, runs of layers 617 and without spilled registers 556.  Bound by the vectors that the backward call stores and
 // reads back.
-// Every matrix is used as 64 x 64 (the first one's missing columns and the last one's missing rows are zeros), so one
-// kernel serves every layer.
+// Every matrix is stored as 64 x 64 (the first one's missing columns and the last one's missing rows are zeros; the products leave
+// their k-steps and blocks of rows out), so one kernel serves every layer.
 //   forward run:   a_l = G_l H_l a_{l-1}  (six-product arithmetic, writes the mask words)
 //                  t_l = G_l H_l t_{l-1}  (WITH_T; t_0 = (de/dx) dL/dn)
 //   reverse run:   S_{l-1} = (H_l^T S_l) G_{l-1}, down to dd/de and the normal
